@@ -224,11 +224,11 @@ int bf16_gemm(const void *x_bf16, int64_t ldx, const void *w_bf16, int64_t ldw,
 
 /*
  * The same product with a caller-owned workspace, for decode batches (the precision that the
- * decode phase keeps, Section 3.3): 33 to 64 tokens against a weight matrix with a narrow N leave
- * most compute units without a row group of W, and the time is the weights' one trip from HBM;
- * with a workspace K is cut into slabs across workgroups (FP32 partial sums, added in ascending
- * order by a second kernel: bit-identical from run to run; the last bits may differ from
- * bf16_gemm's).  Arguments and requirements as bf16_gemm; workspace as in nvfp4_gemm_ws.
+ * decode phase keeps, Section 3.3): 33 to 64 tokens against a weight matrix with a long K and a narrow
+ * N re-read the activations once per narrow tile of W; with a workspace the tiles can be wider, K being
+ * cut into slabs across workgroups (FP32 partial sums, added in ascending order by a second kernel:
+ * bit-identical from run to run; the last bits may differ from bf16_gemm's).  Arguments and
+ * requirements as bf16_gemm; workspace as in nvfp4_gemm_ws.
  * mq_bf16_gemm_workspace_bytes(M, N, K) (host function) returns the size that lets the library
  * choose freely: slabs * M * N * 4 bytes (at most 16 MiB), 0 where slabs are never used
  * (M <= 32, M > 64, N % 4 != 0, K % 128 != 0, K < 8192, N > 16256, or so few rows of W that even

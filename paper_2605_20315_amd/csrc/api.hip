@@ -270,7 +270,7 @@ static int gemm_fp4_entry(const uint8_t *a_codes, const uint8_t *a_scales, const
 int64_t mq_bf16_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    const int ks = gemm_bf16_decode_slabs(M, N, K, INT64_MAX, kMaxComputeUnits);
+    const int ks = gemm_bf16_slab_limit(M, N, K, INT64_MAX, kMaxComputeUnits);
     return ks >= 2 ? (int64_t)ks * M * N * 4 : 0;
 }
 

@@ -24,20 +24,16 @@
 //                       tiles also over workgroups (splitk_reduce_kernel then adds the slabs).
 //   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256 tile, four waves of 128x128,
 //                       tiles loaded from global memory straight into LDS.
-//   gemm_bf16_pipelined the BF16 baseline on smaller problems, same LDS pipeline, tiles staged
-//                       through registers.
-//   bf16_skinny_kernel  BF16 with M <= 64 (decode shapes), weight streaming, K split over the waves.
-//   bf16_decode_kernel  BF16 with 17 <= M <= 64, weight streaming, N split over the waves, the
-//                       activations shared through LDS, K slabs across workgroups with a workspace.
+//   bf16_ring_kernel    BF16 decode batches: narrow tiles, the waves of a workgroup split K, each with a
+//                       ring of its own in LDS; K slabs across workgroups with a workspace.
+//   bf16_stage_kernel   BF16 in between: 96x64 to 256x192 tiles, two to six stages in LDS.
 //   gemm_simple_kernel  any K % 16 == 0 / K % 8 == 0 that the tiled kernels do not take.
 //
-// The LDS pipeline (the BF16 kernels): block tile BM x BN x 64, two LDS stages, and the
-// latencies covered inside each wave:
+// The LDS pipeline of gemm_bf16_d2l: block tile 256 x 256 x 64, two LDS stages, and the latencies
+// covered inside each wave:
 //   * a K step of 64 is four MFMA phases of 16; the fragments of phase p+1 are read from LDS
 //     into a second register set while the MFMAs of phase p run;
-//   * tiles are fetched two K steps ahead straight into the free LDS stage (gemm_bf16_d2l), or
-//     one K step ahead into registers and written to the free stage over two phases
-//     (gemm_bf16_pipelined);
+//   * tiles are fetched two K steps ahead straight into the free LDS stage;
 //   * one barrier per K step, at the start of phase 3: before it every wave has finished writing
 //     tile t+1 and reading tile t; after it tile t's stage is free and receives tile t+2.
 // (An NVFP4 kernel of the same structure, operands expanded once per workgroup on their way
@@ -730,136 +726,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g)
     }
 }
 
-// ---- BF16 -----------------------------------------------------------------------------------
-
-// Same phases as the NVFP4 LDS pipeline.  A tile is fetched into registers right after the
-// barrier of K step t (16 x 128 bits per thread), and written to the free LDS stage during
-// phases 1 and 2 of K step t+1.  Used for the 256x128 and 128x128 tile configurations.
-template <class C, bool OUT_BF16>
-__global__ __launch_bounds__(C::THREADS) void gemm_bf16_pipelined(GemmArgs g, int tiles_m, int tiles_n)
-{
-    extern __shared__ uint4 lds[];
-    char *const L = reinterpret_cast<char *>(lds);
-    int tm, tn;
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
-    const int frow = lane & 31, fhalf = lane >> 5;
-    const int KT = (int)(g.K / BK);
-
-    // chunk j of this thread: row (tid>>3) + j*(THREADS/8) of the tile, 16-byte chunk tid&7 of its 128 bytes
-    constexpr int NL = C::LA + C::LB;
-    uint32_t vo[NL];  // global byte offsets from the tile's first row (K step 0): 32 bits for any operand size
-    int wad[NL];      // LDS byte addresses (stage 0)
-    const char *const ta = static_cast<const char *>(g.a) + m0 * g.lda * 2;  // m0 < M, n0 < N
-    const char *const tb = static_cast<const char *>(g.b) + n0 * g.ldb * 2;
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-        const bool isA = j < C::LA;
-        const int r = (tid >> 3) + (isA ? j : j - C::LA) * (C::THREADS / 8);
-        int64_t grow = (isA ? m0 : n0) + r;
-        const int64_t total = isA ? g.M : g.N;
-        grow = grow < total ? grow : total - 1;
-        vo[j] = (uint32_t)((grow - (isA ? m0 : n0)) * (isA ? g.lda : g.ldb) * 2 + (tid & 7) * 16);
-        wad[j] = (isA ? 0 : C::B_BASE) + (r * 8 + ((tid & 7) ^ swz_key(r))) * 16;
-    }
-    uint4 regs[NL];
-    auto load_tile = [&](int t) {
-        t = t < KT ? t : KT - 1;
-        const char *a = ta + (int64_t)t * (BK * 2);
-        const char *b = tb + (int64_t)t * (BK * 2);
-#pragma unroll
-        for (int j = 0; j < NL; ++j) regs[j] = *reinterpret_cast<const uint4 *>((j < C::LA ? a : b) + vo[j]);
-    };
-    auto store_range = [&](int j0, int j1, int stage) {
-#pragma unroll
-        for (int j = j0; j < j1; ++j) {
-            uint4 v = regs[j];
-            asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));  // first use stays in this phase
-            *reinterpret_cast<uint4 *>(L + wad[j] + stage * (j < C::LA ? C::A_STAGE : C::B_STAGE)) = v;
-        }
-    };
-
-    int fa[4], fb[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        fa[ks] = ((wm0 + frow) * 8 + ((ks * 2 + fhalf) ^ swz_key(frow))) * 16;
-        fb[ks] = C::B_BASE + ((wn0 + frow) * 8 + ((ks * 2 + fhalf) ^ swz_key(frow))) * 16;
-    }
-    uint4 fra[2][C::TM], frb[2][C::TN];
-    auto read_frags = [&](int stage, int ks, uint4(&a)[C::TM], uint4(&b)[C::TN]) {
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-            a[i] = *reinterpret_cast<const uint4 *>(L + fa[ks] + i * 4096 + stage * C::A_STAGE);
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-            b[j] = *reinterpret_cast<const uint4 *>(L + fb[ks] + j * 4096 + stage * C::B_STAGE);
-    };
-    f32x16 acc[C::TM][C::TN];
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    auto mfmas = [&](const uint4(&a)[C::TM], const uint4(&b)[C::TN]) {
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    __builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
-    };
-    constexpr int NMFMA = C::TM * C::TN, NREAD = C::TM + C::TN;
-
-    load_tile(0);
-    store_range(0, NL, 0);
-    load_tile(1);
-    __syncthreads();
-    read_frags(0, 0, fra[0], frb[0]);
-
-    auto kstep = [&](int kt, auto par) {
-        constexpr int PAR = decltype(par)::value;
-        constexpr int cur = PAR, nxt = PAR ^ 1;
-        // phase 0
-        read_frags(cur, 1, fra[1], frb[1]);
-        mfmas(fra[0], frb[0]);
-        sched_phase<NMFMA, NREAD, 0, 0, 0>();
-        // phase 1: first half of tile kt+1 -> LDS
-        read_frags(cur, 2, fra[0], frb[0]);
-        store_range(0, NL / 2, nxt);
-        mfmas(fra[1], frb[1]);
-        sched_phase<NMFMA, NREAD, 0, (NL / 2 < NMFMA ? NL / 2 : NMFMA), 0>();
-        // phase 2: second half
-        read_frags(cur, 3, fra[1], frb[1]);
-        store_range(NL / 2, NL, nxt);
-        mfmas(fra[0], frb[0]);
-        sched_phase<NMFMA, NREAD, 0, (NL / 2 < NMFMA ? NL / 2 : NMFMA), 0>();
-        // phase 3
-        __syncthreads();
-        read_frags(nxt, 0, fra[0], frb[0]);
-        load_tile(kt + 2);
-        mfmas(fra[1], frb[1]);
-        sched_phase<NMFMA, NREAD, 0, 0, NL>();
-    };
-    int kt = 0;
-    for (; kt + 1 < KT; kt += 2) {
-        kstep(kt, std::integral_constant<int, 0>{});
-        kstep(kt + 1, std::integral_constant<int, 1>{});
-    }
-    if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
-
-    epilogue<C, OUT_BF16>(g, acc, 1.0f, m0, n0, wm0, wn0, frow, fhalf);
-}
-
 // ---- BF16, direct global-to-LDS loads ----------------------------------------------------------
 
-// 256x256x64 tile with four waves of 128x128 (one per SIMD), or 256x128x64 with four waves of
-// 128x64; same LDS layout, phases and barrier as gemm_bf16_pipelined, but the tiles never pass
-// through registers: every wave issues 16 (12) global_load_lds_dwordx4 per K step (1 KB each:
-// 8 rows of one operand tile), which write LDS at
-// M0 + 16 * lane.  The bank swizzle is applied on the global side: the lane that fills chunk c' of
+// 256x256x64 tile with four waves of 128x128 (one per SIMD).  The tiles never pass through
+// registers: every wave issues 16 global_load_lds_dwordx4 per K step (1 KB each: 8 rows of one
+// operand tile), which write LDS at M0 + 16 * lane.  The bank swizzle is applied on the global side: the lane that fills chunk c' of
 // row r fetches chunk c' ^ key(r).  The loads are written in inline assembly because the compiler
 // orders every LDS read behind all outstanding LDS-writing loads (s_waitcnt vmcnt(0) right after
 // the load), which serialises the pipeline; here the only wait is the one before the barrier.
@@ -999,300 +870,301 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
     epilogue<C, OUT_BF16>(g, acc, 1.0f, m0, n0, wm0, wn0, frow, fhalf);
 }
 
-// ---- decode-shape BF16 product (M <= 64): weight streaming, HBM-bound ---------------------------
+// ---- BF16, tiles of 16x16 MFMAs: decode batches and everything up to a few thousand tokens --------
 
-// The high-precision decode path multiplies a handful of tokens by the whole weight matrix, so
-// the time is the time to stream W once from HBM.  A workgroup of 8 waves owns 16*RT rows of W;
-// wave w takes the 128-wide K super-steps w, w+8, ... (together 2 KB contiguous per row and round),
-// so 8 x (N / (16*RT)) waves keep enough bytes in flight without splitting K across workgroups.
-// A lane (row r = lane%16, group g = lane/16) loads 64 contiguous bytes of W rows r, r+16, ... and
-// of X rows r, r+16, ...; four v_mfma_f32_16x16x32_bf16 per super-step and (row tile, token tile)
-// pair accumulate D[W row][token]; the 8 partial sums are added pairwise, in a fixed order,
-// through LDS.  Every workgroup re-reads the activations from L2, which delivers about 6 TB/s to
-// the CUs in total: with MT token tiles and RT row tiles per wave the weights stream at
-// 6 / (1 + MT/RT) TB/s at best, so RT grows with N as far as the grid still covers half the chip.
-// DB: two super-steps of loads in flight per wave (when the registers allow), else one.
-template <int MT, int RT, bool DB, bool OUT_BF16>
-__global__ __launch_bounds__(512) void bf16_skinny_kernel(GemmArgs g)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Loads 8 rows x 128 bytes (one 64-wide K step of eight rows, 1 KB) from global memory straight into
+// LDS at `dst`; lane l brings 16 bytes of row l / 8.  In inline assembly for the reason given at
+// gemm_bf16_d2l.  STREAM: non-temporal, for rows of W that no other workgroup reads.
+template <bool STREAM>
+__device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off, const char *base)
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    constexpr int NT = RT * MT;
-    __shared__ f32x4 red[4][NT][64];  // 4 * NT KB: at most 64 KB
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row = lane & 15, grp = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * (16 * RT);
-    const uint4 *wp[RT], *xp[MT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        int64_t wr = n0 + r * 16 + row;
-        wr = wr < g.N ? wr : g.N - 1;
-        wp[r] = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.b) + wr * g.ldb + grp * 32);
-    }
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        int64_t xr = t * 16 + row;
-        xr = xr < g.M ? xr : g.M - 1;
-        xp[t] = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.a) + xr * g.lda + grp * 32);
-    }
-    f32x4 acc[RT][MT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int t = 0; t < MT; ++t) acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    const int S = (int)(g.K / 128);  // super-steps; 16 uint4 per row each
-    auto load = [&](int s, uint4(&w)[RT][4], uint4(&x)[MT][4]) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[r][j] = wp[r][s * 16 + j];
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[t][j] = xp[t][s * 16 + j];
-    };
-    auto step = [&](const uint4(&w)[RT][4], const uint4(&x)[MT][4]) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, w[r][j]), __builtin_bit_cast(bf16x8, x[t][j]), acc[r][t], 0, 0, 0);
-    };
-    int s = wave;
-    if constexpr (DB) {
-        for (; s + 8 < S; s += 16) {  // two super-steps of loads in flight
-            uint4 w0[RT][4], w1[RT][4], x0[MT][4], x1[MT][4];
-            load(s, w0, x0);
-            load(s + 8, w1, x1);
-            __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first MFMA waits
-            step(w0, x0);
-            step(w1, x1);
-        }
-    }
-    for (; s < S; s += 8) {
-        uint4 w0[RT][4], x0[MT][4];
-        load(s, w0, x0);
-        __builtin_amdgcn_sched_barrier(0);
-        step(w0, x0);
-    }
-
-    // waves 4..7 hand their sums to waves 0..3, then 2..3 to 0..1, then 1 to 0
-#pragma unroll
-    for (int h = 4; h >= 1; h >>= 1) {
-        if (wave >= h && wave < 2 * h) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int t = 0; t < MT; ++t) red[wave - h][r * MT + t][lane] = acc[r][t];
-        }
-        __syncthreads();
-        if (wave < h) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int t = 0; t < MT; ++t) acc[r][t] += red[wave][r * MT + t][lane];
-        }
-        __syncthreads();
-    }
-    if (wave != 0) return;
-    // accumulator i of a 16x16 tile: W row 4*(lane/16) + i, token lane%16
-    using T = std::conditional_t<OUT_BF16, __bf16, float>;
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const int64_t m = t * 16 + row, n = n0 + r * 16 + 4 * grp;
-            if (m >= g.M) continue;
-            T *dst = static_cast<T *>(g.y) + m * g.ldy + n;
-            if (n + 3 < g.N) {
-                if constexpr (OUT_BF16) {
-                    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                    *reinterpret_cast<bf16x4 *>(dst) = bf16x4{(__bf16)acc[r][t][0], (__bf16)acc[r][t][1],
-                                                              (__bf16)acc[r][t][2], (__bf16)acc[r][t][3]};
-                } else {
-                    *reinterpret_cast<f32x4 *>(dst) = acc[r][t];
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (n + i < g.N) dst[i] = (T)acc[r][t][i];
-            }
-        }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(dst), "v"(lane_off), "s"(base)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(dst), "v"(lane_off), "s"(base)
+                     : "memory", "m0");
+#pragma clang diagnostic pop
 }
 
-// ---- decode batches of 17 .. 64 tokens: weight streaming with the activations shared through LDS ---
-
-// Above 16 tokens the kernel above is bound by its own re-reads of the activations: every
-// workgroup (16 RT rows of W) fetches all of X from L2, which for 64 tokens is four times the
-// weight traffic at RT = 1.  Here the eight waves of a workgroup split N instead of K (16 rows of
-// W each, 128 per workgroup) and share one copy of X: per 128-wide K super-step the workgroup
-// loads the [16 MT, 128] slice of X once, through registers into a double-buffered LDS tile (rows
-// padded by 16 bytes: the 16 rows a quarter-wave reads then fall on different banks), and every
-// wave reads its MFMA fragments from there; W goes from global memory to registers, 64 contiguous
-// bytes per lane and super-step, four super-steps ahead.  X then costs 1/8 of the weight traffic
-// per token tile.  A narrow N (N = 4096: 32 workgroups) is made up for by K slabs across
-// workgroups when the caller passes a workspace: a work item is (slab, row group), partial sums go
-// to ws[slab][M][N] and splitk_reduce_kernel adds them in ascending order.  Lane roles as above:
-// row r = lane % 16 of the wave's 16 W rows (or of a token tile), group g = lane / 16 holds the
-// 32 k values [32 g, 32 g + 32) of a super-step; accumulator i: W row 4 g + i, token lane % 16.
-template <int MT, bool OUT_BF16>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void bf16_decode_kernel(GemmArgs g,
-                                                                                                  int row_groups)
+// Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
+template <int N>
+__device__ __forceinline__ void wait_loads()
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    constexpr int XROW = 256 + 16;                 // bytes per X row in LDS (128 BF16 + padding)
-    constexpr int XBUF = MT * 16 * XROW;           // one buffer
-    constexpr int XCH = MT * 16 * 16 / 512;        // 16-byte chunks of the X slice per thread: MT / 2 (MT even)
-    static_assert(MT == 2 || MT == 4, "token tiles in pairs: the X slice is loaded by 512 threads");
-    static_assert(XCH == 1 || XCH == 2, "one or two 16-byte chunks of X per thread and super-step");
-    __shared__ __attribute__((aligned(16))) char xl[2 * XBUF];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row = lane & 15, grp = lane >> 4;
-    const int rg = (int)(blockIdx.x % row_groups), slab = (int)(blockIdx.x / row_groups);
-    const int64_t n0 = (int64_t)rg * 128 + wave * 16;
-    const int S = (int)(g.K / 128);
-    const int SL = (S + g.ksplit - 1) / g.ksplit;
-    const int s0 = slab * SL < S ? slab * SL : S, s1 = s0 + SL < S ? s0 + SL : S;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N < 63 ? N : 63) : "memory");
+}
 
-    int64_t wr = n0 + row;
-    wr = wr < g.N ? wr : g.N - 1;
-    const uint4 *wp = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.b) + wr * g.ldb + grp * 32);
-    // this thread's chunks of the X slice: chunk c = tid + 512 u -> token c / 16, bytes 16 (c % 16) of the 256
-    const uint4 *xg[XCH];
-    int xdst[XCH];
-#pragma unroll
-    for (int u = 0; u < XCH; ++u) {
-        const int c = tid + 512 * u;
-        int64_t tok = c >> 4;
-        xdst[u] = (int)tok * XROW + (c & 15) * 16;
-        tok = tok < g.M ? tok : g.M - 1;
-        xg[u] = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.a) + tok * g.lda) + (c & 15);
-    }
-    // Register rings, four super-steps deep: slot of X(st) and of W(st) = (st - s0) % 4.  The X ring
-    // is a set of named registers (as an array the compiler moved it to LDS and waited for every
-    // load right after issuing it); the W ring is indexed by compile-time constants only.
-    uint4 xa0, xa1, xa2, xa3, xb0, xb1, xb2, xb3, wq[4][4];
-    xb0 = xb1 = xb2 = xb3 = make_uint4(0, 0, 0, 0);
-    auto load_x = [&](int st, uint4 &ra, uint4 &rb) __attribute__((always_inline)) {
-        st = st < S ? st : S - 1;
-        ra = xg[0][st * 16];
-        if constexpr (XCH > 1) rb = xg[XCH - 1][st * 16];
-    };
-    auto store_x = [&](auto bufc, const uint4 &ra, const uint4 &rb) __attribute__((always_inline)) {
-        constexpr int B = decltype(bufc)::value;
-        *reinterpret_cast<uint4 *>(xl + B * XBUF + xdst[0]) = ra;
-        if constexpr (XCH > 1) *reinterpret_cast<uint4 *>(xl + B * XBUF + xdst[XCH - 1]) = rb;
-    };
-    auto load_w = [&](int st, auto slot) __attribute__((always_inline)) {
-        constexpr int Q = decltype(slot)::value;
-        st = st < S ? st : S - 1;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) wq[Q][j] = wp[st * 16 + j];
-    };
-    f32x4 acc[MT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    // all fragment reads of a super-step are issued before its first MFMA (one LDS round trip per
-    // step instead of one per MFMA), and the MT accumulation chains are interleaved
-    auto compute = [&](auto bufc, auto slot) __attribute__((always_inline)) {
-        constexpr int B = decltype(bufc)::value, Q = decltype(slot)::value;
-        uint4 xf[MT][4];
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const char *xrow = xl + B * XBUF + (t * 16 + row) * XROW + grp * 64;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) xf[t][j] = *reinterpret_cast<const uint4 *>(xrow + j * 16);
+// Lane offset (bytes from the first row of the tile) of load group `rr / 8`: row rr of the tile, clamped to
+// the last of `total` rows, with the bank swizzle applied on the global side.
+__device__ __forceinline__ uint32_t row_offset(int64_t first, int rr, int64_t total, int64_t ld, int lane)
+{
+    int64_t row = first + rr;
+    row = row < total ? row : total - 1;
+    return (uint32_t)((row - first) * ld * 2 + (((lane & 7) ^ swz_key(rr)) * 16));
+}
+
+// Accumulator i of a 16x16 tile (W rows as the A operand, tokens as the B operand): W row 4 (lane / 16) + i,
+// token lane % 16, i.e. four consecutive columns of one row of Y.
+template <bool OUT_BF16>
+__device__ __forceinline__ void store_quad(const GemmArgs &g, f32x4 v, int64_t m, int64_t n)
+{
+    using T = std::conditional_t<OUT_BF16, __bf16, float>;
+    if (m >= g.M || n >= g.N) return;
+    T *dst = static_cast<T *>(g.y) + m * g.ldy + n;
+    if (n + 3 < g.N) {
+        if constexpr (OUT_BF16) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            *reinterpret_cast<bf16x4 *>(dst) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+        } else {
+            *reinterpret_cast<f32x4 *>(dst) = v;
         }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (n + i < g.N) dst[i] = (T)v[i];
+    }
+}
+
+// Decode batches: a narrow tile per workgroup, its S waves take the 64-wide K steps in turn.
+//
+// What bounds these sizes is the weights' one trip from HBM, and the activations' trips from L2 to
+// the compute units (every workgroup reads its 16 MT tokens for 16 NT rows of W).  Tiles are
+// therefore narrow (a workgroup for every compute unit even at N = 4096) and every byte is fetched in
+// whole 128-byte lines: a lane-per-row load in MFMA operand order touches 64 different lines per
+// instruction and moves a quarter of the bytes per clock (the kernels that this one replaced did
+// that: 64 tokens, K = N = 4096, 22.5 us against 12.2 here; 16 tokens 11.8 against 8.8).  Each wave owns
+// a private ring of two slots in LDS, one K step of X and W rows each, filled by direct-to-LDS loads:
+// no barrier in the K loop, and every byte is read back once, into registers, before the MFMAs of
+// the previous step, after which its slot is refilled at once, so a wave always has between one and
+// two steps of loads in flight (three or four slots: no faster).  The S partial tiles are added through
+// LDS in wave order (bit-identical from run to run).  Measured over the four layers of the 8B shapes,
+// weights from HBM, in us (this kernel / before / one trip of the weights at 5.3 TB/s): 16 tokens
+// 90 / 115 / 82, 48 tokens 112 / 159 / 82, 64 tokens 121 / 170 / 82.
+// g.ksplit > 1: a work item is (K slab, tile), its FP32 partial sums go to g.ws[slab][M][N] and
+// splitk_reduce_kernel adds the slabs in ascending order.
+template <int MT, int NT, int S, bool STREAM, bool OUT_BF16>
+__global__ __launch_bounds__(64 * S) void bf16_ring_kernel(GemmArgs g, int tiles_m, int tiles_n)
+{
+    constexpr int D = 2;                      // slots per wave
+    constexpr int NL = 2 * (MT + NT);         // loads per K step: eight rows each
+    constexpr int SLOT = NL * 1024, NF = MT + NT, T = MT * NT;
+    extern __shared__ uint4 lds[];
+    char *const L = reinterpret_cast<char *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tiles = tiles_m * tiles_n;
+    const int item = logical_id(blockIdx.x, tiles * g.ksplit);
+    const int slab = item / tiles, t = item - slab * tiles;
+    const int64_t m0 = (int64_t)(t % tiles_m) * (16 * MT), n0 = (int64_t)(t / tiles_m) * (16 * NT);
+    const int KT = (int)(g.K / BK);
+    const int SL = (KT + g.ksplit - 1) / g.ksplit;
+    const int s0 = slab * SL < KT ? slab * SL : KT, s1 = s0 + SL < KT ? s0 + SL : KT;
+    const int steps = s1 - s0 > wave ? (s1 - s0 - wave + S - 1) / S : 0;  // of this wave: s0 + wave, + S, ...
+
+    uint32_t vo[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u)
+        vo[u] = u < 2 * MT ? row_offset(m0, u * 8 + (lane >> 3), g.M, g.lda, lane)
+                           : row_offset(n0, (u - 2 * MT) * 8 + (lane >> 3), g.N, g.ldb, lane);
+    const char *const tx = static_cast<const char *>(g.a) + m0 * g.lda * 2;  // m0 < M, n0 < N
+    const char *const tw = static_cast<const char *>(g.b) + n0 * g.ldb * 2;
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)L + wave * (D * SLOT);
+    auto load_step = [&](int i, int slot) {
+        const int k = s0 + wave + i * S;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            if (u < 2 * MT)
+                load_rows_to_lds<false>(ring + slot * SLOT + u * 1024, vo[u], tx + (int64_t)k * (BK * 2));
+            else
+                load_rows_to_lds<STREAM>(ring + slot * SLOT + u * 1024, vo[u], tw + (int64_t)k * (BK * 2));
+        }
+    };
+    const int row = lane & 15, grp = lane >> 4;
+    const int f0 = wave * (D * SLOT) + row * 128 + ((grp ^ swz_key(row)) * 16);
+    const int f1 = wave * (D * SLOT) + row * 128 + (((4 + grp) ^ swz_key(row)) * 16);
+    uint4 fr[2][2][NF];  // [register set][half of the K step][token tiles, then W tiles]
+    auto read_step = [&](int slot, uint4(&f)[2][NF]) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+            f[0][q] = *reinterpret_cast<const uint4 *>(L + f0 + slot * SLOT + q * 2048);
+            f[1][q] = *reinterpret_cast<const uint4 *>(L + f1 + slot * SLOT + q * 2048);
+        }
+    };
+    f32x4 acc[NT][MT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // (steps is uniform over the wave; nothing is loaded past the end: with eight waves on K = 4096 two
+    // idle steps per wave would be a quarter of all loads)
+    if (steps > 0) load_step(0, 0);
+    if (steps > 1) {
+        load_step(1, 1);
+        wait_loads<NL>();
+    } else {
+        wait_loads<0>();
+    }
+    if (steps > 0) read_step(0, fr[0]);
+    // step i: its fragments are in register set i % 2 (or on their way there), its slot is `slot`
+    auto kstep = [&](int i, int slot, auto setc) {
+        constexpr int P = decltype(setc)::value;
+        if (i + D < steps) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // slot read: refill it
+            load_step(i + D, slot);
+            wait_loads<NL>();                                   // the other slot (step i + 1) has landed
+        } else {
+            wait_loads<0>();
+        }
+        if (i + 1 < steps) read_step(slot ^ 1, fr[P ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int t = 0; t < MT; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wq[Q][j]),
-                                                                 __builtin_bit_cast(bf16x8, xf[t][j]), acc[t], 0, 0, 0);
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = 0; b < MT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fr[P][k][MT + a]),
+                                                                        __builtin_bit_cast(bf16x8, fr[P][k][b]),
+                                                                        acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-
-    // prologue: X(s0) into buffer 0; X(s0 + 1 .. s0 + 4) and W(s0 .. s0 + 3) in registers
-    // (issue order pinned: the load counter is in order, and what the loop may leave in flight
-    // follows from the order here)
-    load_x(s0, xa0, xb0);
-    load_w(s0, I0{});
-    __builtin_amdgcn_sched_barrier(0);
-    load_x(s0 + 1, xa1, xb1);
-    load_w(s0 + 1, I1{});
-    __builtin_amdgcn_sched_barrier(0);
-    load_x(s0 + 2, xa2, xb2);
-    load_w(s0 + 2, I2{});
-    __builtin_amdgcn_sched_barrier(0);
-    load_x(s0 + 3, xa3, xb3);
-    load_w(s0 + 3, I3{});
-    __builtin_amdgcn_sched_barrier(0);
-    store_x(I0{}, xa0, xb0);
-    load_x(s0 + 4, xa0, xb0);
-    __builtin_amdgcn_sched_barrier(0);
-    // __syncthreads() would also wait for every global load in flight (it drains the vector-memory
-    // counter), i.e. expose the full HBM latency once per super-step; the barrier here only waits
-    // for this wave's LDS traffic.  The loads return into registers that the compiler tracks itself.
-    auto lds_barrier = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-    lds_barrier();
-    // Super-step st computes from buffer (st - s0) % 2; meanwhile X(st + 1) goes from registers into
-    // the other buffer (everybody left it before the barrier that ended step st - 1), and the
-    // registers just used are refilled four super-steps ahead, X(st + 5) and W(st + 4).  The
-    // hardware counts returning loads in issue order, so a value is only waited for together
-    // with everything issued before it: X, which comes from L2, is therefore fetched as far ahead
-    // as W, or every step would wait for all of the weights in flight.  One barrier per step.
-#define MQ_DECODE_STEP(ST, U, BUF, XA, XB)                                       \
-    if ((ST) < s1) compute(std::integral_constant<int, BUF>{}, U{}); /* uniform */ \
-    store_x(std::integral_constant<int, (BUF) ^ 1>{}, XA, XB);       /* X(st + 1) */ \
-    load_x((ST) + 5, XA, XB);                                                    \
-    load_w((ST) + 4, U{});                                                       \
-    lds_barrier();                                                               \
-    __builtin_amdgcn_sched_barrier(0);
-    for (int st = s0; st < s1; st += 4) {
-        MQ_DECODE_STEP(st, I0, 0, xa1, xb1)
-        MQ_DECODE_STEP(st + 1, I1, 1, xa2, xb2)
-        MQ_DECODE_STEP(st + 2, I2, 0, xa3, xb3)
-        MQ_DECODE_STEP(st + 3, I3, 1, xa0, xb0)
+    int i = 0;
+    for (; i + 1 < steps; i += 2) {
+        kstep(i, 0, std::integral_constant<int, 0>{});
+        kstep(i + 1, 1, std::integral_constant<int, 1>{});
     }
-#undef MQ_DECODE_STEP
+    if (i < steps) kstep(i, 0, std::integral_constant<int, 0>{});
+    __syncthreads();  // every wave is done with its ring: the partial tiles go there
 
-    // accumulator i: W row 4 * grp + i, token lane % 16
-    const int64_t n = n0 + 4 * grp;
+    f32x4 *const X = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        const int64_t m = t * 16 + row;
-        if (m >= g.M || n >= g.N) continue;
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) X[(wave * T + a * MT + b) * 64 + lane] = acc[a][b];
+    __syncthreads();
+    for (int q = wave; q < T; q += S) {
+        f32x4 sum = X[q * 64 + lane];
+        for (int w = 1; w < S; ++w) sum += X[(w * T + q) * 64 + lane];
+        const int64_t m = m0 + (q % MT) * 16 + row, n = n0 + (q / MT) * 16 + 4 * grp;
         if (g.ksplit > 1) {  // unscaled partial sums of this slab (N % 4 == 0 here)
-            *reinterpret_cast<f32x4 *>(g.ws + ((int64_t)slab * g.M + m) * g.N + n) = acc[t];
-            continue;
-        }
-        using T = std::conditional_t<OUT_BF16, __bf16, float>;
-        T *dst = static_cast<T *>(g.y) + m * g.ldy + n;
-        if (n + 3 < g.N) {
-            if constexpr (OUT_BF16) {
-                typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                *reinterpret_cast<bf16x4 *>(dst) =
-                    bf16x4{(__bf16)acc[t][0], (__bf16)acc[t][1], (__bf16)acc[t][2], (__bf16)acc[t][3]};
-            } else {
-                *reinterpret_cast<f32x4 *>(dst) = acc[t];
-            }
+            if (m < g.M && n < g.N) *reinterpret_cast<f32x4 *>(g.ws + ((int64_t)slab * g.M + m) * g.N + n) = sum;
         } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (n + i < g.N) dst[i] = (T)acc[t][i];
+            store_quad<OUT_BF16>(g, sum, m, n);
         }
     }
+}
+
+// From about a hundred tokens: a (16 TM WM) x (16 TN WN) tile per workgroup of WM x WN waves, NST stages of
+// 64-wide K steps in LDS filled by direct-to-LDS loads, one barrier per K step.  Same row layout, swizzle
+// and fragment order as above.  A K step is two phases of 32: the fragments of the next phase are
+// read while the MFMAs of the current one run, the barrier stands in front of the second phase, and
+// the stage it frees receives the K step NST ahead, so NST - 1 steps of loads are in flight at the
+// barrier's wait.  That depth is what the two-stage kernels of the same tiles lacked: their K step
+// waited for HBM (256x128 tile, 2048 tokens, K = 14336, N = 4096: 251 us with two stages, 186 with
+// three; 128x64 tile, 512 tokens: 93 against 211 for a register-staged 128x128 tile with one step of
+// look-ahead).  Beyond 96 to 144 KB of stages nothing is gained.  What bounds them then is the
+// LDS: a tile's bytes are written once at 64 and its fragments read at 128 bytes per clock.
+template <int TM, int TN, int WM, int WN, int NST, bool OUT_BF16>
+__global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, int tiles_m, int tiles_n)
+{
+    constexpr int W = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STAGE = (BM + BN) * 128;
+    constexpr int NLX = BM / 8 / W, NL = (BM + BN) / 8 / W;  // loads per wave and K step: X, all
+    constexpr int NF = TM + TN, NM = TM * TN;
+    static_assert(BM / 8 % W == 0 && BN / 8 % W == 0, "whole loads per wave");
+    extern __shared__ uint4 lds[];
+    char *const L = reinterpret_cast<char *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tm, tn;
+    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    const int wm0 = (wave / WN) * (16 * TM), wn0 = (wave % WN) * (16 * TN);
+    const int KT = (int)(g.K / BK);
+
+    uint32_t vo[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u)
+        vo[u] = u < NLX ? row_offset(m0, (u * W + wave) * 8 + (lane >> 3), g.M, g.lda, lane)
+                        : row_offset(n0, ((u - NLX) * W + wave) * 8 + (lane >> 3), g.N, g.ldb, lane);
+    const char *const tx = static_cast<const char *>(g.a) + m0 * g.lda * 2;  // m0 < M, n0 < N
+    const char *const tw = static_cast<const char *>(g.b) + n0 * g.ldb * 2;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)L;
+    auto load_group = [&](int k, uint32_t stage, int u) {
+        k = k < KT ? k : KT - 1;  // past the end: the last step again, never used
+        load_rows_to_lds<false>(lds0 + stage + (u < NLX ? (u * W + wave) * 1024 : BM * 128 + ((u - NLX) * W + wave) * 1024),
+                                vo[u], (u < NLX ? tx : tw) + (int64_t)k * (BK * 2));
+    };
+    const int row = lane & 15, grp = lane >> 4;
+    int fx[2], fw[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int c = ((4 * k + grp) ^ swz_key(row)) * 16;
+        fx[k] = (wm0 + row) * 128 + c;
+        fw[k] = BM * 128 + (wn0 + row) * 128 + c;
+    }
+    uint4 fr[2][NF];
+    auto read_frag = [&](uint32_t stage, int k, int q) {
+        return *reinterpret_cast<const uint4 *>(L + stage + (q < TM ? fx[k] + q * 2048 : fw[k] + (q - TM) * 2048));
+    };
+    f32x4 acc[TN][TM];
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // The MFMAs on fragments f; between them the fragments of half `k` of `stage` into nf, and (LOAD) the
+    // loads of K step kl into `lstage`, both spread evenly.
+    auto phase = [&](const uint4(&f)[NF], uint4(&nf)[NF], int k, uint32_t stage, int kl, uint32_t lstage, auto loadc) {
+        constexpr bool LOAD = decltype(loadc)::value;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) {
+#pragma unroll
+            for (int q = n * NF / NM; q < (n + 1) * NF / NM; ++q) nf[q] = read_frag(stage, k, q);
+            if constexpr (LOAD)
+#pragma unroll
+                for (int u = n * NL / NM; u < (n + 1) * NL / NM; ++u) load_group(kl, lstage, u);
+            acc[n / TM][n % TM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[TM + n / TM]),
+                                                                          __builtin_bit_cast(bf16x8, f[n % TM]),
+                                                                          acc[n / TM][n % TM], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < NST; ++d)
+#pragma unroll
+        for (int u = 0; u < NL; ++u) load_group(d, d * STAGE, u);
+    wait_loads<(NST - 1) * NL>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < NF; ++q) fr[0][q] = read_frag(0, 0, q);
+    uint32_t cur = 0;
+    for (int k = 0; k < KT; ++k) {
+        const uint32_t nxt = cur + STAGE < NST * STAGE ? cur + STAGE : 0;
+        phase(fr[0], fr[1], 1, cur, 0, 0, std::false_type{});
+        // K step k + 1 has landed in this wave's share of stage nxt, after the barrier in everyone's, and
+        // nobody reads stage cur any more (the waits cover this wave's last fragment reads of it)
+        wait_loads<(NST - 2) * NL>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        phase(fr[1], fr[0], 0, nxt, k + NST, cur, std::true_type{});
+        cur = nxt;
+    }
+    wait_loads<0>();  // the loads past the end still target LDS
+
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+            store_quad<OUT_BF16>(g, acc[a][b], m0 + wm0 + b * 16 + row, n0 + wn0 + a * 16 + 4 * grp);
 }
 
 // ---- fallback for K not a multiple of 64: one thread per output, exact products ---------------
@@ -1446,43 +1318,93 @@ int launch_simple(const GemmArgs &g, hipStream_t s)
     return note_launch(hipGetLastError());
 }
 
-// Token tiles by M.  Row tiles per wave, measured on N = 4096 .. 28672: more than one pays only
-// while the grid keeps every CU busy several times over, and not for a single token (whose
-// activations come from L1 anyway).
-template <bool OUT_BF16>
-int launch_skinny(const GemmArgs &g, hipStream_t s)
+// ---- which BF16 kernel and tile ---------------------------------------------------------------------
+
+// The tiles (tokens x rows of W) that the BF16 kernels are built in.  step: measured time of one 64-wide K
+// step of one round of workgroups (one per compute unit) in ns, as far as it does not overlap with
+// the weights' trip from HBM.
+enum Bf16Kernel { BF16_RING, BF16_STAGE, BF16_D2L };
+struct Bf16Tile {
+    Bf16Kernel kernel;
+    int bm, bn, step;
+};
+#define MQ_RING(X) /* MT, NT, S, step */                                                                     \
+    X(1, 1, 8, 66) X(1, 2, 4, 99) X(1, 4, 4, 174) X(2, 1, 8, 94) X(2, 2, 4, 112) X(2, 4, 4, 196) \
+    X(3, 2, 4, 138) X(3, 4, 4, 217) X(4, 2, 4, 168) X(4, 4, 4, 228)
+#define MQ_STAGE(X) /* TM, TN, WM, WN, NST, step */                                                          \
+    X(3, 2, 2, 2, 6, 311) X(4, 2, 2, 2, 4, 362) X(3, 4, 2, 2, 4, 447) X(4, 2, 2, 4, 4, 511) \
+    X(5, 4, 2, 2, 4, 593) X(7, 4, 2, 2, 3, 727) X(8, 4, 2, 2, 3, 804) X(8, 6, 2, 2, 2, 1168)
+static constexpr Bf16Tile kBf16Tiles[] = {
+#define MQ_X(MT, NT, S, STEP) {BF16_RING, 16 * MT, 16 * NT, STEP},
+    MQ_RING(MQ_X)
+#undef MQ_X
+#define MQ_X(TM, TN, WM, WN, NST, STEP) {BF16_STAGE, 16 * TM * WM, 16 * TN * WN, STEP},
+    MQ_STAGE(MQ_X)
+#undef MQ_X
+    {BF16_D2L, 256, 256, 1440}};
+
+struct Bf16Plan {
+    int tile;   // index into kBf16Tiles
+    int slabs;  // K slabs across workgroups (1: none)
+};
+
+// The tile that costs least.  Two things take the time: the weights' one trip from HBM (5.3 TB/s), and the
+// K steps of the rounds of workgroups; the smaller one hides behind the larger one almost entirely.  A
+// workgroup's first loads, sums and stores cost it seven more steps, and more tiles than compute units
+// cost whole rounds, so a tile shape that leaves a nearly empty last round loses to one that does
+// not.  The steps and these constants are fitted to every tile's time on 160 shapes (1 to 5000 tokens,
+// the 8B and 32B layers and their 2-, 4- and 8-way shards; weights and activations from HBM): the
+// choice is on average 0.6 % slower than the fastest tile, at worst 9 %.  Slabs, when the caller's workspace allows some, shorten the K loop
+// for a second pass of 3 us (64 tokens, K = 14336, N = 4096: 30.8 us against 36.4 without and 48.5 in the
+// kernel before this one; 33 to 57 tokens 27 to 30 us against 45 to 48).
+static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, int cus)
 {
-    const int mt = (int)((g.M + 15) / 16);
-    const int rt = g.M <= 4 ? 1 : g.N >= 24576 ? 4 : g.N >= 6144 ? 2 : 1;
-    const dim3 grid((unsigned)((g.N + 16 * rt - 1) / (16 * rt))), block(512);
-#define MQ_SKINNY(MT_, RT_) bf16_skinny_kernel<MT_, RT_, (MT_ + RT_ <= 5), OUT_BF16><<<grid, block, 0, s>>>(g)
-#define MQ_SKINNY_RT(MT_) (rt == 4 ? MQ_SKINNY(MT_, 4) : rt == 2 ? MQ_SKINNY(MT_, 2) : MQ_SKINNY(MT_, 1))
-    if (mt == 1)
-        MQ_SKINNY_RT(1);
-    else if (mt == 2)
-        MQ_SKINNY_RT(2);
-    else if (mt == 3)
-        MQ_SKINNY_RT(3);
-    else
-        MQ_SKINNY_RT(4);
-#undef MQ_SKINNY_RT
-#undef MQ_SKINNY
-    return note_launch(hipGetLastError());
+    const double kt = (double)(K / BK), hbm = 2.0 * (double)N * (double)K / 5.3e6;
+    Bf16Plan best{0, 1};
+    double best_us = 1e300;
+    for (int i = 0; i < (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); ++i) {
+        const Bf16Tile &t = kBf16Tiles[i];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (tiles > 0x7FFFFFFF) continue;
+        int64_t slabs = 1;
+        for (;;) {
+            const double steps = (double)((tiles * slabs + cus - 1) / cus) * (kt / (double)slabs + 7.0);
+            const double loop = steps * t.step * 1e-3;
+            const double us = (hbm > loop ? hbm + 0.015 * loop : loop + 0.015 * hbm) + (slabs > 1 ? 3.0 : 0.0);
+            if (us < best_us) best_us = us, best = Bf16Plan{i, (int)slabs};
+            if (slabs > 1 || t.kernel != BF16_RING || slab_limit < 2 || 2 * tiles > cus) break;
+            slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
+        }
+    }
+    return best;
 }
 
-// 17 .. 64 tokens with K % 128 == 0 and the row stride rules of the decode kernel.
-template <bool OUT_BF16>
-int launch_decode(const GemmArgs &g0, hipStream_t s, int slabs)
+template <int MT, int NT, int S>
+constexpr size_t ring_lds()
+{
+    constexpr size_t ring = (size_t)S * 2 * (MT + NT) * 2048, sums = (size_t)S * MT * NT * 1024;
+    return ring > sums ? ring : sums;
+}
+template <int TM, int TN, int WM, int WN, int NST>
+constexpr size_t stage_lds()
+{
+    return (size_t)NST * (16 * TM * WM + 16 * TN * WN) * 128;
+}
+
+template <int MT, int NT, int S, bool OUT_BF16>
+int launch_ring(const GemmArgs &g0, hipStream_t s, int slabs)
 {
     GemmArgs g = g0;
     g.ksplit = slabs;
-    const int64_t row_groups = (g.N + 127) / 128;
-    if (row_groups * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    const dim3 grid((unsigned)(row_groups * slabs)), block(512);
-    if (g.M <= 32)
-        bf16_decode_kernel<2, OUT_BF16><<<grid, block, 0, s>>>(g, (int)row_groups);
+    const int64_t tiles_m = (g.M + 16 * MT - 1) / (16 * MT), tiles_n = (g.N + 16 * NT - 1) / (16 * NT);
+    if (tiles_m * tiles_n * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    const dim3 grid((unsigned)(tiles_m * tiles_n * slabs)), block(64 * S);
+    // W rows are read by the workgroups of tiles_m tiles: non-temporal only when that is one (two percent
+    // faster then, slower when the second reader finds the lines gone from L2)
+    if (tiles_m == 1)
+        bf16_ring_kernel<MT, NT, S, true, OUT_BF16><<<grid, block, ring_lds<MT, NT, S>(), s>>>(g, (int)tiles_m, (int)tiles_n);
     else
-        bf16_decode_kernel<4, OUT_BF16><<<grid, block, 0, s>>>(g, (int)row_groups);
+        bf16_ring_kernel<MT, NT, S, false, OUT_BF16><<<grid, block, ring_lds<MT, NT, S>(), s>>>(g, (int)tiles_m, (int)tiles_n);
     int rc = note_launch(hipGetLastError());
     if (rc != MQ_OK || slabs == 1) return rc;
     const int64_t quads = g.M * (g.N / 4);
@@ -1490,27 +1412,38 @@ int launch_decode(const GemmArgs &g0, hipStream_t s, int slabs)
     return note_launch(hipGetLastError());
 }
 
+template <bool OUT_BF16>
+int launch_bf16(const GemmArgs &g, hipStream_t s)
+{
+    int cus = 0;
+    if (int rc = compute_units(cus)) return rc;
+    const Bf16Plan plan = bf16_plan(g.M, g.N, g.K, gemm_bf16_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
+    int i = 0;
+#define MQ_X(MT, NT, S, STEP) \
+    if (plan.tile == i++) return launch_ring<MT, NT, S, OUT_BF16>(g, s, plan.slabs);
+    MQ_RING(MQ_X)
+#undef MQ_X
+#define MQ_X(TM, TN, WM, WN, NST, STEP)                                                                              \
+    if (plan.tile == i++)                                                                                            \
+        return launch_tiles(bf16_stage_kernel<TM, TN, WM, WN, NST, OUT_BF16>, stage_lds<TM, TN, WM, WN, NST>(),      \
+                            16 * TM * WM, 16 * TN * WN, 64 * WM * WN, g, s);
+    MQ_STAGE(MQ_X)
+#undef MQ_X
+    using D = PCfg<256, 256, 2, 2>;
+    return launch_tiles(gemm_bf16_d2l<D, OUT_BF16>, D::LDS_BYTES, 256, 256, D::THREADS, g, s);
+}
+
 template <bool FP4, bool OUT_BF16>
 int launch_any(const GemmArgs &g, hipStream_t s)
 {
     if (g.M == 0 || g.N == 0) return MQ_OK;
-    if constexpr (!FP4) {
-        // decode shapes: a few tokens against the whole weight matrix
-        if (g.M > 16 && g.M <= 64 && g.K % 128 == 0) {
-            int cus = 0;
-            if (int rc = compute_units(cus)) return rc;
-            const int slabs = gemm_bf16_decode_slabs(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus);
-            if (slabs > 0) return launch_decode<OUT_BF16>(g, s, slabs);
-        }
-        if (g.M <= 64 && g.K % 128 == 0 && (g.N + 15) / 16 <= 0x7FFFFFFF) return launch_skinny<OUT_BF16>(g, s);
-    }
     // The tiled kernels step K by 64.
     if (g.K % BK != 0) return launch_simple<FP4, OUT_BF16>(g, s);
-    const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-    using Mid = PCfg<256, 128, 2, 2>;   // BF16 only: 4 waves of 128x64
-    using Small = PCfg<128, 128, 2, 2>;  // BF16 only: 4 waves of 64x64
-    const int64_t mid_tiles = ((g.M + 255) / 256) * ((g.N + 127) / 128);
-    if constexpr (FP4) {
+    if constexpr (!FP4) {
+        return launch_bf16<OUT_BF16>(g, s);
+    } else {
+        const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+        const int64_t mid_tiles = ((g.M + 255) / 256) * ((g.N + 127) / 128);
         // Three workgroup shapes: 256x256 (whole K per wave), 256x128 with K split over wave
         // pairs, 128x128 with K split over the four waves; once the 128x128 tiles fill at least
         // half of the chip, the one whose rounds of workgroups cost least wins, a split workgroup
@@ -1566,19 +1499,6 @@ int launch_any(const GemmArgs &g, hipStream_t s)
             return launch_variant(best_b, gb);
         }
         return launch_variant(one, g);
-    } else {
-        // Same choice by rounds of workgroups as above: 256x256 tiles, or 256x128 tiles (half the
-        // work per workgroup, somewhat less efficient) when they waste less of the last round;
-        // 128x128 register-staged tiles for small problems.
-        int cus = 0;
-        if (int rc = compute_units(cus)) return rc;
-        const int64_t r1 = (big_tiles + cus - 1) / cus, r2 = (mid_tiles + cus - 1) / cus;
-        using D = PCfg<256, 256, 2, 2>;
-        if (2 * mid_tiles >= cus && 100 * r1 > 58 * r2)
-            return launch_tiles(gemm_bf16_d2l<Mid, OUT_BF16>, Mid::LDS_BYTES, 256, 128, Mid::THREADS, g, s);
-        if (2 * mid_tiles >= cus)
-            return launch_tiles(gemm_bf16_d2l<D, OUT_BF16>, D::LDS_BYTES, 256, 256, D::THREADS, g, s);
-        return launch_tiles(gemm_bf16_pipelined<Small, OUT_BF16>, Small::LDS_BYTES, 128, 128, Small::THREADS, g, s);
     }
 }
 
@@ -1594,8 +1514,6 @@ int configure_gemm_kernels()
                                    (int)bytes);
     };
     using D = PCfg<256, 256, 2, 2>;
-    using Mid = PCfg<256, 128, 2, 2>;
-    using Small = PCfg<128, 128, 2, 2>;
     constexpr size_t X = 128 * 1024;  // accumulator exchange of the K-split variants
     hipError_t e = hipSuccess;
     auto both = [&](auto k_bf16, auto k_fp32, size_t bytes) {
@@ -1606,8 +1524,16 @@ int configure_gemm_kernels()
     both(gemm_fp4_direct<true, 4>, gemm_fp4_direct<false, 4>, X);
     both(gemm_fp4_small<2, 2, 8, 4, true>, gemm_fp4_small<2, 2, 8, 4, false>, X);
     both(gemm_bf16_d2l<D, true>, gemm_bf16_d2l<D, false>, D::LDS_BYTES);
-    both(gemm_bf16_d2l<Mid, true>, gemm_bf16_d2l<Mid, false>, Mid::LDS_BYTES);
-    both(gemm_bf16_pipelined<Small, true>, gemm_bf16_pipelined<Small, false>, Small::LDS_BYTES);
+#define MQ_X(MT, NT, S, STEP)                                                                                        \
+    both(bf16_ring_kernel<MT, NT, S, true, true>, bf16_ring_kernel<MT, NT, S, true, false>, ring_lds<MT, NT, S>()); \
+    both(bf16_ring_kernel<MT, NT, S, false, true>, bf16_ring_kernel<MT, NT, S, false, false>, ring_lds<MT, NT, S>());
+    MQ_RING(MQ_X)
+#undef MQ_X
+#define MQ_X(TM, TN, WM, WN, NST, STEP)                                                               \
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false>, \
+         stage_lds<TM, TN, WM, WN, NST>());
+    MQ_STAGE(MQ_X)
+#undef MQ_X
     return note_launch(e);
 }
 
@@ -1639,21 +1565,15 @@ SmallPlan gemm_fp4_small_plan(int64_t M, int64_t N, int64_t K, int64_t ws_bytes,
     return plan;
 }
 
-// K slabs for the decode-batch BF16 kernel (17 .. 64 tokens), given this much workspace; 0: the
-// kernel does not serve the problem, 1: no slabs.  Measured on N = 4096 .. 28672 (us per launch,
-// this kernel / the K-split kernel above): a wide N (at least CUs/2 row groups of 128) needs no
-// slabs: gate_up 41.5 / 69.5 at 64 tokens, 38.3 / 51.1 at 32.  A narrow N needs slabs, i.e. a
-// workspace and a second pass of about 5 us, which pays above 32 tokens with a long K (down,
-// K = 14336: 42.6 / 63.4 at 64 tokens, 40.7 / 51.6 at 48) and not otherwise (K = 4096 at 48 tokens:
-// o 16.1 / 17.0 but qkv 26.1 / 21.6; o at 32 tokens 14.5 / 13.3).  Slabs fill about two workgroups
-// per compute unit, keep at least four 128-wide super-steps each, and keep the partial sums'
-// traffic (8 bytes per output and slab) below half of the weights'.
-int gemm_bf16_decode_slabs(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
+// Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none).
+// Only decode batches of 33 to 64 tokens with a long K and a narrow N can gain from a second pass; there
+// are never more than two work items per compute unit, every slab keeps 512 of K, and the partial sums'
+// traffic (8 bytes per output and slab) stays below half of the weights'.
+int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
-    if (M <= 16 || M > 64 || N <= 0 || K <= 0 || K % 128 != 0) return 0;
+    if (M <= 32 || M > 64 || N <= 0 || K < 8192 || K % 128 != 0) return 0;
     const int64_t groups = (N + 127) / 128, steps = K / 128;
-    if (2 * groups >= cus) return 1;
-    if (M <= 32 || K < 8192 || ws_bytes <= 0 || N % 4 != 0) return 0;
+    if (2 * groups >= cus || ws_bytes <= 0 || N % 4 != 0) return 0;
     int64_t ks = 2 * cus / groups;
     if (ks > steps / 4) ks = steps / 4;
     if (ks > K / (8 * M)) ks = K / (8 * M);

@@ -1,0 +1,49 @@
+"""GPU parity of the BF16 product at one problem per tile shape of its two kernels for decode batches
+and middle sizes (the waves' private rings, the staged tiles), each with ragged M and N, strided
+operands and output, and K of one step up to a few more than the stages or waves, so that prologues,
+idle waves, tails and uneven K shares all run.  Every output is compared with the oracle's FP64
+product; nothing outside [M, N] may be written."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_20315_amd as mq
+from paper_2605_20315_amd import workloads as wl
+
+from _gpu_util import check_gemm_bf16, check_gemm_fp32, dev_bf16, host_bits
+
+pytestmark = pytest.mark.gpu
+
+# tile (tokens x rows of W) on 256 compute units: 16x16 with eight waves (K of 1, 8 and 9 steps), 16x32,
+# 16x64, 32x16, 32x32 (twice), 32x64, 48x32, 48x64, 64x32, 64x64 (K of 5 and 2 steps); staged: 96x64 (K of 7
+# steps and of 2, six stages), 96x128, 128x64, 128x128, 160x128, 224x128, 256x128, 256x192, 256x256;
+# 64x32 with K slabs
+SHAPES = [(1, 8, 64), (3, 40, 512), (16, 1000, 576), (16, 4099, 448), (9, 9000, 128), (2085, 17, 320),
+          (17, 4255, 640), (2729, 33, 192), (65, 4151, 320), (35, 4122, 704), (65, 5834, 448), (49, 4258, 320),
+          (98, 5604, 320), (98, 5604, 128), (129, 5850, 448), (129, 5850, 128), (269, 5655, 192), (207, 5442, 320),
+          (398, 6545, 448), (652, 5426, 192), (667, 6602, 128), (899, 6590, 256), (1327, 7183, 192), (1809, 6157, 64),
+          (61, 4100, 8320)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_bf16_tile_shapes_against_oracle(M, N, K):
+    print(f"\n[case] bf16 tiles M={M} N={N} K={K}", flush=True)
+    rng = np.random.default_rng([M, N, K])
+    x = wl.f32_to_bf16_bits(rng.standard_normal((M, K + 8)).astype(np.float32))
+    w = wl.f32_to_bf16_bits((rng.standard_normal((N, K + 24)) * K ** -0.5).astype(np.float32))
+    a, b = oracle.bf16_to_f64(np.ascontiguousarray(x[:, :K])), oracle.bf16_to_f64(np.ascontiguousarray(w[:, :K]))
+    ref, na, nb = oracle.gemm_f64(a, b), oracle.row_norms(a), oracle.row_norms(b)
+    xd, wd = dev_bf16(x)[:, :K], dev_bf16(w)[:, :K]
+    ld = (N + 7) // 8 * 8 + 8
+    ws = torch.empty(max(mq.mq_bf16_gemm_workspace_bytes(M, N, K), 16), dtype=torch.uint8, device="cuda")
+    b32 = torch.full((M + 1, ld), -7.0, dtype=torch.float32, device="cuda")
+    b16 = torch.full((M + 1, ld), -7.0, dtype=torch.bfloat16, device="cuda")
+    y32 = mq.bf16_gemm_ws(xd, wd, ws, mq.MQ_OUT_FP32, b32[:M, :N])
+    y16 = mq.bf16_gemm_ws(xd, wd, ws, mq.MQ_OUT_BF16, b16[:M, :N])
+    torch.cuda.synchronize()
+    check_gemm_fp32(y32.cpu().numpy(), ref, na, nb)
+    check_gemm_bf16(host_bits(y16), ref, na, nb)
+    assert torch.equal(y32.to(torch.bfloat16), y16)
+    for buf in (b32, b16):
+        assert bool((buf[M:] == -7.0).all()) and bool((buf[:, N:] == -7.0).all())
