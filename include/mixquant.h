@@ -16,7 +16,7 @@
  *    anything is launched: with any status but MQ_ERR_HIP nothing has been enqueued.
  *    MQ_ERR_HIP means the HIP runtime refused a launch (mq_last_hip_error() returns its
  *    hipError_t); an entry point that launches several kernels (nvfp4_global_scale, a product
- *    cut into K slabs or into two column ranges) may then have enqueued the earlier ones, and
+ *    cut into K slabs or into two parts of Y) may then have enqueued the earlier ones, and
  *    its outputs are undefined.
  *  - One-time set-up per device (kernel attributes, the address of the static scratch array):
  *    done by mq_init(), or else by the first product on that device.  A caller that captures

@@ -168,8 +168,8 @@ static constexpr int kMaxComputeUnits = 256;
 int64_t mq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    const SmallPlan plan = gemm_fp4_small_plan(M, N, K, INT64_MAX, kMaxComputeUnits);
-    return plan.waves > 0 && plan.slabs >= 2 ? (int64_t)plan.slabs * M * N * 4 : 0;
+    const int ks = gemm_fp4_slab_limit(M, N, K, INT64_MAX, kMaxComputeUnits);
+    return ks >= 2 ? (int64_t)ks * M * N * 4 : 0;
 }
 
 int mq_init(void) { return ensure_device(nullptr); }

@@ -19,9 +19,10 @@
 //                       registers (described at the kernel).  A 256x256 tile, a 256x128 tile
 //                       with K split over wave pairs, or a 128x128 tile with K split over all
 //                       four waves.
-//   gemm_fp4_small      NVFP4 problems of up to 2 x CUs tiles of 64x64 (a few hundred tokens): one
-//                       workgroup per tile, K split over its waves; for a long K with very few
-//                       tiles also over workgroups (splitk_reduce_kernel then adds the slabs).
+//   gemm_fp4_small      NVFP4 problems of up to a thousand tokens or so, and what whole rounds of the tiles
+//                       above leave over: 32x32 to 128x64 tiles, one workgroup per tile, K split over
+//                       its waves; for a long K with very few tiles also over workgroups
+//                       (splitk_reduce_kernel then adds the slabs).
 //   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256 tile, four waves of 128x128,
 //                       tiles loaded from global memory straight into LDS.
 //   bf16_ring_kernel    BF16 decode batches: narrow tiles, the waves of a workgroup split K, each with a
@@ -476,42 +477,36 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
     }
 }
 
-// ---- NVFP4, register-direct, small tiles: prefill chunks of 64 .. 1024 tokens -------------------
+// ---- NVFP4, register-direct, small tiles: prefill chunks up to a thousand tokens or so ---------------
 
 // With a few hundred tokens the 128x128 wave tiles above are too few to occupy the chip, and the
 // time of a layer is launch latency plus one trip of the weights from HBM.  Here a workgroup owns
-// one (32 TM) x (32 TN) output tile; its S waves (S chosen at launch, S <= MAXS) take consecutive
-// parts of K and each runs the same register-direct K loop as above (operands loaded in MFMA
-// order, expanded in registers, no LDS and no barrier in the loop) with NSETS K steps of codes in
-// flight per wave.  The S partial tiles are then added through LDS in a fixed order (wave 0, 1,
-// ...: bit-identical from run to run), each wave summing, scaling, rounding and storing 1/S of the
-// tile.  No workspace and no second kernel: one launch per layer.  Only a long K with very few
-// tiles is also cut into g.ksplit slabs across workgroups when the caller passes a workspace: a
-// work item is then (slab, tile), its workgroup writes unscaled FP32 partial sums to
-// g.ws[slab][M][N], and splitk_reduce_kernel adds the slabs in ascending order.  Smaller wave tiles raise the
-// conversion work per MFMA (TM + TN operand tiles expanded for TM x TN MFMAs: 8 VALU instructions
-// per MFMA for 64x64, 6 for 128x64) but multiply the number of waves that pull on memory.
-template <int TM_, int TN_>
-struct SmallCfg {
-    static constexpr int TM = TM_, TN = TN_, WN = 32 * TN_;
-};
-
+// one (32 TM) x (32 TN) output tile; its S waves (4 or 8) take consecutive parts of K and each runs
+// the same register-direct K loop as above (operands loaded in MFMA order, expanded in registers, no
+// LDS and no barrier in the loop) with NSETS K steps of codes in flight per wave.  The S partial tiles
+// are then added through LDS in a fixed order (wave 0, 1, ...: bit-identical from run to run), each
+// wave summing, scaling, rounding and storing 1/S of the tile.  One launch per layer, no workspace;
+// with one, a long K may also be cut into g.ksplit slabs across workgroups: a work item is then (slab,
+// tile), its workgroup writes unscaled FP32 partial sums to g.ws[slab][M][N], and
+// splitk_reduce_kernel adds the slabs in ascending order.
+// What bounds it: MFMAs for 64x64 tiles and larger, the expansion below (16 vector instructions per
+// MFMA for 32x32, 8 for 64x64, 6 for 128x64); but a 32x32 tile gives every compute unit work where a
+// 64x64 tile leaves three quarters of them idle (64 tokens, K = N = 4096: 7.0 us against 11.6; K =
+// 14336: 15.6 against 18.7 with K slabs), and 64x128 tiles, two workgroups of four waves to a compute unit,
+// hide each other's sums and stores, which the one-workgroup kernel above cannot (560 tokens on N =
+// 28672: 104 us against 140).  Two waves per SIMD throughout (at most 256 registers).
 // End of the small-tile kernels: the S waves of a workgroup hold partial sums of one
-// (32 TM) x (32 TN) tile over their parts of K.  S == 1: plain epilogue.  Otherwise the partial
+// (32 TM) x (32 TN) tile over their parts of K.  The partial
 // tiles are added through LDS, four 32x32 tiles (16 KB per wave) per pass.  A pass holds 16 chunks
 // of four accumulator registers per wave; wave w adds the S copies of chunks w, w + S, ... in
 // wave order (bit-identical from run to run), scales, rounds and stores them: chunk c of a tile =
 // rows 8c + 4 (lane / 32) .. + 3, column lane % 32.
-template <int TM, int TN, bool OUT_BF16>
+template <int TM, int TN, int S, bool OUT_BF16>
 __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&acc)[TM][TN], float scale, int64_t m0,
-                                                  int64_t n0, int S, int wave, int lane)
+                                                  int64_t n0, int wave, int lane)
 {
     constexpr int NM = TM * TN;
     const int frow = lane & 31, fhalf = lane >> 5;
-    if (S == 1) {
-        epilogue<SmallCfg<TM, TN>, OUT_BF16>(g, acc, scale, m0, n0, 0, 0, frow, fhalf);
-        return;
-    }
     extern __shared__ uint4 lds[];
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     f32x4 *const X = reinterpret_cast<f32x4 *>(lds);
@@ -528,9 +523,16 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
                 X[((wave * PASS + u) * 4 + c) * 64 + lane] = f32x4{tl[4 * c], tl[4 * c + 1], tl[4 * c + 2], tl[4 * c + 3]};
         }
         __syncthreads();
-        for (int ch = wave; ch < PASS * 4; ch += S) {
-            f32x4 sum = X[ch * 64 + lane];
-            for (int w = 1; w < S; ++w) sum += X[(w * PASS * 4 + ch) * 64 + lane];
+#pragma unroll
+        for (int ch0 = 0; ch0 < PASS * 4; ch0 += S) {
+            const int ch = ch0 + wave;
+            if (PASS * 4 % S != 0 && ch >= PASS * 4) break;  // uniform
+            f32x4 part[S];  // all reads in flight, then the additions in wave order
+#pragma unroll
+            for (int w = 0; w < S; ++w) part[w] = X[(w * PASS * 4 + ch) * 64 + lane];
+            f32x4 sum = part[0];
+#pragma unroll
+            for (int w = 1; w < S; ++w) sum += part[w];
             const int tile = p0 + (ch >> 2), c = ch & 3;
             const int64_t n = n0 + (tile % TN) * 32 + frow;
             const int64_t mrow = m0 + (tile / TN) * 32 + 8 * c + 4 * fhalf;
@@ -543,14 +545,13 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
     }
 }
 
-template <int TM, int TN, int MAXS, int NSETS, bool OUT_BF16>
-__global__ __launch_bounds__(64 * MAXS) void gemm_fp4_small(GemmArgs g, int tiles_m, int tiles_n)
+template <int TM, int TN, int S, int NSETS, bool OUT_BF16>
+__global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) void gemm_fp4_small(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int NT = TM + TN;
     static_assert((TM * TN) % 4 == 0 || TM * TN < 4, "the LDS reduction moves four 32x32 tiles per pass");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int S = (int)(blockDim.x >> 6);  // waves that share this tile's K range
     const int frow = lane & 31, fhalf = lane >> 5;
     const int KT = (int)(g.K / BK);
     // work item = (K slab, tile), slab-major; tiles that share a column panel of B are neighbours
@@ -585,8 +586,8 @@ __global__ __launch_bounds__(64 * MAXS) void gemm_fp4_small(GemmArgs g, int tile
     uint4 rc[NSETS][NT];     // this lane's 32 codes of each operand tile, NSETS K steps
     uint32_t rs[NSETS][NT];  // the rows' four E4M3 scale bytes
     // K steps are loaded in ascending order, so the four K-step bases advance by their strides
-    // (scalar additions) instead of being recomputed by 64-bit multiplications; a step past the
-    // end of K re-reads the last one (its products are multiplied by zero scales).
+    // (scalar additions) instead of being recomputed by 64-bit multiplications; loads past the
+    // wave's last step re-read that step (from L1; its products are multiplied by zero scales).
     int next_t = k0 < KT ? k0 : KT - 1;
     const char *pa_c = ta_c + (int64_t)next_t * g.a_c_step, *pb_c = tb_c + (int64_t)next_t * g.b_c_step;
     const char *pa_s = ta_s + (int64_t)next_t * g.a_s_step, *pb_s = tb_s + (int64_t)next_t * g.b_s_step;
@@ -602,7 +603,7 @@ __global__ __launch_bounds__(64 * MAXS) void gemm_fp4_small(GemmArgs g, int tile
             rc[R][q] = make_uint4(c[0], c[1], c[2], c[3]);
             rs[R][q] = __builtin_amdgcn_raw_buffer_load_b32(q < TM ? ras : rbs, (int)vs[q], 0, 0);
         }
-        const int64_t adv = next_t + 1 < KT ? -1 : 0;  // all ones while K steps remain (no branch in the loop)
+        const int64_t adv = next_t + 1 < k1 ? -1 : 0;  // all ones while K steps remain (no branch in the loop)
         next_t -= (int)adv;
         pa_c += g.a_c_step & adv, pb_c += g.b_c_step & adv, pa_s += g.a_s_step & adv, pb_s += g.b_s_step & adv;
     };
@@ -678,7 +679,7 @@ __global__ __launch_bounds__(64 * MAXS) void gemm_fp4_small(GemmArgs g, int tile
         if constexpr (NSETS > 2) fn(std::integral_constant<int, 2>{});
         if constexpr (NSETS > 3) fn(std::integral_constant<int, 3>{});
     };
-    static_assert(NSETS >= 1 && NSETS <= 4, "one to four K steps in flight");
+    static_assert(NSETS >= 2 && NSETS <= 4, "two to four K steps in flight");
     // The first NSETS K steps, issued set by set.  (Left to the scheduler, the B loads of all sets
     // went last, and the counter the compiler waits on in the loop then demanded that nearly
     // everything in flight had landed before each K step: a prefetch distance of one step, not three.)
@@ -689,16 +690,17 @@ __global__ __launch_bounds__(64 * MAXS) void gemm_fp4_small(GemmArgs g, int tile
     const float scale = (*g.a_alpha) * (*g.b_alpha);
     prep_scales(std::integral_constant<int, 0>{}, k0 < k1);
     expand_phase(std::integral_constant<int, 0>{}, 0, fr[0]);
-    // whole groups of NSETS K steps; a step past the end multiplies by zero scales
+    // whole groups of NSETS K steps; a step past the end multiplies by zero scales (leaving the loop in the
+    // middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower)
     for (int kt = k0; kt < k1; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u); });
 
     if (g.ksplit > 1) {
         GemmArgs part = g;  // the slab's [M, N] FP32 matrix of partial sums; splitk_reduce_kernel scales and rounds
         part.y = g.ws + (int64_t)slab * g.M * g.N;
         part.ldy = g.N;
-        small_tile_finish<TM, TN, false>(part, acc, 1.0f, m0, n0, S, wave, lane);
+        small_tile_finish<TM, TN, S, false>(part, acc, 1.0f, m0, n0, wave, lane);
     } else {
-        small_tile_finish<TM, TN, OUT_BF16>(g, acc, scale, m0, n0, S, wave, lane);
+        small_tile_finish<TM, TN, S, OUT_BF16>(g, acc, scale, m0, n0, wave, lane);
     }
 }
 
@@ -1289,19 +1291,23 @@ int launch_persistent(Kern kern, int bm, int bn, size_t lds_bytes, const GemmArg
     return note_launch(hipGetLastError());
 }
 
-// One workgroup of S waves per (32 TM) x (32 TN) tile.
-template <int TM, int TN, int MAXS, int NSETS, bool OUT_BF16>
-int launch_small(const GemmArgs &g0, hipStream_t s, SmallPlan plan)
+template <int TM, int TN, int S>
+constexpr size_t small_lds()
 {
-    const int S = plan.waves;
+    return (size_t)S * (TM * TN < 4 ? TM * TN : 4) * 4096;
+}
+
+// One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
+template <int TM, int TN, int S, int NSETS, bool OUT_BF16>
+int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
+{
     GemmArgs g = g0;
-    g.ksplit = plan.slabs;
+    g.ksplit = slabs;
     const int64_t tiles_m = (g.M + 32 * TM - 1) / (32 * TM), tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
-    if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF || S < 1 || S > MAXS || g.ksplit < 1) return MQ_ERR_SHAPE;
-    constexpr int PASS = TM * TN < 4 ? TM * TN : 4;
-    const size_t lds = S > 1 ? (size_t)S * PASS * 4096 : 0;
-    gemm_fp4_small<TM, TN, MAXS, NSETS, OUT_BF16>
-        <<<dim3((unsigned)(tiles_m * tiles_n * g.ksplit)), dim3(64 * S), lds, s>>>(g, (int)tiles_m, (int)tiles_n);
+    if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16>
+        <<<dim3((unsigned)(tiles_m * tiles_n * g.ksplit)), dim3(64 * S), small_lds<TM, TN, S>(), s>>>(g, (int)tiles_m,
+                                                                                                 (int)tiles_n);
     int rc = note_launch(hipGetLastError());
     if (rc != MQ_OK || g.ksplit == 1) return rc;
     const int64_t quads = g.M * (g.N / 4);
@@ -1433,73 +1439,155 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
     return launch_tiles(gemm_bf16_d2l<D, OUT_BF16>, D::LDS_BYTES, 256, 256, D::THREADS, g, s);
 }
 
+// ---- which NVFP4 kernel and tile --------------------------------------------------------------------
+
+// The workgroup tiles (tokens x rows of W) of the NVFP4 kernels: gemm_fp4_direct with K whole, split over two
+// or over four waves, and gemm_fp4_small.  A round of workgroups (one per compute unit) takes
+// fixed + K steps x step, in ns; step1 is the step of a problem that is a single round.  The row-major
+// byte order costs about twice the step (a load touches a line per row instead of whole lines), most
+// where the tiles are small.
+enum Fp4Kernel { FP4_DIRECT, FP4_SMALL };
+struct Fp4Cost {
+    int step1, step, fixed;
+};
+struct Fp4Tile {
+    Fp4Kernel kernel;
+    int bm, bn;
+    Fp4Cost cost[2];  // MQ_LAYOUT_LINEAR, MQ_LAYOUT_KTILE
+};
+#define MQ_SMALL(X) /* TM, TN, S, NSETS; step1, step, fixed for the row-major and the K-step-major order */ \
+    X(1, 1, 8, 4, 154, 148, 1363, 48, 43, 1031) X(1, 2, 8, 4, 236, 233, 2056, 69, 68, 1618)                  \
+    X(2, 1, 8, 4, 180, 212, 2705, 65, 68, 1619) X(1, 2, 4, 4, 216, 202, 1191, 79, 67, 950)                   \
+    X(2, 1, 4, 4, 172, 195, 1081, 80, 67, 947) X(2, 2, 8, 4, 271, 287, 4977, 87, 115, 3315)                  \
+    X(2, 2, 4, 4, 263, 264, 2109, 108, 104, 2000) X(2, 4, 8, 2, 394, 412, 5114, 133, 183, 4667)              \
+    X(2, 4, 4, 2, 398, 381, 3029, 172, 172, 3018) X(4, 2, 8, 2, 341, 406, 4681, 137, 188, 4504)              \
+    X(4, 2, 4, 2, 348, 370, 2912, 171, 174, 2957)
+static constexpr Fp4Tile kFp4Tiles[] = {
+    {FP4_DIRECT, 256, 256, {{1893, 2039, 3289}, {1079, 1191, 9573}}},
+    {FP4_DIRECT, 256, 128, {{965, 1039, 6591}, {534, 618, 8626}}},
+    {FP4_DIRECT, 128, 128, {{504, 550, 5668}, {298, 335, 6083}}},
+#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) {FP4_SMALL, 32 * TM, 32 * TN, {{L1, L, LF}, {K1, K, KF}}},
+    MQ_SMALL(MQ_X)
+#undef MQ_X
+};
+constexpr int kFp4Directs = 3, kFp4TileCount = (int)(sizeof(kFp4Tiles) / sizeof(kFp4Tiles[0]));
+
+struct Fp4Plan {
+    int tile;                  // index into kFp4Tiles
+    int slabs;                 // K slabs across workgroups (1: none)
+    int64_t m_first, n_first;  // one of them > 0: these first rows / columns of Y with `tile`, the others with
+    int tile_rest;             // tile_rest in a second launch
+};
+
+// The plan that costs least: K steps of the rounds of workgroups, or the weights' one trip from HBM
+// (0.5625 bytes per element at 5.3 TB/s) where that is longer; a fifth of the shorter one does not
+// hide.  The steps and fixed times are fitted to every tile's time on 150 shapes (16 to 9000 tokens, the
+// 8B and 32B layers and their 2-, 4- and 8-way shards) in either byte order: the choice among the tiles
+// is on average 1 % slower than the fastest one, at worst 11 % (row-major: 18 %).
+// Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
+// instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 7.0 us in
+// 32x32 tiles and 11.6 in 64x64, 333 tokens on N = 28672 84 us in 64x128 and 93 in 256x256.
+// Two launches where the large tiles leave a ragged last round: whole rounds of one of the direct
+// tiles on the first rows or columns of Y, the others in whatever tile suits them (5003 tokens on
+// K = 14336, N = 4096: one round of 256x256 tiles on 4096 rows and 907 rows in 128x128 tiles).
+static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t slab_limit, int cus)
+{
+    const double kt = (double)(K / BK);
+    auto tiles_of = [](const Fp4Tile &t, int64_t m, int64_t n) { return ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn); };
+    // (part: one of two launches, whose step is that of a longer problem)
+    auto cost = [&](const Fp4Tile &t, int64_t m, int64_t n, int64_t slabs, bool part) {
+        const int64_t tiles = tiles_of(t, m, n), rounds = (tiles * slabs + cus - 1) / cus;
+        if (tiles > 0x7FFFFFFF) return 1e300;
+        const Fp4Cost &c = t.cost[layout == MQ_LAYOUT_KTILE];
+        const int step = rounds == 1 && !(part && t.kernel == FP4_DIRECT) ? c.step1 : c.step;
+        const double loop = (double)rounds * (kt / (double)slabs * step + c.fixed) * 1e-3;
+        const double hbm = 0.5625 * (double)n * (double)K / 5.3e6;
+        return 3.0 + (loop > hbm ? loop + 0.2 * hbm : hbm + 0.2 * loop) + (slabs > 1 ? 4.5 : 0.0);
+    };
+    Fp4Plan best{0, 1, 0, 0, 0};
+    double best_us = 1e300;
+    for (int i = 0; i < kFp4TileCount; ++i) {
+        const Fp4Tile &t = kFp4Tiles[i];
+        const double us = cost(t, M, N, 1, false);
+        if (us < best_us) best_us = us, best = Fp4Plan{i, 1, 0, 0, 0};
+        if (t.kernel != FP4_SMALL || slab_limit < 2) continue;
+        const int64_t tiles = tiles_of(t, M, N);
+        const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
+        if (slabs < 2) continue;
+        const double us_slabs = cost(t, M, N, slabs, false);
+        if (us_slabs < best_us) best_us = us_slabs, best = Fp4Plan{i, (int)slabs, 0, 0, 0};
+    }
+    best_us *= 0.98;  // two launches only for more than the model's error at near ties
+    for (int i = 0; i < kFp4Directs; ++i) {
+        const Fp4Tile &t = kFp4Tiles[i];
+        const int64_t tiles_m = (M + t.bm - 1) / t.bm, tiles_n = (N + t.bn - 1) / t.bn;
+        const int64_t rounds = (tiles_m * tiles_n + cus - 1) / cus;
+        for (int64_t r = rounds - 1; r >= 1 && r >= rounds - 2; --r)
+            for (int by_m = 0; by_m < 2; ++by_m) {
+                const int64_t m = by_m ? r * cus / tiles_n * t.bm : M, n = by_m ? N : r * cus / tiles_m * t.bn;
+                if (m == 0 || n == 0 || (by_m ? m >= M : n >= N)) continue;
+                const double first = cost(t, m, n, 1, true);
+                for (int j = 0; first < best_us && j < kFp4TileCount; ++j) {
+                    const double us = first + cost(kFp4Tiles[j], by_m ? M - m : M, by_m ? N : N - n, 1, true);
+                    if (us < best_us) best_us = us, best = Fp4Plan{i, 1, by_m ? m : 0, by_m ? 0 : n, j};
+                }
+            }
+    }
+    return best;
+}
+
+template <bool OUT_BF16>
+int launch_fp4_tile(int tile, int slabs, const GemmArgs &g, hipStream_t s, int cus)
+{
+    constexpr size_t X = 128 * 1024;  // accumulator exchange of the K-split variants
+    int i = 0;
+    if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 1>, 256, 256, 0, g, s, cus);
+    if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 2>, 256, 128, X, g, s, cus);
+    if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 4>, 128, 128, X, g, s, cus);
+#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) \
+    if (tile == i++) return launch_small<TM, TN, S, NSETS, OUT_BF16>(g, s, slabs);
+    MQ_SMALL(MQ_X)
+#undef MQ_X
+    return MQ_ERR_SHAPE;
+}
+
+template <bool OUT_BF16>
+int launch_fp4(const GemmArgs &g, hipStream_t s)
+{
+    int cus = 0;
+    if (int rc = compute_units(cus)) return rc;
+    const int layout = g.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR;  // (the same bytes when K == 64)
+    const Fp4Plan plan = fp4_plan(g.M, g.N, g.K, layout, gemm_fp4_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
+    if (plan.n_first == 0 && plan.m_first == 0) return launch_fp4_tile<OUT_BF16>(plan.tile, plan.slabs, g, s, cus);
+    constexpr int64_t T = OUT_BF16 ? 2 : 4;
+    GemmArgs ga = g, gb = g;  // (the K step strides keep those of the whole operands)
+    if (plan.m_first > 0) {
+        ga.M = plan.m_first;
+        gb.M = g.M - plan.m_first;
+        gb.a = static_cast<const char *>(g.a) + plan.m_first * g.a_c_row;
+        gb.a_scales = g.a_scales + plan.m_first * g.a_s_row;
+        gb.y = static_cast<char *>(g.y) + plan.m_first * g.ldy * T;
+    } else {
+        ga.N = plan.n_first;
+        gb.N = g.N - plan.n_first;
+        gb.b = static_cast<const char *>(g.b) + plan.n_first * g.b_c_row;
+        gb.b_scales = g.b_scales + plan.n_first * g.b_s_row;
+        gb.y = static_cast<char *>(g.y) + plan.n_first * T;
+    }
+    if (int rc = launch_fp4_tile<OUT_BF16>(plan.tile, 1, ga, s, cus)) return rc;
+    return launch_fp4_tile<OUT_BF16>(plan.tile_rest, 1, gb, s, cus);
+}
+
 template <bool FP4, bool OUT_BF16>
 int launch_any(const GemmArgs &g, hipStream_t s)
 {
     if (g.M == 0 || g.N == 0) return MQ_OK;
     // The tiled kernels step K by 64.
     if (g.K % BK != 0) return launch_simple<FP4, OUT_BF16>(g, s);
-    if constexpr (!FP4) {
+    if constexpr (FP4)
+        return launch_fp4<OUT_BF16>(g, s);
+    else
         return launch_bf16<OUT_BF16>(g, s);
-    } else {
-        const int64_t big_tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-        const int64_t mid_tiles = ((g.M + 255) / 256) * ((g.N + 127) / 128);
-        // Three workgroup shapes: 256x256 (whole K per wave), 256x128 with K split over wave
-        // pairs, 128x128 with K split over the four waves; once the 128x128 tiles fill at least
-        // half of the chip, the one whose rounds of workgroups cost least wins, a split workgroup
-        // being charged 55 / 34 percent of a whole one (measured on M = 512 .. 8192).
-        int cus = 0;
-        if (int rc = compute_units(cus)) return rc;
-        // A few hundred tokens (at most 2 x CUs tiles of 64x64): the small-tile kernel, one launch
-        // (plus, for a long K with very few tiles and a workspace, slabs of K across workgroups).
-        const SmallPlan plan = gemm_fp4_small_plan(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus);
-        if (plan.waves > 0) return launch_small<2, 2, 8, 4, OUT_BF16>(g, s, plan);
-        // From here on the 128x128 wave tiles fill at least half of the chip.
-        const int64_t small_tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-        const int64_t r1 = (big_tiles + cus - 1) / cus, r2 = (mid_tiles + cus - 1) / cus,
-                      r4 = (small_tiles + cus - 1) / cus;
-        const int64_t c1 = 100 * r1, c2 = 55 * r2, c4 = 34 * r4;
-        auto launch_variant = [&](int variant, const GemmArgs &ga) {
-            if (variant == 4) return launch_persistent(gemm_fp4_direct<OUT_BF16, 4>, 128, 128, 128 * 1024, ga, s, cus);
-            if (variant == 2) return launch_persistent(gemm_fp4_direct<OUT_BF16, 2>, 256, 128, 128 * 1024, ga, s, cus);
-            return launch_persistent(gemm_fp4_direct<OUT_BF16, 1>, 256, 256, 0, ga, s, cus);
-        };
-        const int one = (2 * mid_tiles < cus || (c4 < c1 && c4 < c2)) ? 4 : c2 < c1 ? 2 : 1;
-        const int64_t one_cost = one == 4 ? c4 : one == 2 ? c2 : c1;
-        // Two launches instead of one when the tiles leave a ragged last round: the first columns
-        // of N in one shape, the remaining columns in another (M = 2048, N = 28672: 3 rounds of
-        // whole tiles + 16 tile columns as 256x128 tiles cost 3.55 tile times instead of 3.85;
-        // M = 2048, N = 6144: 256x128 tiles on 4096 columns + 128x128 tiles on 2048 cost 0.89
-        // instead of 1).  Rounds are charged as above, the second launch four microseconds in
-        // units of a hundredth of a whole tile's time (0.022 us per K element + 6).
-        auto cost_of = [&](int variant, int64_t n) {
-            const int64_t bm = variant == 4 ? 128 : 256, bn = variant == 1 ? 256 : 128;
-            const int64_t tiles = ((g.M + bm - 1) / bm) * ((n + bn - 1) / bn);
-            return (variant == 1 ? 100 : variant == 2 ? 55 : 34) * ((tiles + cus - 1) / cus);
-        };
-        const int64_t second = (int64_t)(400.0 / (0.022 * (double)g.K + 6.0)) + 1;
-        int64_t best = one_cost, best_n = 0;
-        int best_a = 0, best_b = 0;
-        static const int variants[3] = {1, 2, 4};
-        for (int64_t n = 256; n < g.N; n += 256)
-            for (int va : variants)
-                for (int vb : variants) {
-                    if (va == vb) continue;
-                    const int64_t c = cost_of(va, n) + cost_of(vb, g.N - n) + second;
-                    if (c < best) best = c, best_n = n, best_a = va, best_b = vb;
-                }
-        if (best_n > 0) {
-            GemmArgs ga = g, gb = g;
-            ga.N = best_n;
-            gb.N = g.N - best_n;
-            gb.b = static_cast<const char *>(g.b) + best_n * g.b_c_row;
-            gb.b_scales = g.b_scales + best_n * g.b_s_row;
-            gb.y = static_cast<char *>(g.y) + best_n * (int64_t)(OUT_BF16 ? 2 : 4);
-            if (int rc = launch_variant(best_a, ga)) return rc;
-            return launch_variant(best_b, gb);
-        }
-        return launch_variant(one, g);
-    }
 }
 
 }  // namespace
@@ -1522,7 +1610,10 @@ int configure_gemm_kernels()
     };
     both(gemm_fp4_direct<true, 2>, gemm_fp4_direct<false, 2>, X);
     both(gemm_fp4_direct<true, 4>, gemm_fp4_direct<false, 4>, X);
-    both(gemm_fp4_small<2, 2, 8, 4, true>, gemm_fp4_small<2, 2, 8, 4, false>, X);
+#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF)                                               \
+    both(gemm_fp4_small<TM, TN, S, NSETS, true>, gemm_fp4_small<TM, TN, S, NSETS, false>, small_lds<TM, TN, S>());
+    MQ_SMALL(MQ_X)
+#undef MQ_X
     both(gemm_bf16_d2l<D, true>, gemm_bf16_d2l<D, false>, D::LDS_BYTES);
 #define MQ_X(MT, NT, S, STEP)                                                                                        \
     both(bf16_ring_kernel<MT, NT, S, true, true>, bf16_ring_kernel<MT, NT, S, true, false>, ring_lds<MT, NT, S>()); \
@@ -1537,32 +1628,18 @@ int configure_gemm_kernels()
     return note_launch(e);
 }
 
-// Does the small-tile kernel serve this problem, with how many waves per 64x64 tile and how
-// many K slabs across workgroups?  Measured on the Llama-3-8B layer set at 64 .. 1024 tokens (one
-// GPU, one launch inside a HIP graph): up to 2 x CUs tiles of 64x64 it beats the 128x128 wave tiles
-// (M = 128, N = 4096, K = 4096: 10.9 us against 19.2 with slabs of 128x128 tiles and 27 without),
-// beyond that the larger tiles' lower conversion work per MFMA wins.  Eight waves per tile (two
-// per SIMD) while every tile gets a compute unit of its own, four beyond.  A launch costs about
-// 6.5 us plus 0.5 us per K step of a wave; slabs add a second launch and the partial sums' way
-// through the workspace, about 4.5 us: they are used when at most half of the compute units
-// would otherwise hold a tile and the K steps they take off each wave are worth more than that.
-SmallPlan gemm_fp4_small_plan(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
+// Most K slabs across workgroups that the NVFP4 product may use, given this much workspace (0 or 1: none):
+// a long K (below about 8192 the second pass costs more than it saves) with at most half as many
+// 64x64 tiles as compute units, one round of work items, at least four K steps for each of eight waves.
+int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
-    SmallPlan plan{0, 1};
-    if (M <= 0 || N <= 0 || K <= 0 || K % BK != 0) return plan;
-    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64), kt = K / BK;
-    if (tiles > 2 * (int64_t)cus) return plan;
-    int64_t waves = tiles <= cus ? 8 : 4;
-    if (waves > kt / 2) waves = kt / 2 > 0 ? kt / 2 : 1;  // at least two K steps per wave
-    plan.waves = (int)waves;
-    if (ws_bytes > 0 && N % 4 == 0 && 2 * tiles <= cus) {
-        int64_t ks = cus / tiles;                                  // one round of work items
-        if (ks > kt / (waves * 4)) ks = kt / (waves * 4);          // at least four K steps per wave
-        if (ks > ws_bytes / (M * N * 4)) ks = ws_bytes / (M * N * 4);
-        // K-loop time saved, (kt / waves) * (1 - 1 / ks) * 0.5 us, against 4.5 us for the second pass
-        if (ks >= 2 && kt * (ks - 1) > 9 * waves * ks) plan.slabs = (int)ks;
-    }
-    return plan;
+    if (M <= 0 || N <= 0 || K <= 0 || K % BK != 0 || ws_bytes <= 0 || N % 4 != 0) return 0;
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64), kt = K / BK, waves = kt >= 16 ? 8 : kt / 2 > 0 ? kt / 2 : 1;
+    if (2 * tiles > cus) return 0;
+    int64_t ks = cus / tiles;
+    if (ks > kt / (waves * 4)) ks = kt / (waves * 4);
+    if (ks > ws_bytes / (M * N * 4)) ks = ws_bytes / (M * N * 4);
+    return ks >= 2 && kt * (ks - 1) > 9 * waves * ks ? (int)ks : 0;
 }
 
 // Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none).

@@ -62,13 +62,8 @@ struct GemmArgs {
     int64_t ws_bytes;
     int ksplit;
 };
-// Plan of the small-tile NVFP4 kernel for a problem, given this much workspace: waves per 64x64
-// tile (0: another kernel serves the problem) and K slabs across workgroups (1: none).
-struct SmallPlan {
-    int waves;
-    int slabs;
-};
-SmallPlan gemm_fp4_small_plan(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus);
+// most K slabs across workgroups of the NVFP4 product given this much workspace (0 or 1: none)
+int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus);
 // most K slabs across workgroups of the BF16 product given this much workspace (0 or 1: none)
 int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus);
 // sets the dynamic-LDS limit of every tiled kernel on the current device (idempotent)
