@@ -335,24 +335,65 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
     }
 }
 
-// Byte permutation between the two layouts of an NVFP4 tensor (offline weight pre-pack).
-// One thread moves one (row, K step) unit: 32 code bytes and 4 scale bytes.
+// Byte permutation between the two layouts of an NVFP4 tensor (offline weight pre-pack), HBM-bound: reads
+// and writes 0.5625 bytes per element.  A workgroup moves 32 rows x 16 K steps through LDS, so that both
+// sides see whole cache lines: 512 contiguous code bytes per row in the row-major order, 1 KB per K step
+// in the K-step-major one: [28672, 4096] 32 us (4.2 TB/s) in either direction, against 40 us to the K-step-major
+// order and 54 us from it with one thread per 32-byte unit, which touched a line per lane on one side.
+// LDS rows hold 32 chunks of 16 bytes plus two: the reads of 8 rows x 2 halves of a K step then fall on
+// different banks.
+constexpr int R_ROWS = 32, R_STEPS = 16, R_CHUNKS = 2 * R_STEPS, R_STRIDE = R_CHUNKS + 2;
+
+template <bool TO_KTILE>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
-                                                            int64_t rows, int64_t ksteps, bool to_ktile)
+                                                            int64_t rows, int ksteps, int groups)
 {
-    const int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // K-step-major unit index
-    if (u >= rows * ksteps) return;
-    const int64_t t = u / rows, r = u - t * rows;
-    const int64_t lin = r * ksteps + t;                              // row-major unit index
-    const int64_t from = to_ktile ? lin : u, to = to_ktile ? u : lin;
-    const uint4 c0 = reinterpret_cast<const uint4 *>(src_c)[from * 2];
-    const uint4 c1 = reinterpret_cast<const uint4 *>(src_c)[from * 2 + 1];
-    const uint32_t sc = reinterpret_cast<const uint32_t *>(src_s)[from];
-    reinterpret_cast<uint4 *>(dst_c)[to * 2] = c0;
-    reinterpret_cast<uint4 *>(dst_c)[to * 2 + 1] = c1;
-    reinterpret_cast<uint32_t *>(dst_s)[to] = sc;
+    __shared__ uint4 lc[R_ROWS * R_STRIDE];
+    __shared__ uint32_t ls[R_ROWS * (R_STEPS + 1)];
+    const int64_t r0 = (int64_t)(blockIdx.x / groups) * R_ROWS;
+    const int t0 = (int)(blockIdx.x % groups) * R_STEPS;
+    // item i of a side: row-major order (row, chunk of 16 bytes); K-step-major order (K step, row, half)
+    auto lin = [](int i, int &row, int &chunk) { row = i / R_CHUNKS, chunk = i % R_CHUNKS; };
+    auto kt = [](int i, int &row, int &chunk) {
+        row = (i / 2) % R_ROWS, chunk = i / (2 * R_ROWS) * 2 + i % 2;
+    };
+    auto inside = [&](int row, int t) { return r0 + row < rows && t0 + t < ksteps; };
+    auto lin_at = [&](int row, int t) { return (r0 + row) * (int64_t)ksteps + t0 + t; };   // unit (row, K step)
+    auto kt_at = [&](int row, int t) { return (int64_t)(t0 + t) * rows + r0 + row; };
+#pragma unroll
+    for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
+        int row, chunk;
+        TO_KTILE ? lin(j * kThreads + threadIdx.x, row, chunk) : kt(j * kThreads + threadIdx.x, row, chunk);
+        if (inside(row, chunk / 2))
+            lc[row * R_STRIDE + chunk] = reinterpret_cast<const uint4 *>(
+                src_c)[(TO_KTILE ? lin_at(row, chunk / 2) : kt_at(row, chunk / 2)) * 2 + chunk % 2];
+    }
+#pragma unroll
+    for (int j = 0; j < R_ROWS * R_STEPS / kThreads; ++j) {
+        const int i = j * kThreads + threadIdx.x;
+        const int row = TO_KTILE ? i / R_STEPS : i % R_ROWS, t = TO_KTILE ? i % R_STEPS : i / R_ROWS;
+        if (inside(row, t))
+            ls[row * (R_STEPS + 1) + t] =
+                reinterpret_cast<const uint32_t *>(src_s)[TO_KTILE ? lin_at(row, t) : kt_at(row, t)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
+        int row, chunk;
+        TO_KTILE ? kt(j * kThreads + threadIdx.x, row, chunk) : lin(j * kThreads + threadIdx.x, row, chunk);
+        if (inside(row, chunk / 2))
+            reinterpret_cast<uint4 *>(dst_c)[(TO_KTILE ? kt_at(row, chunk / 2) : lin_at(row, chunk / 2)) * 2 + chunk % 2] =
+                lc[row * R_STRIDE + chunk];
+    }
+#pragma unroll
+    for (int j = 0; j < R_ROWS * R_STEPS / kThreads; ++j) {
+        const int i = j * kThreads + threadIdx.x;
+        const int row = TO_KTILE ? i % R_ROWS : i / R_STEPS, t = TO_KTILE ? i / R_ROWS : i % R_STEPS;
+        if (inside(row, t))
+            reinterpret_cast<uint32_t *>(dst_s)[TO_KTILE ? kt_at(row, t) : lin_at(row, t)] = ls[row * (R_STEPS + 1) + t];
+    }
 }
 
 // ---- tensor-level scale ------------------------------------------------------------------
@@ -495,11 +536,14 @@ int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t 
 int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, uint8_t *dst_s, int64_t rows,
                     int64_t K, bool to_ktile, hipStream_t s)
 {
-    const int64_t ksteps = K / 64, units = rows * ksteps;
-    if (units == 0) return MQ_OK;
-    const int64_t grid = (units + kThreads - 1) / kThreads;
-    if (grid > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    relayout_kernel<<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, ksteps, to_ktile);
+    const int64_t ksteps = K / 64;
+    if (rows == 0 || ksteps == 0) return MQ_OK;
+    const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, grid = (rows + R_ROWS - 1) / R_ROWS * groups;
+    if (grid > 0x7FFFFFFF || rows * ksteps > (int64_t)0x7FFFFFFF * kThreads) return MQ_ERR_SHAPE;
+    if (to_ktile)
+        relayout_kernel<true><<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, (int)ksteps, (int)groups);
+    else
+        relayout_kernel<false><<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, (int)ksteps, (int)groups);
     return note_launch(hipGetLastError());
 }
 
