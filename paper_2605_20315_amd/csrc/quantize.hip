@@ -74,15 +74,26 @@ __device__ __forceinline__ void quantize_block16(uint4 v0, uint4 v1, float alpha
 
 // ---- where a block's 16 BF16 values come from ---------------------------------------------------
 
+// A source fetches what a block needs (fetch: loads only, so that a thread can have several blocks' loads in
+// flight) and turns it into the 16 values (values).
+
 // The tensor itself.
 struct PlainSrc {
     const uint16_t *x;
     int64_t ldx;
-    __device__ __forceinline__ void load(int64_t row, int64_t col, uint4 &v0, uint4 &v1) const
+    static constexpr int kBatch = 4, kFewGroups = 4096;  // see quantize_ktile_kernel
+    struct Raw {
+        uint4 v[2];
+    };
+    __device__ __forceinline__ Raw fetch(int64_t row, int64_t col) const
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(x + row * ldx + col);
-        v0 = src[0];
-        v1 = src[1];
+        return Raw{{src[0], src[1]}};
+    }
+    __device__ __forceinline__ void values(const Raw &raw, int64_t, int64_t, uint4 &v0, uint4 &v1) const
+    {
+        v0 = raw.v[0];
+        v1 = raw.v[1];
     }
 };
 
@@ -113,11 +124,19 @@ struct SiluMulSrc {
         const float s1 = g1 / (1.0f + __expf(-g1));
         return pack_bf16(s0 * u0, s1 * u1);
     }
-    __device__ __forceinline__ void load(int64_t row, int64_t col, uint4 &v0, uint4 &v1) const
+    static constexpr int kBatch = 1, kFewGroups = 16384;
+    struct Raw {
+        uint4 g[2], u[2];
+    };
+    __device__ __forceinline__ Raw fetch(int64_t row, int64_t col) const
     {
         const uint4 *gs = reinterpret_cast<const uint4 *>(gu + row * ld + col);
         const uint4 *us = reinterpret_cast<const uint4 *>(gu + row * ld + K + col);
-        const uint4 g0 = gs[0], g1 = gs[1], u0 = us[0], u1 = us[1];
+        return Raw{{gs[0], gs[1]}, {us[0], us[1]}};
+    }
+    __device__ __forceinline__ void values(const Raw &r, int64_t row, int64_t col, uint4 &v0, uint4 &v1) const
+    {
+        const uint4 g0 = r.g[0], g1 = r.g[1], u0 = r.u[0], u1 = r.u[1];
         v0 = make_uint4(pair(g0.x, u0.x), pair(g0.y, u0.y), pair(g0.z, u0.z), pair(g0.w, u0.w));
         v1 = make_uint4(pair(g1.x, u1.x), pair(g1.y, u1.y), pair(g1.z, u1.z), pair(g1.w, u1.w));
         if (p) {
@@ -142,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(Src src, int64_t tot
     const int64_t row = g / blocks_per_row;
     const int64_t b = g - row * blocks_per_row;
     uint4 v0, v1;
-    src.load(row, b * kBlock, v0, v1);
+    src.values(src.fetch(row, b * kBlock), row, b * kBlock, v0, v1);
     uint32_t c0, c1;
     int sb;
     quantize_block16(v0, v1, alpha, d6, c0, c1, sb);
@@ -151,72 +170,90 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(Src src, int64_t tot
 }
 
 // K-step-major output: the code and scale bytes of one 64-wide K step are contiguous over rows.
-// A workgroup covers 16 rows x 16 K steps.  Reading: each wave takes four of the rows in turn,
-// 2 KB contiguous per row (lane l: K step l/4, block l%4).  The codes and scale bytes go through
-// LDS so that writing is contiguous too: per K step 16 rows x 32 code bytes = 512 bytes and
-// 16 x 4 scale bytes = 64 bytes.
-constexpr int T_STRIDE = 16 * 4 + 4;  // uint2 units per K step in LDS, padded against bank conflicts
+// A workgroup covers ROWS rows x 16 K steps.  Reading: each wave takes ROWS / 4 of the rows, 2 KB
+// contiguous per row (lane l: K step l/4, block l%4).  The codes and scale bytes go through LDS so that
+// writing is contiguous too: per K step ROWS x 32 code bytes and ROWS x 4 scale bytes.
+// HBM-bound for large tensors, bound by one trip to memory for small ones.  ROWS = 4, one row per wave: every
+// wave waits for memory once and there are four times as many of them ([64, 4096] 2.2 us against 3.3 with 16
+// rows, one after the other, [1000, 14336] with silu_mul 15.1 against 18.1, [8192, 14336] 56 against 61).
+// ROWS = 16 from Src::kFewGroups workgroups of that size: 512 instead of 128 contiguous bytes per K step
+// ([65536, 4096] 129 us against 139); the waves' rows are then loaded Src::kBatch at a time (all four of
+// silu_mul's cost more in registers than they hide).
+constexpr int kt_stride(int rows) { return rows * 4 + 4; }  // uint2 units per K step in LDS, padded against bank conflicts
 
-// Second half of the transposition: thread (K step ot, row orow) writes one unit of 32 + 4 bytes.
-__device__ __forceinline__ void write_ktile_unit(const uint2 *lc, const uint8_t (*ls)[16][4], int t0, int64_t r0,
+// Second half of the transposition: thread `u` < 16 ROWS (K step u / ROWS, row u % ROWS) writes one unit of 32 + 4 bytes.
+template <int ROWS>
+__device__ __forceinline__ void write_ktile_unit(const uint2 *lc, const uint8_t (*ls)[ROWS][4], int u, int t0, int64_t r0,
                                                  int ksteps, int64_t rows, uint8_t *codes, uint8_t *scales)
 {
-    const int ot = (threadIdx.x >> 4) & 15, orow = threadIdx.x & 15;  // 256 consecutive threads: one unit each
+    const int ot = u / ROWS, orow = u % ROWS;
     if (t0 + ot < ksteps && r0 + orow < rows) {
         const int64_t slot = (int64_t)(t0 + ot) * rows + r0 + orow;
-        const uint2 *p = &lc[ot * T_STRIDE + orow * 4];
+        const uint2 *p = &lc[ot * kt_stride(ROWS) + orow * 4];
         reinterpret_cast<uint4 *>(codes)[slot * 2] = make_uint4(p[0].x, p[0].y, p[1].x, p[1].y);
         reinterpret_cast<uint4 *>(codes)[slot * 2 + 1] = make_uint4(p[2].x, p[2].y, p[3].x, p[3].y);
         reinterpret_cast<uint32_t *>(scales)[slot] = *reinterpret_cast<const uint32_t *>(&ls[ot][orow][0]);
     }
 }
 
-template <class Src>
+template <int ROWS, class Src>
 __global__ __launch_bounds__(kThreads) void quantize_ktile_kernel(Src src, int64_t rows, int64_t row_base,
                                                                   int ksteps, const float *__restrict__ alpha_p,
                                                                   uint8_t *__restrict__ codes,
                                                                   uint8_t *__restrict__ scales)
 {
-    __shared__ uint2 lc[16 * T_STRIDE];  // [K step][row][block]
-    __shared__ uint8_t ls[16][16][4];
+    constexpr int RPW = ROWS / 4;                    // rows per wave
+    __shared__ uint2 lc[16 * kt_stride(ROWS)];       // [K step][row][block]
+    __shared__ uint8_t ls[16][ROWS][4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * 16;
-    const int64_t r0 = row_base + (int64_t)blockIdx.y * 16;
+    const int64_t r0 = row_base + (int64_t)blockIdx.y * ROWS;
+    const int tl = lane >> 2, blk = lane & 3;
+    const int t = t0 + tl < ksteps ? t0 + tl : ksteps - 1;  // clamped: loaded, not stored
+    const int64_t col = (int64_t)t * 64 + blk * kBlock;
     const float alpha = *alpha_p;
     const float d6 = 6.0f * alpha;
-    const int tl = lane >> 2, blk = lane & 3;
+    constexpr int BATCH = RPW < Src::kBatch ? RPW : Src::kBatch;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int rl = wave * 4 + it;
-        const int64_t row = r0 + rl;
-        if (row < rows && t0 + tl < ksteps) {
-            uint4 v0, v1;
-            src.load(row, (int64_t)(t0 + tl) * 64 + blk * kBlock, v0, v1);
-            uint32_t c0, c1;
-            int sb;
-            quantize_block16(v0, v1, alpha, d6, c0, c1, sb);
-            lc[tl * T_STRIDE + rl * 4 + blk] = make_uint2(c0, c1);
-            ls[tl][rl][blk] = (uint8_t)sb;
+    for (int it0 = 0; it0 < RPW; it0 += BATCH) {
+        typename Src::Raw raw[BATCH];
+#pragma unroll
+        for (int it = 0; it < BATCH; ++it) {
+            const int64_t row = r0 + wave * RPW + it0 + it;
+            raw[it] = src.fetch(row < rows ? row : rows - 1, col);
+        }
+#pragma unroll
+        for (int it = 0; it < BATCH; ++it) {
+            const int rl = wave * RPW + it0 + it;
+            const int64_t row = r0 + rl;
+            if (row < rows && t0 + tl < ksteps) {
+                uint4 v0, v1;
+                src.values(raw[it], row, col, v0, v1);
+                uint32_t c0, c1;
+                int sb;
+                quantize_block16(v0, v1, alpha, d6, c0, c1, sb);
+                lc[tl * kt_stride(ROWS) + rl * 4 + blk] = make_uint2(c0, c1);
+                ls[tl][rl][blk] = (uint8_t)sb;
+            }
         }
     }
     __syncthreads();
-    write_ktile_unit(lc, ls, t0, r0, ksteps, rows, codes, scales);
+    if (threadIdx.x < 16 * ROWS)
+        write_ktile_unit<ROWS>(lc, ls, threadIdx.x, t0, r0, ksteps, rows, codes, scales);
 }
 
 // ---- RMS normalisation fused with the quantizer ----------------------------------------------
 
 // y[r, k] = x[r, k] / sqrt(mean_k x[r, :]^2 + eps) * w[k] in binary32 (sum of squares: each lane
 // adds its elements in ascending k, then a butterfly over the wave), rounded once to BF16, then
-// quantized as above.  A workgroup of 16 waves owns 16 rows and all of K, one wave per row, so a
+// quantized as above.  A workgroup of ROWS waves owns ROWS rows and all of K, one wave per row, so a
 // row's sum is a reduction over one wave.  Lane l takes K step c*16 + l/4, block l%4 of chunk c
 // (16 K steps = 1024 columns), as in the K-step-major quantizer.
 // NC > 0: the row (NC chunks: 8 registers each) stays in registers between the two passes, so x
 // is read once; NC == 0: any K, x is read again in the second pass (from cache).
 // y_out, when not null, receives the BF16 values (checking aid).
-constexpr int kRmsThreads = 1024;
-
-template <int NC, bool KTILE_OUT>
-__global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uint16_t *__restrict__ x, int64_t rows,
+template <int ROWS, int NC, bool KTILE_OUT>
+__global__ __launch_bounds__(64 * ROWS) void rmsnorm_quantize_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                        int ksteps, int64_t ldx,
                                                                        const uint16_t *__restrict__ w, float eps,
                                                                        float inv_k,
@@ -227,10 +264,11 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
 {
     constexpr int NCR = NC > 0 ? NC : 1;
     // K-step-major output: NC > 0 stages all chunks and synchronises once, NC == 0 chunk by chunk
-    __shared__ uint2 lc[NCR][16 * T_STRIDE];
-    __shared__ uint8_t ls[NCR][16][16][4];
+    __shared__ uint2 lc[KTILE_OUT ? NCR : 1][16 * kt_stride(ROWS)];
+    __shared__ uint8_t ls[KTILE_OUT ? NCR : 1][16][ROWS][4];
+    constexpr int UNITS = 16 * ROWS;  // units of 32 + 4 bytes per chunk
     const int lane = threadIdx.x & 63, rl = threadIdx.x >> 6;  // rl: row within the group = wave
-    const int64_t r0 = (int64_t)blockIdx.x * 16, row = r0 + rl;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS, row = r0 + rl;
     const bool row_ok = row < rows;
     const float alpha = *alpha_p;
     const float d6 = 6.0f * alpha;
@@ -256,7 +294,10 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
         for (int c = 0; c < NC; ++c) {
             const int t = c * 16 + tl;
             uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
-            if (row_ok && t < ksteps) src.load(row, (int64_t)t * 64 + blk * kBlock, v0, v1);
+            if (row_ok && t < ksteps) {
+                const PlainSrc::Raw raw = src.fetch(row, (int64_t)t * 64 + blk * kBlock);
+                v0 = raw.v[0], v1 = raw.v[1];
+            }
             keep[c][0] = v0;
             keep[c][1] = v1;
         }
@@ -266,9 +307,8 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
         for (int c = 0; c < chunks; ++c) {
             const int t = c * 16 + tl;
             if (row_ok && t < ksteps) {
-                uint4 v0, v1;
-                src.load(row, (int64_t)t * 64 + blk * kBlock, v0, v1);
-                ss += sumsq(v0, v1);
+                const PlainSrc::Raw raw = src.fetch(row, (int64_t)t * 64 + blk * kBlock);
+                ss += sumsq(raw.v[0], raw.v[1]);
             }
         }
     }
@@ -301,7 +341,7 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
             quantize_block16(v0, v1, alpha, d6, c0, c1, sb);
             if constexpr (KTILE_OUT) {
                 const int slot = NC > 0 ? c : 0;
-                lc[slot][tl * T_STRIDE + rl * 4 + blk] = make_uint2(c0, c1);
+                lc[slot][tl * kt_stride(ROWS) + rl * 4 + blk] = make_uint2(c0, c1);
                 ls[slot][tl][rl][blk] = (uint8_t)sb;
             } else {
                 const int64_t g = row * ((int64_t)ksteps * 4) + (int64_t)t * 4 + blk;
@@ -311,7 +351,8 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
         }
         if constexpr (KTILE_OUT && NC == 0) {
             __syncthreads();
-            if (threadIdx.x < 256) write_ktile_unit(lc[0], ls[0], c * 16, r0, ksteps, rows, codes, scales);
+            if (threadIdx.x < UNITS)
+                write_ktile_unit<ROWS>(lc[0], ls[0], threadIdx.x, c * 16, r0, ksteps, rows, codes, scales);
             __syncthreads();
         }
     };
@@ -322,14 +363,18 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_quantize_kernel(const uin
         if constexpr (KTILE_OUT) {
             __syncthreads();
 #pragma unroll
-            for (int c = (int)(threadIdx.x >> 8); c < NC; c += kRmsThreads / 256)
-                if (c < chunks) write_ktile_unit(lc[c], ls[c], c * 16, r0, ksteps, rows, codes, scales);
+            for (int c = (int)(threadIdx.x / UNITS); c < NC; c += 64 * ROWS / UNITS)
+                if (c < chunks)
+                    write_ktile_unit<ROWS>(lc[c], ls[c], threadIdx.x % UNITS, c * 16, r0, ksteps, rows, codes, scales);
         }
     } else {
         for (int c = 0; c < chunks; ++c) {
             const int t = c * 16 + tl;
             uint4 x0 = make_uint4(0, 0, 0, 0), x1 = x0;
-            if (row_ok && t < ksteps) src.load(row, (int64_t)t * 64 + blk * kBlock, x0, x1);
+            if (row_ok && t < ksteps) {
+                const PlainSrc::Raw raw = src.fetch(row, (int64_t)t * 64 + blk * kBlock);
+                x0 = raw.v[0], x1 = raw.v[1];
+            }
             chunk(c, x0, x1);
         }
     }
@@ -478,12 +523,17 @@ int launch_quantize_from(const Src &src, int64_t rows, int64_t K, const float *a
     const int64_t total = rows * bpr;
     if (total == 0) return MQ_OK;
     if (layout == MQ_LAYOUT_KTILE) {
-        const int64_t ksteps = K / 64, gy = (rows + 15) / 16;
+        const int64_t ksteps = K / 64, gx = (ksteps + 15) / 16;
+        const int per = gx * ((rows + 15) / 16) < Src::kFewGroups ? 4 : 16;  // rows per workgroup
+        const int64_t gy = (rows + per - 1) / per;
         // grid.y is limited to 65535: fold the excess row groups into extra launches
         for (int64_t y0 = 0; y0 < gy; y0 += 65535) {
             const int64_t ny = gy - y0 < 65535 ? gy - y0 : 65535;
-            quantize_ktile_kernel<Src><<<dim3((unsigned)((ksteps + 15) / 16), (unsigned)ny), dim3(kThreads), 0, s>>>(
-                src, rows, y0 * 16, (int)ksteps, alpha, codes, scales);
+            const dim3 grid((unsigned)gx, (unsigned)ny);
+            if (per == 16)
+                quantize_ktile_kernel<16><<<grid, dim3(kThreads), 0, s>>>(src, rows, y0 * per, (int)ksteps, alpha, codes, scales);
+            else
+                quantize_ktile_kernel<4><<<grid, dim3(kThreads), 0, s>>>(src, rows, y0 * per, (int)ksteps, alpha, codes, scales);
             int rc = note_launch(hipGetLastError());
             if (rc != MQ_OK) return rc;
         }
@@ -514,21 +564,32 @@ int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t 
                             int64_t ldy, hipStream_t s)
 {
     if (rows == 0) return MQ_OK;
-    const int64_t groups = (rows + 15) / 16;
-    if (groups > 0x7FFFFFFF) return MQ_ERR_SHAPE;
     const int ksteps = (int)(K / 64);
     const float inv_k = 1.0f / (float)K;
-    const dim3 grid((unsigned)groups), block(kRmsThreads);
     const bool kt = layout == MQ_LAYOUT_KTILE;
-#define MQ_RMS(NC_)                                                                                              \
-    (kt ? rmsnorm_quantize_kernel<NC_, true><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k, alpha,  \
-                                                                    codes, scales, y, ldy)                      \
-        : rmsnorm_quantize_kernel<NC_, false><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k, alpha, \
-                                                                     codes, scales, y, ldy))
-    if (ksteps <= 64)
-        MQ_RMS(4);  // K <= 4096: the row stays in registers (32 per lane)
+    // Workgroups of four rows: more of them (63 of 16 rows left three quarters of the chip idle at 1000
+    // tokens), and registers for longer rows.  us, four rows against sixteen: K = 4096 (the row in 32
+    // registers per lane either way) [64] 4.5 / 7.4, [1000] 6.0 / 8.6, [4096] 13.6 / 13.5, [65536] 147 / 162; K = 5120
+    // (64 registers against reading x twice) [1000] 7.4 / 12.3, [16384] 62 / 67, [65536] 224 / 213; K = 14336 (128
+    // registers) [1000] 17.5 / 31.7, [4096] 66 / 47.
+    const bool few = ksteps <= 64 || (ksteps <= 128 && rows <= 16384) || (ksteps <= 256 && rows <= 1024);
+    const int per = few ? 4 : 16;
+    const int64_t groups = (rows + per - 1) / per;
+    if (groups > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    const dim3 grid((unsigned)groups), block(64 * per);
+#define MQ_RMS(ROWS_, NC_)                                                                                       \
+    (kt ? rmsnorm_quantize_kernel<ROWS_, NC_, true><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k,  \
+                                                                           alpha, codes, scales, y, ldy)        \
+        : rmsnorm_quantize_kernel<ROWS_, NC_, false><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k, \
+                                                                            alpha, codes, scales, y, ldy))
+    if (few && ksteps <= 64)
+        MQ_RMS(4, 4);
+    else if (few && ksteps <= 128)
+        MQ_RMS(4, 8);
+    else if (few)
+        MQ_RMS(4, 16);
     else
-        MQ_RMS(0);  // (8 chunks in registers spill at 1024 threads per workgroup: measured 2x slower)
+        MQ_RMS(16, 0);
 #undef MQ_RMS
     return note_launch(hipGetLastError());
 }
