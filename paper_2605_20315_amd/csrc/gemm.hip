@@ -1324,6 +1324,10 @@ int launch_simple(const GemmArgs &g, hipStream_t s)
     return note_launch(hipGetLastError());
 }
 
+// A launch holds fewer than 2^32 threads: kernels with a workgroup per tile, of up to 512 threads, take no
+// more tiles than this (hundreds of millions of rows in narrow tiles), the larger tiles serve what is left.
+static constexpr int64_t kMaxSmallTiles = (1ll << 23) - 1;
+
 // ---- which BF16 kernel and tile ---------------------------------------------------------------------
 
 // The tiles (tokens x rows of W) that the BF16 kernels are built in.  step: measured time of one 64-wide K
@@ -1371,7 +1375,7 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
     for (int i = 0; i < (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); ++i) {
         const Bf16Tile &t = kBf16Tiles[i];
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        if (tiles > 0x7FFFFFFF) continue;
+        if (tiles > (t.kernel == BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
         int64_t slabs = 1;
         for (;;) {
             const double steps = (double)((tiles * slabs + cus - 1) / cus) * (kt / (double)slabs + 7.0);
@@ -1497,7 +1501,7 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
     // (part: one of two launches, whose step is that of a longer problem)
     auto cost = [&](const Fp4Tile &t, int64_t m, int64_t n, int64_t slabs, bool part) {
         const int64_t tiles = tiles_of(t, m, n), rounds = (tiles * slabs + cus - 1) / cus;
-        if (tiles > 0x7FFFFFFF) return 1e300;
+        if (tiles > (t.kernel == FP4_SMALL ? kMaxSmallTiles : 0x7FFFFFFF)) return 1e300;
         const Fp4Cost &c = t.cost[layout == MQ_LAYOUT_KTILE];
         const int step = rounds == 1 && !(part && t.kernel == FP4_DIRECT) ? c.step1 : c.step;
         const double loop = (double)rounds * (kt / (double)slabs * step + c.fixed) * 1e-3;

@@ -393,11 +393,11 @@ template <bool TO_KTILE>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
-                                                            int64_t rows, int ksteps, int groups)
+                                                            int64_t rows, int64_t row_base, int ksteps, int groups)
 {
     __shared__ uint4 lc[R_ROWS * R_STRIDE];
     __shared__ uint32_t ls[R_ROWS * (R_STEPS + 1)];
-    const int64_t r0 = (int64_t)(blockIdx.x / groups) * R_ROWS;
+    const int64_t r0 = row_base + (int64_t)(blockIdx.x / groups) * R_ROWS;
     const int t0 = (int)(blockIdx.x % groups) * R_STEPS;
     // item i of a side: row-major order (row, chunk of 16 bytes); K-step-major order (K step, row, half)
     auto lin = [](int i, int &row, int &chunk) { row = i / R_CHUNKS, chunk = i % R_CHUNKS; };
@@ -599,13 +599,22 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
 {
     const int64_t ksteps = K / 64;
     if (rows == 0 || ksteps == 0) return MQ_OK;
-    const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, grid = (rows + R_ROWS - 1) / R_ROWS * groups;
-    if (grid > 0x7FFFFFFF || rows * ksteps > (int64_t)0x7FFFFFFF * kThreads) return MQ_ERR_SHAPE;
-    if (to_ktile)
-        relayout_kernel<true><<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, (int)ksteps, (int)groups);
-    else
-        relayout_kernel<false><<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, (int)ksteps, (int)groups);
-    return note_launch(hipGetLastError());
+    if (rows * ksteps > (int64_t)0x7FFFFFFF * kThreads) return MQ_ERR_SHAPE;
+    const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, panels = (rows + R_ROWS - 1) / R_ROWS;
+    // a launch holds fewer than 2^32 threads: more workgroups than that go into further launches, by rows
+    const int64_t max_panels = ((1ll << 24) - 1) / groups;
+    if (max_panels == 0) return MQ_ERR_SHAPE;
+    for (int64_t p0 = 0; p0 < panels; p0 += max_panels) {
+        const int64_t n = panels - p0 < max_panels ? panels - p0 : max_panels;
+        const dim3 grid((unsigned)(n * groups));
+        if (to_ktile)
+            relayout_kernel<true><<<grid, dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, (int)ksteps, (int)groups);
+        else
+            relayout_kernel<false><<<grid, dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, (int)ksteps, (int)groups);
+        int rc = note_launch(hipGetLastError());
+        if (rc != MQ_OK) return rc;
+    }
+    return MQ_OK;
 }
 
 int launch_global_scale(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx, float *alpha,
