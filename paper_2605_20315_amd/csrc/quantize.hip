@@ -393,20 +393,21 @@ template <bool TO_KTILE>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
-                                                            int64_t rows, int64_t row_base, int ksteps, int groups)
+                                                            int64_t rows, int64_t row_base, int64_t ksteps,
+                                                            int64_t step_base, unsigned groups)
 {
     __shared__ uint4 lc[R_ROWS * R_STRIDE];
     __shared__ uint32_t ls[R_ROWS * (R_STEPS + 1)];
     const int64_t r0 = row_base + (int64_t)(blockIdx.x / groups) * R_ROWS;
-    const int t0 = (int)(blockIdx.x % groups) * R_STEPS;
+    const int64_t t0 = step_base + (int64_t)(blockIdx.x % groups) * R_STEPS;
     // item i of a side: row-major order (row, chunk of 16 bytes); K-step-major order (K step, row, half)
     auto lin = [](int i, int &row, int &chunk) { row = i / R_CHUNKS, chunk = i % R_CHUNKS; };
     auto kt = [](int i, int &row, int &chunk) {
         row = (i / 2) % R_ROWS, chunk = i / (2 * R_ROWS) * 2 + i % 2;
     };
     auto inside = [&](int row, int t) { return r0 + row < rows && t0 + t < ksteps; };
-    auto lin_at = [&](int row, int t) { return (r0 + row) * (int64_t)ksteps + t0 + t; };   // unit (row, K step)
-    auto kt_at = [&](int row, int t) { return (int64_t)(t0 + t) * rows + r0 + row; };
+    auto lin_at = [&](int row, int t) { return (r0 + row) * ksteps + t0 + t; };   // unit (row, K step)
+    auto kt_at = [&](int row, int t) { return (t0 + t) * rows + r0 + row; };
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
         int row, chunk;
@@ -601,19 +602,20 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
     if (rows == 0 || ksteps == 0) return MQ_OK;
     if (rows * ksteps > (int64_t)0x7FFFFFFF * kThreads) return MQ_ERR_SHAPE;
     const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, panels = (rows + R_ROWS - 1) / R_ROWS;
-    // a launch holds fewer than 2^32 threads: more workgroups than that go into further launches, by rows
-    const int64_t max_panels = ((1ll << 24) - 1) / groups;
-    if (max_panels == 0) return MQ_ERR_SHAPE;
-    for (int64_t p0 = 0; p0 < panels; p0 += max_panels) {
-        const int64_t n = panels - p0 < max_panels ? panels - p0 : max_panels;
-        const dim3 grid((unsigned)(n * groups));
-        if (to_ktile)
-            relayout_kernel<true><<<grid, dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, (int)ksteps, (int)groups);
-        else
-            relayout_kernel<false><<<grid, dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, (int)ksteps, (int)groups);
-        int rc = note_launch(hipGetLastError());
-        if (rc != MQ_OK) return rc;
-    }
+    // a launch holds fewer than 2^32 threads: what is more goes into further launches, by rows and, where one panel
+    // of rows has more workgroups than that (K beyond 1.7e10), by K steps
+    constexpr int64_t max_wgs = (1ll << 24) - 1;
+    const int64_t max_groups = groups < max_wgs ? groups : max_wgs, max_panels = max_wgs / max_groups;
+    for (int64_t p0 = 0; p0 < panels; p0 += max_panels)
+        for (int64_t g0 = 0; g0 < groups; g0 += max_groups) {
+            const int64_t n = panels - p0 < max_panels ? panels - p0 : max_panels;
+            const int64_t ng = groups - g0 < max_groups ? groups - g0 : max_groups;
+            auto kern = to_ktile ? relayout_kernel<true> : relayout_kernel<false>;
+            kern<<<dim3((unsigned)(n * ng)), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, ksteps,
+                                                                     g0 * R_STEPS, (unsigned)ng);
+            int rc = note_launch(hipGetLastError());
+            if (rc != MQ_OK) return rc;
+        }
     return MQ_OK;
 }
 

@@ -68,3 +68,20 @@ def test_relayout_ragged_tiles(rows, K):
     ce, se = to_ktile(c, s)
     assert np.array_equal(ck.cpu().numpy(), ce) and np.array_equal(sk.cpu().numpy(), se)
     assert np.array_equal(cl.cpu().numpy(), c) and np.array_equal(sl.cpu().numpy(), s)
+
+
+def test_relayout_of_more_k_steps_than_one_launch_holds():
+    """One row of 2^24 tiles of 16 K steps (8.6 GB of codes), one tile more than a launch of 2^24 - 1 workgroups
+    holds.  With a single row the two orders are the same bytes."""
+    K = 1024 << 24
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GB of device memory")
+    c = torch.arange(K // 16, dtype=torch.int64, device="cuda").mul_(0x9E3779B97F4A7C15 - (1 << 64)).view(torch.uint8).view(1, K // 2)
+    s = torch.arange(K // 64, dtype=torch.int32, device="cuda").view(torch.uint8).view(1, K // 16)
+    for a, b in ((mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE), (mq.MQ_LAYOUT_KTILE, mq.MQ_LAYOUT_LINEAR)):
+        oc, os_ = mq.nvfp4_relayout(c, s, a, b)
+        assert torch.equal(oc.view(torch.int64), c.view(torch.int64))
+        assert torch.equal(os_.view(torch.int32), s.view(torch.int32))
+        del oc, os_
+    del c, s
+    torch.cuda.empty_cache()
