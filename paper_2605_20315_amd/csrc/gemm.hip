@@ -921,6 +921,18 @@ __device__ __forceinline__ void store_quad(const GemmArgs &g, f32x4 v, int64_t m
     using T = std::conditional_t<OUT_BF16, __bf16, float>;
     if (m >= g.M || n >= g.N) return;
     T *dst = static_cast<T *>(g.y) + m * g.ldy + n;
+    if constexpr (!OUT_BF16) {
+        // (a copy that the compiler cannot see through: it may store quads straight from accumulation registers,
+        // and then kept the accumulators of the staged kernels half in one kind of register and half in the other
+        // and moved all of them twice per K step)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a = v[i];
+            float c;
+            asm("v_mov_b32 %0, %1" : "=v"(c) : "v"(a));
+            v[i] = c;
+        }
+    }
     if (n + 3 < g.N) {
         if constexpr (OUT_BF16) {
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));

@@ -47,3 +47,25 @@ def test_bf16_tile_shapes_against_oracle(M, N, K):
     assert torch.equal(y32.to(torch.bfloat16), y16)
     for buf in (b32, b16):
         assert bool((buf[M:] == -7.0).all()) and bool((buf[:, N:] == -7.0).all())
+
+
+def test_fp32_output_costs_its_stores_only():
+    """The staged kernels run the same K loop for either output type: with a long K the FP32 output may cost its
+    larger stores (21 MB more here, under 2 % of the time), not a loop that moves its accumulators about
+    (28 % more).  Bound 1.12, fastest of nine runs of each in turn."""
+    M, N, K = 2048, 5120, 12800
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+    w = (torch.randn((N, K), device="cuda", generator=g) * K ** -0.5).to(torch.bfloat16)
+    best = {}
+    for _ in range(9):
+        for out in (mq.MQ_OUT_BF16, mq.MQ_OUT_FP32):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            y = torch.empty((M, N), dtype=torch.float32 if out else torch.bfloat16, device="cuda")
+            a.record()
+            for _ in range(3):
+                mq.bf16_gemm(x, w, out, y)
+            b.record()
+            b.synchronize()
+            best[out] = min(best.get(out, 1e9), a.elapsed_time(b))
+    assert best[mq.MQ_OUT_FP32] <= 1.12 * best[mq.MQ_OUT_BF16], best
