@@ -6,6 +6,8 @@
 #ifndef MIXQUANT_DIAG_H
 #define MIXQUANT_DIAG_H
 
+#include <stdint.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -20,6 +22,32 @@ extern "C" {
  * 1 <= iters <= 2^20.
  */
 int mq_mfma_probe(float *scratch_dev, int iters, void *stream, double *flop_out);
+
+/*
+ * What the entry points of mixquant.h launch for a problem, so that a test can state which kernel, tile or
+ * number of K slabs it is about.  Host functions, no GPU access: `cus` is the number of compute units
+ * to plan for (256 on an MI355X).
+ *
+ * A product is one launch, or two that cover the first rows or columns of Y and the others; the second
+ * pass of a product cut into K slabs is not counted.  Each launch: the kernel, its workgroups' tile
+ * (bm rows x bn columns of Y) and waves, the number of K slabs (1: none, no workspace is touched), and
+ * the part of Y that it covers.  Returns the number of launches (0 for an empty Y), or minus an
+ * mq_status.
+ */
+typedef enum {
+    MQ_KERNEL_SIMPLE = 0,      /* any K: one thread per output */
+    MQ_KERNEL_FP4_DIRECT = 1,
+    MQ_KERNEL_FP4_SMALL = 2,
+    MQ_KERNEL_BF16_RING = 3,
+    MQ_KERNEL_BF16_STAGE = 4,
+    MQ_KERNEL_BF16_D2L = 5
+} mq_kernel;
+typedef struct {
+    int kernel, bm, bn, waves, slabs;
+    int64_t rows, cols;
+} mq_launch;
+int mq_gemm_launches(int64_t M, int64_t N, int64_t K, int layout, int64_t workspace_bytes, int cus, mq_launch out[2]);
+int mq_bf16_gemm_launches(int64_t M, int64_t N, int64_t K, int64_t workspace_bytes, int cus, mq_launch out[2]);
 
 #ifdef __cplusplus
 }

@@ -21,6 +21,12 @@ class MixQuantError(RuntimeError):
     pass
 
 
+class Launch(ctypes.Structure):
+    """mq_launch of include/mixquant_diag.h."""
+    _fields_ = [(n, ctypes.c_int) for n in ("kernel", "bm", "bn", "waves", "slabs")] + [("rows", ctypes.c_int64),
+                                                                                       ("cols", ctypes.c_int64)]
+
+
 def load() -> ctypes.CDLL:
     global _lib
     if _lib is not None:
@@ -63,6 +69,10 @@ def load() -> ctypes.CDLL:
     lib.mq_bf16_gemm_workspace_bytes.argtypes = [i64, i64, i64]
     lib.mq_mfma_probe.restype = ci
     lib.mq_mfma_probe.argtypes = [vp, ci, vp, ctypes.POINTER(ctypes.c_double)]
+    lib.mq_gemm_launches.restype = ci
+    lib.mq_gemm_launches.argtypes = [i64, i64, i64, ci, i64, ci, ctypes.POINTER(Launch)]
+    lib.mq_bf16_gemm_launches.restype = ci
+    lib.mq_bf16_gemm_launches.argtypes = [i64, i64, i64, i64, ci, ctypes.POINTER(Launch)]
     lib.mq_status_string.restype = ctypes.c_char_p
     lib.mq_status_string.argtypes = [ci]
     lib.mq_last_hip_error.restype = ci

@@ -320,6 +320,22 @@ int mq_mfma_probe(float *scratch_dev, int iters, void *stream, double *flop_out)
     return launch_mfma_probe(scratch_dev, iters, blocks, static_cast<hipStream_t>(stream));
 }
 
+int mq_gemm_launches(int64_t M, int64_t N, int64_t K, int layout, int64_t workspace_bytes, int cus, mq_launch out[2])
+{
+    if (!out) return -MQ_ERR_NULL;
+    if (layout != MQ_LAYOUT_LINEAR && layout != MQ_LAYOUT_KTILE) return -MQ_ERR_ARG;
+    if (M < 0 || N < 0 || K <= 0 || K % kBlock != 0 || workspace_bytes < 0 || cus < 1) return -MQ_ERR_SHAPE;
+    if (layout == MQ_LAYOUT_KTILE && K % 64 != 0) return -MQ_ERR_SHAPE;
+    return M == 0 || N == 0 ? 0 : describe_gemm_fp4(M, N, K, layout, workspace_bytes, cus, out);
+}
+
+int mq_bf16_gemm_launches(int64_t M, int64_t N, int64_t K, int64_t workspace_bytes, int cus, mq_launch out[2])
+{
+    if (!out) return -MQ_ERR_NULL;
+    if (M < 0 || N < 0 || K <= 0 || K % 8 != 0 || workspace_bytes < 0 || cus < 1) return -MQ_ERR_SHAPE;
+    return M == 0 || N == 0 ? 0 : describe_gemm_bf16(M, N, K, workspace_bytes, cus, out);
+}
+
 const char *mq_status_string(int status)
 {
     switch (status) {

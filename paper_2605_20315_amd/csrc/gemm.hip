@@ -1345,10 +1345,9 @@ static constexpr int64_t kMaxSmallTiles = (1ll << 23) - 1;
 // The tiles (tokens x rows of W) that the BF16 kernels are built in.  step: measured time of one 64-wide K
 // step of one round of workgroups (one per compute unit) in ns, as far as it does not overlap with
 // the weights' trip from HBM.
-enum Bf16Kernel { BF16_RING, BF16_STAGE, BF16_D2L };
 struct Bf16Tile {
-    Bf16Kernel kernel;
-    int bm, bn, step;
+    mq_kernel kernel;
+    int bm, bn, waves, step;
 };
 #define MQ_RING(X) /* MT, NT, S, step */                                                                     \
     X(1, 1, 8, 66) X(1, 2, 4, 99) X(1, 4, 4, 174) X(2, 1, 8, 94) X(2, 2, 4, 112) X(2, 4, 4, 196) \
@@ -1357,13 +1356,13 @@ struct Bf16Tile {
     X(3, 2, 2, 2, 6, 311) X(4, 2, 2, 2, 4, 362) X(3, 4, 2, 2, 4, 447) X(4, 2, 2, 4, 4, 511) \
     X(5, 4, 2, 2, 4, 593) X(7, 4, 2, 2, 3, 727) X(8, 4, 2, 2, 3, 804) X(8, 6, 2, 2, 2, 1168)
 static constexpr Bf16Tile kBf16Tiles[] = {
-#define MQ_X(MT, NT, S, STEP) {BF16_RING, 16 * MT, 16 * NT, STEP},
+#define MQ_X(MT, NT, S, STEP) {MQ_KERNEL_BF16_RING, 16 * MT, 16 * NT, S, STEP},
     MQ_RING(MQ_X)
 #undef MQ_X
-#define MQ_X(TM, TN, WM, WN, NST, STEP) {BF16_STAGE, 16 * TM * WM, 16 * TN * WN, STEP},
+#define MQ_X(TM, TN, WM, WN, NST, STEP) {MQ_KERNEL_BF16_STAGE, 16 * TM * WM, 16 * TN * WN, WM * WN, STEP},
     MQ_STAGE(MQ_X)
 #undef MQ_X
-    {BF16_D2L, 256, 256, 1440}};
+    {MQ_KERNEL_BF16_D2L, 256, 256, 4, 1440}};
 
 struct Bf16Plan {
     int tile;   // index into kBf16Tiles
@@ -1387,14 +1386,14 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
     for (int i = 0; i < (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); ++i) {
         const Bf16Tile &t = kBf16Tiles[i];
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        if (tiles > (t.kernel == BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
+        if (tiles > (t.kernel == MQ_KERNEL_BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
         int64_t slabs = 1;
         for (;;) {
             const double steps = (double)((tiles * slabs + cus - 1) / cus) * (kt / (double)slabs + 7.0);
             const double loop = steps * t.step * 1e-3;
             const double us = (hbm > loop ? hbm + 0.015 * loop : loop + 0.015 * hbm) + (slabs > 1 ? 3.0 : 0.0);
             if (us < best_us) best_us = us, best = Bf16Plan{i, (int)slabs};
-            if (slabs > 1 || t.kernel != BF16_RING || slab_limit < 2 || 2 * tiles > cus) break;
+            if (slabs > 1 || t.kernel != MQ_KERNEL_BF16_RING || slab_limit < 2 || 2 * tiles > cus) break;
             slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
         }
     }
@@ -1462,13 +1461,12 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
 // fixed + K steps x step, in ns; step1 is the step of a problem that is a single round.  The row-major
 // byte order costs about twice the step (a load touches a line per row instead of whole lines), most
 // where the tiles are small.
-enum Fp4Kernel { FP4_DIRECT, FP4_SMALL };
 struct Fp4Cost {
     int step1, step, fixed;
 };
 struct Fp4Tile {
-    Fp4Kernel kernel;
-    int bm, bn;
+    mq_kernel kernel;
+    int bm, bn, waves;
     Fp4Cost cost[2];  // MQ_LAYOUT_LINEAR, MQ_LAYOUT_KTILE
 };
 #define MQ_SMALL(X) /* TM, TN, S, NSETS; step1, step, fixed for the row-major and the K-step-major order */ \
@@ -1479,10 +1477,10 @@ struct Fp4Tile {
     X(2, 4, 4, 2, 398, 381, 3029, 172, 172, 3018) X(4, 2, 8, 2, 341, 406, 4681, 137, 188, 4504)              \
     X(4, 2, 4, 2, 348, 370, 2912, 171, 174, 2957)
 static constexpr Fp4Tile kFp4Tiles[] = {
-    {FP4_DIRECT, 256, 256, {{1893, 2039, 3289}, {1079, 1191, 9573}}},
-    {FP4_DIRECT, 256, 128, {{965, 1039, 6591}, {534, 618, 8626}}},
-    {FP4_DIRECT, 128, 128, {{504, 550, 5668}, {298, 335, 6083}}},
-#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) {FP4_SMALL, 32 * TM, 32 * TN, {{L1, L, LF}, {K1, K, KF}}},
+    {MQ_KERNEL_FP4_DIRECT, 256, 256, 4, {{1893, 2039, 3289}, {1079, 1191, 9573}}},
+    {MQ_KERNEL_FP4_DIRECT, 256, 128, 4, {{965, 1039, 6591}, {534, 618, 8626}}},
+    {MQ_KERNEL_FP4_DIRECT, 128, 128, 4, {{504, 550, 5668}, {298, 335, 6083}}},
+#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) {MQ_KERNEL_FP4_SMALL, 32 * TM, 32 * TN, S, {{L1, L, LF}, {K1, K, KF}}},
     MQ_SMALL(MQ_X)
 #undef MQ_X
 };
@@ -1513,9 +1511,9 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
     // (part: one of two launches, whose step is that of a longer problem)
     auto cost = [&](const Fp4Tile &t, int64_t m, int64_t n, int64_t slabs, bool part) {
         const int64_t tiles = tiles_of(t, m, n), rounds = (tiles * slabs + cus - 1) / cus;
-        if (tiles > (t.kernel == FP4_SMALL ? kMaxSmallTiles : 0x7FFFFFFF)) return 1e300;
-        const Fp4Cost &c = t.cost[layout == MQ_LAYOUT_KTILE];
-        const int step = rounds == 1 && !(part && t.kernel == FP4_DIRECT) ? c.step1 : c.step;
+        if (tiles > (t.kernel == MQ_KERNEL_FP4_SMALL ? kMaxSmallTiles : 0x7FFFFFFF)) return 1e300;
+        const Fp4Cost &c = t.cost[layout == MQ_LAYOUT_KTILE || K == BK];  // (the same bytes when K == 64)
+        const int step = rounds == 1 && !(part && t.kernel == MQ_KERNEL_FP4_DIRECT) ? c.step1 : c.step;
         const double loop = (double)rounds * (kt / (double)slabs * step + c.fixed) * 1e-3;
         const double hbm = 0.5625 * (double)n * (double)K / 5.3e6;
         return 3.0 + (loop > hbm ? loop + 0.2 * hbm : hbm + 0.2 * loop) + (slabs > 1 ? 4.5 : 0.0);
@@ -1526,7 +1524,7 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
         const Fp4Tile &t = kFp4Tiles[i];
         const double us = cost(t, M, N, 1, false);
         if (us < best_us) best_us = us, best = Fp4Plan{i, 1, 0, 0, 0};
-        if (t.kernel != FP4_SMALL || slab_limit < 2) continue;
+        if (t.kernel != MQ_KERNEL_FP4_SMALL || slab_limit < 2) continue;
         const int64_t tiles = tiles_of(t, M, N);
         const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
         if (slabs < 2) continue;
@@ -1572,7 +1570,7 @@ int launch_fp4(const GemmArgs &g, hipStream_t s)
 {
     int cus = 0;
     if (int rc = compute_units(cus)) return rc;
-    const int layout = g.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR;  // (the same bytes when K == 64)
+    const int layout = g.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR;
     const Fp4Plan plan = fp4_plan(g.M, g.N, g.K, layout, gemm_fp4_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
     if (plan.n_first == 0 && plan.m_first == 0) return launch_fp4_tile<OUT_BF16>(plan.tile, plan.slabs, g, s, cus);
     constexpr int64_t T = OUT_BF16 ? 2 : 4;
@@ -1673,6 +1671,32 @@ int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int 
     if (ks > ws_bytes / (M * N * 4)) ks = ws_bytes / (M * N * 4);
     if (ks < 2 || 2 * groups * ks < cus) return 0;  // too few workgroups even so
     return (int)ks;
+}
+
+static int describe_simple(int64_t M, int64_t N, mq_launch *out)
+{
+    out[0] = mq_launch{MQ_KERNEL_SIMPLE, 16, 16, 4, 1, M, N};
+    return 1;
+}
+
+int describe_gemm_fp4(int64_t M, int64_t N, int64_t K, int layout, int64_t ws_bytes, int cus, mq_launch *out)
+{
+    if (K % BK != 0) return describe_simple(M, N, out);
+    const Fp4Plan p = fp4_plan(M, N, K, layout, gemm_fp4_slab_limit(M, N, K, ws_bytes, cus), cus);
+    const Fp4Tile &t = kFp4Tiles[p.tile], &r = kFp4Tiles[p.tile_rest];
+    out[0] = mq_launch{t.kernel, t.bm, t.bn, t.waves, p.slabs, p.m_first ? p.m_first : M, p.n_first ? p.n_first : N};
+    if (p.m_first == 0 && p.n_first == 0) return 1;
+    out[1] = mq_launch{r.kernel, r.bm, r.bn, r.waves, 1, p.m_first ? M - p.m_first : M, p.n_first ? N - p.n_first : N};
+    return 2;
+}
+
+int describe_gemm_bf16(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus, mq_launch *out)
+{
+    if (K % BK != 0) return describe_simple(M, N, out);
+    const Bf16Plan p = bf16_plan(M, N, K, gemm_bf16_slab_limit(M, N, K, ws_bytes, cus), cus);
+    const Bf16Tile &t = kBf16Tiles[p.tile];
+    out[0] = mq_launch{t.kernel, t.bm, t.bn, t.waves, p.slabs, M, N};
+    return 1;
 }
 
 int launch_mfma_probe(float *out, int iters, int blocks, hipStream_t s)

@@ -70,6 +70,9 @@ int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int 
 int configure_gemm_kernels();
 int launch_gemm_fp4(const GemmArgs &g, hipStream_t s);
 int launch_gemm_bf16(const GemmArgs &g, hipStream_t s);
+// what the two products launch (mixquant_diag.h); the arguments are valid ones
+int describe_gemm_fp4(int64_t M, int64_t N, int64_t K, int layout, int64_t ws_bytes, int cus, mq_launch *out);
+int describe_gemm_bf16(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus, mq_launch *out);
 int launch_mfma_probe(float *out, int iters, int blocks, hipStream_t s);
 
 }  // namespace mq

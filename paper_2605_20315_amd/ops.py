@@ -275,3 +275,26 @@ def mfma_probe(iters: int = 4000) -> float:
     rc = _lib.load().mq_mfma_probe(scratch.data_ptr(), iters, _stream(), ctypes.byref(flop))
     _lib.check(rc, "mq_mfma_probe")
     return flop.value
+
+
+KERNEL_NAMES = ("simple", "fp4_direct", "fp4_small", "bf16_ring", "bf16_stage", "bf16_d2l")
+
+
+def _launches(n: int, out) -> list:
+    if n < 0:
+        _lib.check(-n, "mq_gemm_launches")
+    return [{"kernel": KERNEL_NAMES[l.kernel], "tile": (l.bm, l.bn), "waves": l.waves, "slabs": l.slabs,
+             "rows": l.rows, "cols": l.cols} for l in out[:n]]
+
+
+def mq_gemm_launches(M: int, N: int, K: int, layout: int = MQ_LAYOUT_LINEAR, workspace_bytes: int = 0,
+                     compute_units: int = 256) -> list:
+    """What the NVFP4 product launches for this problem (host only): kernel, tile, waves, K slabs, part of Y."""
+    out = (_lib.Launch * 2)()
+    return _launches(_lib.load().mq_gemm_launches(M, N, K, layout, workspace_bytes, compute_units, out), out)
+
+
+def mq_bf16_gemm_launches(M: int, N: int, K: int, workspace_bytes: int = 0, compute_units: int = 256) -> list:
+    """What the BF16 product launches for this problem (host only)."""
+    out = (_lib.Launch * 2)()
+    return _launches(_lib.load().mq_bf16_gemm_launches(M, N, K, workspace_bytes, compute_units, out), out)

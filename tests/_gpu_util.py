@@ -81,3 +81,18 @@ def check_gemm_bf16(y_bits: np.ndarray, y_ref: np.ndarray, norm_a: np.ndarray, n
 def to_ktile(codes: np.ndarray, scales: np.ndarray):
     """The K-step-major byte order from the canonical one: the oracle's plain-loop permutation."""
     return oracle.to_ktile(codes, scales)
+
+
+def full_of_nan(nbytes: int) -> torch.Tensor:
+    """A workspace whose every FP32 word is a NaN no sum of finite products can be (all bits set)."""
+    return torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+
+
+def check_workspace_use(ws: torch.Tensor, slabs: int, M: int, N: int):
+    """A product in `slabs` K slabs has written exactly slabs * M * N FP32 words of a `full_of_nan` workspace,
+    one in a single launch (slabs == 1) none."""
+    used = slabs * M * N if slabs > 1 else 0
+    words = ws[:ws.numel() // 4 * 4].view(torch.int32)
+    assert used <= words.numel()
+    assert bool((words[:used] != -1).all()), "part of the slabs' sums was not written"
+    assert bool((words[used:] == -1).all()) and bool((ws[words.numel() * 4:] == 0xFF).all())

@@ -112,6 +112,32 @@ def test_workspace_size_query(lib):
         assert b <= 256 * 64 * 64 * 4
 
 
+def test_launch_queries_cover_the_output_and_respect_the_workspace():
+    """What the products launch, asked on the host: the parts cover Y exactly, K slabs only where the workspace
+    holds them and never in two parts, K not a multiple of 64 takes the simple kernel."""
+    import random
+    import paper_2605_20315_amd as mq
+    rng = random.Random(3)
+    for _ in range(3000):
+        M, N, K = (rng.choice([rng.randint(1, 300), rng.randint(1, 40000)]) for _ in range(3))
+        K, cus, ws = -(-K // 16) * 16, rng.choice([8, 32, 64, 256]), rng.choice([0, 100, rng.randint(0, 16 << 20)])
+        layout = rng.choice([0, 1]) if K % 64 == 0 else 0
+        for parts in (mq.mq_gemm_launches(M, N, K, layout, ws, cus), mq.mq_bf16_gemm_launches(M, N, K, ws, cus)):
+            assert 1 <= len(parts) <= 2
+            assert sum(p["rows"] * p["cols"] for p in parts) == M * N
+            assert all(p["rows"] == M for p in parts) or all(p["cols"] == N for p in parts)
+            for p in parts:
+                assert p["rows"] >= 1 and p["cols"] >= 1 and p["slabs"] >= 1
+                assert p["slabs"] == 1 or (len(parts) == 1 and p["slabs"] * M * N * 4 <= ws and N % 4 == 0)
+                assert (p["kernel"] == "simple") == (K % 64 != 0)
+                tiles = -(-p["rows"] // p["tile"][0]) * -(-p["cols"] // p["tile"][1]) * p["slabs"]
+                assert p["kernel"] in ("simple", "fp4_direct") or tiles * p["waves"] * 64 < 1 << 32
+    assert mq.mq_gemm_launches(0, 4, 64) == [] and mq.mq_bf16_gemm_launches(4, 0, 64) == []
+    for bad in ((4, 4, 40, 1), (4, 4, 64, 2), (-1, 4, 64, 0)):
+        with pytest.raises(mq.MixQuantError):
+            mq.mq_gemm_launches(*bad)
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     import paper_2605_20315_amd as mq

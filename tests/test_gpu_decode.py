@@ -1,7 +1,8 @@
 """GPU parity of the BF16 product on decode batches of 17 .. 64 tokens (the high-precision path
 that the decode phase keeps), with and without a caller-owned workspace: the weight-streaming
-kernel whose waves split N and share the activations through LDS, and its K slabs across
-workgroups.  Every output is compared with the oracle's FP64 product of the BF16 inputs."""
+kernel whose waves take the K steps in turn, and its K slabs across workgroups.  Every output is
+compared with the oracle's FP64 product of the BF16 inputs; where K slabs are meant, the launch rule is
+asked for their number and the workspace is checked for what was written to it."""
 import numpy as np
 import pytest
 import torch
@@ -10,21 +11,19 @@ import oracle
 import paper_2605_20315_amd as mq
 from paper_2605_20315_amd import _lib, workloads as wl
 
-from _gpu_util import check_gemm_bf16, check_gemm_fp32, dev_bf16, host_bits
+from _gpu_util import check_gemm_bf16, check_gemm_fp32, check_workspace_use, dev_bf16, full_of_nan, host_bits
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K).  A wide N (at least 128 row groups of 128) takes the kernel without slabs, with or
-# without a workspace; a narrow N takes it above 32 tokens with K >= 8192 and a workspace, slabs =
-# min(512 / row groups, K / 512, K / (8 M)); everything else the K-split kernel.
-# (64, 4096, 14336): 16 slabs of 7 super-steps; (33, 6152, 8192): ragged N, 10 slabs of 7 or 6;
-# (40, 4096, 8320): 65 super-steps in 16 slabs (5 + 15 x 4); (48, 1000, 8192): N % 128 != 0;
-# (64, 24640, 384): wide N, three super-steps; (32, 16392, 1024), (17, 28672, 512): wide ragged N,
-# two token tiles; (20, 520, 1024), (24, 4096, 8192): narrow N below 33 tokens; (64, 4096, 4096):
-# narrow N, short K; (64, 4098, 8192): N % 4 != 0, no slabs; (40, 4096, 320): K % 128 != 0.
+# (M, N, K).  K slabs with a workspace: (64, 4096, 14336), 224 K steps in 4 slabs; (48, 1000, 8192), N % 64 != 0;
+# otherwise one launch: (33, 6152, 8192), ragged N; (40, 4096, 8320), 130 K steps; (64, 24640, 384), wide N,
+# six K steps; (32, 16392, 1024), (17, 28672, 512): wide ragged N, two token tiles; (20, 520, 1024),
+# (24, 4096, 8192): narrow N below 33 tokens; (64, 4096, 4096): short K; (64, 4098, 8192): N % 4 != 0;
+# (40, 4096, 320): five K steps.
 SHAPES = [(64, 4096, 14336), (33, 6152, 8192), (40, 4096, 8320), (48, 1000, 8192),
           (64, 24640, 384), (32, 16392, 1024), (17, 28672, 512), (20, 520, 1024), (24, 4096, 8192),
           (64, 4096, 4096), (64, 4098, 8192), (40, 4096, 320)]
+SLAB_SHAPES = {(64, 4096, 14336), (48, 1000, 8192)}
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
@@ -38,7 +37,9 @@ def test_decode_batches_with_and_without_workspace(M, N, K):
     xd, wd = dev_bf16(x), dev_bf16(w)
     need = mq.mq_bf16_gemm_workspace_bytes(M, N, K)
     assert need % (M * N * 4) == 0
-    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+    slabs = mq.mq_bf16_gemm_launches(M, N, K, need)[0]["slabs"]
+    assert slabs >= 2 or (M, N, K) not in SLAB_SHAPES
+    ws = full_of_nan(max(need, 16))
     ld = (N + 7) // 8 * 8 + 8
     for workspace in (None, ws):
         b32 = torch.full((M + 1, ld), -7.0, dtype=torch.float32, device="cuda")
@@ -54,6 +55,7 @@ def test_decode_batches_with_and_without_workspace(M, N, K):
         assert torch.equal(again[:, :N], y16)
         for buf in (b32, b16):
             assert bool((buf[M:] == -7.0).all()) and bool((buf[:, N:] == -7.0).all())
+    check_workspace_use(ws, slabs, M, N)
     # the plain entry point is the workspace variant without a workspace
     y_plain = torch.empty((M, ld), dtype=torch.bfloat16, device="cuda")
     mq.bf16_gemm(xd, wd, mq.MQ_OUT_BF16, y_plain[:, :N])
@@ -71,19 +73,24 @@ def test_workspace_query_and_small_workspaces():
     assert q(16, 4096, 8192) == 0 and q(65, 4096, 8192) == 0          # other kernels serve these
     assert q(64, 4098, 8192) == 0 and q(64, 4096, 8256) == 0 and q(64, 4096, 4096) == 0
     assert q(64, 28672, 8192) == 0 and q(32, 4096, 8192) == 0      # wide N: no slabs; up to 32 tokens: none
-    M, N, K = 64, 4096, 8192
+    M, N, K = 64, 4096, 14336
     rng = np.random.default_rng(3)
     x = wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
     w = wl.f32_to_bf16_bits((rng.standard_normal((N, K)) * K ** -0.5).astype(np.float32))
     a, b = oracle.bf16_to_f64(x), oracle.bf16_to_f64(w)
     ref, na, nb = oracle.gemm_f64(a, b), oracle.row_norms(a), oracle.row_norms(b)
     xd, wd = dev_bf16(x), dev_bf16(w)
-    # room for five slabs, for one (= none), for a fraction of one, and an unaligned size
-    for nbytes in (5 * M * N * 4, M * N * 4, 100, q(M, N, K) - 4):
-        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    slab = M * N * 4
+    most = mq.mq_bf16_gemm_launches(M, N, K, q(M, N, K))[0]["slabs"]
+    assert most >= 4
+    # all that can be used, an unaligned size, one slab (= none), a fraction of one
+    for nbytes, slabs in ((q(M, N, K), most), (most * slab + 4, most), (slab, 1), (100, 1)):
+        assert mq.mq_bf16_gemm_launches(M, N, K, nbytes)[0]["slabs"] == slabs
+        ws = full_of_nan(nbytes)
         y = mq.bf16_gemm_ws(xd, wd, ws, mq.MQ_OUT_FP32)
         torch.cuda.synchronize()
         check_gemm_fp32(y.cpu().numpy(), ref, na, nb)
+        check_workspace_use(ws, slabs, M, N)
     lib = _lib.load()
     y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
     ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")

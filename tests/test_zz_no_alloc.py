@@ -10,7 +10,8 @@ import oracle
 import paper_2605_20315_amd as mq
 from paper_2605_20315_amd import _lib
 
-from _gpu_util import check_gemm_bf16, check_gemm_fp32, dev_scalar, dev_u8, host_bits
+from _gpu_util import (check_gemm_bf16, check_gemm_fp32, check_workspace_use, dev_scalar, dev_u8, full_of_nan,
+                       host_bits)
 
 pytestmark = pytest.mark.gpu
 
@@ -34,14 +35,16 @@ def test_noalloc_matches_workspace_entry_point_on_two_calls_in_a_row():
     stream = torch.cuda.current_stream().cuda_stream
     # first a problem that is cut into several slabs, then a smaller one (fewer rows and columns, shorter K)
     # that leaves most of the scratch array holding the first call's partial sums
-    shapes = [(128, 4096, 14336), (40, 264, 8192)]
+    shapes = [(64, 1032, 12288), (40, 264, 8192)]
     for out, dtype in ((mq.MQ_OUT_BF16, torch.bfloat16), (mq.MQ_OUT_FP32, torch.float32)):
         for M, N, K in shapes:
             print(f"\n[case] nvfp4_gemm_noalloc out={out} M={M} N={N} K={K}", flush=True)
             d, a_al, b_al, (ref, na, nb) = _case(M, N, K, 0)
             need = lib.mq_gemm_workspace_bytes(M, N, K)
-            assert 2 * M * N * 4 <= need <= mq.NOALLOC_SCRATCH_BYTES       # slabs are really used
-            ws = torch.empty(mq.NOALLOC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
+            assert 2 * M * N * 4 <= need <= mq.NOALLOC_SCRATCH_BYTES
+            slabs = mq.mq_gemm_launches(M, N, K, mq.MQ_LAYOUT_KTILE, mq.NOALLOC_SCRATCH_BYTES)[0]["slabs"]
+            assert slabs >= 2                                               # the scratch array is really used
+            ws = full_of_nan(mq.NOALLOC_SCRATCH_BYTES)
             y_ws = torch.empty((M, N), dtype=dtype, device="cuda")
             y_na = torch.full((M, N), -5.0, dtype=dtype, device="cuda")
             args = [d[0].data_ptr(), d[1].data_ptr(), a_al.data_ptr(), d[2].data_ptr(), d[3].data_ptr(),
@@ -49,6 +52,7 @@ def test_noalloc_matches_workspace_entry_point_on_two_calls_in_a_row():
             tail = [N, out, mq.MQ_LAYOUT_KTILE]
             assert lib.nvfp4_gemm_ws(*args, y_ws.data_ptr(), *tail, ws.data_ptr(), ws.numel(), stream) == _lib.MQ_OK
             torch.cuda.synchronize()
+            check_workspace_use(ws, slabs, M, N)
             free_before = torch.cuda.mem_get_info()[0]
             assert lib.nvfp4_gemm_noalloc(*args, y_na.data_ptr(), *tail, stream) == _lib.MQ_OK
             torch.cuda.synchronize()
