@@ -73,6 +73,8 @@ def load() -> ctypes.CDLL:
     lib.mq_gemm_launches.argtypes = [i64, i64, i64, ci, i64, ci, ctypes.POINTER(Launch)]
     lib.mq_bf16_gemm_launches.restype = ci
     lib.mq_bf16_gemm_launches.argtypes = [i64, i64, i64, i64, ci, ctypes.POINTER(Launch)]
+    lib.mq_quantize_rows.restype = ci
+    lib.mq_quantize_rows.argtypes = [ci, i64, i64]
     lib.mq_status_string.restype = ctypes.c_char_p
     lib.mq_status_string.argtypes = [ci]
     lib.mq_last_hip_error.restype = ci

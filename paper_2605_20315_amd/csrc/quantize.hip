@@ -81,7 +81,8 @@ __device__ __forceinline__ void quantize_block16(uint4 v0, uint4 v1, float alpha
 struct PlainSrc {
     const uint16_t *x;
     int64_t ldx;
-    static constexpr int kBatch = 4, kFewGroups = 4096;  // see quantize_ktile_kernel
+    static constexpr int kBatch = 4;  // see quantize_ktile_kernel
+    static int few_groups(int64_t rows, int64_t K) { return rows % 4 ? 960 : K < 8192 ? 1100 : 4096; }  // see ktile_rows
     struct Raw {
         uint4 v[2];
     };
@@ -124,7 +125,8 @@ struct SiluMulSrc {
         const float s1 = g1 / (1.0f + __expf(-g1));
         return pack_bf16(s0 * u0, s1 * u1);
     }
-    static constexpr int kBatch = 1, kFewGroups = 16384;
+    static constexpr int kBatch = 1;
+    static int few_groups(int64_t rows, int64_t) { return rows % 4 == 0 ? 16384 : 10240; }
     struct Raw {
         uint4 g[2], u[2];
     };
@@ -174,11 +176,9 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(Src src, int64_t tot
 // contiguous per row (lane l: K step l/4, block l%4).  The codes and scale bytes go through LDS so that
 // writing is contiguous too: per K step ROWS x 32 code bytes and ROWS x 4 scale bytes.
 // HBM-bound for large tensors, bound by one trip to memory for small ones.  ROWS = 4, one row per wave: every
-// wave waits for memory once and there are four times as many of them ([64, 4096] 2.2 us against 3.3 with 16
-// rows, one after the other, [1000, 14336] with silu_mul 15.1 against 18.1, [8192, 14336] 56 against 61).
-// ROWS = 16 from Src::kFewGroups workgroups of that size: 512 instead of 128 contiguous bytes per K step
-// ([65536, 4096] 129 us against 139); the waves' rows are then loaded Src::kBatch at a time (all four of
-// silu_mul's cost more in registers than they hide).
+// wave waits for memory once and there are four times as many of them.  ROWS = 16: 512 instead of 128
+// contiguous bytes per K step; the waves' rows are then loaded Src::kBatch at a time (all four of
+// silu_mul's cost more in registers than they hide).  Which: ktile_rows.
 constexpr int kt_stride(int rows) { return rows * 4 + 4; }  // uint2 units per K step in LDS, padded against bank conflicts
 
 // Second half of the transposition: thread `u` < 16 ROWS (K step u / ROWS, row u % ROWS) writes one unit of 32 + 4 bytes.
@@ -516,6 +516,22 @@ __global__ void amax_final_kernel(uint32_t *acc)
 
 namespace {
 
+// Rows per workgroup of quantize_ktile_kernel, by the number of workgroups of sixteen.  us with four rows against
+// sixteen, inputs from HBM:
+//   plain, K = 4096: [64] 3.8 / 4.5, [2048] 6.3 / 7.7, [3584] 8.4 / 9.5, [4096] 10.0 / 10.4, [5120] 12.9 / 12.6, [8192]
+//     18.7 / 17.7, [65536] 138 / 127; K = 5120: ragged [2861] 9.4 / 9.9, [3261] 11.4 / 10.9, [4096] 14.1 / 13.0: sixteen from a
+//     thousand workgroups, which fill the chip's wave slots.  A long K with whole lines written by four rows
+//     (rows % 4 == 0): [1456, 14336] 12.3 / 13.4, [2336, 14336] 17.4 / 17.9, [4672, 14336] 31.8 / 32.7, [2608, 25600] 31.8 / 32.5,
+//     [6848, 14336] 46.2 / 46.1, [8192, 14336] 54.1 / 56.0, [10480, 25600] 138 / 135; ragged [3421, 14336] 25.9 / 24.9.
+//   silu_mul, K = 14336: [64] 4.3 / 7.6, [1024] 15.6 / 19.0, [8000] 108 / 113, [18720] 247 / 254; rows % 4 != 0 (the 128 bytes
+//     of four rows are then no whole line): [9133] 134.0 / 134.7, [18269] 270 / 261; K = 25600: [7677] 204 / 199.
+template <class Src>
+int ktile_rows(int64_t rows, int64_t K)
+{
+    const int64_t groups = (K / 64 + 15) / 16 * ((rows + 15) / 16);
+    return groups < Src::few_groups(rows, K) ? 4 : 16;
+}
+
 template <class Src>
 int launch_quantize_from(const Src &src, int64_t rows, int64_t K, const float *alpha, uint8_t *codes,
                          uint8_t *scales, int layout, hipStream_t s)
@@ -525,7 +541,7 @@ int launch_quantize_from(const Src &src, int64_t rows, int64_t K, const float *a
     if (total == 0) return MQ_OK;
     if (layout == MQ_LAYOUT_KTILE) {
         const int64_t ksteps = K / 64, gx = (ksteps + 15) / 16;
-        const int per = gx * ((rows + 15) / 16) < Src::kFewGroups ? 4 : 16;  // rows per workgroup
+        const int per = ktile_rows<Src>(rows, K);
         const int64_t gy = (rows + per - 1) / per;
         // grid.y is limited to 65535: fold the excess row groups into extra launches
         for (int64_t y0 = 0; y0 < gy; y0 += 65535) {
@@ -558,6 +574,11 @@ int launch_quantize_silu_mul(const uint16_t *gate_up, int64_t rows, int64_t K, i
                              uint8_t *codes, uint8_t *scales, int layout, uint16_t *p, int64_t ldp, hipStream_t s)
 {
     return launch_quantize_from(SiluMulSrc{gate_up, ld, K, p, ldp}, rows, K, alpha, codes, scales, layout, s);
+}
+
+int describe_quantize(int source, int64_t rows, int64_t K)
+{
+    return source == 0 ? ktile_rows<PlainSrc>(rows, K) : ktile_rows<SiluMulSrc>(rows, K);
 }
 
 int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx, const uint16_t *w, float eps,

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2605_20315_amd as mq
-from paper_2605_20315_amd import workloads as wl
+from paper_2605_20315_amd import _lib, workloads as wl
 
 from _gpu_util import dev_bf16, dev_scalar, dev_u8, host_bits, to_ktile
 
@@ -20,9 +20,11 @@ def _same(c, s, bits, alpha):
     assert np.array_equal(s.cpu().numpy(), se) and np.array_equal(c.cpu().numpy(), ce)
 
 
-# four rows per workgroup up to 4096 workgroups of sixteen, then sixteen; 1 and 17 K steps, ragged rows
-@pytest.mark.parametrize("rows,K", [(3, 64), (18, 1088), (65519, 64), (65543, 64), (32770, 1088)])
-def test_quantize_rows_per_workgroup(rows, K):
+# four rows per workgroup up to 960 (rows % 4 == 0: 1100) workgroups of sixteen, then sixteen; 1 and 17 K steps, ragged rows
+@pytest.mark.parametrize("rows,K,per", [(3, 64, 4), (18, 1088, 4), (15343, 64, 4), (15347, 64, 16), (7660, 1088, 4), (7670, 1088, 16), (8784, 1088, 4), (8800, 1088, 16),
+                                        (65543, 64, 16), (32770, 1088, 16)])
+def test_quantize_rows_per_workgroup(rows, K, per):
+    assert _lib.load().mq_quantize_rows(0, rows, K) == per
     rng = np.random.default_rng([rows, K])
     bits = wl.f32_to_bf16_bits(rng.standard_normal((rows, K), dtype=np.float32))
     c, s = mq.nvfp4_quantize(dev_bf16(bits), dev_scalar(0.002), layout=mq.MQ_LAYOUT_KTILE)
@@ -30,8 +32,10 @@ def test_quantize_rows_per_workgroup(rows, K):
     _same(c, s, bits, np.float32(0.002))
 
 
-@pytest.mark.parametrize("rows,K", [(5, 1088), (262129, 64), (262153, 64)])  # sixteen rows from 16384 workgroups
-def test_silu_mul_rows_per_workgroup(rows, K):
+# sixteen rows from 16384 workgroups, from 10240 where rows % 4 != 0
+@pytest.mark.parametrize("rows,K,per", [(5, 1088, 4), (163823, 64, 4), (163825, 64, 16), (262124, 64, 4), (262136, 64, 16)])
+def test_silu_mul_rows_per_workgroup(rows, K, per):
+    assert _lib.load().mq_quantize_rows(1, rows, K) == per
     gu = torch.randn((rows, 2 * K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(rows)).to(torch.bfloat16)
     c, s, p = mq.nvfp4_quantize_silu_mul(gu, dev_scalar(0.002), layout=mq.MQ_LAYOUT_KTILE, return_bf16=True)
     ref = oracle.bf16_round(oracle.silu_mul_f64(host_bits(gu)))
