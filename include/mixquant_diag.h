@@ -49,9 +49,9 @@ typedef struct {
 int mq_gemm_launches(int64_t M, int64_t N, int64_t K, int layout, int64_t workspace_bytes, int cus, mq_launch out[2]);
 int mq_bf16_gemm_launches(int64_t M, int64_t N, int64_t K, int64_t workspace_bytes, int cus, mq_launch out[2]);
 
-/* Rows per workgroup of the quantizers with K-step-major output (K % 64 == 0): nvfp4_quantize (silu_mul == 0) or
- * nvfp4_quantize_silu_mul.  Minus an mq_status for a bad shape. */
-int mq_quantize_rows(int silu_mul, int64_t rows, int64_t K);
+/* Rows per workgroup of the quantizers with K-step-major output (K % 64 == 0): source 0 nvfp4_quantize,
+ * 1 nvfp4_quantize_silu_mul, 2 nvfp4_quantize_rmsnorm.  Minus an mq_status for bad arguments. */
+int mq_quantize_rows(int source, int64_t rows, int64_t K);
 
 #ifdef __cplusplus
 }

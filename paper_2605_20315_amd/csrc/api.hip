@@ -336,10 +336,11 @@ int mq_bf16_gemm_launches(int64_t M, int64_t N, int64_t K, int64_t workspace_byt
     return M == 0 || N == 0 ? 0 : describe_gemm_bf16(M, N, K, workspace_bytes, cus, out);
 }
 
-int mq_quantize_rows(int silu_mul, int64_t rows, int64_t K)
+int mq_quantize_rows(int source, int64_t rows, int64_t K)
 {
+    if (source < 0 || source > 2) return -MQ_ERR_ARG;
     if (rows < 1 || K <= 0 || K % 64 != 0) return -MQ_ERR_SHAPE;
-    return describe_quantize(silu_mul, rows, K);
+    return describe_quantize(source, rows, K);
 }
 
 const char *mq_status_string(int status)

@@ -34,7 +34,7 @@ int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t 
                             const float *alpha, uint8_t *codes, uint8_t *scales, int layout, uint16_t *y,
                             int64_t ldy, hipStream_t s);
 
-// rows per workgroup of the K-step-major quantizers (source: 0 the tensor itself, 1 silu_mul)
+// rows per workgroup of the K-step-major quantizers (source: 0 the tensor itself, 1 silu_mul, 2 rmsnorm)
 int describe_quantize(int source, int64_t rows, int64_t K);
 
 int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, uint8_t *dst_s, int64_t rows,

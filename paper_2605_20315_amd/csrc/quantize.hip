@@ -576,9 +576,24 @@ int launch_quantize_silu_mul(const uint16_t *gate_up, int64_t rows, int64_t K, i
     return launch_quantize_from(SiluMulSrc{gate_up, ld, K, p, ldp}, rows, K, alpha, codes, scales, layout, s);
 }
 
+// Rows per workgroup of rmsnorm_quantize_kernel.  Four: more workgroups (63 of 16 rows left three quarters of the
+// chip idle at 1000 tokens), and registers for longer rows.  us, four rows against sixteen: K = 4096 (the row in 32
+// registers per lane either way) [64] 4.5 / 7.4, [1000] 6.0 / 8.6, [4096] 13.6 / 13.5, [65536] 147 / 162; K = 5120
+// (64 registers against reading x twice) [1000] 7.4 / 12.3, row-major [8192] 28.2 / 32.4, [65536] 18 % faster, but
+// K-step-major, where four rows write 128 bytes per K step and sixteen 512: [6000] 26.9 / 29.1, [8192] 34.1 / 33.1,
+// [12000] 1.5 % slower, [65536] 5 % slower, and K = 4160 [8192] 32.2 / 29.1; K = 6144 and 8192 6 to 25 % faster up to
+// 32768 rows; K = 14336 (128 registers) [1000] 17.5 / 31.7, [4096] 66 / 47.
+static int rmsnorm_rows(int64_t rows, int ksteps, bool ktile)
+{
+    if (ksteps > 128) return ksteps <= 256 && rows <= 1024 ? 4 : 16;
+    return ktile && ksteps > 64 && ksteps < 96 && rows > 6144 ? 16 : 4;
+}
+
 int describe_quantize(int source, int64_t rows, int64_t K)
 {
-    return source == 0 ? ktile_rows<PlainSrc>(rows, K) : ktile_rows<SiluMulSrc>(rows, K);
+    return source == 0   ? ktile_rows<PlainSrc>(rows, K)
+           : source == 1 ? ktile_rows<SiluMulSrc>(rows, K)
+                         : rmsnorm_rows(rows, (int)(K / 64), true);
 }
 
 int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx, const uint16_t *w, float eps,
@@ -589,13 +604,8 @@ int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t 
     const int ksteps = (int)(K / 64);
     const float inv_k = 1.0f / (float)K;
     const bool kt = layout == MQ_LAYOUT_KTILE;
-    // Workgroups of four rows: more of them (63 of 16 rows left three quarters of the chip idle at 1000
-    // tokens), and registers for longer rows.  us, four rows against sixteen: K = 4096 (the row in 32
-    // registers per lane either way) [64] 4.5 / 7.4, [1000] 6.0 / 8.6, [4096] 13.6 / 13.5, [65536] 147 / 162; K = 5120
-    // (64 registers against reading x twice) [1000] 7.4 / 12.3, [16384] 62 / 67, [65536] 224 / 213; K = 14336 (128
-    // registers) [1000] 17.5 / 31.7, [4096] 66 / 47.
-    const bool few = ksteps <= 64 || (ksteps <= 128 && rows <= 16384) || (ksteps <= 256 && rows <= 1024);
-    const int per = few ? 4 : 16;
+    const int per = rmsnorm_rows(rows, ksteps, kt);
+    const bool few = per == 4;
     const int64_t groups = (rows + per - 1) / per;
     if (groups > 0x7FFFFFFF) return MQ_ERR_SHAPE;
     const dim3 grid((unsigned)groups), block(64 * per);

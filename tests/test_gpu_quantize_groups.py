@@ -45,7 +45,7 @@ def test_silu_mul_rows_per_workgroup(rows, K, per):
 
 
 # four rows with the row in 4, 8 or 16 chunks of registers, then sixteen with x read twice
-@pytest.mark.parametrize("rows,K", [(3, 4096), (6, 4160), (33, 8192), (5, 8256), (1021, 16384), (2, 16448), (1027, 8256)])
+@pytest.mark.parametrize("rows,K", [(3, 4096), (6, 4160), (33, 8192), (5, 8256), (1021, 16384), (2, 16448), (1027, 8256), (6145, 4160)])
 @pytest.mark.parametrize("layout", [mq.MQ_LAYOUT_KTILE, mq.MQ_LAYOUT_LINEAR])
 def test_rmsnorm_rows_per_workgroup(rows, K, layout):
     g = torch.Generator(device="cuda").manual_seed(rows * K)
