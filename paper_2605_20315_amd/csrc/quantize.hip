@@ -393,21 +393,21 @@ template <bool TO_KTILE>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
-                                                            int64_t rows, int64_t row_base, int64_t ksteps,
-                                                            int64_t step_base, unsigned groups)
+                                                            int64_t rows, int64_t row_base, int64_t row_stride,
+                                                            int ksteps, int groups)
 {
     __shared__ uint4 lc[R_ROWS * R_STRIDE];
     __shared__ uint32_t ls[R_ROWS * (R_STEPS + 1)];
     const int64_t r0 = row_base + (int64_t)(blockIdx.x / groups) * R_ROWS;
-    const int64_t t0 = step_base + (int64_t)(blockIdx.x % groups) * R_STEPS;
+    const int t0 = (int)(blockIdx.x % groups) * R_STEPS;
     // item i of a side: row-major order (row, chunk of 16 bytes); K-step-major order (K step, row, half)
     auto lin = [](int i, int &row, int &chunk) { row = i / R_CHUNKS, chunk = i % R_CHUNKS; };
     auto kt = [](int i, int &row, int &chunk) {
         row = (i / 2) % R_ROWS, chunk = i / (2 * R_ROWS) * 2 + i % 2;
     };
     auto inside = [&](int row, int t) { return r0 + row < rows && t0 + t < ksteps; };
-    auto lin_at = [&](int row, int t) { return (r0 + row) * ksteps + t0 + t; };   // unit (row, K step)
-    auto kt_at = [&](int row, int t) { return (t0 + t) * rows + r0 + row; };
+    auto lin_at = [&](int row, int t) { return (r0 + row) * row_stride + t0 + t; };   // unit (row, K step)
+    auto kt_at = [&](int row, int t) { return (int64_t)(t0 + t) * rows + r0 + row; };
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
         int row, chunk;
@@ -440,6 +440,29 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
         if (inside(row, t))
             reinterpret_cast<uint32_t *>(dst_s)[TO_KTILE ? kt_at(row, t) : lin_at(row, t)] = ls[row * (R_STEPS + 1) + t];
     }
+}
+
+// The same permutation, one thread per (row, K step) unit of 32 + 4 bytes, for tensors that the tiles above serve
+// badly: fewer than four K steps leave most of a tile empty ([262144, 64] 6.2 us here, 11.6 and 14.2 in tiles;
+// [262144, 128] 14.0 / 10.9 against 15.0 / 21.1), and small ones are over before a tile has been through LDS
+// ([4096, 1024] 4.1 against 5.0, [8192, 512] 4.0 against 5.1; to the K-step-major order also [16384, 512] 4.9
+// against 5.7, but [16384, 1024] 7.0 against 6.6; from it [16384, 512] 5.3 against 4.9).
+template <bool TO_KTILE>
+__global__ __launch_bounds__(kThreads) void relayout_units_kernel(const uint8_t *__restrict__ src_c,
+                                                                  const uint8_t *__restrict__ src_s,
+                                                                  uint8_t *__restrict__ dst_c,
+                                                                  uint8_t *__restrict__ dst_s, uint32_t rows,
+                                                                  uint32_t ksteps, uint32_t units)
+{
+    const uint32_t u = blockIdx.x * kThreads + threadIdx.x;  // K-step-major unit
+    if (u >= units) return;
+    const uint32_t t = u / rows, r = u - t * rows;
+    const size_t lin = r * ksteps + t, from = TO_KTILE ? lin : u, to = TO_KTILE ? u : lin;
+    const uint4 c0 = reinterpret_cast<const uint4 *>(src_c)[from * 2], c1 = reinterpret_cast<const uint4 *>(src_c)[from * 2 + 1];
+    const uint32_t sc = reinterpret_cast<const uint32_t *>(src_s)[from];
+    reinterpret_cast<uint4 *>(dst_c)[to * 2] = c0;
+    reinterpret_cast<uint4 *>(dst_c)[to * 2 + 1] = c1;
+    reinterpret_cast<uint32_t *>(dst_s)[to] = sc;
 }
 
 // ---- tensor-level scale ------------------------------------------------------------------
@@ -632,6 +655,13 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
     const int64_t ksteps = K / 64;
     if (rows == 0 || ksteps == 0) return MQ_OK;
     if (rows * ksteps > (int64_t)0x7FFFFFFF * kThreads) return MQ_ERR_SHAPE;
+    const int64_t units = rows * ksteps;
+    if ((ksteps < 4 && units < (1ll << 31)) || units < (to_ktile ? 3 << 16 : 1 << 17)) {
+        auto kern = to_ktile ? relayout_units_kernel<true> : relayout_units_kernel<false>;
+        kern<<<dim3((unsigned)((units + kThreads - 1) / kThreads)), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, (uint32_t)rows,
+                                                                                         (uint32_t)ksteps, (uint32_t)units);
+        return note_launch(hipGetLastError());
+    }
     const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, panels = (rows + R_ROWS - 1) / R_ROWS;
     // a launch holds fewer than 2^32 threads: what is more goes into further launches, by rows and, where one panel
     // of rows has more workgroups than that (K beyond 1.7e10), by K steps
@@ -641,9 +671,12 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
         for (int64_t g0 = 0; g0 < groups; g0 += max_groups) {
             const int64_t n = panels - p0 < max_panels ? panels - p0 : max_panels;
             const int64_t ng = groups - g0 < max_groups ? groups - g0 : max_groups;
+            // (a launch sees its K steps as the first ones: the arrays from there on, with the whole row's stride)
+            const int64_t t = g0 * R_STEPS, left = ksteps - t < ng * R_STEPS ? ksteps - t : ng * R_STEPS;
+            const int64_t from = to_ktile ? t : t * rows, to = to_ktile ? t * rows : t;
             auto kern = to_ktile ? relayout_kernel<true> : relayout_kernel<false>;
-            kern<<<dim3((unsigned)(n * ng)), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, rows, p0 * R_ROWS, ksteps,
-                                                                     g0 * R_STEPS, (unsigned)ng);
+            kern<<<dim3((unsigned)(n * ng)), dim3(kThreads), 0, s>>>(src_c + from * 32, src_s + from * 4, dst_c + to * 32,
+                                                                     dst_s + to * 4, rows, p0 * R_ROWS, ksteps, (int)left, (int)ng);
             int rc = note_launch(hipGetLastError());
             if (rc != MQ_OK) return rc;
         }

@@ -61,7 +61,9 @@ def test_rmsnorm_rows_per_workgroup(rows, K, layout):
     assert np.array_equal(s.cpu().numpy(), se) and np.array_equal(c.cpu().numpy(), ce)
 
 
-@pytest.mark.parametrize("rows,K", [(31, 960), (33, 1088), (64, 2048), (1, 8256)])  # tiles of 32 rows x 16 K steps
+# one thread per unit of (row, K step) below 2^17 units (3 * 2^16 to the K-step-major order) or four K steps, else tiles of 32 rows x 16 K steps
+@pytest.mark.parametrize("rows,K", [(31, 960), (33, 1088), (64, 2048), (1, 8256), (1, 64), (140001, 64), (70001, 192), (131071, 64),
+                                    (32767, 256), (32769, 256), (49151, 256), (49153, 256), (7711, 1088), (1025, 8192), (33, 256064)])
 def test_relayout_ragged_tiles(rows, K):
     rng = np.random.default_rng([rows, K])
     c = rng.integers(0, 256, size=(rows, K // 2)).astype(np.uint8)
