@@ -31,7 +31,8 @@ int mq_mfma_probe(float *scratch_dev, int iters, void *stream, double *flop_out)
  * A product is one launch, or two that cover the first rows or columns of Y and the others; the second
  * pass of a product cut into K slabs is not counted.  Each launch: the kernel, its workgroups' tile
  * (bm rows x bn columns of Y) and waves, the number of K slabs (1: none, no workspace is touched), and
- * the part of Y that it covers.  Returns the number of launches (0 for an empty Y), or minus an
+ * the part of Y that it covers.  (The same for either output type, so that the BF16 output is the rounded
+ * FP32 output bit for bit.)  Returns the number of launches (0 for an empty Y), or minus an
  * mq_status.
  */
 typedef enum {
@@ -40,7 +41,8 @@ typedef enum {
     MQ_KERNEL_FP4_SMALL = 2,
     MQ_KERNEL_BF16_RING = 3,
     MQ_KERNEL_BF16_STAGE = 4,
-    MQ_KERNEL_BF16_D2L = 5
+    MQ_KERNEL_BF16_D2L = 5,
+    MQ_KERNEL_BF16_SHORT = 6
 } mq_kernel;
 typedef struct {
     int kernel, bm, bn, waves, slabs;

@@ -23,10 +23,11 @@
 //                       above leave over: 32x32 to 128x64 tiles, one workgroup per tile, K split over
 //                       its waves; for a long K with very few tiles also over workgroups
 //                       (splitk_reduce_kernel then adds the slabs).
-//   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256 tile, four waves of 128x128,
-//                       tiles loaded from global memory straight into LDS.
+//   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256 tile, four waves of 128x128 (256x128, four
+//                       of 128x64, for a short K), tiles loaded from global memory straight into LDS.
 //   bf16_ring_kernel    BF16 decode batches: narrow tiles, the waves of a workgroup split K, each with a
 //                       ring of its own in LDS; K slabs across workgroups with a workspace.
+//   bf16_short_kernel   BF16, up to 16 tokens and K <= 1024: 16x16 tiles, fragments straight into registers.
 //   bf16_stage_kernel   BF16 in between: 96x64 to 256x192 tiles, two to six stages in LDS.
 //   gemm_simple_kernel  any K % 16 == 0 / K % 8 == 0 that the tiled kernels do not take.
 //
@@ -1077,6 +1078,51 @@ __global__ __launch_bounds__(64 * S) void bf16_ring_kernel(GemmArgs g, int tiles
     }
 }
 
+// A few tokens against a short K: the same tile, K order and sums as bf16_ring_kernel<1, 1, S>, but every lane
+// loads its fragments straight into registers, two K steps per wave in flight.  With one or two steps per
+// wave there is no stream to keep up; what counts is the latency of one load, and the trip through the ring
+// is added to it.  us, here / in the ring / in the register-streaming kernel before both: one token on K = 256, N = 4096
+// 4.4 / 4.8 / 4.4, K = 512 4.8 / 5.1 / 4.8, K = 1024 5.5 / 5.8 / 5.5 (K = 2048 7.2 / 7.3 / 7.1: left to the
+// ring); 16 tokens, K = 512 5.2 / 5.2 / 5.1.
+template <int S, bool OUT_BF16>
+__global__ __launch_bounds__(64 * S) void bf16_short_kernel(GemmArgs g, int tiles_m, int tiles_n)
+{
+    constexpr int D = 2;
+    __shared__ f32x4 X[S * 64];
+    const int tid = threadIdx.x, lane = tid & 63, row = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = logical_id(blockIdx.x, tiles_m * tiles_n);
+    const int64_t m0 = (int64_t)(t % tiles_m) * 16, n0 = (int64_t)(t / tiles_m) * 16;  // m0 < M, n0 < N
+    const int KT = (int)(g.K / BK);
+    const int64_t mr = m0 + row < g.M ? m0 + row : g.M - 1, nr = n0 + row < g.N ? n0 + row : g.N - 1;
+    const uint4 *const px = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.a) + mr * g.lda) + grp;
+    const uint4 *const pw = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(g.b) + nr * g.ldb) + grp;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k0 = wave; k0 < KT; k0 += D * S) {
+        uint4 x[D][2], w[D][2];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int64_t k = k0 + d * S;
+            if (k < KT) {  // uniform
+                w[d][0] = pw[k * 8], w[d][1] = pw[k * 8 + 4];
+                x[d][0] = px[k * 8], x[d][1] = px[k * 8 + 4];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (k0 + d * S < KT)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[d][h]),
+                                                                  __builtin_bit_cast(bf16x8, x[d][h]), acc, 0, 0, 0);
+    }
+    X[wave * 64 + lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    for (int w = 1; w < S; ++w) acc += X[w * 64 + lane];
+    store_quad<OUT_BF16>(g, acc, m0 + row, n0 + 4 * grp);
+}
+
 // From about a hundred tokens: a (16 TM WM) x (16 TN WN) tile per workgroup of WM x WN waves, NST stages of
 // 64-wide K steps in LDS filled by direct-to-LDS loads, one barrier per K step.  Same row layout, swizzle
 // and fragment order as above.  A K step is two phases of 32: the fragments of the next phase are
@@ -1340,58 +1386,84 @@ int launch_simple(const GemmArgs &g, hipStream_t s)
 // more tiles than this (hundreds of millions of rows in narrow tiles), the larger tiles serve what is left.
 static constexpr int64_t kMaxSmallTiles = (1ll << 23) - 1;
 
+// ---- what a launch costs, as the choice of a tile sees it -------------------------------------------
+
+// Time of one launch in a given tile: two things hide behind each other for the most part, the operands' one trip
+// from memory (`mem` us) and the K steps of the rounds of workgroups (one per compute unit); what is written
+// comes on top.  In ns: `start` once, `round` per round (first loads, sums, stores of a workgroup), `step` per K
+// step and round, `share` per K step and full round by how full the chip is on average (all
+// compute units busy share caches and clock: a round of 224 workgroups of 256 is no eighth cheaper, but cheaper).
+// `out`: percent of what writing Y takes at 5 TB/s.
+struct TileCost {
+    float start, round, step, share, out;
+};
+static double launch_us(const TileCost &c, int64_t tiles, double kt, double mem, double hidden, double out_bytes, int cus)
+{
+    const double loop = ((double)((tiles + cus - 1) / cus) * (c.round + kt * c.step) + (double)tiles / cus * kt * c.share) * 1e-3;
+    return c.start * 1e-3 + (loop > mem ? loop + hidden * mem : mem + hidden * loop) + c.out * 1e-2 * out_bytes / 5e6;
+}
+
 // ---- which BF16 kernel and tile ---------------------------------------------------------------------
 
-// The tiles (tokens x rows of W) that the BF16 kernels are built in.  step: measured time of one 64-wide K
-// step of one round of workgroups (one per compute unit) in ns, as far as it does not overlap with
-// the weights' trip from HBM.
+// The tiles (tokens x rows of W) that the BF16 kernels are built in, and their costs (above).
 struct Bf16Tile {
     mq_kernel kernel;
-    int bm, bn, waves, step;
+    int bm, bn, waves;
 };
-#define MQ_RING(X) /* MT, NT, S, step */                                                                     \
-    X(1, 1, 8, 66) X(1, 2, 4, 99) X(1, 4, 4, 174) X(2, 1, 8, 94) X(2, 2, 4, 112) X(2, 4, 4, 196) \
-    X(3, 2, 4, 138) X(3, 4, 4, 217) X(4, 2, 4, 168) X(4, 4, 4, 228)
-#define MQ_STAGE(X) /* TM, TN, WM, WN, NST, step */                                                          \
-    X(3, 2, 2, 2, 6, 311) X(4, 2, 2, 2, 4, 362) X(3, 4, 2, 2, 4, 447) X(4, 2, 2, 4, 4, 511) \
-    X(5, 4, 2, 2, 4, 593) X(7, 4, 2, 2, 3, 727) X(8, 4, 2, 2, 3, 804) X(8, 6, 2, 2, 2, 1168)
+#define MQ_RING(X) /* MT, NT, S */ \
+    X(1, 1, 8) X(1, 2, 4) X(1, 4, 4) X(2, 1, 8) X(2, 2, 4) X(2, 4, 4) X(3, 2, 4) X(3, 4, 4) X(4, 2, 4) X(4, 4, 4)
+#define MQ_STAGE(X) /* TM, TN, WM, WN, NST */ \
+    X(3, 2, 2, 2, 6) X(4, 2, 2, 2, 4) X(3, 4, 2, 2, 4) X(4, 2, 2, 4, 4) X(5, 4, 2, 2, 4) X(7, 4, 2, 2, 3) X(8, 4, 2, 2, 3) X(8, 6, 2, 2, 2)
 static constexpr Bf16Tile kBf16Tiles[] = {
-#define MQ_X(MT, NT, S, STEP) {MQ_KERNEL_BF16_RING, 16 * MT, 16 * NT, S, STEP},
+#define MQ_X(MT, NT, S) {MQ_KERNEL_BF16_RING, 16 * MT, 16 * NT, S},
     MQ_RING(MQ_X)
 #undef MQ_X
-#define MQ_X(TM, TN, WM, WN, NST, STEP) {MQ_KERNEL_BF16_STAGE, 16 * TM * WM, 16 * TN * WN, WM * WN, STEP},
+#define MQ_X(TM, TN, WM, WN, NST) {MQ_KERNEL_BF16_STAGE, 16 * TM * WM, 16 * TN * WN, WM * WN},
     MQ_STAGE(MQ_X)
 #undef MQ_X
-    {MQ_KERNEL_BF16_D2L, 256, 256, 4, 1440}};
+    {MQ_KERNEL_BF16_D2L, 256, 128, 4}, {MQ_KERNEL_BF16_D2L, 256, 256, 4}, {MQ_KERNEL_BF16_SHORT, 16, 16, 8}};
+static constexpr TileCost kBf16Costs[] = {
+    {3990.7, 490.23, 33.944, 0, 215.64}, {4232.3, 285.89, 67.673, 0, 121.71}, {4290.4, 1760.9, 116.09, 0, 101.7},
+    {2500, 1917.2, 67.252, 0, 400}, {4165.3, 476.99, 85.889, 0, 152.39}, {3802.9, 1712.7, 145.39, 0, 63.315},
+    {4418.7, 542.73, 126.77, 0, 42.119}, {3161.5, 2935.1, 160.67, 0, 139.48},
+    {3178.4, 1632.6, 142.34, 3.1851, 395.14}, {3862.2, 2348.2, 178.4, 0, 108.89},
+    {3306.3, 2445.4, 255.17, 0, 27.392}, {3621.8, 2048.8, 209.56, 109.8, 48.971},
+    {3525.3, 2209.3, 219.72, 172.63, 116.05}, {3155.8, 3656.7, 320.78, 117.18, 96.95},
+    {3107.7, 5612.9, 439.75, 59.295, 35.466}, {2500, 5177.6, 384.7, 203.85, 95.535},
+    {2500, 6277.5, 638.11, 0, 134.09}, {2795.2, 9151.5, 684.2, 285.04, 37.859},
+    {6000, 2435.8, 866.71, 91.375, 59.163}, {6000, 6331.1, 699.25, 535.96, 41.413},
+    {2665.9, 650.8, 106.65, 17.193, 247.09}};
+static_assert(sizeof(kBf16Costs) / sizeof(TileCost) == sizeof(kBf16Tiles) / sizeof(Bf16Tile), "one cost per tile");
 
 struct Bf16Plan {
     int tile;   // index into kBf16Tiles
     int slabs;  // K slabs across workgroups (1: none)
 };
 
-// The tile that costs least.  Two things take the time: the weights' one trip from HBM (5.3 TB/s), and the
-// K steps of the rounds of workgroups; the smaller one hides behind the larger one almost entirely.  A
-// workgroup's first loads, sums and stores cost it seven more steps, and more tiles than compute units
-// cost whole rounds, so a tile shape that leaves a nearly empty last round loses to one that does
-// not.  The steps and these constants are fitted to every tile's time on 160 shapes (1 to 5000 tokens,
-// the 8B and 32B layers and their 2-, 4- and 8-way shards; weights and activations from HBM): the
-// choice is on average 0.6 % slower than the fastest tile, at worst 9 %.  Slabs, when the caller's workspace allows some, shorten the K loop
-// for a second pass of 3 us (64 tokens, K = 14336, N = 4096: 30.8 us against 36.4 without and 48.5 in the
-// kernel before this one; 33 to 57 tokens 27 to 30 us against 45 to 48).
+// The tile that costs least: the weights, and a third of the activations, make the trip from memory (5.3 TB/s; the other
+// two thirds come from caches), of which 55 % of the shorter one of trip and K steps hides.  A tile shape that leaves
+// a nearly empty last round loses to one that does not.  The costs are fitted to every tile's time on 4100 shapes
+// (1 to 8192 tokens; the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter, narrower and wider ones;
+// weights from HBM; both output types): the choice is on average 0.6 % slower than the fastest tile, 95 % of the shapes
+// within 3.3 %.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096, N = 28672: the weights alone take 44 us, the 224x128 tile 73: K steps and
+// trip overlap only in part there.
+// Slabs, when the caller's workspace allows some, shorten the K loop for a second pass of 3 us (64 tokens, K = 14336,
+// N = 4096: 30.8 us against 36.4 without; 33 to 57 tokens 27 to 30 us).
 static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, int cus)
 {
-    const double kt = (double)(K / BK), hbm = 2.0 * (double)N * (double)K / 5.3e6;
+    const double kt = (double)(K / BK), mem = 2.0 * ((double)N + 0.3 * (double)M) * (double)K / 5.3e6;
+    const double out_bytes = 2.0 * (double)M * (double)N;
     Bf16Plan best{0, 1};
     double best_us = 1e300;
     for (int i = 0; i < (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); ++i) {
         const Bf16Tile &t = kBf16Tiles[i];
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (tiles > (t.kernel == MQ_KERNEL_BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
+        if (t.kernel == MQ_KERNEL_BF16_SHORT && (M > 16 || K > 1024)) continue;
         int64_t slabs = 1;
         for (;;) {
-            const double steps = (double)((tiles * slabs + cus - 1) / cus) * (kt / (double)slabs + 7.0);
-            const double loop = steps * t.step * 1e-3;
-            const double us = (hbm > loop ? hbm + 0.015 * loop : loop + 0.015 * hbm) + (slabs > 1 ? 3.0 : 0.0);
+            const double us = launch_us(kBf16Costs[i], tiles * slabs, kt / (double)slabs, mem, 0.45, out_bytes, cus) +
+                              (slabs > 1 ? 3.0 : 0.0);
             if (us < best_us) best_us = us, best = Bf16Plan{i, (int)slabs};
             if (slabs > 1 || t.kernel != MQ_KERNEL_BF16_RING || slab_limit < 2 || 2 * tiles > cus) break;
             slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
@@ -1438,20 +1510,24 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
 {
     int cus = 0;
     if (int rc = compute_units(cus)) return rc;
-    const Bf16Plan plan = bf16_plan(g.M, g.N, g.K, gemm_bf16_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
+    const Bf16Plan plan =
+        bf16_plan(g.M, g.N, g.K, gemm_bf16_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
     int i = 0;
-#define MQ_X(MT, NT, S, STEP) \
+#define MQ_X(MT, NT, S) \
     if (plan.tile == i++) return launch_ring<MT, NT, S, OUT_BF16>(g, s, plan.slabs);
     MQ_RING(MQ_X)
 #undef MQ_X
-#define MQ_X(TM, TN, WM, WN, NST, STEP)                                                                              \
+#define MQ_X(TM, TN, WM, WN, NST) \
     if (plan.tile == i++)                                                                                            \
         return launch_tiles(bf16_stage_kernel<TM, TN, WM, WN, NST, OUT_BF16>, stage_lds<TM, TN, WM, WN, NST>(),      \
                             16 * TM * WM, 16 * TN * WN, 64 * WM * WN, g, s);
     MQ_STAGE(MQ_X)
 #undef MQ_X
-    using D = PCfg<256, 256, 2, 2>;
-    return launch_tiles(gemm_bf16_d2l<D, OUT_BF16>, D::LDS_BYTES, 256, 256, D::THREADS, g, s);
+    using Mid = PCfg<256, 128, 2, 2>;
+    using Big = PCfg<256, 256, 2, 2>;
+    if (plan.tile == i++) return launch_tiles(gemm_bf16_d2l<Mid, OUT_BF16>, Mid::LDS_BYTES, 256, 128, Mid::THREADS, g, s);
+    if (plan.tile == i++) return launch_tiles(gemm_bf16_d2l<Big, OUT_BF16>, Big::LDS_BYTES, 256, 256, Big::THREADS, g, s);
+    return launch_tiles(bf16_short_kernel<8, OUT_BF16>, 0, 16, 16, 512, g, s);
 }
 
 // ---- which NVFP4 kernel and tile --------------------------------------------------------------------
@@ -1615,7 +1691,8 @@ int configure_gemm_kernels()
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)bytes);
     };
-    using D = PCfg<256, 256, 2, 2>;
+    using Mid = PCfg<256, 128, 2, 2>;
+    using Big = PCfg<256, 256, 2, 2>;
     constexpr size_t X = 128 * 1024;  // accumulator exchange of the K-split variants
     hipError_t e = hipSuccess;
     auto both = [&](auto k_bf16, auto k_fp32, size_t bytes) {
@@ -1628,13 +1705,14 @@ int configure_gemm_kernels()
     both(gemm_fp4_small<TM, TN, S, NSETS, true>, gemm_fp4_small<TM, TN, S, NSETS, false>, small_lds<TM, TN, S>());
     MQ_SMALL(MQ_X)
 #undef MQ_X
-    both(gemm_bf16_d2l<D, true>, gemm_bf16_d2l<D, false>, D::LDS_BYTES);
-#define MQ_X(MT, NT, S, STEP)                                                                                        \
+    both(gemm_bf16_d2l<Mid, true>, gemm_bf16_d2l<Mid, false>, Mid::LDS_BYTES);
+    both(gemm_bf16_d2l<Big, true>, gemm_bf16_d2l<Big, false>, Big::LDS_BYTES);
+#define MQ_X(MT, NT, S) \
     both(bf16_ring_kernel<MT, NT, S, true, true>, bf16_ring_kernel<MT, NT, S, true, false>, ring_lds<MT, NT, S>()); \
     both(bf16_ring_kernel<MT, NT, S, false, true>, bf16_ring_kernel<MT, NT, S, false, false>, ring_lds<MT, NT, S>());
     MQ_RING(MQ_X)
 #undef MQ_X
-#define MQ_X(TM, TN, WM, WN, NST, STEP)                                                               \
+#define MQ_X(TM, TN, WM, WN, NST) \
     both(bf16_stage_kernel<TM, TN, WM, WN, NST, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false>, \
          stage_lds<TM, TN, WM, WN, NST>());
     MQ_STAGE(MQ_X)

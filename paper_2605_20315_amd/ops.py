@@ -277,7 +277,7 @@ def mfma_probe(iters: int = 4000) -> float:
     return flop.value
 
 
-KERNEL_NAMES = ("simple", "fp4_direct", "fp4_small", "bf16_ring", "bf16_stage", "bf16_d2l")
+KERNEL_NAMES = ("simple", "fp4_direct", "fp4_small", "bf16_ring", "bf16_stage", "bf16_d2l", "bf16_short")
 
 
 def _launches(n: int, out) -> list:
@@ -290,11 +290,11 @@ def _launches(n: int, out) -> list:
 def mq_gemm_launches(M: int, N: int, K: int, layout: int = MQ_LAYOUT_LINEAR, workspace_bytes: int = 0,
                      compute_units: int = 256) -> list:
     """What the NVFP4 product launches for this problem (host only): kernel, tile, waves, K slabs, part of Y."""
-    out = (_lib.Launch * 2)()
-    return _launches(_lib.load().mq_gemm_launches(M, N, K, layout, workspace_bytes, compute_units, out), out)
+    got = (_lib.Launch * 2)()
+    return _launches(_lib.load().mq_gemm_launches(M, N, K, layout, workspace_bytes, compute_units, got), got)
 
 
 def mq_bf16_gemm_launches(M: int, N: int, K: int, workspace_bytes: int = 0, compute_units: int = 256) -> list:
     """What the BF16 product launches for this problem (host only)."""
-    out = (_lib.Launch * 2)()
-    return _launches(_lib.load().mq_bf16_gemm_launches(M, N, K, workspace_bytes, compute_units, out), out)
+    got = (_lib.Launch * 2)()
+    return _launches(_lib.load().mq_bf16_gemm_launches(M, N, K, workspace_bytes, compute_units, got), got)

@@ -1,7 +1,6 @@
-"""GPU parity of the BF16 product at one problem per tile shape of its two kernels for decode batches
-and middle sizes (the waves' private rings, the staged tiles), each with ragged M and N, strided
-operands and output, and K of one step up to a few more than the stages or waves, so that prologues,
-idle waves, tails and uneven K shares all run.  Every output is compared with the oracle's FP64
+"""GPU parity of the BF16 product at one problem or more per tile of its kernels, each with ragged M and
+N, strided operands and output, and K of one step up to a few more than the stages or waves, so that
+prologues, idle waves, tails and uneven K shares all run.  Every output is compared with the oracle's FP64
 product; nothing outside [M, N] may be written."""
 import numpy as np
 import pytest
@@ -15,19 +14,26 @@ from _gpu_util import check_gemm_bf16, check_gemm_fp32, dev_bf16, host_bits
 
 pytestmark = pytest.mark.gpu
 
-# tile (tokens x rows of W) on 256 compute units: 16x16 with eight waves (K of 1, 8 and 9 steps), 16x32,
-# 16x64, 32x16, 32x32 (twice), 32x64, 48x32, 48x64, 64x32, 64x64 (K of 5 and 2 steps); staged: 96x64 (K of 7
-# steps and of 2, six stages), 96x128, 128x64, 128x128, 160x128, 224x128, 256x128, 256x192, 256x256;
-# 64x32 with K slabs
-SHAPES = [(1, 8, 64), (3, 40, 512), (16, 1000, 576), (16, 4099, 448), (9, 9000, 128), (2085, 17, 320),
-          (17, 4255, 640), (2729, 33, 192), (65, 4151, 320), (35, 4122, 704), (65, 5834, 448), (49, 4258, 320),
-          (98, 5604, 320), (98, 5604, 128), (129, 5850, 448), (129, 5850, 128), (269, 5655, 192), (207, 5442, 320),
-          (398, 6545, 448), (652, 5426, 192), (667, 6602, 128), (899, 6590, 256), (1327, 7183, 192), (1809, 6157, 64),
-          (61, 4100, 8320)]
+# one problem or two per tile (tokens x rows of W) on 256 compute units; what the launch rule takes is asserted
+SHAPES = [(1, 9, 64, "bf16_short", (16, 16)), (3, 40, 512, "bf16_short", (16, 16)), (16, 1003, 704, "bf16_short", (16, 16)),
+          (1, 4096, 1024, "bf16_short", (16, 16)), (17, 9, 192, "bf16_ring", (16, 16)), (16, 1000, 2112, "bf16_ring", (16, 16)),
+          (1, 4099, 256, "bf16_ring", (16, 32)), (2083, 17, 192, "bf16_ring", (32, 16)), (18, 4197, 320, "bf16_ring", (32, 32)),
+          (71, 4246, 704, "bf16_ring", (32, 64)), (33, 5505, 192, "bf16_ring", (48, 32)), (69, 5849, 576, "bf16_ring", (48, 64)),
+          (49, 4129, 256, "bf16_ring", (64, 32)), (145, 4199, 576, "bf16_ring", (64, 64)), (145, 4133, 192, "bf16_stage", (96, 64)),
+          (265, 5510, 192, "bf16_stage", (96, 128)), (197, 5655, 192, "bf16_stage", (128, 64)), (395, 6686, 192, "bf16_stage", (128, 128)),
+          (530, 7457, 192, "bf16_stage", (160, 128)), (653, 6550, 192, "bf16_stage", (224, 128)),
+          (898, 6837, 512, "bf16_stage", (256, 128)), (1423, 5387, 192, "bf16_stage", (256, 192)),
+          (912, 6685, 192, "bf16_d2l", (256, 128)), (2067, 5411, 192, "bf16_d2l", (256, 256))]
+# K of one step and of two, and K slabs, in whatever tile
+SHAPES += [(s[0], s[1], K, None, None) for s in SHAPES if s[3] in ("bf16_stage", "bf16_d2l") for K in (64, 128)]
+SHAPES += [(61, 2052, 12800, "slabs", None)]
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES)
-def test_bf16_tile_shapes_against_oracle(M, N, K):
+@pytest.mark.parametrize("M,N,K,kernel,tile", SHAPES)
+def test_bf16_tile_shapes_against_oracle(M, N, K, kernel, tile):
+    need = mq.mq_bf16_gemm_workspace_bytes(M, N, K)
+    plan = mq.mq_bf16_gemm_launches(M, N, K, need)[0]
+    assert kernel is None or (plan["slabs"] >= 2 if kernel == "slabs" else (plan["kernel"], plan["tile"]) == (kernel, tile))
     print(f"\n[case] bf16 tiles M={M} N={N} K={K}", flush=True)
     rng = np.random.default_rng([M, N, K])
     x = wl.f32_to_bf16_bits(rng.standard_normal((M, K + 8)).astype(np.float32))
@@ -36,7 +42,7 @@ def test_bf16_tile_shapes_against_oracle(M, N, K):
     ref, na, nb = oracle.gemm_f64(a, b), oracle.row_norms(a), oracle.row_norms(b)
     xd, wd = dev_bf16(x)[:, :K], dev_bf16(w)[:, :K]
     ld = (N + 7) // 8 * 8 + 8
-    ws = torch.empty(max(mq.mq_bf16_gemm_workspace_bytes(M, N, K), 16), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
     b32 = torch.full((M + 1, ld), -7.0, dtype=torch.float32, device="cuda")
     b16 = torch.full((M + 1, ld), -7.0, dtype=torch.bfloat16, device="cuda")
     y32 = mq.bf16_gemm_ws(xd, wd, ws, mq.MQ_OUT_FP32, b32[:M, :N])

@@ -15,15 +15,15 @@ from _gpu_util import check_gemm_bf16, check_gemm_fp32, check_workspace_use, dev
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K).  K slabs with a workspace: (64, 4096, 14336), 224 K steps in 4 slabs; (48, 1000, 8192), N % 64 != 0;
+# (M, N, K).  K slabs with a workspace: (64, 4096, 14336), 224 K steps in 4 slabs; (48, 1000, 16384), N % 64 != 0;
 # otherwise one launch: (33, 6152, 8192), ragged N; (40, 4096, 8320), 130 K steps; (64, 24640, 384), wide N,
 # six K steps; (32, 16392, 1024), (17, 28672, 512): wide ragged N, two token tiles; (20, 520, 1024),
 # (24, 4096, 8192): narrow N below 33 tokens; (64, 4096, 4096): short K; (64, 4098, 8192): N % 4 != 0;
 # (40, 4096, 320): five K steps.
-SHAPES = [(64, 4096, 14336), (33, 6152, 8192), (40, 4096, 8320), (48, 1000, 8192),
+SHAPES = [(64, 4096, 14336), (33, 6152, 8192), (40, 4096, 8320), (48, 1000, 8192), (48, 1000, 16384),
           (64, 24640, 384), (32, 16392, 1024), (17, 28672, 512), (20, 520, 1024), (24, 4096, 8192),
           (64, 4096, 4096), (64, 4098, 8192), (40, 4096, 320)]
-SLAB_SHAPES = {(64, 4096, 14336), (48, 1000, 8192)}
+SLAB_SHAPES = {(64, 4096, 14336), (48, 1000, 16384)}
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)

@@ -2,6 +2,7 @@
 faster.  Host only."""
 import pytest
 
+import paper_2605_20315_amd as mq
 from paper_2605_20315_amd import _lib
 
 
@@ -20,3 +21,15 @@ def lib():
     (2, 24000, 4160, 16), (2, 8192, 6144, 4), (2, 32768, 8192, 4), (2, 1000, 14336, 4), (2, 4096, 14336, 16), (2, 64, 25600, 16)])
 def test_quantizer_rows_per_workgroup(lib, source, rows, K, want):
     assert lib.mq_quantize_rows(source, rows, K) == want
+
+
+# BF16 product, whatever the output type: (M, N, K, kernel and tile that was within 2 % of the fastest, where what ran
+# there before or the next best choice was 4 % slower or more)
+@pytest.mark.parametrize("M,N,K,kernel,tile", [
+    (1, 4096, 512, "bf16_short", (16, 16)), (1, 4096, 14336, "bf16_ring", (16, 16)), (3, 5120, 25600, "bf16_ring", (16, 32)),
+    (8192, 6400, 5120, "bf16_d2l", (256, 256)), (4096, 12800, 5120, "bf16_d2l", (256, 256)),
+    (2048, 28672, 4096, "bf16_d2l", (256, 256)), (2048, 4096, 512, "bf16_d2l", (256, 128)),
+    (8192, 5120, 640, "bf16_d2l", (256, 256)), (2048, 4096, 4096, "bf16_stage", (256, 128))])
+def test_bf16_tile(M, N, K, kernel, tile):
+    p = mq.mq_bf16_gemm_launches(M, N, K, 16 << 20)
+    assert len(p) == 1 and (p[0]["kernel"], p[0]["tile"]) == (kernel, tile)
