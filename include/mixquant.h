@@ -184,10 +184,12 @@ int nvfp4_gemm(const uint8_t *a_codes, const uint8_t *a_scales, const float *a_a
  * workspace: device memory, 16-byte aligned, workspace_bytes >= 0 bytes, or NULL with 0; its
  * contents are undefined afterwards and it must not be used by other work on another stream
  * until this call's kernels have finished.  mq_gemm_workspace_bytes(M, N, K) (host function, no
- * GPU access) returns the size that lets the library choose freely: slabs * M * N * 4 bytes,
- * never more than 4 MiB, and 0 where slabs are never used (N % 4 != 0, K % 64 != 0, more than 128
- * output tiles of 64x64, or a K too short for the second pass to pay: below about 8192).  A
- * smaller workspace is legal and only limits the number of slabs.
+ * GPU access) returns the size that lets the library choose freely: the most slabs it may take, for either
+ * byte order and any number of compute units, * M * N * 4 bytes; never more than 4 MiB, and 0 where
+ * slabs are never used (N % 4 != 0, K % 64 != 0, more than 128 output tiles of 64x64, or a K too
+ * short for the second pass to pay: below about 7000).  How many of them a call takes, often none
+ * (tiles of 32x32 occupy the GPU without), is decided by expected time.  A smaller workspace is
+ * legal and only limits the number of slabs.
  */
 int64_t mq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int nvfp4_gemm_ws(const uint8_t *a_codes, const uint8_t *a_scales, const float *a_alpha_dev,
@@ -229,8 +231,9 @@ int bf16_gemm(const void *x_bf16, int64_t ldx, const void *w_bf16, int64_t ldw,
  * cut into slabs across workgroups (FP32 partial sums, added in ascending order by a second kernel:
  * bit-identical from run to run; the last bits may differ from bf16_gemm's).  Arguments and
  * requirements as bf16_gemm; workspace as in nvfp4_gemm_ws.
- * mq_bf16_gemm_workspace_bytes(M, N, K) (host function) returns the size that lets the library
- * choose freely: slabs * M * N * 4 bytes (at most 16 MiB), 0 where slabs are never used
+ * mq_bf16_gemm_workspace_bytes(M, N, K) (host function) returns a size that lets the library
+ * choose freely: an upper bound of the slabs * M * N * 4 bytes (at most 16 MiB; no more than 4 MiB of
+ * it are written on 256 compute units), 0 where slabs are never used
  * (M <= 32, M > 64, N % 4 != 0, K % 128 != 0, K < 8192, N > 16256, or so few rows of W that even
  * with slabs half of the compute units would stay empty).
  */

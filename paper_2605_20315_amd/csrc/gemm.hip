@@ -496,6 +496,11 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
 // 14336: 15.6 against 18.7 with K slabs), and 64x128 tiles, two workgroups of four waves to a compute unit,
 // hide each other's sums and stores, which the one-workgroup kernel above cannot (560 tokens on N =
 // 28672: 104 us against 140).  Two waves per SIMD throughout (at most 256 registers).
+template <int TM_, int TN_>
+struct SmallCfg {
+    static constexpr int TM = TM_, TN = TN_, WN = 32 * TN_;
+};
+
 // End of the small-tile kernels: the S waves of a workgroup hold partial sums of one
 // (32 TM) x (32 TN) tile over their parts of K.  The partial
 // tiles are added through LDS, four 32x32 tiles (16 KB per wave) per pass.  A pass holds 16 chunks
@@ -508,6 +513,10 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
 {
     constexpr int NM = TM * TN;
     const int frow = lane & 31, fhalf = lane >> 5;
+    if constexpr (S == 1) {  // nothing to add
+        epilogue<SmallCfg<TM, TN>, OUT_BF16>(g, acc, scale, m0, n0, 0, 0, frow, fhalf);
+        return;
+    }
     extern __shared__ uint4 lds[];
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     f32x4 *const X = reinterpret_cast<f32x4 *>(lds);
@@ -1352,7 +1361,7 @@ int launch_persistent(Kern kern, int bm, int bn, size_t lds_bytes, const GemmArg
 template <int TM, int TN, int S>
 constexpr size_t small_lds()
 {
-    return (size_t)S * (TM * TN < 4 ? TM * TN : 4) * 4096;
+    return S == 1 ? 0 : (size_t)S * (TM * TN < 4 ? TM * TN : 4) * 4096;
 }
 
 // One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
@@ -1532,35 +1541,40 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
 
 // ---- which NVFP4 kernel and tile --------------------------------------------------------------------
 
-// The workgroup tiles (tokens x rows of W) of the NVFP4 kernels: gemm_fp4_direct with K whole, split over two
-// or over four waves, and gemm_fp4_small.  A round of workgroups (one per compute unit) takes
-// fixed + K steps x step, in ns; step1 is the step of a problem that is a single round.  The row-major
-// byte order costs about twice the step (a load touches a line per row instead of whole lines), most
-// where the tiles are small.
-struct Fp4Cost {
-    int step1, step, fixed;
-};
+// The workgroup tiles (tokens x rows of W) of the NVFP4 kernels, gemm_fp4_direct with K whole, split over two or
+// over four waves, and gemm_fp4_small, and their costs (TileCost) in either byte order.  The row-major one costs
+// about twice the step (a load touches a line per row instead of whole lines), most where the tiles are small.
 struct Fp4Tile {
     mq_kernel kernel;
     int bm, bn, waves;
-    Fp4Cost cost[2];  // MQ_LAYOUT_LINEAR, MQ_LAYOUT_KTILE
 };
-#define MQ_SMALL(X) /* TM, TN, S, NSETS; step1, step, fixed for the row-major and the K-step-major order */ \
-    X(1, 1, 8, 4, 154, 148, 1363, 48, 43, 1031) X(1, 2, 8, 4, 236, 233, 2056, 69, 68, 1618)                  \
-    X(2, 1, 8, 4, 180, 212, 2705, 65, 68, 1619) X(1, 2, 4, 4, 216, 202, 1191, 79, 67, 950)                   \
-    X(2, 1, 4, 4, 172, 195, 1081, 80, 67, 947) X(2, 2, 8, 4, 271, 287, 4977, 87, 115, 3315)                  \
-    X(2, 2, 4, 4, 263, 264, 2109, 108, 104, 2000) X(2, 4, 8, 2, 394, 412, 5114, 133, 183, 4667)              \
-    X(2, 4, 4, 2, 398, 381, 3029, 172, 172, 3018) X(4, 2, 8, 2, 341, 406, 4681, 137, 188, 4504)              \
-    X(4, 2, 4, 2, 348, 370, 2912, 171, 174, 2957)
+#define MQ_SMALL(X) /* TM, TN, S, NSETS */                                                                        \
+    X(1, 1, 8, 4) X(1, 2, 8, 4) X(2, 1, 8, 4) X(1, 2, 4, 4) X(2, 1, 4, 4) X(2, 2, 8, 4) X(2, 2, 4, 4) X(2, 4, 8, 2) \
+    X(2, 4, 4, 2) X(4, 2, 8, 2) X(4, 2, 4, 2) X(2, 2, 1, 4)
 static constexpr Fp4Tile kFp4Tiles[] = {
-    {MQ_KERNEL_FP4_DIRECT, 256, 256, 4, {{1893, 2039, 3289}, {1079, 1191, 9573}}},
-    {MQ_KERNEL_FP4_DIRECT, 256, 128, 4, {{965, 1039, 6591}, {534, 618, 8626}}},
-    {MQ_KERNEL_FP4_DIRECT, 128, 128, 4, {{504, 550, 5668}, {298, 335, 6083}}},
-#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) {MQ_KERNEL_FP4_SMALL, 32 * TM, 32 * TN, S, {{L1, L, LF}, {K1, K, KF}}},
+    {MQ_KERNEL_FP4_DIRECT, 256, 256, 4}, {MQ_KERNEL_FP4_DIRECT, 256, 128, 4}, {MQ_KERNEL_FP4_DIRECT, 128, 128, 4},
+#define MQ_X(TM, TN, S, NSETS) {MQ_KERNEL_FP4_SMALL, 32 * TM, 32 * TN, S},
     MQ_SMALL(MQ_X)
 #undef MQ_X
 };
 constexpr int kFp4Directs = 3, kFp4TileCount = (int)(sizeof(kFp4Tiles) / sizeof(kFp4Tiles[0]));
+static constexpr TileCost kFp4Costs[2][kFp4TileCount] = {
+    {{6271.7, 6184.9, 1209.8, 886.09, 17.221}, {3469.8, 7200.5, 713.71, 346.48, 107.32},
+     {6440.7, 4307, 376.79, 172.48, 107.44},
+     {4239.8, 2522.9, 115.35, 20.165, 27.543}, {4933.4, 1970.5, 213.73, 28.547, 158.6},
+     {5169.4, 417.19, 215.26, 26.575, 374.97}, {4841.2, 1108, 225.34, 0, 19.288},
+     {5092, 646.75, 176.73, 18.397, 234.85}, {4109.1, 3679.6, 289.57, 0, 600}, {4943.6, 2717.7, 247.73, 17.939, 10},
+     {7478.9, 719.42, 302.3, 186.41, 261.14}, {4944.2, 3294, 386.65, 44.621, 116.6},
+     {7500.5, 2876.1, 181.1, 338.58, 107.4}, {6575.9, 100, 394.94, 6.7359, 330.19}, {6876.3, 100, 346.69, 0, 10}},
+    {{6938.1, 8606.2, 630.39, 663.88, 10.011}, {6208.2, 8413, 320.75, 329.2, 15.19},
+     {3592.6, 8314.6, 175.14, 152.97, 58.696},
+     {4834.1, 650.02, 40.736, 0, 599.03}, {5083.6, 1144.7, 61.699, 0, 352.11}, {4619.3, 1740.6, 59.549, 0, 80.653},
+     {5090.5, 1048, 66.056, 0, 12.508}, {5521.9, 647.44, 73.158, 0, 94.201}, {4017.3, 4636.2, 82.99, 15.263, 10},
+     {5542, 1414.6, 106.68, 0, 161.94}, {2858.6, 5845, 117.66, 43.751, 157.24},
+     {6685.8, 1570.7, 125.65, 48.555, 119.15}, {3251.3, 5072.4, 119.84, 88.484, 25.163},
+     {6802.3, 1402.1, 109.41, 83.132, 94.333}, {6682.4, 460.65, 144.03, 0, 10}}};
+// us: the second pass of K slabs, and what two launches overlap by
+static constexpr double kSecondPass[2] = {4.02, 2.95}, kOverlap[2] = {1.00, 3.80};
 
 struct Fp4Plan {
     int tile;                  // index into kFp4Tiles
@@ -1569,45 +1583,42 @@ struct Fp4Plan {
     int tile_rest;             // tile_rest in a second launch
 };
 
-// The plan that costs least: K steps of the rounds of workgroups, or the weights' one trip from HBM
-// (0.5625 bytes per element at 5.3 TB/s) where that is longer; a fifth of the shorter one does not
-// hide.  The steps and fixed times are fitted to every tile's time on 150 shapes (16 to 9000 tokens, the
-// 8B and 32B layers and their 2-, 4- and 8-way shards) in either byte order: the choice among the tiles
-// is on average 1 % slower than the fastest one, at worst 11 % (row-major: 18 %).
+// The plan that costs least (launch_us; the weights' 0.5625 bytes per element at 5.3 TB/s, a fifth of the shorter one of
+// trip and K steps does not hide).  The costs are fitted to every tile's time, and to pairs of them, on 3200 shapes
+// (K-step-major; row-major 1800) of 16 to 16384 tokens: the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter,
+// narrower and wider ones.  The plan is on average 0.6 % (row-major 1.1 %) slower than the fastest one measured, 95 % of
+// the shapes within 4 % (7 %).  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
 // instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 7.0 us in
-// 32x32 tiles and 11.6 in 64x64, 333 tokens on N = 28672 84 us in 64x128 and 93 in 256x256.
+// 32x32 tiles and 11.6 in 64x64; 512 tokens on N = 28672 92 us in 256x256 and 104 in 64x128.
 // Two launches where the large tiles leave a ragged last round: whole rounds of one of the direct
 // tiles on the first rows or columns of Y, the others in whatever tile suits them (5003 tokens on
-// K = 14336, N = 4096: one round of 256x256 tiles on 4096 rows and 907 rows in 128x128 tiles).
+// K = 14336, N = 4096: one round of 256x256 tiles on 4096 rows and 907 rows in 128x128 tiles; 333 tokens on N = 28672: 256
+// rows in 256x128 tiles and 77 in 128x128, 83 us against 86 in 64x128 tiles and 96 in 256x256, which hold 333 rows of 512).
 static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t slab_limit, int cus)
 {
-    const double kt = (double)(K / BK);
+    const int order = layout == MQ_LAYOUT_KTILE || K == BK;  // (the same bytes when K == 64)
     auto tiles_of = [](const Fp4Tile &t, int64_t m, int64_t n) { return ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn); };
-    // (part: one of two launches, whose step is that of a longer problem)
-    auto cost = [&](const Fp4Tile &t, int64_t m, int64_t n, int64_t slabs, bool part) {
-        const int64_t tiles = tiles_of(t, m, n), rounds = (tiles * slabs + cus - 1) / cus;
-        if (tiles > (t.kernel == MQ_KERNEL_FP4_SMALL ? kMaxSmallTiles : 0x7FFFFFFF)) return 1e300;
-        const Fp4Cost &c = t.cost[layout == MQ_LAYOUT_KTILE || K == BK];  // (the same bytes when K == 64)
-        const int step = rounds == 1 && !(part && t.kernel == MQ_KERNEL_FP4_DIRECT) ? c.step1 : c.step;
-        const double loop = (double)rounds * (kt / (double)slabs * step + c.fixed) * 1e-3;
-        const double hbm = 0.5625 * (double)n * (double)K / 5.3e6;
-        return 3.0 + (loop > hbm ? loop + 0.2 * hbm : hbm + 0.2 * loop) + (slabs > 1 ? 4.5 : 0.0);
+    auto cost = [&](int i, int64_t m, int64_t n, int64_t slabs) {
+        const int64_t tiles = tiles_of(kFp4Tiles[i], m, n);
+        if (tiles > (kFp4Tiles[i].kernel == MQ_KERNEL_FP4_SMALL ? kMaxSmallTiles : 0x7FFFFFFF)) return 1e300;
+        return launch_us(kFp4Costs[order][i], tiles * slabs, (double)(K / BK) / (double)slabs, 0.5625 * (double)n * (double)K / 5.3e6,
+                         0.2, 2.0 * (double)m * (double)n, cus) +
+               (slabs > 1 ? kSecondPass[order] : 0.0);
     };
     Fp4Plan best{0, 1, 0, 0, 0};
     double best_us = 1e300;
     for (int i = 0; i < kFp4TileCount; ++i) {
         const Fp4Tile &t = kFp4Tiles[i];
-        const double us = cost(t, M, N, 1, false);
+        const double us = cost(i, M, N, 1);
         if (us < best_us) best_us = us, best = Fp4Plan{i, 1, 0, 0, 0};
         if (t.kernel != MQ_KERNEL_FP4_SMALL || slab_limit < 2) continue;
         const int64_t tiles = tiles_of(t, M, N);
         const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
         if (slabs < 2) continue;
-        const double us_slabs = cost(t, M, N, slabs, false);
+        const double us_slabs = cost(i, M, N, slabs);
         if (us_slabs < best_us) best_us = us_slabs, best = Fp4Plan{i, (int)slabs, 0, 0, 0};
     }
-    best_us *= 0.98;  // two launches only for more than the model's error at near ties
     for (int i = 0; i < kFp4Directs; ++i) {
         const Fp4Tile &t = kFp4Tiles[i];
         const int64_t tiles_m = (M + t.bm - 1) / t.bm, tiles_n = (N + t.bn - 1) / t.bn;
@@ -1616,9 +1627,9 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
             for (int by_m = 0; by_m < 2; ++by_m) {
                 const int64_t m = by_m ? r * cus / tiles_n * t.bm : M, n = by_m ? N : r * cus / tiles_m * t.bn;
                 if (m == 0 || n == 0 || (by_m ? m >= M : n >= N)) continue;
-                const double first = cost(t, m, n, 1, true);
+                const double first = cost(i, m, n, 1) - kOverlap[order];
                 for (int j = 0; first < best_us && j < kFp4TileCount; ++j) {
-                    const double us = first + cost(kFp4Tiles[j], by_m ? M - m : M, by_m ? N : N - n, 1, true);
+                    const double us = first + cost(j, by_m ? M - m : M, by_m ? N : N - n, 1);
                     if (us < best_us) best_us = us, best = Fp4Plan{i, 1, by_m ? m : 0, by_m ? 0 : n, j};
                 }
             }
@@ -1634,7 +1645,7 @@ int launch_fp4_tile(int tile, int slabs, const GemmArgs &g, hipStream_t s, int c
     if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 1>, 256, 256, 0, g, s, cus);
     if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 2>, 256, 128, X, g, s, cus);
     if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 4>, 128, 128, X, g, s, cus);
-#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF) \
+#define MQ_X(TM, TN, S, NSETS) \
     if (tile == i++) return launch_small<TM, TN, S, NSETS, OUT_BF16>(g, s, slabs);
     MQ_SMALL(MQ_X)
 #undef MQ_X
@@ -1688,6 +1699,7 @@ int launch_any(const GemmArgs &g, hipStream_t s)
 int configure_gemm_kernels()
 {
     auto set = [](auto kern, size_t bytes) {
+        if (bytes == 0) return hipSuccess;
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)bytes);
     };
@@ -1701,7 +1713,7 @@ int configure_gemm_kernels()
     };
     both(gemm_fp4_direct<true, 2>, gemm_fp4_direct<false, 2>, X);
     both(gemm_fp4_direct<true, 4>, gemm_fp4_direct<false, 4>, X);
-#define MQ_X(TM, TN, S, NSETS, L1, L, LF, K1, K, KF)                                               \
+#define MQ_X(TM, TN, S, NSETS) \
     both(gemm_fp4_small<TM, TN, S, NSETS, true>, gemm_fp4_small<TM, TN, S, NSETS, false>, small_lds<TM, TN, S>());
     MQ_SMALL(MQ_X)
 #undef MQ_X

@@ -1,10 +1,10 @@
-"""GPU parity of the one-launch small-tile NVFP4 kernel (64x64 output tiles, K split over the
-waves of a workgroup and summed through LDS in wave order), the path of prefill chunks of up to a
-few hundred tokens.  Every output is compared with the oracle's FP64 product of the dequantized
-operands; shapes cover eight, four and fewer waves per tile (K of 2 .. 224 steps, including
-counts that the waves do not divide), a single wave (no reduction), ragged M and N, N that is
+"""GPU parity of the NVFP4 product on prefill chunks of up to a few hundred tokens, which the small-tile kernel
+serves (one launch, K split over the waves of a workgroup and summed through LDS in wave order, or a single
+wave).  Every output is compared with the oracle's FP64 product of the dequantized operands; shapes
+cover K of 1 .. 224 steps, including counts that the waves do not divide, ragged M and N, N that is
 not a multiple of 32, one row, strided outputs with guard bands, both byte orders and both
-output types, and every K position of a K step on its own."""
+output types, and every K position of a K step on its own.  (Which tile serves which shape is
+pinned in test_gpu_fp4_tiles.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -26,11 +26,9 @@ def _operands(M, N, K, seed, lo=0x28, hi=0x48):
     return ac, asc, np.float32(0.75), bc, bsc, np.float32(1.5)
 
 
-# tiles of 64x64 <= 512 selects the kernel; waves per tile = 8 up to 256 tiles, else 4, capped at
-# (K / 64) / 2.  (64, 4096, 4096): 64 tiles x 8 waves x 8 steps; (128, 6144, 4096): 192 x 8;
-# (256, 6144, 1024): 384 tiles x 4 waves; (250, 1000, 704): 11 K steps over 5 waves (3, 3, 3, 2, 0);
-# (77, 200, 448): 7 steps over 3 waves; (33, 72, 128): one wave; (1, 8, 64): one K step;
-# (64, 4096, 14336): without a workspace, 224 steps over 8 waves; (500, 4000, 192): 504 tiles.
+# (250, 1000, 704): 11 K steps, which neither four nor eight waves divide; (77, 200, 448): 7; (33, 72, 128): 2;
+# (1, 8, 64): one row, one K step; (64, 4096, 14336): 224 K steps without a workspace; the others whole or ragged
+# tiles of every size
 SHAPES = [(64, 4096, 4096), (128, 6144, 4096), (256, 6144, 1024), (250, 1000, 704), (77, 200, 448),
           (33, 72, 128), (1, 8, 64), (64, 4096, 14336), (500, 4000, 192), (129, 130, 1280)]
 

@@ -33,3 +33,11 @@ def test_quantizer_rows_per_workgroup(lib, source, rows, K, want):
 def test_bf16_tile(M, N, K, kernel, tile):
     p = mq.mq_bf16_gemm_launches(M, N, K, 16 << 20)
     assert len(p) == 1 and (p[0]["kernel"], p[0]["tile"]) == (kernel, tile)
+
+
+# NVFP4 product, K-step-major: (M, N, K, tiles of the launches) where what ran before was 4 % slower or more
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (333, 28672, 4096, [(256, 128), (128, 128)]), (512, 28672, 4096, [(256, 256)]), (256, 8192, 128, [(64, 64)]),
+    (640, 4096, 512, [(64, 64)]), (640, 4096, 256, [(64, 64)]), (2048, 5120, 1280, [(256, 256)]), (64, 4096, 4096, [(32, 32)])])
+def test_fp4_tiles(M, N, K, tiles):
+    assert [p["tile"] for p in mq.mq_gemm_launches(M, N, K, mq.MQ_LAYOUT_KTILE, 4 << 20)] == tiles
