@@ -38,7 +38,7 @@ CASES = [
     (KTILE, 328, 5978, 3008, "direct 128x128x4"),
     (KTILE, 916, 7684, 576, "direct 256x128x4"),
     (KTILE, 2182, 6084, 192, "direct 256x256x4"),
-    (KTILE, 2587, 6169, 64, "small 64x64x1"),
+    (KTILE, 2587, 6169, 64, "direct 256x256x4; small 32x32x8 rows"),
     (KTILE, 3139, 1293, 1600, "direct 128x128x4; small 32x32x8 columns"),
     (KTILE, 1171, 6882, 704, "direct 256x128x4; small 32x64x4 columns"),
     (KTILE, 2646, 5929, 256, "direct 256x256x4; small 32x32x8 columns"),

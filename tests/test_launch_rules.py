@@ -38,6 +38,6 @@ def test_bf16_tile(M, N, K, kernel, tile):
 # NVFP4 product, K-step-major: (M, N, K, tiles of the launches) where what ran before was 4 % slower or more
 @pytest.mark.parametrize("M,N,K,tiles", [
     (333, 28672, 4096, [(256, 128), (128, 128)]), (512, 28672, 4096, [(256, 256)]), (256, 8192, 128, [(64, 64)]),
-    (640, 4096, 512, [(64, 64)]), (640, 4096, 256, [(64, 64)]), (2048, 5120, 1280, [(256, 256)]), (64, 4096, 4096, [(32, 32)])])
+    (640, 4096, 512, [(64, 64)]), (640, 4096, 256, [(64, 64)]), (6144, 2048, 128, [(256, 256)]), (2048, 5120, 1280, [(256, 256)]), (64, 4096, 4096, [(32, 32)])])
 def test_fp4_tiles(M, N, K, tiles):
     assert [p["tile"] for p in mq.mq_gemm_launches(M, N, K, mq.MQ_LAYOUT_KTILE, 4 << 20)] == tiles
