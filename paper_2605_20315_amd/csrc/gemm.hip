@@ -13,7 +13,7 @@
 // applied once in the epilogue.
 //
 // Kernels in this file
-//   gemm_fp4_direct     every NVFP4 problem with K % 64 == 0.  Four waves of 128x128 per
+//   gemm_fp4_direct     NVFP4 from a few hundred tokens on (K % 64 == 0).  Four waves of 128x128 per
 //                       workgroup, persistent workgroups, no LDS and no barriers in the K loop:
 //                       each wave loads its own operand rows in MFMA order and expands them in
 //                       registers (described at the kernel).  A 256x256 tile, a 256x128 tile
@@ -68,12 +68,11 @@ struct PCfg {
     static constexpr int THREADS = 64 * WAVES_M * WAVES_N;
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
     static constexpr int TM = WM / 32, TN = WN / 32;      // 32x32 MFMA tiles per wave
-    static constexpr int LA = BM * 8 / THREADS, LB = BN * 8 / THREADS;                // BF16 direct loads
     // LDS map in bytes: A stage 0, A stage 1, B stage 0, B stage 1 (stage strides fit the
     // 16-bit immediate offset of the LDS instructions)
     static constexpr int A_STAGE = BM * 128, B_STAGE = BN * 128, B_BASE = 2 * A_STAGE;
     static constexpr size_t LDS_BYTES = 2ull * (A_STAGE + B_STAGE);
-    static_assert(TM >= 1 && TN >= 1 && LA >= 1 && LB >= 1, "tile too small for this wave grid");
+    static_assert(TM >= 1 && TN >= 1, "tile too small for this wave grid");
 };
 
 // ---- tile order -----------------------------------------------------------------------------
@@ -105,20 +104,17 @@ __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int &t
     tile_of_logical(logical_id(wg, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
 }
 
-// Scheduling hint for one phase: per MFMA one LDS read (while any remain), a few VALU
-// instructions, and now and then an LDS write / a global load.  Nothing moves across a phase
+// Scheduling hint for one phase: per MFMA a few VALU instructions, and now and then a global load
+// or a scalar instruction.  Nothing moves across a phase
 // boundary: in particular no consumer of a global load is hoisted towards the load, which would
 // turn the prefetch distance into a stall.
-template <int MFMAS, int READS, int VALU_PER, int WRITES, int VMEMS, int SALUS = 0>
+template <int MFMAS, int VALU_PER, int VMEMS = 0, int SALUS = 0>
 __device__ __forceinline__ void sched_phase()
 {
 #pragma unroll
     for (int i = 0; i < MFMAS; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // MFMA
-        if (i < READS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // DS read
         if (VALU_PER > 0) __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER, 0);
-        if (WRITES > 0 && (i % (MFMAS / WRITES)) == (MFMAS / WRITES) - 1)
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                 // DS write
         if (VMEMS > 0 && i < VMEMS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
         if (SALUS > 0 && i < SALUS) __builtin_amdgcn_sched_group_barrier(0x004, 1, 0);  // SALU
     }
@@ -368,15 +364,15 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         expand_phase(cur, 0, fr[0], 2, 4);
         expand_phase(cur, 1, fr[1]);
         mfmas(fr[0]);
-        sched_phase<16, 0, 5, 0, 0>();
+        sched_phase<16, 5>();
         expand_phase(cur, 2, fr[0]);
         mfmas(fr[1]);
-        sched_phase<16, 0, 4, 0, 0>();
+        sched_phase<16, 4>();
         // the scalar pointer arithmetic of the loads below, spread under this phase's MFMAs
         advance();
         expand_phase(cur, 3, fr[1]);
         mfmas(fr[0]);
-        sched_phase<16, 0, 4, 0, 0, 16>();
+        sched_phase<16, 4, 0, 16>();
         // The only loads in flight here are the 16 of the next K step, a whole step old: one wait
         // for all of them instead of one in front of each first use (this phase is the one that
         // fills the wave's issue slots, and a wait is an instruction like any other: +0.5-0.8 %).
@@ -386,7 +382,7 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         expand_phase(nxt, 0, fr[0], 4, 8);
         load_tile(cur);
         mfmas(fr[1]);
-        sched_phase<16, 0, 5, 0, 16>();
+        sched_phase<16, 5, 16>();
     };
 
     // Persistent workgroups: tile ids blockIdx.x, blockIdx.x + gridDim.x, ...  The first loads of
@@ -482,7 +478,7 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
 
 // With a few hundred tokens the 128x128 wave tiles above are too few to occupy the chip, and the
 // time of a layer is launch latency plus one trip of the weights from HBM.  Here a workgroup owns
-// one (32 TM) x (32 TN) output tile; its S waves (4 or 8) take consecutive parts of K and each runs
+// one (32 TM) x (32 TN) output tile; its S waves (8, 4 or, for a short K, 1) take consecutive parts of K and each runs
 // the same register-direct K loop as above (operands loaded in MFMA order, expanded in registers, no
 // LDS and no barrier in the loop) with NSETS K steps of codes in flight per wave.  The S partial tiles
 // are then added through LDS in a fixed order (wave 0, 1, ...: bit-identical from run to run), each
@@ -490,12 +486,12 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
 // with one, a long K may also be cut into g.ksplit slabs across workgroups: a work item is then (slab,
 // tile), its workgroup writes unscaled FP32 partial sums to g.ws[slab][M][N], and
 // splitk_reduce_kernel adds the slabs in ascending order.
-// What bounds it: MFMAs for 64x64 tiles and larger, the expansion below (16 vector instructions per
-// MFMA for 32x32, 8 for 64x64, 6 for 128x64); but a 32x32 tile gives every compute unit work where a
+// What bounds it: the expansion (16 vector instructions per MFMA for 32x32, 8 for 64x64, 6 for 128x64; at two
+// waves per SIMD 8 take 40 to 44 cycles and 6 take 34 to 37 per MFMA, of 32); but a 32x32 tile gives every compute unit work where a
 // 64x64 tile leaves three quarters of them idle (64 tokens, K = N = 4096: 7.0 us against 11.6; K =
 // 14336: 15.6 against 18.7 with K slabs), and 64x128 tiles, two workgroups of four waves to a compute unit,
-// hide each other's sums and stores, which the one-workgroup kernel above cannot (560 tokens on N =
-// 28672: 104 us against 140).  Two waves per SIMD throughout (at most 256 registers).
+// hide each other's sums and stores, which the one-workgroup kernel above cannot (576 tokens on N =
+// 28672: 116 us against 170 in 256x256 tiles; 110 with 512 of them in those).  Two waves per SIMD throughout (at most 256 registers).
 template <int TM_, int TN_>
 struct SmallCfg {
     static constexpr int TM = TM_, TN = TN_, WN = 32 * TN_;
@@ -670,18 +666,18 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         using Next = std::integral_constant<int, (R + 1) % NSETS>;
         expand_phase(setc, 1, fr[1]);
         mfmas(fr[0]);
-        sched_phase<NM, 0, VPER, 0, 0>();
+        sched_phase<NM, VPER>();
         expand_phase(setc, 2, fr[0]);
         mfmas(fr[1]);
-        sched_phase<NM, 0, VPER, 0, 0>();
+        sched_phase<NM, VPER>();
         expand_phase(setc, 3, fr[1]);
         mfmas(fr[0]);
-        sched_phase<NM, 0, VPER, 0, 0>();
+        sched_phase<NM, VPER>();
         prep_scales(Next{}, kt + 1 < k1);
         expand_phase(Next{}, 0, fr[0]);
         load_step(setc);  // K step kt + NSETS
         mfmas(fr[1]);
-        sched_phase<NM, 0, VPER + 2, 0, (2 * NT + NM - 1) / NM>();
+        sched_phase<NM, VPER + 2, (2 * NT + NM - 1) / NM>();
     };
     auto for_sets = [&](auto &&fn) {  // fn(set index as a constant), sets 0 .. NSETS-1
         fn(std::integral_constant<int, 0>{});
@@ -740,12 +736,35 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g)
 
 // ---- BF16, direct global-to-LDS loads ----------------------------------------------------------
 
+// Loads 8 rows x 128 bytes (one 64-wide K step of eight rows, 1 KB) from global memory straight into
+// LDS at `dst`; lane l brings 16 bytes of row l / 8.  In inline assembly because the
+// compiler orders every LDS read behind all outstanding LDS-writing loads (s_waitcnt vmcnt(0) right
+// after the load), which serialises a pipeline; with it the only waits are the ones written.  m0 is named as clobbered
+// so that the compiler never keeps a value of its own in it across the statement (it calls m0 "reserved" and
+// warns about any clobber of it: silenced here).  STREAM: non-temporal, for rows of W that no other workgroup reads.
+template <bool STREAM>
+__device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off, const char *base)
+{
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(dst), "v"(lane_off), "s"(base)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(dst), "v"(lane_off), "s"(base)
+                     : "memory", "m0");
+#pragma clang diagnostic pop
+}
+
 // 256x256x64 tile with four waves of 128x128 (one per SIMD).  The tiles never pass through
 // registers: every wave issues 16 global_load_lds_dwordx4 per K step (1 KB each: 8 rows of one
 // operand tile), which write LDS at M0 + 16 * lane.  The bank swizzle is applied on the global side: the lane that fills chunk c' of
-// row r fetches chunk c' ^ key(r).  The loads are written in inline assembly because the compiler
-// orders every LDS read behind all outstanding LDS-writing loads (s_waitcnt vmcnt(0) right after
-// the load), which serialises the pipeline; here the only wait is the one before the barrier.
+// row r fetches chunk c' ^ key(r).  The only wait is the one before the
+// barrier.
 // The loads of tile t+2 are issued one per two MFMAs: the first half in the phase behind the
 // barrier that frees their stage, the second half in the first phase of the next K step.  All
 // 16 in the one phase measured 3 to 8 % slower (the texture path is shared by the four waves and
@@ -789,15 +808,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
         const char *base = (isA ? ta : tb) + (int64_t)t * (BK * 2);
         const uint32_t dst = lds0 + (isA ? stage * C::A_STAGE + (wave * GA + u) * 1024
                                          : C::B_BASE + stage * C::B_STAGE + (wave * GB + (u - GA)) * 1024);
-        // m0 is named as clobbered so that the compiler never keeps a value of its own in it across
-        // this statement (it calls m0 "reserved" and warns about any clobber of it: silenced here)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(dst), "v"(vo[u]), "s"(base)
-                     : "memory", "m0");
-#pragma clang diagnostic pop
+        load_rows_to_lds<false>(dst, vo[u], base);
     };
     auto load_tile = [&](int t, int stage) {
 #pragma unroll
@@ -885,27 +896,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
 // ---- BF16, tiles of 16x16 MFMAs: decode batches and everything up to a few thousand tokens --------
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Loads 8 rows x 128 bytes (one 64-wide K step of eight rows, 1 KB) from global memory straight into
-// LDS at `dst`; lane l brings 16 bytes of row l / 8.  In inline assembly for the reason given at
-// gemm_bf16_d2l.  STREAM: non-temporal, for rows of W that no other workgroup reads.
-template <bool STREAM>
-__device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off, const char *base)
-{
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-    if constexpr (STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
-                     :
-                     : "s"(dst), "v"(lane_off), "s"(base)
-                     : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(dst), "v"(lane_off), "s"(base)
-                     : "memory", "m0");
-#pragma clang diagnostic pop
-}
 
 // Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
 template <int N>
@@ -1346,14 +1336,11 @@ inline int compute_units(int &n)
 }
 
 template <class Kern>
-int launch_persistent(Kern kern, int bm, int bn, size_t lds_bytes, const GemmArgs &g, hipStream_t s, int cus,
-                      int items_per_tile = 1)
+int launch_persistent(Kern kern, int bm, int bn, size_t lds_bytes, const GemmArgs &g, hipStream_t s, int cus)
 {
     const int64_t tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
     if (tiles_m * tiles_n > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    const int64_t items = tiles_m * tiles_n * items_per_tile;
-    if (items > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    const int64_t grid = items < cus ? items : cus;
+    const int64_t grid = tiles_m * tiles_n < cus ? tiles_m * tiles_n : cus;
     kern<<<dim3((unsigned)grid), dim3(256), lds_bytes, s>>>(g, (int)tiles_m, (int)tiles_n);
     return note_launch(hipGetLastError());
 }
@@ -1735,9 +1722,11 @@ int configure_gemm_kernels()
     return note_launch(e);
 }
 
-// Most K slabs across workgroups that the NVFP4 product may use, given this much workspace (0 or 1: none):
-// a long K (below about 8192 the second pass costs more than it saves) with at most half as many
-// 64x64 tiles as compute units, one round of work items, at least four K steps for each of eight waves.
+// Most K slabs across workgroups that the NVFP4 product may use, given this much workspace (0 or 1: none); how many it
+// does use, if any, is the cost rule's choice (at most one work item per compute unit), and depends on the byte
+// order.  A bound in 64x64 tiles for either of them: a long K (below about 7000 the second pass costs more than it saves)
+// with at most half as many such tiles as compute units, one round of work items, at least four K steps
+// for each of eight waves.
 int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
     if (M <= 0 || N <= 0 || K <= 0 || K % BK != 0 || ws_bytes <= 0 || N % 4 != 0) return 0;
@@ -1749,10 +1738,10 @@ int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int c
     return ks >= 2 && kt * (ks - 1) > 9 * waves * ks ? (int)ks : 0;
 }
 
-// Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none).
-// Only decode batches of 33 to 64 tokens with a long K and a narrow N can gain from a second pass; there
-// are never more than two work items per compute unit, every slab keeps 512 of K, and the partial sums'
-// traffic (8 bytes per output and slab) stays below half of the weights'.
+// Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none); the cost
+// rule decides how many it does use, at most one work item per compute unit, which is less than this
+// bound.  Only decode batches of 33 to 64 tokens with a long K and a narrow N can gain from a second pass; every slab keeps
+// 512 of K, and the partial sums' traffic (8 bytes per output and slab) stays below half of the weights'.
 int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
     if (M <= 32 || M > 64 || N <= 0 || K < 8192 || K % 128 != 0) return 0;
