@@ -1555,13 +1555,14 @@ static constexpr TileCost kFp4Costs[2][kFp4TileCount] = {
      {7500.5, 2876.1, 181.1, 338.58, 107.4}, {6575.9, 100, 394.94, 6.7359, 330.19}, {6876.3, 100, 346.69, 0, 10}},
     {{6938.1, 8606.2, 630.39, 663.88, 10.011}, {6208.2, 8413, 320.75, 329.2, 15.19},
      {3592.6, 8314.6, 175.14, 152.97, 58.696},
-     {4834.1, 650.02, 40.736, 0, 599.03}, {5083.6, 1144.7, 61.699, 0, 352.11}, {4619.3, 1740.6, 59.549, 0, 80.653},
-     {5090.5, 1048, 66.056, 0, 12.508}, {5521.9, 647.44, 73.158, 0, 94.201}, {4017.3, 4636.2, 82.99, 15.263, 10},
-     {5542, 1414.6, 106.68, 0, 161.94}, {2858.6, 5845, 117.66, 43.751, 157.24},
-     {6685.8, 1570.7, 125.65, 48.555, 119.15}, {3251.3, 5072.4, 119.84, 88.484, 25.163},
-     {6802.3, 1402.1, 109.41, 83.132, 94.333}, {6682.4, 460.65, 144.03, 0, 10}}};
+     {4868.5, 564.77, 41.643, 0, 594.93}, {5062.1, 1191.6, 60.656, 0, 276}, {4130.7, 2109.2, 62.464, 0, 12.686},
+     {5059.1, 1075.9, 64.775, 0, 12.815}, {5511.2, 673.55, 73.031, 0, 85.618},
+     {3776.4, 4046.2, 85.976, 11.681, 40.941}, {5723.5, 1305.4, 106.28, 0, 142.13},
+     {2750.6, 5815.8, 118.51, 43.59, 175.04}, {6678.2, 1478.8, 126.74, 47.794, 133.13},
+     {3251.3, 5072.4, 119.84, 88.484, 25.163}, {6802.3, 1402.1, 109.41, 83.132, 94.333},
+     {6680.1, 481.62, 141.96, 0, 10}}};
 // us: the second pass of K slabs, and what two launches overlap by
-static constexpr double kSecondPass[2] = {4.02, 2.95}, kOverlap[2] = {1.00, 3.80};
+static constexpr double kSecondPass[2] = {4.02, 3.20}, kOverlap[2] = {1.00, 3.64};
 
 struct Fp4Plan {
     int tile;                  // index into kFp4Tiles
@@ -1573,7 +1574,7 @@ struct Fp4Plan {
 // The plan that costs least (launch_us; the weights' 0.5625 bytes per element at 5.3 TB/s, a fifth of the shorter one of
 // trip and K steps does not hide).  The costs are fitted to every tile's time, and to pairs of them, on 3200 shapes
 // (K-step-major; row-major 1800) of 16 to 16384 tokens: the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter,
-// narrower and wider ones.  The plan is on average 0.6 % (row-major 1.1 %) slower than the fastest one measured, 95 % of
+// narrower and wider ones.  The plan is on average 0.7 % (row-major 1.1 %) slower than the fastest one measured, 95 % of
 // the shapes within 4 % (7 %).  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
 // instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 7.0 us in
