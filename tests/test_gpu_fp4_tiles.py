@@ -69,6 +69,11 @@ CASES = [
     (KTILE, 637, 4101, 576, "small 64x64x1"),
     (KTILE, 35, 9001, 320, "small 64x32x4"),
     (LINEAR, 261, 4093, 320, "small 128x64x4"),
+    (LINEAR, 452, 10285, 320, "direct 256x128x4"),
+    (LINEAR, 329, 10941, 448, "direct 256x128x4"),
+    (LINEAR, 258, 9797, 448, "direct 128x128x4"),
+    (LINEAR, 130, 10917, 1280, "direct 128x128x4"),
+    (KTILE, 578, 9937, 1280, "direct 256x128x4"),
 ]
 
 

@@ -23,6 +23,12 @@ def _rand_nvfp4(rng, rows, K, lo=0x28, hi=0x48):
     return codes, scales
 
 
+def _tiles(M, N, K, layout):
+    """Kernel and tile of each launch of the NVFP4 product on 256 compute units."""
+    return [f"{p['kernel'][4:]} {p['tile'][0]}x{p['tile'][1]}x{p['waves']}"
+            for p in mq.mq_gemm_launches(M, N, K, layout)]
+
+
 def _gpu_gemm(ac, asc, aa, bc, bsc, ba, out, layout=None):
     """Operands are given in the canonical linear order; layout=None alternates: the K-step-major
     layout for the BF16 output and the linear one for FP32, so both are exercised on every case."""
@@ -115,9 +121,9 @@ def test_large_tile_path_with_ragged_edges(K):
 
 @pytest.mark.parametrize("M,N", [(256 * 16, 256 * 32), (2048, 4096), (1024, 4096)])
 def test_register_direct_k_positions_one_hot(M, N):
-    """Register-direct kernel, whole tiles and K split two and four ways: an element at every k of a K step must
-    meet exactly its partner.  A is a tall stack of one-hot rows (row r has a 1.0 at k = r % K),
-    so Y[r, n] = B_hat[n, r % K]."""
+    """Two K steps on whole tiles of 256x256 and on the small tiles that serve fewer tokens: an element at
+    every k must meet exactly its partner.  A is a tall stack of one-hot rows (row r has a 1.0 at
+    k = r % K), so Y[r, n] = B_hat[n, r % K]."""
     K = 128
     ac = np.zeros((M, K // 2), dtype=np.uint8)
     asc = np.full((M, K // 16), 0x38, dtype=np.uint8)
@@ -131,11 +137,40 @@ def test_register_direct_k_positions_one_hot(M, N):
         assert np.array_equal(y, b.T[k])
 
 
+@pytest.mark.parametrize("M,N,K,layout,tile", [
+    (452, 10285, 320, mq.MQ_LAYOUT_LINEAR, "direct 256x128x4"),
+    (329, 10941, 448, mq.MQ_LAYOUT_LINEAR, "direct 256x128x4"),
+    (258, 9797, 448, mq.MQ_LAYOUT_LINEAR, "direct 128x128x4"),
+    (130, 10917, 1280, mq.MQ_LAYOUT_LINEAR, "direct 128x128x4"),
+    (578, 9937, 1280, mq.MQ_LAYOUT_KTILE, "direct 256x128x4"),
+    (328, 5978, 3008, mq.MQ_LAYOUT_KTILE, "direct 128x128x4"),
+])
+def test_split_k_positions_one_hot(M, N, K, layout, tile):
+    """K over wave pairs (256x128) and over the four waves (128x128), each share but the last in whole
+    pairs of steps: 4 + 1, 4 + 3 and 10 + 10; 2, 2, 2, 1, then 6, 6, 6, 2 and 12, 12, 12, 11.  The
+    one-hot rows of the test above, shifted until every k has been met: a wave that drops, repeats or
+    misplaces a step cannot give these outputs."""
+    assert _tiles(M, N, K, layout) == [tile]
+    print(f"\n[case] one-hot M={M} N={N} K={K} layout={layout}", flush=True)
+    rng = np.random.default_rng([M, N, K])
+    bc, bsc = _rand_nvfp4(rng, N, K)
+    b = oracle.dequantize(bc, bsc, 1.0)
+    asc = np.full((M, K // 16), 0x38, dtype=np.uint8)
+    for shift in range(0, K, M):
+        ac = np.zeros((M, K // 2), dtype=np.uint8)
+        k = (np.arange(M) + shift) % K
+        ac[np.arange(M), k // 2] = (0x2 << (4 * (k & 1))).astype(np.uint8)
+        y = _gpu_gemm(ac, asc, 1.0, bc, bsc, 1.0, mq.MQ_OUT_FP32, layout).cpu().numpy().astype(np.float64)
+        assert np.array_equal(y, b.T[k])
+
+
 @pytest.mark.parametrize("K", [64, 192, 448])
-def test_split_k_path_with_ragged_edges(K):
-    """256 workgroup tiles of 256x128 select the register-direct kernel with K split over wave
-    pairs (one K step: the second half is empty; three and seven: halves of unequal length, the
-    second ending on a zeroed extra step).  The BF16 baseline takes its 256x128 configuration."""
+def test_short_k_at_2000_by_4000(K):
+    """One, three and seven K steps at a size that single-wave tiles serve, but for seven steps in linear
+    order, which take 256x128 tiles with K over wave pairs (four and three steps).  The BF16 product
+    of the same shape."""
+    split = _tiles(2000, 4000, K, mq.MQ_LAYOUT_LINEAR) == ["direct 256x128x4"]
+    assert split == (K == 448)
     rng = np.random.default_rng(15 + K)
     M, N = 2000, 4000
     ac, asc = _rand_nvfp4(rng, M, K)
@@ -161,12 +196,14 @@ def test_split_k_path_with_ragged_edges(K):
 
 def test_two_column_ranges_in_two_tile_shapes():
     """M = 2040, N = 6096, K = 4096: 192 tiles of 256x256 would leave a quarter of the compute
-    units idle, so the launcher gives the first 4096 columns to 256x128 tiles with K over wave
+    units idle, so the rule gives the first 4096 columns to 256x128 tiles with K over wave
     pairs and the remaining 2000 to 128x128 tiles with K over the four waves (two launches on
     offset B, scale and output pointers).  Sampled rows, all columns: the seam at column 4096,
     the ragged last column tile and the guard band behind N must all be right."""
     rng = np.random.default_rng(77)
     M, N, K = 2040, 6096, 4096
+    for layout in (mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE):
+        assert _tiles(M, N, K, layout) == ["direct 256x128x4", "direct 128x128x4"]
     ac, asc = _rand_nvfp4(rng, M, K)
     bc, bsc = _rand_nvfp4(rng, N, K)
     a = oracle.dequantize(ac, asc, 0.5)
@@ -194,12 +231,9 @@ def test_two_column_ranges_in_two_tile_shapes():
         assert bool((b32[:, N:] == -7.0).all()) and bool((b16[:, N:] == -7.0).all())
 
 
-# (M, N, K): ragged shapes with a long K on both sides of the launcher's choices.  With 256
-# compute units: (1530, 6128, 4096) = 768 columns of 128x128 tiles + 5360 of 256x128 tiles;
-# (3070, 6160, 4096) = 1024 columns of 128x128 + 5136 of 256x256; (3000, 6000, 4608) the same pair
-# at another K; (2500, 9000, 4096) and (3300, 7000, 3072) = 256x128 + 256x256; (1300, 12000, 4096)
-# = 128x128 + 256x256; (1800, 7360, 4992), (2900, 5008, 4096) one launch of 256x256 tiles;
-# (911, 4128, 4800) of 256x128 tiles; (1190, 1888, 4224) of 128x128 tiles.
+# (M, N, K): ragged shapes with a long K, which the rule gives to one tile shape or to two (whole tiles
+# first, then what a last round of them would leave mostly idle, by columns or by rows), and which
+# differ between the byte orders; the test prints the launches.
 LAUNCH_SHAPES = [(1530, 6128, 4096), (3070, 6160, 4096), (3000, 6000, 4608), (2500, 9000, 4096),
                  (3300, 7000, 3072), (1300, 12000, 4096), (1800, 7360, 4992), (2900, 5008, 4096),
                  (911, 4128, 4800), (1190, 1888, 4224)]
@@ -207,10 +241,11 @@ LAUNCH_SHAPES = [(1530, 6128, 4096), (3070, 6160, 4096), (3000, 6000, 4608), (25
 
 @pytest.mark.parametrize("M,N,K", LAUNCH_SHAPES)
 def test_ragged_shapes_across_launch_paths(M, N, K):
-    """One tile shape or two column ranges in two shapes: sampled rows (tile seams, the ragged
+    """One tile shape, or two for two ranges of columns or rows: sampled rows (tile seams, the ragged
     tail), all columns, both layouts, both output types."""
     rng = np.random.default_rng([M, N, K])
-    print(f"\n[case] launch paths M={M} N={N} K={K}", flush=True)
+    paths = [_tiles(M, N, K, layout) for layout in (mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE)]
+    print(f"\n[case] launch paths M={M} N={N} K={K} {paths}", flush=True)
     ac, asc = _rand_nvfp4(rng, M, K)
     bc, bsc = _rand_nvfp4(rng, N, K)
     a = oracle.dequantize(ac, asc, 0.5)
@@ -286,9 +321,12 @@ def test_bf16_operand_larger_than_4_gib():
 
 
 @pytest.mark.parametrize("K", [64, 192, 448, 1280])
-def test_four_way_split_k_path_with_ragged_edges(K):
-    """256 workgroup tiles of 128x128 select the register-direct kernel with K split over its four
-    waves (one K step: three parts are empty; three and seven: parts of unequal length)."""
+def test_short_k_at_1000_by_4000(K):
+    """One, three, seven and twenty K steps at a size that small tiles serve, but for seven and twenty steps
+    in linear order, which take 128x128 tiles with K over the four waves (shares 2, 2, 2, 1 and
+    6, 6, 6, 2)."""
+    split = _tiles(1000, 4000, K, mq.MQ_LAYOUT_LINEAR) == ["direct 128x128x4"]
+    assert split == (K >= 448)
     rng = np.random.default_rng(25 + K)
     M, N = 1000, 4000
     ac, asc = _rand_nvfp4(rng, M, K)
@@ -376,10 +414,10 @@ def test_determinism_and_guard_band():
 def test_bf16_gemm_against_oracle():
     rng = np.random.default_rng(10)
     for M, N, K in [(256, 1024, 1024), (77, 200, 320), (5, 16, 40), (513, 264, 64),
-                    # decode shapes (M <= 64, K % 128 == 0): the weight-streaming kernel
+                    # few tokens
                     (1, 4096, 4096), (7, 272, 128), (16, 1000, 1024), (17, 48, 384), (33, 520, 2048),
                     (49, 16, 256), (64, 264, 14336),
-                    # ... with two and four row tiles per wave (N >= 6144, N >= 24576), ragged N
+                    # ... on wide weights, ragged N
                     (16, 6152, 256), (33, 8200, 384), (64, 8264, 256), (48, 9000, 128), (1, 8192, 1024),
                     (20, 4096, 2176), (5, 24584, 128), (40, 24640, 256), (64, 24576, 384)]:
         x = wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))

@@ -33,9 +33,13 @@ def _assert_only_block_written(buf, M, N, left):
     assert bool((rest == SENTINEL).all()), "a kernel wrote outside its [M, N] block"
 
 
-# (M, N, K): register-direct whole-K / split-in-two / split-in-four workgroups, the 128x128 LDS
-# pipeline, the simple kernel (K % 64 != 0)
-FP4_SHAPES = [(4093, 4072, 128), (2000, 4000, 192), (1000, 4000, 192), (300, 520, 128), (70, 40, 80)]
+# (M, N, K): whole 256x256 tiles, single-wave tiles (twice), small tiles with K over the waves, the simple
+# kernel (K % 64 != 0), the tiles that split K in two and in four, and a launch in two parts
+FP4_SHAPES = [(4093, 4072, 128), (2000, 4000, 192), (1000, 4000, 192), (300, 520, 128), (70, 40, 80),
+              (916, 7688, 576), (328, 5984, 3008), (2587, 6168, 128)]
+FP4_KERNELS = {(4093, 4072, 128): "direct 256x256", (2000, 4000, 192): "small 64x64", (1000, 4000, 192): "small 64x64",
+               (300, 520, 128): "small 32x32", (916, 7688, 576): "direct 256x128", (328, 5984, 3008): "direct 128x128",
+               (2587, 6168, 128): "direct 256x256; small 32x32"}
 
 
 @pytest.mark.parametrize("M,N,K", FP4_SHAPES)
@@ -49,6 +53,9 @@ def test_nvfp4_gemm_into_a_column_slice(M, N, K, out):
     aa, ba = np.float32(0.75), np.float32(1.5)
     layout = mq.MQ_LAYOUT_KTILE if K % 64 == 0 else mq.MQ_LAYOUT_LINEAR
     ops = (to_ktile(ac, asc) + to_ktile(bc, bsc)) if layout == mq.MQ_LAYOUT_KTILE else (ac, asc, bc, bsc)
+    if layout == mq.MQ_LAYOUT_KTILE:
+        parts = mq.mq_gemm_launches(M, N, K, layout)
+        assert "; ".join(f"{p['kernel'][4:]} {p['tile'][0]}x{p['tile'][1]}" for p in parts) == FP4_KERNELS[M, N, K]
     d = [dev_u8(t) for t in ops]
     a_al, b_al = dev_scalar(aa), dev_scalar(ba)
     dtype = torch.bfloat16 if out == mq.MQ_OUT_BF16 else torch.float32
@@ -69,13 +76,20 @@ def test_nvfp4_gemm_into_a_column_slice(M, N, K, out):
         check_gemm_fp32(view.cpu().numpy(), ref, oracle.row_norms(a), oracle.row_norms(b))
 
 
-# direct-to-LDS 256x256 and 256x128 tiles, register-staged 128x128 tiles, simple kernel, decode kernel
-BF16_SHAPES = [(4093, 4072, 128), (2040, 4088, 128), (300, 520, 128), (70, 40, 72), (16, 1000, 256), (3, 264, 128)]
+# direct-to-LDS 256x256 and 256x128 tiles, the ring kernel, the simple kernel (K % 64 != 0), the short kernel
+# (twice), the staged kernel
+BF16_SHAPES = [(4093, 4072, 128), (2040, 4088, 128), (300, 520, 128), (70, 40, 72), (16, 1000, 256), (3, 264, 128),
+               (653, 6552, 192)]
+BF16_KERNELS = {(4093, 4072, 128): "d2l 256x256", (2040, 4088, 128): "d2l 256x128", (300, 520, 128): "ring 32x32",
+                (16, 1000, 256): "short 16x16", (3, 264, 128): "short 16x16", (653, 6552, 192): "stage 224x128"}
 
 
 @pytest.mark.parametrize("M,N,K", BF16_SHAPES)
 @pytest.mark.parametrize("out", [mq.MQ_OUT_BF16, mq.MQ_OUT_FP32])
 def test_bf16_gemm_into_a_column_slice(M, N, K, out):
+    if K % 64 == 0:
+        parts = mq.mq_bf16_gemm_launches(M, N, K)
+        assert "; ".join(f"{p['kernel'][5:]} {p['tile'][0]}x{p['tile'][1]}" for p in parts) == BF16_KERNELS[M, N, K]
     torch.manual_seed(M * 131 + N * 7 + K + out)
     x = torch.randn(M, K, device="cuda").bfloat16()
     w = (torch.randn(N, K, device="cuda") * K ** -0.5).bfloat16()
