@@ -1,6 +1,7 @@
 """GPU parity of the BF16 product on decode batches of 17 .. 64 tokens (the high-precision path
-that the decode phase keeps), with and without a caller-owned workspace: the weight-streaming
-kernel whose waves take the K steps in turn, and its K slabs across workgroups.  Every output is
+that the decode phase keeps), with and without a caller-owned workspace: the ring kernel,
+whose waves take the K steps in turn, its K slabs across workgroups, and the staged kernel on the widest
+weights.  Every output is
 compared with the oracle's FP64 product of the BF16 inputs; where K slabs are meant, the launch rule is
 asked for their number and the workspace is checked for what was written to it."""
 import numpy as np

@@ -1,7 +1,7 @@
 """GPU parity on seeded random shapes: quantize in either layout, multiply, compare with the
-oracle.  Small enough that the oracle computes every output; shapes are drawn so that they hit
-every workgroup shape of the register-direct NVFP4 kernel and the tiled BF16 kernels, the simple kernel (K % 64 != 0), ragged M and N,
-and the decode-shape BF16 kernel."""
+oracle.  Small enough that the oracle computes every output; shapes are drawn over few
+and many tokens, ragged M and N, K off the step of 64 (the simple kernel) and whole tiles.  Which
+kernel and tile serve a shape is for the tests of the tiles, which assert it."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,7 @@ def _cases():
         K = int(rng.integers(1, 40)) * 16
         out.append((M, N, K))
     out += [(4100, 4120, 64), (4352, 4352, 128), (3, 8, 16), (64, 8, 128), (65, 16, 128)]
-    # large enough for the register-direct kernels (whole tiles and split K), every output checked
+    # thousands of rows and columns at a short K, every output checked
     for _ in range(6):
         M = int(rng.integers(1400, 3200))
         N = int(rng.integers(256, 520)) * 8
