@@ -14,6 +14,8 @@ MQ_OK = 0
 MQ_OUT_BF16, MQ_OUT_FP32 = 0, 1
 MQ_LAYOUT_LINEAR, MQ_LAYOUT_KTILE = 0, 1
 
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
+
 _lib = None
 
 
@@ -83,6 +85,18 @@ def load() -> ctypes.CDLL:
     lib.mq_version.argtypes = []
     _lib = lib
     return lib
+
+
+def load_binding():
+    """The native part of the binding (csrc/binding.cpp), bound to the functions of the loaded library."""
+    lib = load()
+    if not os.path.exists(BINDING_PATH):
+        raise MixQuantError(f"{BINDING_PATH} is missing: build it with `python -m paper_2605_20315_amd.build`")
+    from . import _binding
+    names = ("nvfp4_global_scale", "nvfp4_quantize", "nvfp4_quantize_silu_mul", "nvfp4_quantize_rmsnorm",
+             "nvfp4_relayout", "nvfp4_gemm_ws", "bf16_gemm_ws")
+    _binding.bind(check, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names})
+    return _binding
 
 
 def check(rc: int, what: str) -> None:

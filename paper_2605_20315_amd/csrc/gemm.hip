@@ -1314,8 +1314,7 @@ int launch_tiles(Kern kern, size_t lds_bytes, int bm, int bn, int threads, const
 {
     const int64_t tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
     if (tiles_m * tiles_n > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    kern<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(threads), lds_bytes, s>>>(g, (int)tiles_m, (int)tiles_n);
-    return note_launch(hipGetLastError());
+    return enqueue(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(threads), lds_bytes, s, g, (int)tiles_m, (int)tiles_n);
 }
 
 // Persistent register-direct kernels: one workgroup per compute unit (a wave of 512 registers
@@ -1341,14 +1340,21 @@ int launch_persistent(Kern kern, int bm, int bn, size_t lds_bytes, const GemmArg
     const int64_t tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
     if (tiles_m * tiles_n > 0x7FFFFFFF) return MQ_ERR_SHAPE;
     const int64_t grid = tiles_m * tiles_n < cus ? tiles_m * tiles_n : cus;
-    kern<<<dim3((unsigned)grid), dim3(256), lds_bytes, s>>>(g, (int)tiles_m, (int)tiles_n);
-    return note_launch(hipGetLastError());
+    return enqueue(kern, dim3((unsigned)grid), dim3(256), lds_bytes, s, g, (int)tiles_m, (int)tiles_n);
 }
 
 template <int TM, int TN, int S>
 constexpr size_t small_lds()
 {
     return S == 1 ? 0 : (size_t)S * (TM * TN < 4 ? TM * TN : 4) * 4096;
+}
+
+// The second pass of a product in K slabs.
+template <bool OUT_BF16>
+int launch_slab_sum(const GemmArgs &g, hipStream_t s)
+{
+    const int64_t quads = g.M * (g.N / 4);
+    return enqueue(splitk_reduce_kernel<OUT_BF16>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, g);
 }
 
 // One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
@@ -1359,14 +1365,9 @@ int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
     g.ksplit = slabs;
     const int64_t tiles_m = (g.M + 32 * TM - 1) / (32 * TM), tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
     if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16>
-        <<<dim3((unsigned)(tiles_m * tiles_n * g.ksplit)), dim3(64 * S), small_lds<TM, TN, S>(), s>>>(g, (int)tiles_m,
-                                                                                                 (int)tiles_n);
-    int rc = note_launch(hipGetLastError());
-    if (rc != MQ_OK || g.ksplit == 1) return rc;
-    const int64_t quads = g.M * (g.N / 4);
-    splitk_reduce_kernel<OUT_BF16><<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>(g);
-    return note_launch(hipGetLastError());
+    const int rc = enqueue(gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16>, dim3((unsigned)(tiles_m * tiles_n * g.ksplit)),
+                           dim3(64 * S), small_lds<TM, TN, S>(), s, g, (int)tiles_m, (int)tiles_n);
+    return rc != MQ_OK || g.ksplit == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
 
 template <bool FP4, bool OUT_BF16>
@@ -1374,8 +1375,7 @@ int launch_simple(const GemmArgs &g, hipStream_t s)
 {
     dim3 grid((unsigned)((g.N + 15) / 16), (unsigned)((g.M + 15) / 16));
     if ((g.M + 15) / 16 > 65535) return MQ_ERR_SHAPE;
-    gemm_simple_kernel<FP4, OUT_BF16><<<grid, dim3(256), 0, s>>>(g);
-    return note_launch(hipGetLastError());
+    return enqueue(gemm_simple_kernel<FP4, OUT_BF16>, grid, dim3(256), 0, s, g);
 }
 
 // A launch holds fewer than 2^32 threads: kernels with a workgroup per tile, of up to 512 threads, take no
@@ -1398,6 +1398,31 @@ static double launch_us(const TileCost &c, int64_t tiles, double kt, double mem,
     const double loop = ((double)((tiles + cus - 1) / cus) * (c.round + kt * c.step) + (double)tiles / cus * kt * c.share) * 1e-3;
     return c.start * 1e-3 + (loop > mem ? loop + hidden * mem : mem + hidden * loop) + c.out * 1e-2 * out_bytes / 5e6;
 }
+
+// The plans of the shapes that this thread asked for last (a program comes back with the same few): a plan is a pure
+// function of its key, the search for it takes 0.4 (BF16, few tokens) to 0.8 us (NVFP4, hundreds of tokens).
+template <class Plan>
+struct RecentPlans {
+    struct Key {
+        int64_t M, N, K, slab_limit;
+        int cus, order;
+        bool operator==(const Key &o) const
+        {
+            return M == o.M && N == o.N && K == o.K && slab_limit == o.slab_limit && cus == o.cus && order == o.order;
+        }
+    };
+    static constexpr int kEntries = 32;
+    Key keys[kEntries] = {};  // (M == 0: empty; no such product reaches the search)
+    Plan plans[kEntries] = {};
+    template <class Search>
+    const Plan &get(const Key &k, Search &&search)
+    {
+        const uint64_t h = ((uint64_t)k.M * 0x9E3779B97F4A7C15ull ^ (uint64_t)k.N) * 0xC2B2AE3D27D4EB4Full ^ (uint64_t)k.K;
+        const int i = (int)((h * 0x9E3779B97F4A7C15ull) >> 59);
+        if (!(keys[i] == k)) plans[i] = search(), keys[i] = k;
+        return plans[i];
+    }
+};
 
 // ---- which BF16 kernel and tile ---------------------------------------------------------------------
 
@@ -1490,15 +1515,9 @@ int launch_ring(const GemmArgs &g0, hipStream_t s, int slabs)
     const dim3 grid((unsigned)(tiles_m * tiles_n * slabs)), block(64 * S);
     // W rows are read by the workgroups of tiles_m tiles: non-temporal only when that is one (two percent
     // faster then, slower when the second reader finds the lines gone from L2)
-    if (tiles_m == 1)
-        bf16_ring_kernel<MT, NT, S, true, OUT_BF16><<<grid, block, ring_lds<MT, NT, S>(), s>>>(g, (int)tiles_m, (int)tiles_n);
-    else
-        bf16_ring_kernel<MT, NT, S, false, OUT_BF16><<<grid, block, ring_lds<MT, NT, S>(), s>>>(g, (int)tiles_m, (int)tiles_n);
-    int rc = note_launch(hipGetLastError());
-    if (rc != MQ_OK || slabs == 1) return rc;
-    const int64_t quads = g.M * (g.N / 4);
-    splitk_reduce_kernel<OUT_BF16><<<dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s>>>(g);
-    return note_launch(hipGetLastError());
+    auto *const kern = tiles_m == 1 ? bf16_ring_kernel<MT, NT, S, true, OUT_BF16> : bf16_ring_kernel<MT, NT, S, false, OUT_BF16>;
+    const int rc = enqueue(kern, grid, block, ring_lds<MT, NT, S>(), s, g, (int)tiles_m, (int)tiles_n);
+    return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
 
 template <bool OUT_BF16>
@@ -1506,8 +1525,10 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
 {
     int cus = 0;
     if (int rc = compute_units(cus)) return rc;
+    static thread_local RecentPlans<Bf16Plan> recent;
+    const int64_t slab_limit = gemm_bf16_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus);
     const Bf16Plan plan =
-        bf16_plan(g.M, g.N, g.K, gemm_bf16_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
+        recent.get({g.M, g.N, g.K, slab_limit, cus, 0}, [&] { return bf16_plan(g.M, g.N, g.K, slab_limit, cus); });
     int i = 0;
 #define MQ_X(MT, NT, S) \
     if (plan.tile == i++) return launch_ring<MT, NT, S, OUT_BF16>(g, s, plan.slabs);
@@ -1649,7 +1670,10 @@ int launch_fp4(const GemmArgs &g, hipStream_t s)
     int cus = 0;
     if (int rc = compute_units(cus)) return rc;
     const int layout = g.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR;
-    const Fp4Plan plan = fp4_plan(g.M, g.N, g.K, layout, gemm_fp4_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus), cus);
+    static thread_local RecentPlans<Fp4Plan> recent;
+    const int64_t slab_limit = gemm_fp4_slab_limit(g.M, g.N, g.K, g.ws ? g.ws_bytes : 0, cus);
+    const Fp4Plan plan = recent.get({g.M, g.N, g.K, slab_limit, cus, layout},
+                                    [&] { return fp4_plan(g.M, g.N, g.K, layout, slab_limit, cus); });
     if (plan.n_first == 0 && plan.m_first == 0) return launch_fp4_tile<OUT_BF16>(plan.tile, plan.slabs, g, s, cus);
     constexpr int64_t T = OUT_BF16 ? 2 : 4;
     GemmArgs ga = g, gb = g;  // (the K step strides keep those of the whole operands)
@@ -1784,8 +1808,7 @@ int describe_gemm_bf16(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cu
 
 int launch_mfma_probe(float *out, int iters, int blocks, hipStream_t s)
 {
-    mfma_probe_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(out, iters);
-    return note_launch(hipGetLastError());
+    return enqueue(mfma_probe_kernel, dim3((unsigned)blocks), dim3(256), 0, s, out, iters);
 }
 
 int launch_gemm_fp4(const GemmArgs &g, hipStream_t s)

@@ -570,19 +570,15 @@ int launch_quantize_from(const Src &src, int64_t rows, int64_t K, const float *a
         for (int64_t y0 = 0; y0 < gy; y0 += 65535) {
             const int64_t ny = gy - y0 < 65535 ? gy - y0 : 65535;
             const dim3 grid((unsigned)gx, (unsigned)ny);
-            if (per == 16)
-                quantize_ktile_kernel<16><<<grid, dim3(kThreads), 0, s>>>(src, rows, y0 * per, (int)ksteps, alpha, codes, scales);
-            else
-                quantize_ktile_kernel<4><<<grid, dim3(kThreads), 0, s>>>(src, rows, y0 * per, (int)ksteps, alpha, codes, scales);
-            int rc = note_launch(hipGetLastError());
+            const int rc = enqueue(per == 16 ? quantize_ktile_kernel<16, Src> : quantize_ktile_kernel<4, Src>, grid, dim3(kThreads), 0, s,
+                                   src, rows, y0 * per, (int)ksteps, alpha, codes, scales);
             if (rc != MQ_OK) return rc;
         }
         return MQ_OK;
     }
     const int64_t grid = (total + kThreads - 1) / kThreads;
     if (grid > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    quantize_kernel<Src><<<dim3((unsigned)grid), dim3(kThreads), 0, s>>>(src, total, (int)bpr, alpha, codes, scales);
-    return note_launch(hipGetLastError());
+    return enqueue(quantize_kernel<Src>, dim3((unsigned)grid), dim3(kThreads), 0, s, src, total, (int)bpr, alpha, codes, scales);
 }
 
 }  // namespace
@@ -632,21 +628,14 @@ int launch_quantize_rmsnorm(const uint16_t *x, int64_t rows, int64_t K, int64_t 
     const int64_t groups = (rows + per - 1) / per;
     if (groups > 0x7FFFFFFF) return MQ_ERR_SHAPE;
     const dim3 grid((unsigned)groups), block(64 * per);
-#define MQ_RMS(ROWS_, NC_)                                                                                       \
-    (kt ? rmsnorm_quantize_kernel<ROWS_, NC_, true><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k,  \
-                                                                           alpha, codes, scales, y, ldy)        \
-        : rmsnorm_quantize_kernel<ROWS_, NC_, false><<<grid, block, 0, s>>>(x, rows, ksteps, ldx, w, eps, inv_k, \
-                                                                            alpha, codes, scales, y, ldy))
-    if (few && ksteps <= 64)
-        MQ_RMS(4, 4);
-    else if (few && ksteps <= 128)
-        MQ_RMS(4, 8);
-    else if (few)
-        MQ_RMS(4, 16);
-    else
-        MQ_RMS(16, 0);
+#define MQ_RMS(ROWS_, NC_) \
+    enqueue(kt ? rmsnorm_quantize_kernel<ROWS_, NC_, true> : rmsnorm_quantize_kernel<ROWS_, NC_, false>, grid, block, 0, s, \
+            x, rows, ksteps, ldx, w, eps, inv_k, alpha, codes, scales, y, ldy)
+    if (few && ksteps <= 64) return MQ_RMS(4, 4);
+    if (few && ksteps <= 128) return MQ_RMS(4, 8);
+    if (few) return MQ_RMS(4, 16);
+    return MQ_RMS(16, 0);
 #undef MQ_RMS
-    return note_launch(hipGetLastError());
 }
 
 int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, uint8_t *dst_s, int64_t rows,
@@ -658,9 +647,8 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
     const int64_t units = rows * ksteps;
     if ((ksteps < 4 && units < (1ll << 31)) || units < (to_ktile ? 3 << 16 : 1 << 17)) {
         auto kern = to_ktile ? relayout_units_kernel<true> : relayout_units_kernel<false>;
-        kern<<<dim3((unsigned)((units + kThreads - 1) / kThreads)), dim3(kThreads), 0, s>>>(src_c, src_s, dst_c, dst_s, (uint32_t)rows,
-                                                                                         (uint32_t)ksteps, (uint32_t)units);
-        return note_launch(hipGetLastError());
+        return enqueue(kern, dim3((unsigned)((units + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, src_c, src_s, dst_c, dst_s,
+                       (uint32_t)rows, (uint32_t)ksteps, (uint32_t)units);
     }
     const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, panels = (rows + R_ROWS - 1) / R_ROWS;
     // a launch holds fewer than 2^32 threads: what is more goes into further launches, by rows and, where one panel
@@ -675,9 +663,8 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
             const int64_t t = g0 * R_STEPS, left = ksteps - t < ng * R_STEPS ? ksteps - t : ng * R_STEPS;
             const int64_t from = to_ktile ? t : t * rows, to = to_ktile ? t * rows : t;
             auto kern = to_ktile ? relayout_kernel<true> : relayout_kernel<false>;
-            kern<<<dim3((unsigned)(n * ng)), dim3(kThreads), 0, s>>>(src_c + from * 32, src_s + from * 4, dst_c + to * 32,
-                                                                     dst_s + to * 4, rows, p0 * R_ROWS, ksteps, (int)left, (int)ng);
-            int rc = note_launch(hipGetLastError());
+            const int rc = enqueue(kern, dim3((unsigned)(n * ng)), dim3(kThreads), 0, s, src_c + from * 32, src_s + from * 4,
+                                   dst_c + to * 32, dst_s + to * 4, rows, p0 * R_ROWS, ksteps, (int)left, (int)ng);
             if (rc != MQ_OK) return rc;
         }
     return MQ_OK;
@@ -687,22 +674,17 @@ int launch_global_scale(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx,
                         hipStream_t s)
 {
     uint32_t *acc = reinterpret_cast<uint32_t *>(alpha);
-    amax_init_kernel<<<1, 1, 0, s>>>(acc);
-    int rc = note_launch(hipGetLastError());
+    int rc = enqueue(amax_init_kernel, dim3(1), dim3(1), 0, s, acc);
     if (rc != MQ_OK) return rc;
     if (rows > 0) {
         const int64_t total = rows * (K / 8);
         int64_t grid = (total + kAmaxThreads * 4 - 1) / (kAmaxThreads * 4);
         grid = grid < 1 ? 1 : (grid > 256 ? 256 : grid);   // one workgroup per compute unit
-        if (ldx == K)
-            amax_kernel<true><<<dim3((unsigned)grid), dim3(kAmaxThreads), 0, s>>>(x, total, (int)(K / 8), ldx, acc);
-        else
-            amax_kernel<false><<<dim3((unsigned)grid), dim3(kAmaxThreads), 0, s>>>(x, total, (int)(K / 8), ldx, acc);
-        rc = note_launch(hipGetLastError());
+        rc = enqueue(ldx == K ? amax_kernel<true> : amax_kernel<false>, dim3((unsigned)grid), dim3(kAmaxThreads), 0, s, x, total,
+                     (int)(K / 8), ldx, acc);
         if (rc != MQ_OK) return rc;
     }
-    amax_final_kernel<<<1, 1, 0, s>>>(acc);
-    return note_launch(hipGetLastError());
+    return enqueue(amax_final_kernel, dim3(1), dim3(1), 0, s, acc);
 }
 
 }  // namespace mq

@@ -1,0 +1,116 @@
+"""The native call forms of the binding against its general path: what is not of the plain form is left to the general path,
+which accepts or refuses it; what is of the plain form gives the same tensors."""
+import pytest
+import torch
+
+import paper_2605_20315_amd as mq
+from paper_2605_20315_amd import _lib, ops
+
+
+class _General:
+    """Takes the native module's place: every call goes to the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def test_calls_that_are_not_of_the_plain_form_are_left_alone():
+    fast = _lib.load_binding()
+    x, u8, f = torch.zeros(4, 64, dtype=torch.bfloat16), torch.zeros(4, 32, dtype=torch.uint8), torch.zeros(1)
+    assert fast.global_scale(x, None) is None                      # not on the GPU
+    assert fast.quantize(x, f, None, None, 0) is None
+    assert fast.quantize(None, f, None, None, 0) is None           # not a tensor
+    assert fast.quantize_silu_mul(x, f, None, None, 0) is None
+    assert fast.quantize_rmsnorm(x, x, 1e-6, f, None, None, 0) is None
+    assert fast.relayout(u8, u8, 0, 1) is None
+    assert fast.gemm_ws(u8, u8, f, u8, u8, f, None, 0, None, 0) is None
+    assert fast.linear(x, f, u8, u8, f, 0, None, None, None, 0, None) is None
+    assert fast.bf16_gemm_ws(x, x, None, 0, None) is None
+    with pytest.raises(TypeError):
+        fast.bf16_gemm_ws(x, x)
+    with pytest.raises(mq.MixQuantError, match="GPU"):
+        mq.nvfp4_linear(x, f, u8, u8, f)
+
+
+def _x(M, K, seed=0, ld=None):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(M, ld or K, device="cuda", generator=g).to(torch.bfloat16)[:, :K]
+
+
+def _flat(r):
+    return [t for p in r for t in _flat(p)] if isinstance(r, (tuple, list)) else [r]
+
+
+def _calls(M, N, K, ld, out):
+    x, w = _x(M, K, 1, ld), _x(N, K, 2)
+    ax, aw = mq.nvfp4_global_scale(x), mq.nvfp4_global_scale(w)
+    ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    dtype = torch.float32 if out == mq.MQ_OUT_FP32 else torch.bfloat16
+    for layout in (mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE):
+        wc, wsc = mq.nvfp4_quantize(w, aw, layout=layout)
+        for given in (False, True):
+            y = torch.empty(M, N + 8, dtype=dtype, device="cuda")[:, :N] if given else None
+            c = torch.empty(M, K // 2, dtype=torch.uint8, device="cuda") if given else None
+            s = torch.empty(M, K // 16, dtype=torch.uint8, device="cuda") if given else None
+            yield lambda: mq.nvfp4_quantize(x, ax, c, s, layout)
+            yield lambda: mq.nvfp4_quantize_rmsnorm(x, w[0].clone(), 1e-6, ax, c, s, layout)
+            yield lambda: mq.nvfp4_linear(x, ax, wc, wsc, aw, out, y, c, s, layout, ws if given else None)
+            yield lambda: mq.nvfp4_gemm_ws(*mq.nvfp4_quantize(x, ax, layout=layout), ax, wc, wsc, aw, ws, out, y, layout)
+            yield lambda: mq.bf16_gemm_ws(x, w, ws if given else None, out, y)
+        yield lambda: mq.nvfp4_quantize_silu_mul(w, aw, layout=layout)
+        yield lambda: mq.nvfp4_relayout(wc, wsc, layout, 1 - layout)
+    yield lambda: mq.nvfp4_global_scale(x)
+    yield lambda: mq.nvfp4_global_scale(w, torch.empty(1, device="cuda"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,ld", [(1, 16, 128, None), (1, 64, 256, 512), (33, 72, 256, 264), (64, 512, 1024, None)])
+@pytest.mark.parametrize("out", [mq.MQ_OUT_BF16, mq.MQ_OUT_FP32])
+def test_native_and_general_path_give_the_same_tensors(monkeypatch, M, N, K, ld, out):
+    for i, call in enumerate(_calls(M, N, K, ld, out)):
+        with monkeypatch.context() as m:
+            m.setattr(ops, "_fast", _General())
+            want = [t.clone() for t in _flat(call())]
+        got = _flat(call())
+        assert len(got) == len(want), i
+        for g, w in zip(got, want):
+            assert g.dtype == w.dtype and g.shape == w.shape and torch.equal(g, w), i
+
+
+@pytest.mark.gpu
+def test_given_outputs_come_back_and_refusals_stay(monkeypatch):
+    x, w = _x(8, 128), _x(16, 128)
+    y = torch.empty(8, 16, dtype=torch.bfloat16, device="cuda")
+    assert mq.bf16_gemm_ws(x, w, None, mq.MQ_OUT_BF16, y) is y
+    a = torch.empty(1, device="cuda")
+    assert mq.nvfp4_global_scale(x, a) is a
+    for general in (False, True):
+        if general:
+            monkeypatch.setattr(ops, "_fast", _General())
+        with pytest.raises(mq.MixQuantError, match="nvfp4_quantize: MQ_ERR_ARG"):
+            mq.nvfp4_quantize(x, a, layout=7)
+        with pytest.raises(mq.MixQuantError, match="bf16_gemm_ws: MQ_ERR_ALIGN"):
+            mq.bf16_gemm_ws(x, w, None, mq.MQ_OUT_BF16, torch.empty(8, 20, dtype=torch.bfloat16, device="cuda")[:, 4:])
+        with pytest.raises(AssertionError):
+            mq.bf16_gemm_ws(x.float(), w, None)
+        with pytest.raises(mq.MixQuantError, match="contiguous"):
+            mq.bf16_gemm_ws(x.t(), w, None)
+
+
+@pytest.mark.gpu
+def test_current_stream_is_used():
+    x, w = _x(64, 1024), _x(256, 1024)
+    want = mq.bf16_gemm_ws(x, w, None)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    y = torch.zeros_like(want)
+    graph = torch.cuda.CUDAGraph()
+    mq.mq_init()
+    with torch.cuda.graph(graph, stream=side):   # a launch on any other stream would not be captured
+        mq.bf16_gemm_ws(x, w, None, mq.MQ_OUT_BF16, y)
+    assert not y.any()
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
