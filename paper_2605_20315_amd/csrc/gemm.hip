@@ -272,15 +272,15 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         pb_c = static_cast<const char *>(g.b) + rb * g.b_c_row + t_next * g.b_c_step;
         pa_s = reinterpret_cast<const char *>(g.a_scales) + ra * g.a_s_row + t_next * g.a_s_step;
         pb_s = reinterpret_cast<const char *>(g.b_scales) + rb * g.b_s_row + t_next * g.b_s_step;
+        // (32-bit arithmetic per lane: offsets within 128 rows fit)
+        const int last_a = (int)(g.M - 1 - ra < 127 ? g.M - 1 - ra : 127), last_b = (int)(g.N - 1 - rb < 127 ? g.N - 1 - rb : 127);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const bool isA = q < 4;
-            const int64_t total = isA ? g.M : g.N;
-            int64_t grow = (isA ? m0 + wm0 + ((q & 3) ^ aswap) * 32 : n0 + wn0 + (q & 3) * 32) + frow;
-            grow = grow < total ? grow : total - 1;
-            const int64_t rel = grow - (isA ? ra : rb);  // 0 .. 127
-            vc[q] = (uint32_t)(rel * (isA ? g.a_c_row : g.b_c_row) + fhalf * 16);
-            vs[q] = (uint32_t)(rel * (isA ? g.a_s_row : g.b_s_row));
+            const int row = (isA ? (q ^ aswap) : q - 4) * 32 + frow, last = isA ? last_a : last_b;
+            const uint32_t rel = (uint32_t)(row < last ? row : last);
+            vc[q] = rel * (uint32_t)(isA ? g.a_c_row : g.b_c_row) + fhalf * 16;
+            vs[q] = rel * (uint32_t)(isA ? g.a_s_row : g.b_s_row);
         }
     };
     RawTile st[NSETS];
@@ -580,38 +580,42 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     const char *const ta_s = reinterpret_cast<const char *>(g.a_scales) + m0 * g.a_s_row;
     const char *const tb_s = reinterpret_cast<const char *>(g.b_scales) + n0 * g.b_s_row;
     uint32_t vc[NT], vs[NT];
+    const int last_a = (int)(g.M - m0 < 32 * TM ? g.M - m0 : 32 * TM) - 1, last_b = (int)(g.N - n0 < 32 * TN ? g.N - n0 : 32 * TN) - 1;
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
         const bool isA = q < TM;
-        const int64_t total = isA ? g.M : g.N, first = isA ? m0 : n0;
-        int64_t grow = first + (isA ? q : q - TM) * 32 + frow;
-        grow = grow < total ? grow : total - 1;
-        vc[q] = (uint32_t)((grow - first) * (isA ? g.a_c_row : g.b_c_row) + fhalf * 16);
-        vs[q] = (uint32_t)((grow - first) * (isA ? g.a_s_row : g.b_s_row));
+        const int row = (isA ? q : q - TM) * 32 + frow, last = isA ? last_a : last_b;
+        const uint32_t rel = (uint32_t)(row < last ? row : last);
+        vc[q] = rel * (uint32_t)(isA ? g.a_c_row : g.b_c_row) + fhalf * 16;
+        vs[q] = rel * (uint32_t)(isA ? g.a_s_row : g.b_s_row);
     }
     uint4 rc[NSETS][NT];     // this lane's 32 codes of each operand tile, NSETS K steps
     uint32_t rs[NSETS][NT];  // the rows' four E4M3 scale bytes
-    // K steps are loaded in ascending order, so the four K-step bases advance by their strides
-    // (scalar additions) instead of being recomputed by 64-bit multiplications; loads past the
-    // wave's last step re-read that step (from L1; its products are multiplied by zero scales).
-    int next_t = k0 < KT ? k0 : KT - 1;
-    const char *pa_c = ta_c + (int64_t)next_t * g.a_c_step, *pb_c = tb_c + (int64_t)next_t * g.b_c_step;
-    const char *pa_s = ta_s + (int64_t)next_t * g.a_s_step, *pb_s = tb_s + (int64_t)next_t * g.b_s_step;
-    auto load_step = [&](auto setc) {
+    // Resources that start at the wave's first K step; the K step goes into the loads' scalar offset (32 bits: the
+    // launch rule keeps a wave's part of K below that), one multiplication each.  Loads past the wave's last step re-read
+    // that step (from L1; its products are multiplied by zero scales).  With running 64-bit pointers and a resource built
+    // per load and K step there were 38 scalar instructions per K step instead of 9, and at two waves per SIMD a scalar
+    // instruction per MFMA costs about two cycles of the forty.  With the last group below: 64 tokens, K = N = 4096 in 32x32
+    // tiles 7.1 -> 6.4 us, 256 tokens in 64x64 12.7 -> 11.2, 128 tokens on K = 14336 in 64x32 21.6 -> 20.4.
+    const int len = k1 - k0;
+    const int64_t first = k0 < KT ? k0 : KT - 1;
+    auto rsrc = [](const char *base) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, -1, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t rac = rsrc(ta_c + first * g.a_c_step), rbc = rsrc(tb_c + first * g.b_c_step);
+    const __amdgpu_buffer_rsrc_t ras = rsrc(ta_s + first * g.a_s_step), rbs = rsrc(tb_s + first * g.b_s_step);
+    const uint32_t ca = (uint32_t)g.a_c_step, cb = (uint32_t)g.b_c_step, sa = (uint32_t)g.a_s_step, sb = (uint32_t)g.b_s_step;
+    auto load_step = [&](int t, auto setc) {  // K step t of this wave
         constexpr int R = decltype(setc)::value;
-        auto rsrc = [](const char *base) {
-            return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, -1, 0x00020000);
-        };
-        const __amdgpu_buffer_rsrc_t rac = rsrc(pa_c), rbc = rsrc(pb_c), ras = rsrc(pa_s), rbs = rsrc(pb_s);
+        t = t < len - 1 ? t : len - 1;
+        const uint32_t u = (uint32_t)(t > 0 ? t : 0);
+        const int oac = (int)(u * ca), obc = (int)(u * cb), oas = (int)(u * sa), obs = (int)(u * sb);
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
-            const u32x4 c = __builtin_amdgcn_raw_buffer_load_b128(q < TM ? rac : rbc, (int)vc[q], 0, 0);
+            const u32x4 c = __builtin_amdgcn_raw_buffer_load_b128(q < TM ? rac : rbc, (int)vc[q], q < TM ? oac : obc, 0);
             rc[R][q] = make_uint4(c[0], c[1], c[2], c[3]);
-            rs[R][q] = __builtin_amdgcn_raw_buffer_load_b32(q < TM ? ras : rbs, (int)vs[q], 0, 0);
+            rs[R][q] = __builtin_amdgcn_raw_buffer_load_b32(q < TM ? ras : rbs, (int)vs[q], q < TM ? oas : obs, 0);
         }
-        const int64_t adv = next_t + 1 < k1 ? -1 : 0;  // all ones while K steps remain (no branch in the loop)
-        next_t -= (int)adv;
-        pa_c += g.a_c_step & adv, pb_c += g.b_c_step & adv, pa_s += g.a_s_step & adv, pb_s += g.b_s_step & adv;
     };
     // scales, expansion and MFMAs exactly as in gemm_fp4_direct (K index of a lane: 32h + 8p + j)
     uint32_t sg[NT];
@@ -661,8 +665,10 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
                     __builtin_bit_cast(f16x8, f[i]), __builtin_bit_cast(f16x8, f[TM + j]), acc[i][j], 0, 0, 0);
     };
     constexpr int NM = TM * TN, VPER = (NT * 8 + NM - 1) / NM;
-    auto kstep = [&](int kt, auto setc) {
+    // K step kt (of this wave); LAST: of its last group, behind which nothing is loaded
+    auto kstep = [&](int kt, auto setc, auto lastc) {
         constexpr int R = decltype(setc)::value;
+        constexpr bool LAST = decltype(lastc)::value;
         using Next = std::integral_constant<int, (R + 1) % NSETS>;
         expand_phase(setc, 1, fr[1]);
         mfmas(fr[0]);
@@ -673,11 +679,13 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         expand_phase(setc, 3, fr[1]);
         mfmas(fr[0]);
         sched_phase<NM, VPER>();
-        prep_scales(Next{}, kt + 1 < k1);
-        expand_phase(Next{}, 0, fr[0]);
-        load_step(setc);  // K step kt + NSETS
+        if constexpr (!LAST || R + 1 < NSETS) {
+            prep_scales(Next{}, kt + 1 < len);
+            expand_phase(Next{}, 0, fr[0]);
+        }
+        if constexpr (!LAST) load_step(kt + NSETS, setc);
         mfmas(fr[1]);
-        sched_phase<NM, VPER + 2, (2 * NT + NM - 1) / NM>();
+        sched_phase<NM, VPER + 2, LAST ? 0 : (2 * NT + NM - 1) / NM>();
     };
     auto for_sets = [&](auto &&fn) {  // fn(set index as a constant), sets 0 .. NSETS-1
         fn(std::integral_constant<int, 0>{});
@@ -690,15 +698,24 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     // went last, and the counter the compiler waits on in the loop then demanded that nearly
     // everything in flight had landed before each K step: a prefetch distance of one step, not three.)
     for_sets([&](auto u) {
-        load_step(u);
+        load_step(decltype(u)::value, u);
         __builtin_amdgcn_sched_barrier(0);
     });
     const float scale = (*g.a_alpha) * (*g.b_alpha);
-    prep_scales(std::integral_constant<int, 0>{}, k0 < k1);
+    prep_scales(std::integral_constant<int, 0>{}, len > 0);
     expand_phase(std::integral_constant<int, 0>{}, 0, fr[0]);
-    // whole groups of NSETS K steps; a step past the end multiplies by zero scales (leaving the loop in the
-    // middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower)
-    for (int kt = k0; kt < k1; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u); });
+    // Whole groups of NSETS K steps, then the last one, which loads nothing and ends at the wave's last step.  (Leaving the
+    // loop in the middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower.  Behind the
+    // loop they are moved once.  When the last group was run whole, on zero scales, K = 512 took 5.0 us instead of 3.5, and
+    // 100 tokens on K = 6400, N = 5120 17.0 instead of 14.0.)
+    int kt = 0;
+    for (; kt + NSETS < len; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u, std::false_type{}); });
+    auto tail = [&](auto self, auto u) -> void {
+        kstep(kt + decltype(u)::value, u, std::true_type{});
+        if constexpr (decltype(u)::value + 1 < NSETS)
+            if (kt + decltype(u)::value + 1 < len) self(self, std::integral_constant<int, decltype(u)::value + 1>{});
+    };
+    tail(tail, std::integral_constant<int, 0>{});
 
     if (g.ksplit > 1) {
         GemmArgs part = g;  // the slab's [M, N] FP32 matrix of partial sums; splitk_reduce_kernel scales and rounds
@@ -1614,6 +1631,10 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
         // (many rounds of one-wave tiles: 6144 tokens on K = 128, N = 2048 15.4 us against 13.4 in 256x256 tiles, 6342 on K = 64, N = 15304
         // 83 against 66)
         if (kFp4Tiles[i].waves == 1 && tiles > 8 * cus) return 1e300;
+        // the small tiles address a wave's part of K with 32 bits
+        const int64_t part = (K / BK + slabs * kFp4Tiles[i].waves - 1) / (slabs * kFp4Tiles[i].waves);
+        if (kFp4Tiles[i].kernel == MQ_KERNEL_FP4_SMALL && layout == MQ_LAYOUT_KTILE && (part - 1) * (M > N ? M : N) * 32 >= (1ll << 31))
+            return 1e300;
         return launch_us(kFp4Costs[order][i], tiles * slabs, (double)(K / BK) / (double)slabs, 0.5625 * (double)n * (double)K / 5.3e6,
                          0.2, 2.0 * (double)m * (double)n, cus) +
                (slabs > 1 ? kSecondPass[order] : 0.0);
