@@ -480,15 +480,30 @@ __device__ __forceinline__ uint32_t amax8_bits(uint4 v)
     return lo > hi ? lo : hi;
 }
 
-// Largest |x| of the tensor as BF16 bits, folded into *acc with one atomic per workgroup.  At
+__device__ __forceinline__ float alpha_of(uint32_t amax_bits)  // from the largest |x| as BF16 bits
+{
+    const float amax = __uint_as_float(amax_bits << 16);
+    return amax == 0.0f ? 1.0f : amax / 2688.0f;
+}
+
+// Largest |x| of the tensor, into the caller's word `acc`, which is all the memory there is.  At
 // most one workgroup of 1024 threads per compute unit, each reading one contiguous share of the
 // tensor with four 16-byte loads in flight per thread: atomics on a single address serialise in
 // L2, and with 2048 workgroups they cost more than the read itself (measured on [8192, 4096]:
 // 30.7 us with 2048 atomics, 13.4 us for the same reads without any, 14.5 us with 256).
+// One workgroup writes alpha itself.  Several start from a word that amax_init_kernel has cleared.  COUNT: the word holds the
+// largest |x| as BF16 bits in its high half and the number of workgroups accounted for in the low half: a workgroup first
+// raises the maximum where its own is larger, which wipes the count it gets back, then adds itself and what it wiped.
+// No workgroup is counted before its maximum is in and none is lost, so the one that completes the count holds the
+// maximum of all of them and overwrites the word with alpha.  Without COUNT the word holds the BF16 bits, and
+// amax_final_kernel does that in a launch of its own (1.6 us on the GPU, 2.2 on the host).  us per call, counted / own
+// launch: 64 KB (one workgroup) 2.6 / 7.1, 256 KB (one) 4.0 / 7.3, 1 MB 5.7 / 7.3, 8 MB (128 workgroups) 8.4 / 8.8; 34 MB
+// (256 of them, whose atomics on the one word then take longer than the launch) 14.3 / 12.5, 143 MB 32.5 / 30.0.
 // CONTIG: ldx == K.
 constexpr int kAmaxThreads = 1024;
+constexpr int64_t kAmaxOne = 4, kAmaxCounted = 128;  // most workgroups of 64 KB served by one, and that count themselves
 
-template <bool CONTIG>
+template <bool CONTIG, bool COUNT>
 __global__ __launch_bounds__(kAmaxThreads) void amax_kernel(const uint16_t *__restrict__ x, int64_t total_chunks,
                                                             int chunks_per_row, int64_t ldx, uint32_t *acc)
 {
@@ -523,17 +538,26 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_kernel(const uint16_t *__re
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < kAmaxThreads / 64; ++w) m = wave_max[w] > m ? wave_max[w] : m;
-        if (m != 0) atomicMax(acc, m);
+        if (gridDim.x == 1) {
+            *acc = __float_as_uint(alpha_of(m));
+            return;
+        }
+        if constexpr (!COUNT) {
+            if (m != 0) atomicMax(acc, m);
+            return;
+        }
+        uint32_t add = 1;
+        if (m > __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) {
+            const uint32_t old = __hip_atomic_fetch_max(acc, m << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (m > old >> 16) add += old & 0xFFFFu;
+        }
+        const uint32_t now = __hip_atomic_fetch_add(acc, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+        if ((now & 0xFFFFu) == gridDim.x)
+            __hip_atomic_store(acc, __float_as_uint(alpha_of(now >> 16)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-// *acc holds the largest |x| as BF16 bits; overwrite it with alpha = amax / (6 * 448).
-__global__ void amax_final_kernel(uint32_t *acc)
-{
-    const float amax = __uint_as_float(*acc << 16);
-    const float alpha = (amax == 0.0f) ? 1.0f : amax / 2688.0f;
-    *reinterpret_cast<float *>(acc) = alpha;
-}
+__global__ void amax_final_kernel(uint32_t *acc) { *acc = __float_as_uint(alpha_of(*acc)); }
 
 }  // namespace
 
@@ -674,17 +698,16 @@ int launch_global_scale(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx,
                         hipStream_t s)
 {
     uint32_t *acc = reinterpret_cast<uint32_t *>(alpha);
-    int rc = enqueue(amax_init_kernel, dim3(1), dim3(1), 0, s, acc);
-    if (rc != MQ_OK) return rc;
-    if (rows > 0) {
-        const int64_t total = rows * (K / 8);
-        int64_t grid = (total + kAmaxThreads * 4 - 1) / (kAmaxThreads * 4);
-        grid = grid < 1 ? 1 : (grid > 256 ? 256 : grid);   // one workgroup per compute unit
-        rc = enqueue(ldx == K ? amax_kernel<true> : amax_kernel<false>, dim3((unsigned)grid), dim3(kAmaxThreads), 0, s, x, total,
-                     (int)(K / 8), ldx, acc);
-        if (rc != MQ_OK) return rc;
-    }
-    return enqueue(amax_final_kernel, dim3(1), dim3(1), 0, s, acc);
+    const int64_t total = rows * (K / 8);
+    int64_t grid = (total + kAmaxThreads * 4 - 1) / (kAmaxThreads * 4);
+    grid = grid <= kAmaxOne ? 1 : grid > 256 ? 256 : grid;  // one workgroup per compute unit at most
+    const bool count = grid <= kAmaxCounted;                // both lines: see amax_kernel
+    if (grid > 1)
+        if (int rc = enqueue(amax_init_kernel, dim3(1), dim3(1), 0, s, acc)) return rc;
+    auto *const kern = ldx == K ? (count ? amax_kernel<true, true> : amax_kernel<true, false>)
+                                : (count ? amax_kernel<false, true> : amax_kernel<false, false>);
+    if (int rc = enqueue(kern, dim3((unsigned)grid), dim3(kAmaxThreads), 0, s, x, total, (int)(K / 8), ldx, acc)) return rc;
+    return count ? MQ_OK : enqueue(amax_final_kernel, dim3(1), dim3(1), 0, s, acc);
 }
 
 }  // namespace mq
