@@ -551,15 +551,28 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
     }
 }
 
-template <int TM, int TN, int S, int NSETS, bool OUT_BF16>
+// LINE (row-major operands, K % 256 == 0): the unit of work is four K steps, whose codes of a row are one 128-byte line.  In K
+// order a load takes 32 bytes of each of 32 lines, and by the time the next K step asks for the next 32 bytes the other waves
+// have pushed the lines out of the 32 KB of L1: every line was fetched four times, and a line per row for four scale bytes
+// besides.  Those fetches, 64 bytes per clock and compute unit from L2, bound the kernel.  Here lane (r, h) takes the half line
+// h of row r in four loads that stand together (chunk t of 16 bytes holds elements 128 h + 32 t ..: A and B permute K alike) and
+// the eight scale bytes of the half line in one load, every four K steps.  Tiles of up to three operand rows hold two groups,
+// the next one under way while this one is multiplied; 64x64 reloads the registers under the group's last K step.  us, in K order
+// and by lines: 64 tokens on K = N = 4096 in 32x32 tiles 11.6 and 8.9; 128 on K = 14336, N = 4096 in 64x32 51 and 32; 256 on
+// K = N = 4096 in 64x64 20.3 and 14.8; 512 28.9 and 24.9; 32 on K = 2048, N = 4096 6.5 and 5.7.
+template <int TM, int TN, int S, int NSETS, bool OUT_BF16, bool LINE>
 __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) void gemm_fp4_small(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int NT = TM + TN;
+    constexpr int UNIT = LINE ? 4 : 1;                     // K steps of a unit
+    constexpr bool TWO = LINE && NT <= 3;                  // two groups in registers
+    constexpr int SETS = TWO ? 8 : NSETS;                  // K steps in registers
+    static_assert(!LINE || NSETS == 4, "a line is four K steps");
     static_assert((TM * TN) % 4 == 0 || TM * TN < 4, "the LDS reduction moves four 32x32 tiles per pass");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int frow = lane & 31, fhalf = lane >> 5;
-    const int KT = (int)(g.K / BK);
+    const int KT = (int)(g.K / (BK * UNIT));  // units: K steps, or lines
     // work item = (K slab, tile), slab-major; tiles that share a column panel of B are neighbours
     // in that order and run on one XCD.  g.ksplit == 1: the tile's whole K.
     const int tiles = tiles_m * tiles_n;
@@ -586,11 +599,12 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         const bool isA = q < TM;
         const int row = (isA ? q : q - TM) * 32 + frow, last = isA ? last_a : last_b;
         const uint32_t rel = (uint32_t)(row < last ? row : last);
-        vc[q] = rel * (uint32_t)(isA ? g.a_c_row : g.b_c_row) + fhalf * 16;
-        vs[q] = rel * (uint32_t)(isA ? g.a_s_row : g.b_s_row);
+        vc[q] = rel * (uint32_t)(isA ? g.a_c_row : g.b_c_row) + fhalf * (16 * UNIT);
+        vs[q] = rel * (uint32_t)(isA ? g.a_s_row : g.b_s_row) + (LINE ? fhalf * 8 : 0);
     }
-    uint4 rc[NSETS][NT];     // this lane's 32 codes of each operand tile, NSETS K steps
-    uint32_t rs[NSETS][NT];  // the rows' four E4M3 scale bytes
+    uint4 rc[SETS][NT];                  // this lane's 32 codes of each operand tile, SETS K steps
+    uint32_t rs[LINE ? 1 : SETS][NT];    // the rows' four E4M3 scale bytes of a K step
+    uint2 rl[LINE ? SETS / 4 : 1][NT];   // or this lane's eight of a line
     // Resources that start at the wave's first K step; the K step goes into the loads' scalar offset (32 bits: the
     // launch rule keeps a wave's part of K below that), one multiplication each.  Loads past the wave's last step re-read
     // that step (from L1; its products are multiplied by zero scales).  With running 64-bit pointers and a resource built
@@ -602,8 +616,23 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     auto rsrc = [](const char *base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, -1, 0x00020000);
     };
-    const __amdgpu_buffer_rsrc_t rac = rsrc(ta_c + first * g.a_c_step), rbc = rsrc(tb_c + first * g.b_c_step);
-    const __amdgpu_buffer_rsrc_t ras = rsrc(ta_s + first * g.a_s_step), rbs = rsrc(tb_s + first * g.b_s_step);
+    const __amdgpu_buffer_rsrc_t rac = rsrc(ta_c + first * UNIT * g.a_c_step), rbc = rsrc(tb_c + first * UNIT * g.b_c_step);
+    const __amdgpu_buffer_rsrc_t ras = rsrc(ta_s + first * UNIT * g.a_s_step), rbs = rsrc(tb_s + first * UNIT * g.b_s_step);
+    // Line l of this wave into register group `buf`: operand tile q, its four chunks one behind the other (apart, the lines have
+    // left L1 by the next chunk) and its scales.
+    auto load_line = [&](int l, auto bufc, int q) {
+        constexpr int buf = decltype(bufc)::value;
+        l = l < len - 1 ? l : len - 1;
+        const int u = l > 0 ? l : 0;
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const u32x4 c = __builtin_amdgcn_raw_buffer_load_b128(q < TM ? rac : rbc, (int)(vc[q] + 16 * t), u * 128, 0);
+            rc[4 * buf + t][q] = make_uint4(c[0], c[1], c[2], c[3]);
+        }
+        const u32x2 sc = __builtin_amdgcn_raw_buffer_load_b64(q < TM ? ras : rbs, (int)vs[q], u * 16, 0);
+        rl[buf][q] = make_uint2(sc[0], sc[1]);
+    };
     const uint32_t ca = (uint32_t)g.a_c_step, cb = (uint32_t)g.b_c_step, sa = (uint32_t)g.a_s_step, sb = (uint32_t)g.b_s_step;
     auto load_step = [&](int t, auto setc) {  // K step t of this wave
         constexpr int R = decltype(setc)::value;
@@ -622,10 +651,10 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     const uint32_t sel_valid = 0x0C000C00u | (uint32_t)(2 * fhalf) | ((uint32_t)(2 * fhalf + 1) << 16);
     auto prep_scales = [&](auto setc, bool valid) {
         constexpr int R = decltype(setc)::value;
-        const uint32_t sel = valid ? sel_valid : 0x0C0C0C0Cu;
+        const uint32_t sel = LINE ? (R % 2 ? 0x0C030C02u : 0x0C010C00u) : valid ? sel_valid : 0x0C0C0C0Cu;
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
-            uint32_t sc = rs[R][q];
+            uint32_t sc = LINE ? (R % 4 < 2 ? rl[LINE ? R / 4 : 0][q].x : rl[LINE ? R / 4 : 0][q].y) : rs[LINE ? 0 : R][q];
             asm("" : "+v"(sc));
             sg[q] = __builtin_amdgcn_perm(0u, sc, sel) << 7;
         }
@@ -665,57 +694,119 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
                     __builtin_bit_cast(f16x8, f[i]), __builtin_bit_cast(f16x8, f[TM + j]), acc[i][j], 0, 0, 0);
     };
     constexpr int NM = TM * TN, VPER = (NT * 8 + NM - 1) / NM;
-    // K step kt (of this wave); LAST: of its last group, behind which nothing is loaded
-    auto kstep = [&](int kt, auto setc, auto lastc) {
-        constexpr int R = decltype(setc)::value;
-        constexpr bool LAST = decltype(lastc)::value;
-        using Next = std::integral_constant<int, (R + 1) % NSETS>;
-        expand_phase(setc, 1, fr[1]);
-        mfmas(fr[0]);
-        sched_phase<NM, VPER>();
-        expand_phase(setc, 2, fr[0]);
-        mfmas(fr[1]);
-        sched_phase<NM, VPER>();
-        expand_phase(setc, 3, fr[1]);
-        mfmas(fr[0]);
-        sched_phase<NM, VPER>();
-        if constexpr (!LAST || R + 1 < NSETS) {
-            prep_scales(Next{}, kt + 1 < len);
-            expand_phase(Next{}, 0, fr[0]);
-        }
-        if constexpr (!LAST) load_step(kt + NSETS, setc);
-        mfmas(fr[1]);
-        sched_phase<NM, VPER + 2, LAST ? 0 : (2 * NT + NM - 1) / NM>();
-    };
+    using std::integral_constant;
     auto for_sets = [&](auto &&fn) {  // fn(set index as a constant), sets 0 .. NSETS-1
-        fn(std::integral_constant<int, 0>{});
-        if constexpr (NSETS > 1) fn(std::integral_constant<int, 1>{});
-        if constexpr (NSETS > 2) fn(std::integral_constant<int, 2>{});
-        if constexpr (NSETS > 3) fn(std::integral_constant<int, 3>{});
+        fn(integral_constant<int, 0>{});
+        if constexpr (NSETS > 1) fn(integral_constant<int, 1>{});
+        if constexpr (NSETS > 2) fn(integral_constant<int, 2>{});
+        if constexpr (NSETS > 3) fn(integral_constant<int, 3>{});
     };
     static_assert(NSETS >= 2 && NSETS <= 4, "two to four K steps in flight");
-    // The first NSETS K steps, issued set by set.  (Left to the scheduler, the B loads of all sets
-    // went last, and the counter the compiler waits on in the loop then demanded that nearly
-    // everything in flight had landed before each K step: a prefetch distance of one step, not three.)
-    for_sets([&](auto u) {
-        load_step(decltype(u)::value, u);
-        __builtin_amdgcn_sched_barrier(0);
-    });
     const float scale = (*g.a_alpha) * (*g.b_alpha);
-    prep_scales(std::integral_constant<int, 0>{}, len > 0);
-    expand_phase(std::integral_constant<int, 0>{}, 0, fr[0]);
-    // Whole groups of NSETS K steps, then the last one, which loads nothing and ends at the wave's last step.  (Leaving the
-    // loop in the middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower.  Behind the
-    // loop they are moved once.  When the last group was run whole, on zero scales, K = 512 took 5.0 us instead of 3.5, and
-    // 100 tokens on K = 6400, N = 5120 17.0 instead of 14.0.)
-    int kt = 0;
-    for (; kt + NSETS < len; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u, std::false_type{}); });
-    auto tail = [&](auto self, auto u) -> void {
-        kstep(kt + decltype(u)::value, u, std::true_type{});
-        if constexpr (decltype(u)::value + 1 < NSETS)
-            if (kt + decltype(u)::value + 1 < len) self(self, std::integral_constant<int, decltype(u)::value + 1>{});
-    };
-    tail(tail, std::integral_constant<int, 0>{});
+    if constexpr (!LINE) {
+        // K step kt (of this wave); LAST: of its last group, behind which nothing is loaded
+        auto kstep = [&](int kt, auto setc, auto lastc) {
+            constexpr int R = decltype(setc)::value;
+            constexpr bool LAST = decltype(lastc)::value;
+            using Next = integral_constant<int, (R + 1) % NSETS>;
+            expand_phase(setc, 1, fr[1]);
+            mfmas(fr[0]);
+            sched_phase<NM, VPER>();
+            expand_phase(setc, 2, fr[0]);
+            mfmas(fr[1]);
+            sched_phase<NM, VPER>();
+            expand_phase(setc, 3, fr[1]);
+            mfmas(fr[0]);
+            sched_phase<NM, VPER>();
+            if constexpr (!LAST || R + 1 < NSETS) {
+                prep_scales(Next{}, kt + 1 < len);
+                expand_phase(Next{}, 0, fr[0]);
+            }
+            if constexpr (!LAST) load_step(kt + NSETS, setc);
+            mfmas(fr[1]);
+            sched_phase<NM, VPER + 2, LAST ? 0 : (2 * NT + NM - 1) / NM>();
+        };
+        // The first NSETS K steps, issued set by set.  (Left to the scheduler, the B loads of all sets
+        // went last, and the counter the compiler waits on in the loop then demanded that nearly
+        // everything in flight had landed before each K step: a prefetch distance of one step, not three.)
+        for_sets([&](auto u) {
+            load_step(decltype(u)::value, u);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        prep_scales(integral_constant<int, 0>{}, len > 0);
+        expand_phase(integral_constant<int, 0>{}, 0, fr[0]);
+        // Whole groups of NSETS K steps, then the last one, which loads nothing and ends at the wave's last step.  (Leaving the
+        // loop in the middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower.  Behind the
+        // loop they are moved once.  When the last group was run whole, on zero scales, K = 512 took 5.0 us instead of 3.5, and
+        // 100 tokens on K = 6400, N = 5120 17.0 instead of 14.0.)
+        int kt = 0;
+        for (; kt + NSETS < len; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u, std::false_type{}); });
+        auto tail = [&](auto self, auto u) -> void {
+            kstep(kt + decltype(u)::value, u, std::true_type{});
+            if constexpr (decltype(u)::value + 1 < NSETS)
+                if (kt + decltype(u)::value + 1 < len) self(self, integral_constant<int, decltype(u)::value + 1>{});
+        };
+        tail(tail, integral_constant<int, 0>{});
+    } else if (len > 0) {
+        // line l of this wave, in register group `buf`; LAST: nothing follows
+        auto line = [&](int l, auto bufc, auto lastc) {
+            constexpr int buf = decltype(bufc)::value, other = TWO ? buf ^ 1 : buf;
+            constexpr bool LAST = decltype(lastc)::value;
+            using Other = integral_constant<int, other>;
+            for_sets([&](auto tc) {
+                constexpr int t = decltype(tc)::value, R = 4 * buf + t;
+                using Set = integral_constant<int, R>;
+                using Next = integral_constant<int, t < 3 ? R + 1 : 4 * other>;
+                constexpr bool LOADS = !LAST && TWO && t == 0;
+                if constexpr (LOADS) load_line(l + 1, Other{}, 0);
+                expand_phase(Set{}, 1, fr[1]);
+                mfmas(fr[0]);
+                sched_phase<NM, VPER, LOADS ? NM : 0>();
+                if constexpr (LOADS) load_line(l + 1, Other{}, 1);
+                expand_phase(Set{}, 2, fr[0]);
+                mfmas(fr[1]);
+                sched_phase<NM, VPER, LOADS ? NM : 0>();
+                if constexpr (LOADS && NT > 2) load_line(l + 1, Other{}, NT - 1);
+                expand_phase(Set{}, 3, fr[1]);
+                mfmas(fr[0]);
+                sched_phase<NM, VPER, (LOADS && (NT > 2)) ? NM : 0>();
+                if constexpr (!LAST && !TWO && t == 3) {  // the codes have all been expanded
+#pragma unroll
+                    for (int q = 0; q < NT; ++q) load_line(l + 1, Other{}, q);
+                    mfmas(fr[1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    prep_scales(Next{}, true);
+                    expand_phase(Next{}, 0, fr[0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                } else {
+                    if constexpr (!LAST || t < 3) {
+                        prep_scales(Next{}, true);
+                        expand_phase(Next{}, 0, fr[0]);
+                    }
+                    mfmas(fr[1]);
+                    sched_phase<NM, VPER + 2>();
+                }
+            });
+        };
+        using Zero = integral_constant<int, 0>;
+        using One = integral_constant<int, TWO ? 1 : 0>;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) load_line(0, Zero{}, q);
+        __builtin_amdgcn_sched_barrier(0);
+        prep_scales(Zero{}, true);
+        expand_phase(Zero{}, 0, fr[0]);
+        int l = 0;
+        for (; l + 2 < len; l += 2) {
+            line(l, Zero{}, std::false_type{});
+            line(l + 1, One{}, std::false_type{});
+        }
+        if (l + 1 < len) {
+            line(l, Zero{}, std::false_type{});
+            line(l + 1, One{}, std::true_type{});
+        } else {
+            line(l, Zero{}, std::true_type{});
+        }
+    }
 
     if (g.ksplit > 1) {
         GemmArgs part = g;  // the slab's [M, N] FP32 matrix of partial sums; splitk_reduce_kernel scales and rounds
@@ -1374,15 +1465,27 @@ int launch_slab_sum(const GemmArgs &g, hipStream_t s)
     return enqueue(splitk_reduce_kernel<OUT_BF16>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, g);
 }
 
+// Row-major operands are read in whole lines (LINE) where a line is four K steps of one row and each of eight waves has one: at
+// K = 1024 and 1536 half or a quarter of the waves would be idle.  Tiles of six operand rows have no registers for a line.
+static bool fp4_lines(int layout, int64_t K) { return layout == MQ_LAYOUT_LINEAR && K % (4 * BK) == 0 && K >= 32 * BK; }
+template <int TM, int TN, int S>
+constexpr bool has_lines()
+{
+    return TM + TN <= 4 && S > 1;
+}
+
 // One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
-template <int TM, int TN, int S, int NSETS, bool OUT_BF16>
+template <int TM, int TN, int S, int NSETS, bool OUT_BF16, bool LINE = false>
 int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
 {
+    if constexpr (!LINE && has_lines<TM, TN, S>())
+        if (fp4_lines(g0.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR, g0.K))
+            return launch_small<TM, TN, S, 4, OUT_BF16, true>(g0, s, slabs);
     GemmArgs g = g0;
     g.ksplit = slabs;
     const int64_t tiles_m = (g.M + 32 * TM - 1) / (32 * TM), tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
     if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    const int rc = enqueue(gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16>, dim3((unsigned)(tiles_m * tiles_n * g.ksplit)),
+    const int rc = enqueue(gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16, LINE>, dim3((unsigned)(tiles_m * tiles_n * g.ksplit)),
                            dim3(64 * S), small_lds<TM, TN, S>(), s, g, (int)tiles_m, (int)tiles_n);
     return rc != MQ_OK || g.ksplit == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
@@ -1567,8 +1670,9 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
 // ---- which NVFP4 kernel and tile --------------------------------------------------------------------
 
 // The workgroup tiles (tokens x rows of W) of the NVFP4 kernels, gemm_fp4_direct with K whole, split over two or
-// over four waves, and gemm_fp4_small, and their costs (TileCost) in either byte order.  The row-major one costs
-// about twice the step (a load touches a line per row instead of whole lines), most where the tiles are small.
+// over four waves, and gemm_fp4_small, and their costs (TileCost) in either byte order.  The row-major one costs about twice
+// the step (a load touches a line per row instead of whole lines), most where the tiles are small, but for the tiles that
+// read it in lines.
 struct Fp4Tile {
     mq_kernel kernel;
     int bm, bn, waves;
@@ -1583,7 +1687,8 @@ static constexpr Fp4Tile kFp4Tiles[] = {
 #undef MQ_X
 };
 constexpr int kFp4Directs = 3, kFp4TileCount = (int)(sizeof(kFp4Tiles) / sizeof(kFp4Tiles[0]));
-static constexpr TileCost kFp4Costs[2][kFp4TileCount] = {
+enum { ROW_MAJOR, K_STEP_MAJOR, ROW_MAJOR_LINES };  // rows of kFp4Costs
+static constexpr TileCost kFp4Costs[3][kFp4TileCount] = {
     {{6271.7, 6184.9, 1209.8, 886.09, 17.221}, {3469.8, 7200.5, 713.71, 346.48, 107.32},
      {6440.7, 4307, 376.79, 172.48, 107.44},
      {4239.8, 2522.9, 115.35, 20.165, 27.543}, {4933.4, 1970.5, 213.73, 28.547, 158.6},
@@ -1598,9 +1703,17 @@ static constexpr TileCost kFp4Costs[2][kFp4TileCount] = {
      {3776.4, 4046.2, 85.976, 11.681, 40.941}, {5723.5, 1305.4, 106.28, 0, 142.13},
      {2750.6, 5815.8, 118.51, 43.59, 175.04}, {6678.2, 1478.8, 126.74, 47.794, 133.13},
      {3251.3, 5072.4, 119.84, 88.484, 25.163}, {6802.3, 1402.1, 109.41, 83.132, 94.333},
-     {6680.1, 481.62, 141.96, 0, 10}}};
+     {6680.1, 481.62, 141.96, 0, 10}},
+    {{6271.7, 6184.9, 1209.8, 886.09, 17.221}, {3469.8, 7200.5, 713.71, 346.48, 107.32},
+     {6440.7, 4307, 376.79, 172.48, 107.44},
+     {4565, 100, 79.548, 5.9507, 18.338}, {4544.5, 1285.5, 106.98, 10.254, 210.88},
+     {3670.7, 1464.6, 105.09, 2.7519, 568.11}, {6222.6, 100, 109.07, 0, 10},
+     {5675.1, 292.8, 81.694, 19.625, 135.81}, {4527.3, 2156.6, 159.02, 0, 96.95},
+     {7216.7, 634.16, 136.7, 9.1363, 67.916},
+     {7478.9, 719.42, 302.3, 186.41, 261.14}, {4944.2, 3294, 386.65, 44.621, 116.6},
+     {7500.5, 2876.1, 181.1, 338.58, 107.4}, {6575.9, 100, 394.94, 6.7359, 330.19}, {6876.3, 100, 346.69, 0, 10}}};
 // us: the second pass of K slabs, and what two launches overlap by
-static constexpr double kSecondPass[2] = {4.02, 3.20}, kOverlap[2] = {1.00, 3.64};
+static constexpr double kSecondPass[3] = {4.02, 3.20, 4.02}, kOverlap[3] = {1.00, 3.64, 1.00};
 
 struct Fp4Plan {
     int tile;                  // index into kFp4Tiles
@@ -1611,9 +1724,10 @@ struct Fp4Plan {
 
 // The plan that costs least (launch_us; the weights' 0.5625 bytes per element at 5.3 TB/s, a fifth of the shorter one of
 // trip and K steps does not hide).  The costs are fitted to every tile's time, and to pairs of them, on 3200 shapes
-// (K-step-major; row-major 1800) of 16 to 16384 tokens: the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter,
-// narrower and wider ones.  The plan is on average 0.7 % (row-major 1.1 %) slower than the fastest one measured, 95 % of
-// the shapes within 4 % (7 %).  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
+// (K-step-major; row-major 1800, by lines 1900) of 16 to 16384 tokens: the 8B and 32B layers, their 2-, 4- and 8-way shards
+// and shorter, narrower and wider ones.  The plan is on average 1.7 % (row-major 1.5 %, by lines 0.8 %) slower than the fastest
+// one measured.  By lines, on 569 shapes other than those of the fit, against row-major tiles in K order: 0.65 of the time up to
+// 64 tokens, 0.73 up to 256, 0.86 up to 1024, 0.94 up to 3000.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
 // instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 7.0 us in
 // 32x32 tiles and 11.6 in 64x64; 512 tokens on N = 28672 92 us in 256x256 and 104 in 64x128.
@@ -1623,7 +1737,9 @@ struct Fp4Plan {
 // rows in 256x128 tiles and 77 in 128x128, 83 us against 86 in 64x128 tiles and 96 in 256x256, which hold 333 rows of 512).
 static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t slab_limit, int cus)
 {
-    const int order = layout == MQ_LAYOUT_KTILE || K == BK;  // (the same bytes when K == 64)
+    const int order = layout == MQ_LAYOUT_KTILE || K == BK ? K_STEP_MAJOR  // (the same bytes when K == 64)
+                      : fp4_lines(layout, K)               ? ROW_MAJOR_LINES
+                                                           : ROW_MAJOR;
     auto tiles_of = [](const Fp4Tile &t, int64_t m, int64_t n) { return ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn); };
     auto cost = [&](int i, int64_t m, int64_t n, int64_t slabs) {
         const int64_t tiles = tiles_of(kFp4Tiles[i], m, n);
@@ -1750,7 +1866,9 @@ int configure_gemm_kernels()
     both(gemm_fp4_direct<true, 2>, gemm_fp4_direct<false, 2>, X);
     both(gemm_fp4_direct<true, 4>, gemm_fp4_direct<false, 4>, X);
 #define MQ_X(TM, TN, S, NSETS) \
-    both(gemm_fp4_small<TM, TN, S, NSETS, true>, gemm_fp4_small<TM, TN, S, NSETS, false>, small_lds<TM, TN, S>());
+    both(gemm_fp4_small<TM, TN, S, NSETS, true, false>, gemm_fp4_small<TM, TN, S, NSETS, false, false>, small_lds<TM, TN, S>()); \
+    if constexpr (has_lines<TM, TN, S>()) \
+        both(gemm_fp4_small<TM, TN, S, 4, true, true>, gemm_fp4_small<TM, TN, S, 4, false, true>, small_lds<TM, TN, S>());
     MQ_SMALL(MQ_X)
 #undef MQ_X
     both(gemm_bf16_d2l<Mid, true>, gemm_bf16_d2l<Mid, false>, Mid::LDS_BYTES);
