@@ -488,10 +488,10 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
 // splitk_reduce_kernel adds the slabs in ascending order.
 // What bounds it: the expansion (16 vector instructions per MFMA for 32x32, 8 for 64x64, 6 for 128x64; at two
 // waves per SIMD 8 take 40 to 44 cycles and 6 take 34 to 37 per MFMA, of 32); but a 32x32 tile gives every compute unit work where a
-// 64x64 tile leaves three quarters of them idle (64 tokens, K = N = 4096: 7.0 us against 11.6; K =
-// 14336: 15.6 against 18.7 with K slabs), and 64x128 tiles, two workgroups of four waves to a compute unit,
+// 64x64 tile leaves three quarters of them idle (64 tokens, K = N = 4096, weights from HBM: 8.0 us against 12.3; K =
+// 14336: 15.6 against 17.3 with K slabs), and 64x128 tiles, two workgroups of four waves to a compute unit,
 // hide each other's sums and stores, which the one-workgroup kernel above cannot (576 tokens on N =
-// 28672: 116 us against 170 in 256x256 tiles; 110 with 512 of them in those).  Two waves per SIMD throughout (at most 256 registers).
+// 28672: 108 us against 165 in 256x256 tiles; 105 with 512 of them in those).  Two waves per SIMD throughout (at most 256 registers).
 template <int TM_, int TN_>
 struct SmallCfg {
     static constexpr int TM = TM_, TN = TN_, WN = 32 * TN_;
@@ -1729,12 +1729,12 @@ struct Fp4Plan {
 // one measured.  By lines, on 569 shapes other than those of the fit, against row-major tiles in K order: 0.65 of the time up to
 // 64 tokens, 0.73 up to 256, 0.86 up to 1024, 0.94 up to 3000.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
-// instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 7.0 us in
-// 32x32 tiles and 11.6 in 64x64; 512 tokens on N = 28672 92 us in 256x256 and 104 in 64x128.
+// instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 8.0 us in
+// 32x32 tiles and 12.3 in 64x64; 512 tokens on N = 28672 88 us in 256x256 and 96 in 64x128.
 // Two launches where the large tiles leave a ragged last round: whole rounds of one of the direct
 // tiles on the first rows or columns of Y, the others in whatever tile suits them (5003 tokens on
 // K = 14336, N = 4096: one round of 256x256 tiles on 4096 rows and 907 rows in 128x128 tiles; 333 tokens on N = 28672: 256
-// rows in 256x128 tiles and 77 in 128x128, 83 us against 86 in 64x128 tiles and 96 in 256x256, which hold 333 rows of 512).
+// rows in 256x128 tiles and 77 in 128x128, 78 us against 79 in 64x128 tiles and 90 in 256x256, which hold 333 rows of 512).
 static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t slab_limit, int cus)
 {
     const int order = layout == MQ_LAYOUT_KTILE || K == BK ? K_STEP_MAJOR  // (the same bytes when K == 64)
