@@ -17,6 +17,7 @@
 #include <ATen/ops/empty.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
@@ -220,7 +221,11 @@ PyObject *entry(Py_ssize_t n, Py_ssize_t want, F &&body)
         return body();
     } catch (const General &) {
         Py_RETURN_NONE;
+    } catch (python_error &e) {  // raised by Python code that an allocation went through (a dispatch mode): the call's answer
+        e.restore();
+        return nullptr;
     } catch (const std::exception &) {  // nothing has been enqueued: the general path meets the same and reports it
+        if (PyErr_Occurred()) return nullptr;
         Py_RETURN_NONE;
     }
 }

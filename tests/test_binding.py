@@ -2,6 +2,7 @@
 which accepts or refuses it; what is of the plain form gives the same tensors."""
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_2605_20315_amd as mq
 from paper_2605_20315_amd import _lib, ops
@@ -114,3 +115,28 @@ def test_current_stream_is_used():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+class _Refused(Exception):
+    pass
+
+
+class _NoAllocation(TorchDispatchMode):
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        if func is torch.ops.aten.empty.memory_format:
+            raise _Refused("no allocation here")
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.gpu
+def test_an_error_raised_by_a_dispatch_mode_reaches_the_caller():
+    x, w = _x(8, 128), _x(16, 128)
+    a = mq.nvfp4_global_scale(x)
+    c, s = mq.nvfp4_quantize(x, a)
+    for call in (lambda: mq.nvfp4_global_scale(x), lambda: mq.nvfp4_quantize(x, a), lambda: mq.bf16_gemm_ws(x, w, None),
+                 lambda: mq.nvfp4_linear(x, a, c, s, a), lambda: mq.nvfp4_relayout(c, s, 0, 1)):
+        with _NoAllocation(), pytest.raises(_Refused, match="no allocation here"):
+            call()
+    y = torch.empty(8, 16, dtype=torch.bfloat16, device="cuda")
+    with _NoAllocation():  # nothing to allocate
+        assert mq.bf16_gemm_ws(x, w, None, mq.MQ_OUT_BF16, y) is y
