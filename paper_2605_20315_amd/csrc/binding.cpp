@@ -35,45 +35,52 @@ decltype(&::nvfp4_gemm_ws) p_gemm_ws;
 decltype(&::bf16_gemm_ws) p_bf16_gemm_ws;
 PyObject *g_check;
 
-// The call is not of the plain form.
-struct General {};
+// "Not of the plain form" is a return value (false, a null pointer, None) and no C++ exception: one of those takes 3.7 us, as
+// much as the general path's own marshalling.
+PyObject *general() { Py_RETURN_NONE; }
 
 void *current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-const at::Tensor &tensor(PyObject *o)
+const at::Tensor *tensor(PyObject *o)
 {
-    if (!THPVariable_CheckExact(o)) throw General{};
+    if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
-    if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || !t.has_storage() ||
-        t.unsafeGetTensorImpl()->is_python_dispatch())
-        throw General{};
-    return t;
+    const bool plain = t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.has_storage() &&
+                       !t.unsafeGetTensorImpl()->is_python_dispatch();
+    return plain ? &t : nullptr;
 }
 
-const at::Tensor &typed(PyObject *o, at::ScalarType type)
+const at::Tensor *typed(PyObject *o, at::ScalarType type)
 {
-    const at::Tensor &t = tensor(o);
-    if (t.scalar_type() != type) throw General{};
-    return t;
+    const at::Tensor *t = tensor(o);
+    return t && t->scalar_type() == type ? t : nullptr;
 }
 
-int64_t integer(PyObject *o)
+bool integer(PyObject *o, int &value)  // (an int, or one of its subclasses such as an IntEnum member)
 {
-    if (!PyLong_CheckExact(o)) throw General{};
+    if (!PyLong_Check(o)) return false;
     int overflow = 0;
     const long long v = PyLong_AsLongLongAndOverflow(o, &overflow);
-    if (overflow || v < INT32_MIN || v > INT32_MAX) throw General{};
-    return v;
+    value = (int)v;
+    return !overflow && v >= INT32_MIN && v <= INT32_MAX;
+}
+
+bool real(PyObject *o, float &value)
+{
+    int i;
+    if (PyFloat_CheckExact(o)) return value = (float)PyFloat_AS_DOUBLE(o), true;
+    return integer(o, i) ? (value = (float)i, true) : false;
 }
 
 // rows, columns and row stride of a 2-D tensor whose last dimension is contiguous
 struct Rows {
     int64_t rows, K, ld;
-    explicit Rows(const at::Tensor &t)
+    bool read(const at::Tensor &t)
     {
-        if (t.dim() != 2 || t.stride(1) != 1) throw General{};
+        if (t.dim() != 2 || t.stride(1) != 1) return false;
         rows = t.size(0), K = t.size(1);
         ld = rows > 1 ? t.stride(0) : std::max(t.stride(0), K);
+        return true;
     }
 };
 
@@ -90,19 +97,17 @@ PyObject *new_ref(PyObject *o)
 
 // an output that the caller may have passed: kept as the same Python object
 struct Out {
-    PyObject *obj;
+    PyObject *obj = nullptr;
     at::Tensor made;
-    const at::Tensor *t;
-};
-Out bytes_out(PyObject *o)
-{
-    if (o != Py_None) {
-        const at::Tensor &t = tensor(o);
-        if (!t.is_contiguous()) throw General{};
-        return Out{o, {}, &t};
+    const at::Tensor *t = nullptr;
+    bool read(PyObject *o)
+    {
+        if (o == Py_None) return true;
+        obj = o;
+        return (t = tensor(o));
     }
-    return Out{nullptr, {}, nullptr};
-}
+    bool read_bytes(PyObject *o) { return read(o) && (!obj || t->is_contiguous()); }
+};
 void allocate(Out &o, int64_t rows, int64_t cols, at::ScalarType type, const at::Tensor &like)
 {
     if (o.obj) return;
@@ -117,29 +122,21 @@ struct Product {
     int64_t ldy, ws_bytes = 0;
     void *ws = nullptr;
     int out;
-    Product(PyObject *workspace, PyObject *out_o, PyObject *y_o, int64_t M, int64_t N)
+    bool read(PyObject *workspace, PyObject *out_o, PyObject *y_o)
     {
-        out = (int)integer(out_o);
-        if (y_o != Py_None) {
-            const at::Tensor &t = tensor(y_o);
-            if (t.dim() != 2) throw General{};
-            y = Out{y_o, {}, &t};
-            ldy = M > 1 ? t.stride(0) : std::max(t.stride(0), N);
-        } else {
-            y = Out{nullptr, {}, nullptr};
-            ldy = N;  // until allocate_y
-        }
-        if (workspace != Py_None) {
-            const at::Tensor &t = tensor(workspace);
-            if (!t.is_contiguous()) throw General{};
-            ws = t.data_ptr();
-            ws_bytes = t.numel() * t.element_size();
-        }
+        if (!integer(out_o, out) || !y.read(y_o)) return false;
+        if (y.obj && y.t->dim() != 2 && y.t->dim() != 1) return false;  // (one row may come as a vector)
+        if (workspace == Py_None) return true;
+        const at::Tensor *t = tensor(workspace);
+        if (!t || !t->is_contiguous()) return false;
+        ws = t->data_ptr();
+        ws_bytes = t->numel() * t->element_size();
+        return true;
     }
     void allocate_y(int64_t M, int64_t N, const at::Tensor &like)
     {
         allocate(y, M, N, out == MQ_OUT_BF16 ? at::kBFloat16 : at::kFloat, like);
-        if (!y.obj) ldy = M > 1 ? y.t->stride(0) : std::max(y.t->stride(0), N);
+        ldy = M > 1 ? y.t->stride(0) : std::max(y.t->stride(0), N);
     }
 };
 
@@ -157,33 +154,26 @@ bool enqueue(const char *what, F &&call)
     return false;
 }
 
-struct QuantIn {
-    const at::Tensor &x, &alpha;
+struct Quant {
+    const at::Tensor *x, *alpha;
     Rows r;
-    QuantIn(PyObject *xo, PyObject *ao) : x(typed(xo, at::kBFloat16)), alpha(typed(ao, at::kFloat)), r(x) {}
-};
-
-struct Quant : QuantIn {
     Out codes, scales;
     int layout;
     int64_t K;
-    Quant(PyObject *xo, PyObject *ao, PyObject *codes_o, PyObject *scales_o, PyObject *layout_o, int per = 1)
-        : QuantIn(xo, ao)
+    bool read(PyObject *xo, PyObject *ao, PyObject *codes_o, PyObject *scales_o, PyObject *layout_o, int per = 1)
     {
+        if (!(x = typed(xo, at::kBFloat16)) || !(alpha = typed(ao, at::kFloat)) || !r.read(*x)) return false;
         K = r.K / per;
-        if (r.K % (per * 16)) throw General{};
-        layout = (int)integer(layout_o);
-        codes = bytes_out(codes_o);
-        scales = bytes_out(scales_o);
+        return r.K % (per * 16) == 0 && integer(layout_o, layout) && codes.read_bytes(codes_o) && scales.read_bytes(scales_o);
     }
     void allocate_outputs()
     {
-        allocate(codes, r.rows, K / 2, at::kByte, x);
-        allocate(scales, r.rows, K / 16, at::kByte, x);
+        allocate(codes, r.rows, K / 2, at::kByte, *x);
+        allocate(scales, r.rows, K / 16, at::kByte, *x);
     }
     uint8_t *codes_ptr() const { return static_cast<uint8_t *>(codes.t->data_ptr()); }
     uint8_t *scales_ptr() const { return static_cast<uint8_t *>(scales.t->data_ptr()); }
-    const float *alpha_ptr() const { return static_cast<const float *>(alpha.data_ptr()); }
+    const float *alpha_ptr() const { return static_cast<const float *>(alpha->data_ptr()); }
     PyObject *result() const
     {
         PyObject *c = give(codes), *s = c ? give(scales) : nullptr;
@@ -196,16 +186,17 @@ struct Quant : QuantIn {
 
 // weights (or activations) of the block-scaled product: codes [rows, K/2], scales [rows, K/16]
 struct Packed {
-    const at::Tensor &c, &s;
+    const at::Tensor *c, *s;
     int64_t rows, K;
-    Packed(PyObject *co, PyObject *so) : c(typed(co, at::kByte)), s(typed(so, at::kByte))
+    bool read(PyObject *co, PyObject *so)
     {
-        if (c.dim() != 2 || s.dim() != 2 || !c.is_contiguous() || !s.is_contiguous()) throw General{};
-        rows = c.size(0), K = c.size(1) * 2;
-        if (s.size(0) != rows || s.size(1) != K / 16) throw General{};
+        if (!(c = typed(co, at::kByte)) || !(s = typed(so, at::kByte))) return false;
+        if (c->dim() != 2 || s->dim() != 2 || !c->is_contiguous() || !s->is_contiguous()) return false;
+        rows = c->size(0), K = c->size(1) * 2;
+        return s->size(0) == rows && s->size(1) == K / 16;
     }
-    const uint8_t *codes() const { return static_cast<const uint8_t *>(c.data_ptr()); }
-    const uint8_t *scales() const { return static_cast<const uint8_t *>(s.data_ptr()); }
+    const uint8_t *codes() const { return static_cast<const uint8_t *>(c->data_ptr()); }
+    const uint8_t *scales() const { return static_cast<const uint8_t *>(s->data_ptr()); }
 };
 
 // Entry points take positional arguments only (the keyword forms are those of ops.py) and end here.
@@ -216,30 +207,30 @@ PyObject *entry(Py_ssize_t n, Py_ssize_t want, F &&body)
         PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", want, n);
         return nullptr;
     }
-    if (!g_check || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
+    if (!g_check || at::impl::torch_function_mode_enabled()) return general();
     try {
         return body();
-    } catch (const General &) {
-        Py_RETURN_NONE;
     } catch (python_error &e) {  // raised by Python code that an allocation went through (a dispatch mode): the call's answer
         e.restore();
         return nullptr;
     } catch (const std::exception &) {  // nothing has been enqueued: the general path meets the same and reports it
-        if (PyErr_Occurred()) return nullptr;
-        Py_RETURN_NONE;
+        return PyErr_Occurred() ? nullptr : general();
     }
 }
 
 PyObject *global_scale(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 2, [&]() -> PyObject * {
-        const at::Tensor &x = typed(a[0], at::kBFloat16);
-        const Rows r(x);
-        Out alpha = a[1] == Py_None ? Out{nullptr, at::empty({1}, at::TensorOptions().dtype(at::kFloat).device(x.device())), nullptr}
-                                    : Out{a[1], {}, nullptr};
-        alpha.t = alpha.obj ? &tensor(alpha.obj) : &alpha.made;
+        const at::Tensor *x = typed(a[0], at::kBFloat16);
+        Rows r;
+        Out alpha;
+        if (!x || !r.read(*x) || !alpha.read(a[1])) return general();
+        if (!alpha.obj) {
+            alpha.made = at::empty({1}, at::TensorOptions().dtype(at::kFloat).device(x->device()));
+            alpha.t = &alpha.made;
+        }
         void *const st = current_stream();
-        const void *xp = x.data_ptr();
+        const void *xp = x->data_ptr();
         float *ap = static_cast<float *>(alpha.t->data_ptr());
         if (!enqueue("nvfp4_global_scale", [&] { return p_global_scale(xp, r.rows, r.K, r.ld, ap, st); })) return nullptr;
         return give(alpha);
@@ -249,10 +240,11 @@ PyObject *global_scale(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 5, [&]() -> PyObject * {
-        Quant q(a[0], a[1], a[2], a[3], a[4]);
+        Quant q;
+        if (!q.read(a[0], a[1], a[2], a[3], a[4])) return general();
         q.allocate_outputs();
         void *const st = current_stream();
-        const void *xp = q.x.data_ptr();
+        const void *xp = q.x->data_ptr();
         const float *ap = q.alpha_ptr();
         uint8_t *cp = q.codes_ptr(), *sp = q.scales_ptr();
         if (!enqueue("nvfp4_quantize", [&] { return p_quantize(xp, q.r.rows, q.K, q.r.ld, ap, cp, sp, q.layout, st); }))
@@ -264,10 +256,11 @@ PyObject *quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *quantize_silu_mul(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 5, [&]() -> PyObject * {
-        Quant q(a[0], a[1], a[2], a[3], a[4], 2);
+        Quant q;
+        if (!q.read(a[0], a[1], a[2], a[3], a[4], 2)) return general();
         q.allocate_outputs();
         void *const st = current_stream();
-        const void *xp = q.x.data_ptr();
+        const void *xp = q.x->data_ptr();
         const float *ap = q.alpha_ptr();
         uint8_t *cp = q.codes_ptr(), *sp = q.scales_ptr();
         if (!enqueue("nvfp4_quantize_silu_mul", [&] {
@@ -281,13 +274,14 @@ PyObject *quantize_silu_mul(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *quantize_rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 7, [&]() -> PyObject * {
-        Quant q(a[0], a[3], a[4], a[5], a[6]);
-        const at::Tensor &w = typed(a[1], at::kBFloat16);
-        if (w.dim() != 1 || w.size(0) != q.K || !w.is_contiguous() || q.K % 64 || !PyFloat_CheckExact(a[2])) throw General{};
-        const float eps = (float)PyFloat_AS_DOUBLE(a[2]);
+        Quant q;
+        float eps;
+        const at::Tensor *w = typed(a[1], at::kBFloat16);
+        if (!w || !real(a[2], eps) || !q.read(a[0], a[3], a[4], a[5], a[6])) return general();
+        if (w->dim() != 1 || w->size(0) != q.K || !w->is_contiguous() || q.K % 64) return general();
         q.allocate_outputs();
         void *const st = current_stream();
-        const void *xp = q.x.data_ptr(), *wp = w.data_ptr();
+        const void *xp = q.x->data_ptr(), *wp = w->data_ptr();
         const float *ap = q.alpha_ptr();
         uint8_t *cp = q.codes_ptr(), *sp = q.scales_ptr();
         if (!enqueue("nvfp4_quantize_rmsnorm", [&] {
@@ -301,11 +295,12 @@ PyObject *quantize_rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *relayout(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 4, [&]() -> PyObject * {
-        const Packed p(a[0], a[1]);
-        const int from = (int)integer(a[2]), to = (int)integer(a[3]);
-        Out c{nullptr, {}, nullptr}, s{nullptr, {}, nullptr};
-        allocate(c, p.rows, p.K / 2, at::kByte, p.c);
-        allocate(s, p.rows, p.K / 16, at::kByte, p.s);
+        Packed p;
+        int from, to;
+        if (!p.read(a[0], a[1]) || !integer(a[2], from) || !integer(a[3], to)) return general();
+        Out c, s;
+        allocate(c, p.rows, p.K / 2, at::kByte, *p.c);
+        allocate(s, p.rows, p.K / 16, at::kByte, *p.s);
         void *const st = current_stream();
         const uint8_t *pc = p.codes(), *ps = p.scales();
         uint8_t *oc = static_cast<uint8_t *>(c.t->data_ptr()), *os = static_cast<uint8_t *>(s.t->data_ptr());
@@ -320,16 +315,17 @@ PyObject *relayout(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *gemm_ws(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 10, [&]() -> PyObject * {
-        const Packed pa(a[0], a[1]), pb(a[3], a[4]);
-        const at::Tensor &aa = tensor(a[2]), &ba = tensor(a[5]);
-        if (pa.K != pb.K) throw General{};
+        Packed pa, pb;
+        Product p;
+        int layout;
+        const at::Tensor *aa = tensor(a[2]), *ba = tensor(a[5]);
+        if (!aa || !ba || !pa.read(a[0], a[1]) || !pb.read(a[3], a[4]) || pa.K != pb.K) return general();
+        if (!p.read(a[6], a[7], a[8]) || !integer(a[9], layout)) return general();
         const int64_t M = pa.rows, N = pb.rows, K = pa.K;
-        Product p(a[6], a[7], a[8], M, N);
-        const int layout = (int)integer(a[9]);
-        p.allocate_y(M, N, pa.c);
+        p.allocate_y(M, N, *pa.c);
         void *const st = current_stream(), *const y = p.y.t->data_ptr();
         const uint8_t *ac = pa.codes(), *as = pa.scales(), *bc = pb.codes(), *bs = pb.scales();
-        const float *aap = static_cast<const float *>(aa.data_ptr()), *bap = static_cast<const float *>(ba.data_ptr());
+        const float *aap = static_cast<const float *>(aa->data_ptr()), *bap = static_cast<const float *>(ba->data_ptr());
         if (!enqueue("nvfp4_gemm_ws", [&] {
                 return p_gemm_ws(ac, as, aap, bc, bs, bap, M, N, K, y, p.ldy, p.out, layout, p.ws, p.ws_bytes, st);
             }))
@@ -343,21 +339,22 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 11, [&]() -> PyObject * {
         // x, alpha_x, w_codes, w_scales, alpha_w, out, y, codes, scales, layout, workspace
-        Quant q(a[0], a[1], a[7], a[8], a[9]);
-        const Packed pb(a[2], a[3]);
-        const at::Tensor &ba = tensor(a[4]);
+        Quant q;
+        Packed pb;
+        Product p;
+        const at::Tensor *ba = tensor(a[4]);
+        if (!ba || !q.read(a[0], a[1], a[7], a[8], a[9]) || !pb.read(a[2], a[3]) || !p.read(a[10], a[5], a[6])) return general();
         const int64_t M = q.r.rows, N = pb.rows, K = q.K;
-        if (pb.K != K) throw General{};
+        if (pb.K != K) return general();
         auto matches = [&](const Out &o, int64_t cols) {  // what the product asks of the quantizer's outputs
             return !o.obj || (o.t->scalar_type() == at::kByte && o.t->dim() == 2 && o.t->size(0) == M && o.t->size(1) == cols);
         };
-        if (!matches(q.codes, K / 2) || !matches(q.scales, K / 16)) throw General{};
-        Product p(a[10], a[5], a[6], M, N);
+        if (!matches(q.codes, K / 2) || !matches(q.scales, K / 16)) return general();
         q.allocate_outputs();
         p.allocate_y(M, N, *q.codes.t);
         void *const st = current_stream(), *const y = p.y.t->data_ptr();
-        const void *xp = q.x.data_ptr();
-        const float *ap = q.alpha_ptr(), *bap = static_cast<const float *>(ba.data_ptr());
+        const void *xp = q.x->data_ptr();
+        const float *ap = q.alpha_ptr(), *bap = static_cast<const float *>(ba->data_ptr());
         uint8_t *cp = q.codes_ptr(), *sp = q.scales_ptr();
         const uint8_t *bc = pb.codes(), *bs = pb.scales();
         const char *what = "nvfp4_quantize";
@@ -380,14 +377,14 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *bf16_gemm_ws(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 5, [&]() -> PyObject * {
-        const at::Tensor &x = typed(a[0], at::kBFloat16), &w = typed(a[1], at::kBFloat16);
-        const Rows rx(x), rw(w);
-        if (rx.K != rw.K) throw General{};
+        const at::Tensor *x = typed(a[0], at::kBFloat16), *w = typed(a[1], at::kBFloat16);
+        Rows rx, rw;
+        Product p;
+        if (!x || !w || !rx.read(*x) || !rw.read(*w) || rx.K != rw.K || !p.read(a[2], a[3], a[4])) return general();
         const int64_t M = rx.rows, N = rw.rows;
-        Product p(a[2], a[3], a[4], M, N);
-        p.allocate_y(M, N, x);
+        p.allocate_y(M, N, *x);
         void *const st = current_stream(), *const y = p.y.t->data_ptr();
-        const void *xp = x.data_ptr(), *wp = w.data_ptr();
+        const void *xp = x->data_ptr(), *wp = w->data_ptr();
         if (!enqueue("bf16_gemm_ws", [&] {
                 return p_bf16_gemm_ws(xp, rx.ld, wp, rw.ld, M, N, rx.K, y, p.ldy, p.out, p.ws, p.ws_bytes, st);
             }))
