@@ -31,12 +31,18 @@ def _stream() -> int:
 
 
 class _Unbound:
-    """Stands for the native module until the first call loads it."""
+    """Stands for the native module until the first call on GPU tensors loads it.  Anything else is refused by the
+    general path, with neither library loaded."""
 
     def __getattr__(self, name):
-        global _fast
-        _fast = _lib.load_binding()
-        return getattr(_fast, name)
+        def first(*args):
+            global _fast
+            tensors = [a for a in args if isinstance(a, torch.Tensor)]
+            if not tensors or not all(t.is_cuda for t in tensors):
+                return None
+            _fast = _lib.load_binding()
+            return getattr(_fast, name)(*args)
+        return first
 
 
 _fast = _Unbound()

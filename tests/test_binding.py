@@ -1,7 +1,9 @@
 """The native call forms of the binding against its general path: what is not of the plain form is left to the general path,
 which accepts or refuses it; what is of the plain form gives the same tensors."""
 import enum
+import sys
 import time
+import warnings
 
 import pytest
 import torch
@@ -199,3 +201,39 @@ def test_forms_that_the_general_path_accepts_are_taken(monkeypatch):
             got = _flat(call())
             assert native.calls == [(name, True)]
         assert len(got) == len(want) and all(torch.equal(g, v) for g, v in zip(got, want)), name
+
+
+def test_cpu_tensors_are_refused_with_no_library_loaded(monkeypatch):
+    x, f = torch.zeros(4, 64, dtype=torch.bfloat16), torch.zeros(1)
+    monkeypatch.setattr(ops, "_fast", ops._Unbound())
+    monkeypatch.setattr(_lib, "load", lambda: pytest.fail("a library was loaded"))
+    for call in (lambda: mq.nvfp4_global_scale(x), lambda: mq.nvfp4_quantize(x, f), lambda: mq.bf16_gemm_ws(x, x, None)):
+        with pytest.raises(mq.MixQuantError, match="GPU"):
+            call()
+
+
+@pytest.mark.parametrize("content", [None, b"no library"])
+def test_a_binding_that_is_missing_or_does_not_load_takes_no_call(monkeypatch, tmp_path, content):
+    path = tmp_path / "_binding.so"
+    if content:
+        path.write_bytes(content)
+        monkeypatch.setitem(sys.modules, "paper_2605_20315_amd._binding", None)  # its import raises ImportError
+        monkeypatch.delattr(mq, "_binding", raising=False)
+    monkeypatch.setattr(_lib, "BINDING_PATH", str(path))
+    with warnings.catch_warnings(record=True) as seen:
+        warnings.simplefilter("always")
+        fast = _lib.load_binding()
+    assert len(seen) == (content is not None)
+    x = torch.zeros(4, 64, dtype=torch.bfloat16)
+    assert fast.global_scale(x, None) is None and fast.bf16_gemm_ws(x, x, None, 0, None) is None
+
+
+@pytest.mark.gpu
+def test_calls_without_the_native_part_of_the_binding(monkeypatch, tmp_path):
+    x, w = _x(8, 128), _x(16, 128)
+    a = mq.nvfp4_global_scale(x)
+    want = _flat([mq.nvfp4_quantize(x, a), mq.bf16_gemm_ws(x, w, None)])
+    monkeypatch.setattr(ops, "_fast", ops._Unbound())
+    monkeypatch.setattr(_lib, "BINDING_PATH", str(tmp_path / "_binding.so"))
+    got = _flat([mq.nvfp4_quantize(x, a), mq.bf16_gemm_ws(x, w, None)])
+    assert isinstance(ops._fast, _lib._NoBinding) and all(torch.equal(g, v) for g, v in zip(got, want))
