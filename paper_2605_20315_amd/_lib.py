@@ -87,7 +87,7 @@ def load() -> ctypes.CDLL:
     return lib
 
 
-class _NoBinding:
+class NoBinding:
     """Stands for the native part of the binding where that is not built: takes no call."""
 
     def __getattr__(self, name):
@@ -99,14 +99,14 @@ def load_binding():
     time: where it has not been built, or not for this Python or torch, the general path of ops.py serves every call."""
     lib = load()
     if not os.path.exists(BINDING_PATH):
-        return _NoBinding()
+        return NoBinding()
     try:
         from . import _binding
     except ImportError as e:
         import warnings
         warnings.warn(f"{BINDING_PATH} does not load ({e}): calls take 3 to 7 us more host time until it is built again "
                       "with `python -m paper_2605_20315_amd.build`", RuntimeWarning)
-        return _NoBinding()
+        return NoBinding()
     names = ("nvfp4_global_scale", "nvfp4_quantize", "nvfp4_quantize_silu_mul", "nvfp4_quantize_rmsnorm",
              "nvfp4_relayout", "nvfp4_gemm_ws", "bf16_gemm_ws")
     _binding.bind(check, {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names})

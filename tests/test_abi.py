@@ -15,6 +15,8 @@ def lib():
     from paper_2605_20315_amd import _lib, build
     if not os.path.exists(_lib.LIB_PATH):
         build.build_library()
+    if not os.path.exists(_lib.BINDING_PATH):
+        build.build_binding()
     return _lib.load()
 
 
@@ -143,3 +145,19 @@ def test_binding_refuses_cpu_tensors():
     import paper_2605_20315_amd as mq
     with pytest.raises(mq.MixQuantError):
         mq.bf16_gemm(torch.zeros(4, 8, dtype=torch.bfloat16), torch.zeros(4, 8, dtype=torch.bfloat16))
+
+
+@pytest.mark.parametrize("flags", [[], ["-O"]])
+def test_build_compiles_every_part(lib, flags):
+    """Also where Python drops assertions.  (The compilers are not run: their stand-ins say that they were called.)"""
+    import subprocess
+    import sys
+    code = ("import __graft_entry__ as g, oracle\n"
+            "from paper_2605_20315_amd import build as b\n"
+            "b.build_library = lambda: print('library') or b.LIB\n"
+            "b.build_binding = lambda: print('binding') or b.BINDING\n"
+            "oracle.build = lambda force: print('oracle')\n"
+            "g.build()")
+    run = subprocess.run([sys.executable, *flags, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stderr
+    assert run.stdout.split() == ["library", "binding", "oracle"]

@@ -236,4 +236,4 @@ def test_calls_without_the_native_part_of_the_binding(monkeypatch, tmp_path):
     monkeypatch.setattr(ops, "_fast", ops._Unbound())
     monkeypatch.setattr(_lib, "BINDING_PATH", str(tmp_path / "_binding.so"))
     got = _flat([mq.nvfp4_quantize(x, a), mq.bf16_gemm_ws(x, w, None)])
-    assert isinstance(ops._fast, _lib._NoBinding) and all(torch.equal(g, v) for g, v in zip(got, want))
+    assert isinstance(ops._fast, _lib.NoBinding) and all(torch.equal(g, v) for g, v in zip(got, want))
