@@ -491,17 +491,19 @@ __device__ __forceinline__ float alpha_of(uint32_t amax_bits)  // from the large
 // tensor with four 16-byte loads in flight per thread: atomics on a single address serialise in
 // L2, and with 2048 workgroups they cost more than the read itself (measured on [8192, 4096]:
 // 30.7 us with 2048 atomics, 13.4 us for the same reads without any, 14.5 us with 256).
-// One workgroup writes alpha itself.  Several start from a word that amax_init_kernel has cleared.  COUNT: the word holds the
+// One workgroup (COUNT) writes alpha itself.  Several start from a word that amax_init_kernel has cleared.  COUNT: the word holds the
 // largest |x| as BF16 bits in its high half and the number of workgroups accounted for in the low half: a workgroup first
-// raises the maximum where its own is larger, which wipes the count it gets back, then adds itself and what it wiped.
+// raises the maximum to its own, which wipes the count it gets back where its own is larger, then adds itself and what it wiped.
 // No workgroup is counted before its maximum is in and none is lost, so the one that completes the count holds the
 // maximum of all of them and overwrites the word with alpha.  Without COUNT the word holds the BF16 bits, and
-// amax_final_kernel does that in a launch of its own (1.6 us on the GPU, 2.2 on the host).  us per call, counted / own
-// launch: 64 KB (one workgroup) 2.6 / 7.1, 256 KB (one) 4.0 / 7.3, 1 MB 5.7 / 7.3, 8 MB (128 workgroups) 8.4 / 8.8; 34 MB
-// (256 of them, whose atomics on the one word then take longer than the launch) 14.3 / 12.5, 143 MB 32.5 / 30.0.
+// amax_final_kernel does that in a launch of its own.  Counting is two trips to the word in a row behind the last load, and
+// they queue with those of the other workgroups; the launch is worth about a hundred of them.  us per call replayed from a
+// graph, counted / own launch: 64 KB (one workgroup) 2.5 / 5.5, 256 KB (one) 4.2 / 6.2, 1 MB 5.4 / 6.1, 4 MB 6.2 / 6.7, 6 MB
+// (96 workgroups) 7.3 / 7.4; 8 MB 8.1 / 7.8, 12 MB 10.2 / 9.2, 16 MB 12.1 / 10.3.  (A look at the word in front of the first trip,
+// which spares the workgroups with a smaller maximum that trip, took 0.4 us more at every size.)
 // CONTIG: ldx == K.
 constexpr int kAmaxThreads = 1024;
-constexpr int64_t kAmaxOne = 4, kAmaxCounted = 128;  // most workgroups of 64 KB served by one, and that count themselves
+constexpr int64_t kAmaxOne = 4, kAmaxCounted = 96;  // most workgroups of 64 KB served by one, and that count themselves
 
 template <bool CONTIG, bool COUNT>
 __global__ __launch_bounds__(kAmaxThreads) void amax_kernel(const uint16_t *__restrict__ x, int64_t total_chunks,
@@ -538,19 +540,16 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_kernel(const uint16_t *__re
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < kAmaxThreads / 64; ++w) m = wave_max[w] > m ? wave_max[w] : m;
-        if (gridDim.x == 1) {
-            *acc = __float_as_uint(alpha_of(m));
-            return;
-        }
         if constexpr (!COUNT) {
             if (m != 0) atomicMax(acc, m);
             return;
         }
-        uint32_t add = 1;
-        if (m > __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) {
-            const uint32_t old = __hip_atomic_fetch_max(acc, m << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (m > old >> 16) add += old & 0xFFFFu;
+        if (gridDim.x == 1) {
+            *acc = __float_as_uint(alpha_of(m));
+            return;
         }
+        const uint32_t old = __hip_atomic_fetch_max(acc, m << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t add = 1 + (m > old >> 16 ? old & 0xFFFFu : 0u);
         const uint32_t now = __hip_atomic_fetch_add(acc, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
         if ((now & 0xFFFFu) == gridDim.x)
             __hip_atomic_store(acc, __float_as_uint(alpha_of(now >> 16)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

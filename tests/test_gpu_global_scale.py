@@ -1,5 +1,5 @@
 """The tensor-level scale at the sizes where its launch changes: one workgroup of 64 KB shares up to four of them, workgroups
-that count themselves up to 128, a launch of its own for the last step beyond.  Exact: a maximum and one IEEE division."""
+that count themselves up to 96, a launch of its own for the last step beyond.  Exact: a maximum and one IEEE division."""
 import numpy as np
 import pytest
 import torch
@@ -12,8 +12,9 @@ from _gpu_util import dev_bf16
 pytestmark = pytest.mark.gpu
 
 SHARE = 32768  # elements a workgroup takes
-# (rows, K): 0, 1 and 16 elements, 4 shares and a row more, 128 shares and a row more, 256 and more
-SIZES = [(0, 64), (1, 16), (3, 48), (4 * SHARE // 64, 64), (4 * SHARE // 64 + 1, 64), (128 * SHARE // 4096, 4096),
+# (rows, K): 0, 1 and 16 elements, 4 shares and a row more, 96 shares and a row more, 128, 256 and more
+SIZES = [(0, 64), (1, 16), (3, 48), (4 * SHARE // 64, 64), (4 * SHARE // 64 + 1, 64), (96 * SHARE // 4096, 4096),
+         (96 * SHARE // 4096 + 1, 4096), (128 * SHARE // 4096, 4096),
          (128 * SHARE // 4096 + 1, 4096), (256 * SHARE // 4096 + 1, 4096), (977, 14336)]
 
 
