@@ -605,19 +605,19 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     uint4 rc[SETS][NT];                  // this lane's 32 codes of each operand tile, SETS K steps
     uint32_t rs[LINE ? 1 : SETS][NT];    // the rows' four E4M3 scale bytes of a K step
     uint2 rl[LINE ? SETS / 4 : 1][NT];   // or this lane's eight of a line
-    // Resources that start at the wave's first K step; the K step goes into the loads' scalar offset (32 bits: the
-    // launch rule keeps a wave's part of K below that), one multiplication each.  Loads past the wave's last step re-read
+    // Resources that start at the wave's first K step (or at a later one, where offsets from there would reach 2 GiB: below); the
+    // K step goes into the loads' scalar offset, one multiplication each.  Loads past the wave's last step re-read
     // that step (from L1; its products are multiplied by zero scales).  With running 64-bit pointers and a resource built
     // per load and K step there were 38 scalar instructions per K step instead of 9, and at two waves per SIMD a scalar
     // instruction per MFMA costs about two cycles of the forty.  With the last group below: 64 tokens, K = N = 4096 in 32x32
     // tiles 7.1 -> 6.4 us, 256 tokens in 64x64 12.7 -> 11.2, 128 tokens on K = 14336 in 64x32 21.6 -> 20.4.
     const int len = k1 - k0;
-    const int64_t first = k0 < KT ? k0 : KT - 1;
+    int64_t first = k0 < KT ? k0 : KT - 1;
     auto rsrc = [](const char *base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, -1, 0x00020000);
     };
-    const __amdgpu_buffer_rsrc_t rac = rsrc(ta_c + first * UNIT * g.a_c_step), rbc = rsrc(tb_c + first * UNIT * g.b_c_step);
-    const __amdgpu_buffer_rsrc_t ras = rsrc(ta_s + first * UNIT * g.a_s_step), rbs = rsrc(tb_s + first * UNIT * g.b_s_step);
+    __amdgpu_buffer_rsrc_t rac = rsrc(ta_c + first * UNIT * g.a_c_step), rbc = rsrc(tb_c + first * UNIT * g.b_c_step);
+    __amdgpu_buffer_rsrc_t ras = rsrc(ta_s + first * UNIT * g.a_s_step), rbs = rsrc(tb_s + first * UNIT * g.b_s_step);
     // Line l of this wave into register group `buf`: operand tile q, its four chunks one behind the other (apart, the lines have
     // left L1 by the next chunk) and its scales.
     auto load_line = [&](int l, auto bufc, int q) {
@@ -634,10 +634,9 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         rl[buf][q] = make_uint2(sc[0], sc[1]);
     };
     const uint32_t ca = (uint32_t)g.a_c_step, cb = (uint32_t)g.b_c_step, sa = (uint32_t)g.a_s_step, sb = (uint32_t)g.b_s_step;
-    auto load_step = [&](int t, auto setc) {  // K step t of this wave
+    auto load_step = [&](int t, auto setc) {  // K step t from `first`
         constexpr int R = decltype(setc)::value;
-        t = t < len - 1 ? t : len - 1;
-        const uint32_t u = (uint32_t)(t > 0 ? t : 0);
+        const uint32_t u = (uint32_t)t;
         const int oac = (int)(u * ca), obc = (int)(u * cb), oas = (int)(u * sa), obs = (int)(u * sb);
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
@@ -704,7 +703,8 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     static_assert(NSETS >= 2 && NSETS <= 4, "two to four K steps in flight");
     const float scale = (*g.a_alpha) * (*g.b_alpha);
     if constexpr (!LINE) {
-        // K step kt (of this wave); LAST: of its last group, behind which nothing is loaded
+        int end = len;  // of this wave's part, as kt counted from `first`
+        // K step kt; LAST: of the last group, behind which nothing is loaded
         auto kstep = [&](int kt, auto setc, auto lastc) {
             constexpr int R = decltype(setc)::value;
             constexpr bool LAST = decltype(lastc)::value;
@@ -719,10 +719,10 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
             mfmas(fr[0]);
             sched_phase<NM, VPER>();
             if constexpr (!LAST || R + 1 < NSETS) {
-                prep_scales(Next{}, kt + 1 < len);
+                prep_scales(Next{}, !LAST || kt + 1 < end);
                 expand_phase(Next{}, 0, fr[0]);
             }
-            if constexpr (!LAST) load_step(kt + NSETS, setc);
+            if constexpr (!LAST) load_step(kt + NSETS < end ? kt + NSETS : end - 1, setc);
             mfmas(fr[1]);
             sched_phase<NM, VPER + 2, LAST ? 0 : (2 * NT + NM - 1) / NM>();
         };
@@ -730,7 +730,7 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         // went last, and the counter the compiler waits on in the loop then demanded that nearly
         // everything in flight had landed before each K step: a prefetch distance of one step, not three.)
         for_sets([&](auto u) {
-            load_step(decltype(u)::value, u);
+            load_step(decltype(u)::value < len ? decltype(u)::value : len > 0 ? len - 1 : 0, u);
             __builtin_amdgcn_sched_barrier(0);
         });
         prep_scales(integral_constant<int, 0>{}, len > 0);
@@ -739,12 +739,25 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
         // loop in the middle of a group made the compiler move all accumulators at the joins: 1.2 to 1.6x slower.  Behind the
         // loop they are moved once.  When the last group was run whole, on zero scales, K = 512 took 5.0 us instead of 3.5, and
         // 100 tokens on K = 6400, N = 5120 17.0 instead of 14.0.)
+        // Where the loads of a group would reach further than 2 GiB (g.reach K steps), the resources move up to it: K-step-major
+        // operands of 19 GB and more in these tiles (16 tokens on K = 65536, N = 600000 3.7 ms; 7.8 in the direct tiles).
         int kt = 0;
-        for (; kt + NSETS < len; kt += NSETS) for_sets([&](auto u) { kstep(kt + decltype(u)::value, u, std::false_type{}); });
+        while (kt + NSETS < end) {
+            if (kt + 2 * NSETS - 1 > g.reach) {
+                first += kt + NSETS, end -= kt + NSETS, kt = -NSETS;
+                rac = rsrc(ta_c + first * g.a_c_step), rbc = rsrc(tb_c + first * g.b_c_step);
+                ras = rsrc(ta_s + first * g.a_s_step), rbs = rsrc(tb_s + first * g.b_s_step);
+            }
+            const int most = end - NSETS < g.reach - 2 * NSETS + 2 ? end - NSETS : g.reach - 2 * NSETS + 2;
+            do {
+                for_sets([&](auto u) { kstep(kt + decltype(u)::value, u, std::false_type{}); });
+                kt += NSETS;
+            } while (kt < most);
+        }
         auto tail = [&](auto self, auto u) -> void {
             kstep(kt + decltype(u)::value, u, std::true_type{});
             if constexpr (decltype(u)::value + 1 < NSETS)
-                if (kt + decltype(u)::value + 1 < len) self(self, integral_constant<int, decltype(u)::value + 1>{});
+                if (kt + decltype(u)::value + 1 < end) self(self, integral_constant<int, decltype(u)::value + 1>{});
         };
         tail(tail, integral_constant<int, 0>{});
     } else if (len > 0) {
@@ -1474,6 +1487,9 @@ constexpr bool has_lines()
     return TM + TN <= 4 && S > 1;
 }
 
+// K steps of `step` bytes that a scalar offset of less than 2 GiB spans.
+static int fp4_reach(int64_t step) { return (int)(0x7FFFFFFF / step); }
+
 // One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
 template <int TM, int TN, int S, int NSETS, bool OUT_BF16, bool LINE = false>
 int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
@@ -1483,6 +1499,7 @@ int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
             return launch_small<TM, TN, S, 4, OUT_BF16, true>(g0, s, slabs);
     GemmArgs g = g0;
     g.ksplit = slabs;
+    g.reach = fp4_reach(g.a_c_step > g.b_c_step ? g.a_c_step : g.b_c_step);
     const int64_t tiles_m = (g.M + 32 * TM - 1) / (32 * TM), tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
     if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF) return MQ_ERR_SHAPE;
     const int rc = enqueue(gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16, LINE>, dim3((unsigned)(tiles_m * tiles_n * g.ksplit)),
@@ -1747,9 +1764,9 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
         // (many rounds of one-wave tiles: 6144 tokens on K = 128, N = 2048 15.4 us against 13.4 in 256x256 tiles, 6342 on K = 64, N = 15304
         // 83 against 66)
         if (kFp4Tiles[i].waves == 1 && tiles > 8 * cus) return 1e300;
-        // the small tiles address a wave's part of K with 32 bits
-        const int64_t part = (K / BK + slabs * kFp4Tiles[i].waves - 1) / (slabs * kFp4Tiles[i].waves);
-        if (kFp4Tiles[i].kernel == MQ_KERNEL_FP4_SMALL && layout == MQ_LAYOUT_KTILE && (part - 1) * (M > N ? M : N) * 32 >= (1ll << 31))
+        // a wave of the small tiles loads up to four K steps of its part from one base (22 million rows, K-step-major)
+        const int64_t part = (K / BK + slabs * kFp4Tiles[i].waves - 1) / (slabs * kFp4Tiles[i].waves), span = part < 4 ? part - 1 : 3;
+        if (kFp4Tiles[i].kernel == MQ_KERNEL_FP4_SMALL && layout == MQ_LAYOUT_KTILE && fp4_reach((M > N ? M : N) * 32) < span)
             return 1e300;
         return launch_us(kFp4Costs[order][i], tiles * slabs, (double)(K / BK) / (double)slabs, 0.5625 * (double)n * (double)K / 5.3e6,
                          0.2, 2.0 * (double)m * (double)n, cus) +
