@@ -79,36 +79,54 @@ def _flat(r):
 
 
 def _calls(M, N, K, ld, out):
+    """(the native forms that a call goes through, the outputs given to it, the call)"""
     x, w = _x(M, K, 1, ld), _x(N, K, 2)
     ax, aw = mq.nvfp4_global_scale(x), mq.nvfp4_global_scale(w)
-    ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+    w0, ws = w[0].clone(), torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
     dtype = torch.float32 if out == mq.MQ_OUT_FP32 else torch.bfloat16
     for layout in (mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE):
         wc, wsc = mq.nvfp4_quantize(w, aw, layout=layout)
+        xc, xsc = mq.nvfp4_quantize(x, ax, layout=layout)
         for given in (False, True):
             y = torch.empty(M, N + 8, dtype=dtype, device="cuda")[:, :N] if given else None
             c = torch.empty(M, K // 2, dtype=torch.uint8, device="cuda") if given else None
             s = torch.empty(M, K // 16, dtype=torch.uint8, device="cuda") if given else None
-            yield lambda: mq.nvfp4_quantize(x, ax, c, s, layout)
-            yield lambda: mq.nvfp4_quantize_rmsnorm(x, w[0].clone(), 1e-6, ax, c, s, layout)
-            yield lambda: mq.nvfp4_linear(x, ax, wc, wsc, aw, out, y, c, s, layout, ws if given else None)
-            yield lambda: mq.nvfp4_gemm_ws(*mq.nvfp4_quantize(x, ax, layout=layout), ax, wc, wsc, aw, ws, out, y, layout)
-            yield lambda: mq.bf16_gemm_ws(x, w, ws if given else None, out, y)
-        yield lambda: mq.nvfp4_quantize_silu_mul(w, aw, layout=layout)
-        yield lambda: mq.nvfp4_relayout(wc, wsc, layout, 1 - layout)
-    yield lambda: mq.nvfp4_global_scale(x)
-    yield lambda: mq.nvfp4_global_scale(w, torch.empty(1, device="cuda"))
+            yield ["quantize"], [c, s], lambda: mq.nvfp4_quantize(x, ax, c, s, layout)
+            yield ["quantize_rmsnorm"], [c, s], lambda: mq.nvfp4_quantize_rmsnorm(x, w0, 1e-6, ax, c, s, layout)
+            yield ["linear"], [y, c, s, ws], lambda: (mq.nvfp4_linear(x, ax, wc, wsc, aw, out, y, c, s, layout, ws if given else None), c, s)
+            yield ["gemm_ws"], [y, ws], lambda: mq.nvfp4_gemm_ws(xc, xsc, ax, wc, wsc, aw, ws, out, y, layout)
+            yield ["bf16_gemm_ws"], [y, ws], lambda: mq.bf16_gemm_ws(x, w, ws if given else None, out, y)
+        yield ["quantize_silu_mul"], [], lambda: mq.nvfp4_quantize_silu_mul(w, aw, layout=layout)
+        yield ["relayout"], [], lambda: mq.nvfp4_relayout(wc, wsc, layout, 1 - layout)
+    yield ["global_scale"], [], lambda: mq.nvfp4_global_scale(x)
+    a = torch.empty(1, device="cuda")
+    yield ["global_scale"], [a], lambda: mq.nvfp4_global_scale(w, a)
+
+
+def _spoil(given, sizes):
+    """No right bytes are left in the given outputs, nor in the blocks that the allocator may hand out next."""
+    for t in given:
+        if t is not None:
+            t.fill_(0xA5 if t.dtype == torch.uint8 else float("nan"))
+    held = [torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda") for n in sizes for _ in range(4)]
+    del held
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,ld", [(1, 16, 128, None), (1, 64, 256, 512), (33, 72, 256, 264), (64, 512, 1024, None)])
 @pytest.mark.parametrize("out", [mq.MQ_OUT_BF16, mq.MQ_OUT_FP32])
 def test_native_and_general_path_give_the_same_tensors(monkeypatch, M, N, K, ld, out):
-    for i, call in enumerate(_calls(M, N, K, ld, out)):
-        with monkeypatch.context() as m:
-            m.setattr(ops, "_fast", _General())
-            want = [t.clone() for t in _flat(call())]
-        got = _flat(call())
+    sizes = [4] + [r * K // d for r in (M, N) for d in (2, 4, 16, 32)] + [M * N * 2, M * N * 4]
+    for i, (forms, given, call) in enumerate(_calls(M, N, K, ld, out)):
+        results = []
+        for path in (_General(), _Recorder()):
+            _spoil(given, sizes)
+            with monkeypatch.context() as m:
+                m.setattr(ops, "_fast", path)
+                made = [t for t in _flat(call()) if t is not None]
+            results.append((made, [t.clone() for t in made]))  # both stay alive: no block is handed out twice
+        assert path.calls == [(f, True) for f in forms], i     # (by the native form, and by nothing else)
+        (_, want), (_, got) = results
         assert len(got) == len(want), i
         for g, w in zip(got, want):
             assert g.dtype == w.dtype and g.shape == w.shape and torch.equal(g, w), i
@@ -135,7 +153,9 @@ def test_given_outputs_come_back_and_refusals_stay(monkeypatch):
 
 
 @pytest.mark.gpu
-def test_current_stream_is_used():
+def test_current_stream_is_used(monkeypatch):
+    native = _Recorder()
+    monkeypatch.setattr(ops, "_fast", native)
     x, w = _x(64, 1024), _x(256, 1024)
     want = mq.bf16_gemm_ws(x, w, None)
     side = torch.cuda.Stream()
@@ -145,7 +165,7 @@ def test_current_stream_is_used():
     mq.mq_init()
     with torch.cuda.graph(graph, stream=side):   # a launch on any other stream would not be captured
         mq.bf16_gemm_ws(x, w, None, mq.MQ_OUT_BF16, y)
-    assert not y.any()
+    assert native.calls == [("bf16_gemm_ws", True)] * 2 and not y.any()
     for _ in range(3):
         y.zero_()
         graph.replay()
