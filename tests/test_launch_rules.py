@@ -41,3 +41,12 @@ def test_bf16_tile(M, N, K, kernel, tile):
     (640, 4096, 512, [(64, 64)]), (640, 4096, 256, [(64, 64)]), (6144, 2048, 128, [(256, 256)]), (2048, 5120, 1280, [(256, 256)]), (64, 4096, 4096, [(32, 32)])])
 def test_fp4_tiles(M, N, K, tiles):
     assert [p["tile"] for p in mq.mq_gemm_launches(M, N, K, mq.MQ_LAYOUT_KTILE, 4 << 20)] == tiles
+
+
+# A wave of the small tiles reaches 2 GiB from one base and moves it up for more, four K steps at least: (M, N, K, small tiles)
+@pytest.mark.parametrize("M,N,K,small", [
+    (16, 1048576, 65536, True), (16, 600000, 65536, True), (2500000, 16, 28672, True), (600000, 64, 28672, True),
+    (16, (2**31 - 1) // 96, 4096, True), (16, (2**31 - 1) // 96 + 1, 4096, False), (16, 40000000, 4096, False)])
+def test_fp4_small_tiles_reach(M, N, K, small):
+    kernels = {p["kernel"] for p in mq.mq_gemm_launches(M, N, K, mq.MQ_LAYOUT_KTILE)}
+    assert kernels == ({"fp4_small"} if small else {"fp4_direct"})
