@@ -104,7 +104,7 @@ def load_binding():
         from . import _binding
     except ImportError as e:
         import warnings
-        warnings.warn(f"{BINDING_PATH} does not load ({e}): calls take 3 to 7 us more host time until it is built again "
+        warnings.warn(f"{BINDING_PATH} does not load ({e}): calls take 3 to 9 us more host time until it is built again "
                       "with `python -m paper_2605_20315_amd.build`", RuntimeWarning)
         return NoBinding()
     names = ("nvfp4_global_scale", "nvfp4_quantize", "nvfp4_quantize_silu_mul", "nvfp4_quantize_rmsnorm",

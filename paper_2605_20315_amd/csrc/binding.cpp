@@ -1,9 +1,9 @@
 // Marshalling of the common call forms in native code: torch tensors to the C ABI of include/mixquant.h.
 //
 // A small product is over in a few microseconds on the GPU, so what bounds such a call is the host.  Through ctypes
-// an nvfp4_linear call (64 tokens, K = N = 4096) took 12.8 us, of which the two launches were 4.8: the rest were attribute
-// look-ups on eight tensors, argument conversion and the search for a plan.  Here a tensor is unpacked in nanoseconds, and the
-// call takes 6.0 us; a small bf16_gemm_ws 3.5 us instead of 7.3.
+// an nvfp4_linear call takes 11.7 us with its outputs given and 16.7 with them allocated, of which the two launches are 4.4 to
+// 4.8: the rest are attribute look-ups on eight tensors and argument conversion.  Here a tensor is unpacked in nanoseconds, and the
+// call takes 5.2 and 7.6 us; a small bf16_gemm_ws 2.7 and 3.6 us instead of 6.3 and 7.9, of which its launch is 2.2.
 //
 // Every function returns None, before anything has been enqueued, for a call that is not of the plain form (another
 // type, shape or stride than the kernels take, a tensor subclass, a tensor that is not on the GPU, a
@@ -334,7 +334,9 @@ PyObject *gemm_ws(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// The quantizer and the product of one layer; every check of both stands in front of the first launch.
+// The quantizer and the product of one layer.  What the two native forms ask of their arguments is asked in front of the first
+// launch; what the library refuses by a status (an unknown `out`, a misaligned y or weight) it refuses call by call, so a
+// refused product comes behind an enqueued quantizer, as it does in the general path.
 PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return entry(n, 11, [&]() -> PyObject * {
