@@ -560,6 +560,12 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
 // the next one under way while this one is multiplied; 64x64 reloads the registers under the group's last K step.  us, in K order
 // and by lines: 64 tokens on K = N = 4096 in 32x32 tiles 11.6 and 8.9; 128 on K = 14336, N = 4096 in 64x32 51 and 32; 256 on
 // K = N = 4096 in 64x64 20.3 and 14.8; 512 28.9 and 24.9; 32 on K = 2048, N = 4096 6.5 and 5.7.
+template <int TM, int TN, int S>
+constexpr bool may_be_even()
+{
+    return TM == 2 && TN == 2 && S == 4;
+}
+
 template <int TM, int TN, int S, int NSETS, bool OUT_BF16, bool LINE>
 __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) void gemm_fp4_small(GemmArgs g, int tiles_m, int tiles_n)
 {
@@ -567,6 +573,7 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     constexpr int UNIT = LINE ? 4 : 1;                     // K steps of a unit
     constexpr bool TWO = LINE && NT <= 3;                  // two groups in registers
     constexpr int SETS = TWO ? 8 : NSETS;                  // K steps in registers
+    constexpr bool EVEN = LINE && may_be_even<TM, TN, S>();
     static_assert(!LINE || NSETS == 4, "a line is four K steps");
     static_assert((TM * TN) % 4 == 0 || TM * TN < 4, "the LDS reduction moves four 32x32 tiles per pass");
     const int tid = threadIdx.x, lane = tid & 63;
@@ -587,18 +594,25 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     const int k0 = s0 + wave * KH < s1 ? s0 + wave * KH : s1;
     const int k1 = k0 + KH < s1 ? k0 + KH : s1;
 
-    // operand q: A row tile q (q < TM), else B row tile q - TM.  Lane offsets relative to the tile.
-    const char *const ta_c = static_cast<const char *>(g.a) + m0 * g.a_c_row;
-    const char *const tb_c = static_cast<const char *>(g.b) + n0 * g.b_c_row;
-    const char *const ta_s = reinterpret_cast<const char *>(g.a_scales) + m0 * g.a_s_row;
-    const char *const tb_s = reinterpret_cast<const char *>(g.b_scales) + n0 * g.b_s_row;
+    // operand q: A row tile q (q < TM), else B row tile q - TM.  Lane offsets relative to the row a0 (b0) of the operand, the tile's
+    // first.  Lanes past the operand's last row read that row again: fewer lines, so a last tile of few rows is done early.
+    // g.even: they read the rows in front of the tile instead, so that it takes as long as the others (see fp4_even).
+    auto first_row = [&](int64_t tile0, int64_t rows, int size) {
+        return EVEN && g.even && rows > size && tile0 > rows - size ? rows - size : tile0;
+    };
+    const int64_t a0 = first_row(m0, g.M, 32 * TM), b0 = first_row(n0, g.N, 32 * TN);
+    const char *const ta_c = static_cast<const char *>(g.a) + a0 * g.a_c_row;
+    const char *const tb_c = static_cast<const char *>(g.b) + b0 * g.b_c_row;
+    const char *const ta_s = reinterpret_cast<const char *>(g.a_scales) + a0 * g.a_s_row;
+    const char *const tb_s = reinterpret_cast<const char *>(g.b_scales) + b0 * g.b_s_row;
     uint32_t vc[NT], vs[NT];
-    const int last_a = (int)(g.M - m0 < 32 * TM ? g.M - m0 : 32 * TM) - 1, last_b = (int)(g.N - n0 < 32 * TN ? g.N - n0 : 32 * TN) - 1;
+    const int last_a = (int)(g.M - a0 < 32 * TM ? g.M - a0 : 32 * TM) - 1, last_b = (int)(g.N - b0 < 32 * TN ? g.N - b0 : 32 * TN) - 1;
+    const int skip_a = (int)(m0 - a0), skip_b = (int)(n0 - b0);  // (0 unless g.even and the last tile; `last` is the tile's size - 1 then)
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
         const bool isA = q < TM;
-        const int row = (isA ? q : q - TM) * 32 + frow, last = isA ? last_a : last_b;
-        const uint32_t rel = (uint32_t)(row < last ? row : last);
+        const int row = (isA ? q : q - TM) * 32 + frow, last = isA ? last_a : last_b, skip = isA ? skip_a : skip_b;
+        const uint32_t rel = (uint32_t)(row + skip <= last ? row + skip : skip > 0 ? row : last);
         vc[q] = rel * (uint32_t)(isA ? g.a_c_row : g.b_c_row) + fhalf * (16 * UNIT);
         vs[q] = rel * (uint32_t)(isA ? g.a_s_row : g.b_s_row) + (LINE ? fhalf * 8 : 0);
     }
@@ -1490,18 +1504,31 @@ constexpr bool has_lines()
 // K steps of `step` bytes that a scalar offset of less than 2 GiB spans.
 static int fp4_reach(int64_t step) { return (int)(0x7FFFFFFF / step); }
 
+// By lines, 64x64 tiles of four waves stand two to a compute unit.  Where what is left behind the first 2 * cus tiles has a unit
+// each to itself, it has it only if those end together: where a last row of tiles with few rows ends early, pairs form on their
+// units while others stand empty.  449 to 479 tokens on K = 4096, N = 6144 (768 tiles, 256 units) took 47 to 43 us, 480 to 512 tokens
+// 35; 36 with even tiles; 966 on K = 4096, N = 3072 44 and 36.  The early end is worth more with fewer tiles (65 to 96 tokens on
+// N = 51200, 96 us, 105 even; 386 to 415 on N = 5120, 2.19 tiles to a unit, 39 and 41), with more (130 to 158 on N = 28672, 5.25, 65 and
+// 68), where the last row is a third of all (129 on N = 14336 33.7 and 36.8), and a long K gains nothing (459 on K = 12800,
+// N = 5120 88 and 92).
+static bool fp4_even(int64_t tiles_m, int64_t tiles, int64_t K, int cus)
+{
+    return tiles > 2 * cus + cus / 4 && tiles <= 3 * cus && tiles_m >= 7 && K <= 8192;
+}
+
 // One workgroup of S waves per (32 TM) x (32 TN) tile and K slab.
 template <int TM, int TN, int S, int NSETS, bool OUT_BF16, bool LINE = false>
-int launch_small(const GemmArgs &g0, hipStream_t s, int slabs)
+int launch_small(const GemmArgs &g0, hipStream_t s, int slabs, int cus)
 {
     if constexpr (!LINE && has_lines<TM, TN, S>())
         if (fp4_lines(g0.b_c_row == 32 ? MQ_LAYOUT_KTILE : MQ_LAYOUT_LINEAR, g0.K))
-            return launch_small<TM, TN, S, 4, OUT_BF16, true>(g0, s, slabs);
+            return launch_small<TM, TN, S, 4, OUT_BF16, true>(g0, s, slabs, cus);
     GemmArgs g = g0;
     g.ksplit = slabs;
     g.reach = fp4_reach(g.a_c_step > g.b_c_step ? g.a_c_step : g.b_c_step);
     const int64_t tiles_m = (g.M + 32 * TM - 1) / (32 * TM), tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
     if (tiles_m * tiles_n * g.ksplit > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    g.even = fp4_even(tiles_m, tiles_m * tiles_n * g.ksplit, g.K, cus);
     const int rc = enqueue(gemm_fp4_small<TM, TN, S, NSETS, OUT_BF16, LINE>, dim3((unsigned)(tiles_m * tiles_n * g.ksplit)),
                            dim3(64 * S), small_lds<TM, TN, S>(), s, g, (int)tiles_m, (int)tiles_n);
     return rc != MQ_OK || g.ksplit == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
@@ -1812,7 +1839,7 @@ int launch_fp4_tile(int tile, int slabs, const GemmArgs &g, hipStream_t s, int c
     if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 2>, 256, 128, X, g, s, cus);
     if (tile == i++) return launch_persistent(gemm_fp4_direct<OUT_BF16, 4>, 128, 128, X, g, s, cus);
 #define MQ_X(TM, TN, S, NSETS) \
-    if (tile == i++) return launch_small<TM, TN, S, NSETS, OUT_BF16>(g, s, slabs);
+    if (tile == i++) return launch_small<TM, TN, S, NSETS, OUT_BF16>(g, s, slabs, cus);
     MQ_SMALL(MQ_X)
 #undef MQ_X
     return MQ_ERR_SHAPE;

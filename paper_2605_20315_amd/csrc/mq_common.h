@@ -79,12 +79,13 @@ struct GemmArgs {
     int64_t ldy;
     int out;                  // mq_out
     // optional workspace for partial sums (NVFP4, a long K with very few output tiles): ws_bytes of
-    // device memory, 16-byte aligned, or NULL / 0.  ksplit (K slabs across workgroups, >= 1) and
-    // reach (K steps that the loads of gemm_fp4_small may be away from their base) are
-    // filled in by the launcher.
+    // device memory, 16-byte aligned, or NULL / 0.  ksplit (K slabs across workgroups, >= 1) and, for
+    // gemm_fp4_small, reach (K steps that its loads may be away from their base) and even (whether its
+    // last tiles of few rows take as long as the others) are filled in by the launcher.
     float *ws;
     int64_t ws_bytes;
     int ksplit, reach;
+    bool even;
 };
 // most K slabs across workgroups of the NVFP4 product given this much workspace (0 or 1: none)
 int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus);

@@ -27,6 +27,8 @@ CASES = [
     (65, 6001, (9,), 0, "64x64x8"),
     (97, 4097, (20,), 0, "64x64x4"),
     (161, 3001, (17,), 0, "64x64x4"),
+    (65, 6273, (20,), 0, "64x64x4"),   # the last tiles hold one row and one column
+    (589, 3669, (8,), 0, "64x64x4"),   # 580 tiles: the lanes past the end read the rows in front of the last tiles
     (1, 8, (32, 33, 47), WS, "32x32x8 in slabs"),
     (65, 1000, (47,), WS, "32x64x8 in slabs"),
     (65, 1000, (32,), WS, "64x32x8 in slabs"),
