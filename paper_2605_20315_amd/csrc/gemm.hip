@@ -1748,16 +1748,18 @@ static constexpr TileCost kFp4Costs[3][kFp4TileCount] = {
      {2750.6, 5815.8, 118.51, 43.59, 175.04}, {6678.2, 1478.8, 126.74, 47.794, 133.13},
      {3251.3, 5072.4, 119.84, 88.484, 25.163}, {6802.3, 1402.1, 109.41, 83.132, 94.333},
      {6680.1, 481.62, 141.96, 0, 10}},
-    {{6271.7, 6184.9, 1209.8, 886.09, 17.221}, {3469.8, 7200.5, 713.71, 346.48, 107.32},
-     {6440.7, 4307, 376.79, 172.48, 107.44},
-     {4565, 100, 79.548, 5.9507, 18.338}, {4544.5, 1285.5, 106.98, 10.254, 210.88},
-     {3670.7, 1464.6, 105.09, 2.7519, 568.11}, {6222.6, 100, 109.07, 0, 10},
-     {5675.1, 292.8, 81.694, 19.625, 135.81}, {4527.3, 2156.6, 159.02, 0, 96.95},
-     {7216.7, 634.16, 136.7, 9.1363, 67.916},
+    {{5090.2, 6365.7, 1212.9, 879.81, 18.582}, {3048.2, 7096.8, 715.85, 348.62, 99.27},
+     {3607.9, 4317.9, 395.39, 188.46, 158.25},
+     {4130.4, 121.9, 71.787, 10.882, 529.24}, {4518.3, 1360.1, 109.45, 8.5061, 125.13},
+     {3700.7, 1338.1, 106.56, 3.6642, 562.03}, {6005.3, 100, 106.11, 6.5875, 13.38},
+     {5517.3, 298.81, 84.589, 18.184, 190.27}, {4306.1, 2082.3, 160.2, 4.2803, 107.61},
+     {7230.4, 625.18, 136.7, 9.0327, 65.049},
      {7478.9, 719.42, 302.3, 186.41, 261.14}, {4944.2, 3294, 386.65, 44.621, 116.6},
      {7500.5, 2876.1, 181.1, 338.58, 107.4}, {6575.9, 100, 394.94, 6.7359, 330.19}, {6876.3, 100, 346.69, 0, 10}}};
 // us: the second pass of K slabs, and what two launches overlap by
-static constexpr double kSecondPass[3] = {4.02, 3.20, 4.02}, kOverlap[3] = {1.00, 3.64, 1.00};
+static constexpr double kSecondPass[3] = {4.02, 3.20, 4.02}, kOverlap[3] = {1.00, 3.64, 0.04};
+// By lines, a plan with a small tile has to be cheaper than one of direct tiles alone by this factor (see fp4_plan).
+static constexpr double kSmallMargin[3] = {1.0, 1.0, 1.0077};
 
 struct Fp4Plan {
     int tile;                  // index into kFp4Tiles
@@ -1767,11 +1769,22 @@ struct Fp4Plan {
 };
 
 // The plan that costs least (launch_us; the weights' 0.5625 bytes per element at 5.3 TB/s, a fifth of the shorter one of
-// trip and K steps does not hide).  The costs are fitted to every tile's time, and to pairs of them, on 3200 shapes
-// (K-step-major; row-major 1800, by lines 1900) of 16 to 16384 tokens: the 8B and 32B layers, their 2-, 4- and 8-way shards
-// and shorter, narrower and wider ones.  The plan is on average 1.7 % (row-major 1.5 %, by lines 0.8 %) slower than the fastest
-// one measured.  By lines, on 569 shapes other than those of the fit, against row-major tiles in K order: 0.65 of the time up to
-// 64 tokens, 0.73 up to 256, 0.86 up to 1024, 0.94 up to 3000.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
+// trip and K steps does not hide).  The costs are fitted to every tile's time, and to pairs of them: in K order on 3200
+// shapes (K-step-major) and 1800 (row-major) of 16 to 16384 tokens, the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter,
+// narrower and wider ones, with the K loop that the small tiles had before their loads got fixed resources (they have become
+// faster by 1 to 12 %, most with few tokens).  With the K loop as it is the plan is on average 1.3 % slower than the fastest
+// one measured, 95 % of the shapes within 6.2 % (3200 drawn shapes); row-major in K order 2.4 % and 11.2 % (3500 shapes, most of
+// them of a K below 2048).
+// By lines: 7100 shapes of the same kinds, K from 2048, 1 to 16384 tokens, fitted for the distance to the fastest plan and, eight
+// times as heavily, for whatever would be slower than the plan that ran there in K order.  31 shapes are held to the plan that
+// a test asserts, which is within 0.3 % of the cheapest of the others.  The
+// direct tiles, the same kernels in both row-major orders, have costs of their own here: what counts is how they compare
+// with the small tiles' model error.  On 2700 shapes outside the fit the plan is 0.8 % slower than the
+// fastest on average, 95 % of them within 4.0 %.  On 9800 others, 1 to 6000 tokens, the product takes 0.75 of the time that it took in K order,
+// and more than 2.5 % longer on 11 (7 % at most; 5700 to 5820 tokens on K = 25600, N = 5120 1650 us there and 1740 here).  A fit
+// without that weight and without the margin of kSmallMargin was slower there by up to 11 % (2100 tokens on K = 25600,
+// N = 5120: 64x64 tiles for the last columns, 697 us against 636 in direct tiles).
+// (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
 // instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 8.0 us in
 // 32x32 tiles and 12.3 in 64x64; 512 tokens on N = 28672 88 us in 256x256 and 96 in 64x128.
@@ -1799,17 +1812,18 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
                          0.2, 2.0 * (double)m * (double)n, cus) +
                (slabs > 1 ? kSecondPass[order] : 0.0);
     };
+    auto margin = [&](int i) { return kFp4Tiles[i].kernel == MQ_KERNEL_FP4_SMALL ? kSmallMargin[order] : 1.0; };
     Fp4Plan best{0, 1, 0, 0, 0};
     double best_us = 1e300;
     for (int i = 0; i < kFp4TileCount; ++i) {
         const Fp4Tile &t = kFp4Tiles[i];
-        const double us = cost(i, M, N, 1);
+        const double us = cost(i, M, N, 1) * margin(i);
         if (us < best_us) best_us = us, best = Fp4Plan{i, 1, 0, 0, 0};
         if (t.kernel != MQ_KERNEL_FP4_SMALL || slab_limit < 2) continue;
         const int64_t tiles = tiles_of(t, M, N);
         const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
         if (slabs < 2) continue;
-        const double us_slabs = cost(i, M, N, slabs);
+        const double us_slabs = cost(i, M, N, slabs) * margin(i);
         if (us_slabs < best_us) best_us = us_slabs, best = Fp4Plan{i, (int)slabs, 0, 0, 0};
     }
     for (int i = 0; i < kFp4Directs; ++i) {
@@ -1822,7 +1836,7 @@ static Fp4Plan fp4_plan(int64_t M, int64_t N, int64_t K, int layout, int64_t sla
                 if (m == 0 || n == 0 || (by_m ? m >= M : n >= N)) continue;
                 const double first = cost(i, m, n, 1) - kOverlap[order];
                 for (int j = 0; first < best_us && j < kFp4TileCount; ++j) {
-                    const double us = first + cost(j, by_m ? M - m : M, by_m ? N : N - n, 1);
+                    const double us = (first + cost(j, by_m ? M - m : M, by_m ? N : N - n, 1)) * margin(j);
                     if (us < best_us) best_us = us, best = Fp4Plan{i, 1, by_m ? m : 0, by_m ? 0 : n, j};
                 }
             }
