@@ -557,7 +557,9 @@ __device__ __forceinline__ void small_tile_finish(const GemmArgs &g, f32x16 (&ac
 // besides.  Those fetches, 64 bytes per clock and compute unit from L2, bound the kernel.  Here lane (r, h) takes the half line
 // h of row r in four loads that stand together (chunk t of 16 bytes holds elements 128 h + 32 t ..: A and B permute K alike) and
 // the eight scale bytes of the half line in one load, every four K steps.  Tiles of up to three operand rows hold two groups,
-// the next one under way while this one is multiplied; 64x64 reloads the registers under the group's last K step.  us, in K order
+// the next one under way while this one is multiplied; 64x64 reloads the registers under the group's last K step, holds all of 256
+// registers and spills 8 to 10 of them, in the lines behind the loop, where a short K spends all its time (one or two lines to a
+// wave: K = 2048 to 4096 in eight waves), and is faster there than in K order all the same.  us, in K order
 // and by lines: 64 tokens on K = N = 4096 in 32x32 tiles 11.6 and 8.9; 128 on K = 14336, N = 4096 in 64x32 51 and 32; 256 on
 // K = N = 4096 in 64x64 20.3 and 14.8; 512 28.9 and 24.9; 32 on K = 2048, N = 4096 6.5 and 5.7.
 template <int TM, int TN, int S>
@@ -622,9 +624,9 @@ __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(2))) voi
     // Resources that start at the wave's first K step (or at a later one, where offsets from there would reach 2 GiB: below); the
     // K step goes into the loads' scalar offset, one multiplication each.  Loads past the wave's last step re-read
     // that step (from L1; its products are multiplied by zero scales).  With running 64-bit pointers and a resource built
-    // per load and K step there were 38 scalar instructions per K step instead of 9, and at two waves per SIMD a scalar
+    // per load and K step there were 38 scalar instructions per K step instead of 8, and at two waves per SIMD a scalar
     // instruction per MFMA costs about two cycles of the forty.  With the last group below: 64 tokens, K = N = 4096 in 32x32
-    // tiles 7.1 -> 6.4 us, 256 tokens in 64x64 12.7 -> 11.2, 128 tokens on K = 14336 in 64x32 21.6 -> 20.4.
+    // tiles 7.1 -> 6.4 us with W in cache, 256 tokens in 64x64 12.7 -> 11.2, 128 tokens on K = 14336 in 64x32 21.6 -> 20.4.
     const int len = k1 - k0;
     int64_t first = k0 < KT ? k0 : KT - 1;
     auto rsrc = [](const char *base) {
@@ -1777,16 +1779,15 @@ struct Fp4Plan {
 // them of a K below 2048).
 // By lines: 7100 shapes of the same kinds, K from 2048, 1 to 16384 tokens, fitted for the distance to the fastest plan and, eight
 // times as heavily, for whatever would be slower than the plan that ran there in K order.  31 shapes are held to the plan that
-// a test asserts, which is within 0.3 % of the cheapest of the others.  The
-// direct tiles, the same kernels in both row-major orders, have costs of their own here: what counts is how they compare
-// with the small tiles' model error.  On 2700 shapes outside the fit the plan is 0.8 % slower than the
+// a test asserts.  The direct tiles, the same kernels in both row-major orders, have costs of their own here: what counts is how
+// they compare with the small tiles' model error.  On 2700 shapes outside the fit the plan is 0.8 % slower than the
 // fastest on average, 95 % of them within 4.0 %.  On 9800 others, 1 to 6000 tokens, the product takes 0.75 of the time that it took in K order,
 // and more than 2.5 % longer on 11 (7 % at most; 5700 to 5820 tokens on K = 25600, N = 5120 1650 us there and 1740 here).  A fit
 // without that weight and without the margin of kSmallMargin was slower there by up to 11 % (2100 tokens on K = 25600,
 // N = 5120: 64x64 tiles for the last columns, 697 us against 636 in direct tiles).
 // (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)
 // Small tiles occupy more compute units and larger ones expand fewer operand rows per product (8 vector
-// instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096 take 8.0 us in
+// instructions per MFMA for 64x64, 16 for 32x32, 4 for 128x128): 64 tokens on K = N = 4096, weights from HBM, take 8.0 us in
 // 32x32 tiles and 12.3 in 64x64; 512 tokens on N = 28672 88 us in 256x256 and 96 in 64x128.
 // Two launches where the large tiles leave a ragged last round: whole rounds of one of the direct
 // tiles on the first rows or columns of Y, the others in whatever tile suits them (5003 tokens on
