@@ -227,15 +227,15 @@ int bf16_gemm(const void *x_bf16, int64_t ldx, const void *w_bf16, int64_t ldw,
 /*
  * The same product with a caller-owned workspace, for decode batches (the precision that the
  * decode phase keeps, Section 3.3): 33 to 64 tokens against a weight matrix with a long K and a narrow
- * N re-read the activations once per narrow tile of W; with a workspace the tiles can be wider, K being
- * cut into slabs across workgroups (FP32 partial sums, added in ascending order by a second kernel:
+ * N re-read the activations once per narrow tile of W, and more tokens with a K above 8192 both operands once per
+ * tile; with a workspace the tiles can be wider, K being cut into slabs across workgroups (FP32 partial sums, added in ascending order by a second kernel:
  * bit-identical from run to run; the last bits may differ from bf16_gemm's).  Arguments and
  * requirements as bf16_gemm; workspace as in nvfp4_gemm_ws.
  * mq_bf16_gemm_workspace_bytes(M, N, K) (host function) returns a size that lets the library
- * choose freely: an upper bound of the slabs * M * N * 4 bytes (at most 16 MiB; no more than 4 MiB of
- * it are written on 256 compute units), 0 where slabs are never used
- * (M <= 32, M > 64, N % 4 != 0, K % 128 != 0, K < 8192, N > 16256, or so few rows of W that even
- * with slabs half of the compute units would stay empty).
+ * choose freely: an upper bound of the slabs * M * N * 4 bytes (at most 16 MiB), 0 where slabs are never used:
+ * M <= 32, N % 4 != 0, K % 64 != 0; up to 64 tokens also K % 128 != 0, K < 8192, N > 16256, or so few rows of W that even
+ * with slabs half of the compute units would stay empty; more tokens K <= 8192, or two slabs of more than 16 MiB
+ * (M * N > 2^21).
  */
 int64_t mq_bf16_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int bf16_gemm_ws(const void *x_bf16, int64_t ldx, const void *w_bf16, int64_t ldw,

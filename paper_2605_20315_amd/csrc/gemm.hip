@@ -23,21 +23,23 @@
 //                       above leave over: 32x32 to 128x64 tiles, one workgroup per tile, K split over
 //                       its waves; for a long K with very few tiles also over workgroups
 //                       (splitk_reduce_kernel then adds the slabs).
-//   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256 tile, four waves of 128x128 (256x128, four
-//                       of 128x64, for a short K), tiles loaded from global memory straight into LDS.
+//   gemm_bf16_d2l       the BF16 baseline on large problems: 256x256, 256x192 and 256x128 tiles, four waves of 128x128
+//                       to 128x64, tiles loaded from global memory straight into LDS.
 //   bf16_ring_kernel    BF16 decode batches: narrow tiles, the waves of a workgroup split K, each with a
 //                       ring of its own in LDS; K slabs across workgroups with a workspace.
 //   bf16_short_kernel   BF16, up to 16 tokens and K <= 1024: 16x16 tiles, fragments straight into registers.
-//   bf16_stage_kernel   BF16 in between: 96x64 to 256x192 tiles, two to six stages in LDS.
+//   bf16_stage_kernel   BF16 in between: 96x64 to 256x192 tiles, two to six stages in LDS; for a long K with few
+//                       tiles K slabs across workgroups with a workspace.
 //   gemm_simple_kernel  any K % 16 == 0 / K % 8 == 0 that the tiled kernels do not take.
 //
-// The LDS pipeline of gemm_bf16_d2l: block tile 256 x 256 x 64, two LDS stages, and the latencies
-// covered inside each wave:
+// The LDS pipeline of gemm_bf16_d2l: block tile 256 x 256 x 64, three LDS stages of A and two of B, and the
+// latencies covered inside each wave:
 //   * a K step of 64 is four MFMA phases of 16; the fragments of phase p+1 are read from LDS
 //     into a second register set while the MFMAs of phase p run;
-//   * tiles are fetched two K steps ahead straight into the free LDS stage;
+//   * tiles are fetched two K steps ahead straight into the free LDS stages;
 //   * one barrier per K step, at the start of phase 3: before it every wave has finished writing
-//     tile t+1 and reading tile t; after it tile t's stage is free and receives tile t+2.
+//     tile t+1 and reading tile t; after it tile t's stages are free: B's receives tile t+2 at once, A's
+//     tile t+3 in the next K step.
 // (An NVFP4 kernel of the same structure, operands expanded once per workgroup on their way
 // into LDS, measured 6 % slower than the register-direct kernel on large problems and 1.4-1.8x
 // slower on small ones, and is gone.)
@@ -68,10 +70,10 @@ struct PCfg {
     static constexpr int THREADS = 64 * WAVES_M * WAVES_N;
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // per-wave tile
     static constexpr int TM = WM / 32, TN = WN / 32;      // 32x32 MFMA tiles per wave
-    // LDS map in bytes: A stage 0, A stage 1, B stage 0, B stage 1 (stage strides fit the
-    // 16-bit immediate offset of the LDS instructions)
-    static constexpr int A_STAGE = BM * 128, B_STAGE = BN * 128, B_BASE = 2 * A_STAGE;
-    static constexpr size_t LDS_BYTES = 2ull * (A_STAGE + B_STAGE);
+    // LDS map in bytes: three A stages, two B stages (whose stride fits the 16-bit immediate offset
+    // of the LDS instructions)
+    static constexpr int A_STAGE = BM * 128, B_STAGE = BN * 128, B_BASE = 3 * A_STAGE;
+    static constexpr size_t LDS_BYTES = 3ull * A_STAGE + 2ull * B_STAGE;
     static_assert(TM >= 1 && TN >= 1, "tile too small for this wave grid");
 };
 
@@ -897,15 +899,45 @@ __device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off
 #pragma clang diagnostic pop
 }
 
-// 256x256x64 tile with four waves of 128x128 (one per SIMD).  The tiles never pass through
-// registers: every wave issues 16 global_load_lds_dwordx4 per K step (1 KB each: 8 rows of one
+// The order in which a workgroup takes its K steps: groups of four in turn, each from a step of its own on.  Workgroups of
+// one XCD that read the same rows would otherwise all reach a K step together, and all of them wait for its trip from
+// memory; so one of them makes the trip and the others, a step or two later, find the lines in L2.  From `from` steps on: a
+// short K has the first trip of every line at its start, where four times as many different lines in flight cost more (staged
+// tiles, K = 512 to 1800: 3.5 % slower; 2000 to 4000: 1 % slower to 5 % faster; 4096: 3 % faster; 5120 and more: 7 %, up to 26 %).
+// Groups of two or eight: the same within 1 %.
+struct KOrder {
+    int KT, whole, first;
+    __device__ __forceinline__ KOrder(int kt, int from, int tm, int tn)
+        : KT(kt), whole(kt >= from ? kt & ~3 : 0), first(__builtin_amdgcn_readfirstlane(tm + 2 * tn))
+    {
+    }
+    __device__ __forceinline__ int at(int k) const
+    {
+        k = k < KT ? k : KT - 1;  // past the end: a step that was read before, never used
+        return k < whole ? (k & ~3) | ((k + first) & 3) : k;
+    }
+};
+
+// Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N < 63 ? N : 63) : "memory");
+}
+
+// 256x256x64 tile with four waves of 128x128 (one per SIMD), 256x192 with 128x96 and 256x128 with 128x64.  The tiles never
+// pass through registers: every wave issues 16 global_load_lds_dwordx4 per K step (1 KB each: 8 rows of one
 // operand tile), which write LDS at M0 + 16 * lane.  The bank swizzle is applied on the global side: the lane that fills chunk c' of
 // row r fetches chunk c' ^ key(r).  The only wait is the one before the
 // barrier.
-// The loads of tile t+2 are issued one per two MFMAs: the first half in the phase behind the
-// barrier that frees their stage, the second half in the first phase of the next K step.  All
-// 16 in the one phase measured 3 to 8 % slower (the texture path is shared by the four waves and
-// the same instants see everybody's loads), in one burst 5 % slower again; three phases no better.
+// The loads of tile t+2 are issued one per two MFMAs: B's in the phase behind the barrier that frees their stage, A's in
+// the first phase of K step t, into the third stage that the 160 KB of LDS hold for A: four and seven phases before the
+// barrier that waits for them.  With two stages of both A's came half a K step later, and their wait was what a K step took
+// beyond its MFMAs; K steps in an order of the workgroup's own (KOrder) take another 1 to 6 % off (matrix pipe busy 80 -> 88 % of
+// cycles).  us, two stages / three / three and own order: 4096 tokens on K = 4096, N = 6144 187 (in 256x192 staged tiles) / 163 / 160;
+// 8192 on K = 14336, N = 4096 725 / 688 / 668; 8192 on K = 4096, N = 28672 1428 / 1422 / 1380; 2048 on N = 4096
+// in 256x128 tiles 73 / 63 / 62.  (All 16 loads in one phase: 3 to 8 % slower, the texture path is shared by the four waves and the same
+// instants see everybody's loads; 16x16 MFMAs in the same pipeline: no faster, nor the row's MFMAs in alternating order.)
 template <class C, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, int tiles_n)
 {
@@ -921,6 +953,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
     const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
     const int frow = lane & 31, fhalf = lane >> 5;
     const int KT = (int)(g.K / BK);
+    const KOrder order(KT, 64, tm, tn);
 
     // load u of this wave: rows 8 * (wave * GA + u) .. + 7 of the A tile (u < GA), else of the B tile
     // byte offsets from the tile's first row: 32 bits for any operand size
@@ -938,18 +971,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
     }
     // LDS byte address of the dynamic segment
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)L;
-    // load u of tile t into LDS stage `stage`
-    auto load_group = [&](int t, int stage, int u) {
-        t = t < KT ? t : KT - 1;
+    // load u of the K step that starts `ko` bytes into the rows, into the A stage at byte `sa` (u < GA) or the B stage `sb`
+    auto load_group = [&](int64_t ko, uint32_t sa, int sb, int u) {
         const bool isA = u < GA;
-        const char *base = (isA ? ta : tb) + (int64_t)t * (BK * 2);
-        const uint32_t dst = lds0 + (isA ? stage * C::A_STAGE + (wave * GA + u) * 1024
-                                         : C::B_BASE + stage * C::B_STAGE + (wave * GB + (u - GA)) * 1024);
+        const char *base = (isA ? ta : tb) + ko;
+        const uint32_t dst = lds0 + (isA ? sa + (wave * GA + u) * 1024
+                                         : C::B_BASE + sb * C::B_STAGE + (wave * GB + (u - GA)) * 1024);
         load_rows_to_lds<false>(dst, vo[u], base);
-    };
-    auto load_tile = [&](int t, int stage) {
-#pragma unroll
-        for (int u = 0; u < NL; ++u) load_group(t, stage, u);
     };
 
     int fa[4], fb[4];
@@ -959,14 +987,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
         fb[ks] = C::B_BASE + ((wn0 + frow) * 8 + ((ks * 2 + fhalf) ^ swz_key(frow))) * 16;
     }
     uint4 fra[2][C::TM], frb[2][C::TN];
-    auto read_frags = [&](int stage, int ks, uint4(&a)[C::TM], uint4(&b)[C::TN]) {
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-            a[i] = *reinterpret_cast<const uint4 *>(L + fa[ks] + i * 4096 + stage * C::A_STAGE);
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-            b[j] = *reinterpret_cast<const uint4 *>(L + fb[ks] + j * 4096 + stage * C::B_STAGE);
-    };
     f32x16 acc[C::TM][C::TN];
 #pragma unroll
     for (int i = 0; i < C::TM; ++i)
@@ -976,48 +996,60 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     constexpr int NMFMA = C::TM * C::TN;
 
-    load_tile(0, 0);
-    load_tile(1, 1);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    read_frags(0, 0, fra[0], frb[0]);
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int u = 0; u < NL; ++u) load_group((int64_t)order.at(d) * (BK * 2), d * C::A_STAGE, d, u);
+    wait_loads<NL>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i) fra[0][i] = *reinterpret_cast<const uint4 *>(L + fa[0] + i * 4096);
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) frb[0][j] = *reinterpret_cast<const uint4 *>(L + fb[0] + j * 4096);
 
     // One phase: the MFMAs of one 16-wide K sub-step on fragments (ca, cb); meanwhile the
-    // fragments of sub-step ks of stage rs are read into (na, nb), one per MFMA while any remain,
-    // and loads [U0, U1) of tile t go to stage ls, spread evenly over the MFMAs.
+    // fragments of sub-step ks of the stages (ra, rb) are read into (na, nb), one per MFMA while any remain,
+    // and loads [U0, U1) of tile t go to the stages (la, lb), spread evenly over the MFMAs.
     auto phase = [&](const uint4(&ca)[C::TM], const uint4(&cb)[C::TN], uint4(&na)[C::TM], uint4(&nb)[C::TN], int ks,
-                     int rs, int t, int ls, auto u0c, auto u1c) {
+                     uint32_t ra, int rb, int t, uint32_t la, int lb, auto u0c, auto u1c) {
         constexpr int U0 = decltype(u0c)::value, U1 = decltype(u1c)::value;
+        const char *const pa = L + fa[ks] + ra;
+        const int64_t ko = U0 < U1 ? (int64_t)order.at(t) * (BK * 2) : 0;
 #pragma unroll
         for (int n = 0; n < NMFMA; ++n) {
             const int i = n / C::TN, j = n % C::TN;
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                 __builtin_bit_cast(bf16x8, ca[i]), __builtin_bit_cast(bf16x8, cb[j]), acc[i][j], 0, 0, 0);
             if (n < C::TM)
-                na[n] = *reinterpret_cast<const uint4 *>(L + fa[ks] + n * 4096 + rs * C::A_STAGE);
+                na[n] = *reinterpret_cast<const uint4 *>(pa + n * 4096);
             else if (n < C::TM + C::TN)
-                nb[n - C::TM] = *reinterpret_cast<const uint4 *>(L + fb[ks] + (n - C::TM) * 4096 + rs * C::B_STAGE);
+                nb[n - C::TM] = *reinterpret_cast<const uint4 *>(L + fb[ks] + (n - C::TM) * 4096 + rb * C::B_STAGE);
 #pragma unroll
-            for (int u = U0 + n * (U1 - U0) / NMFMA; u < U0 + (n + 1) * (U1 - U0) / NMFMA; ++u) load_group(t, ls, u);
+            for (int u = U0 + n * (U1 - U0) / NMFMA; u < U0 + (n + 1) * (U1 - U0) / NMFMA; ++u) load_group(ko, la, lb, u);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     using U_0 = std::integral_constant<int, 0>;
-    using U_H = std::integral_constant<int, NL / 2>;
+    using U_A = std::integral_constant<int, GA>;
     using U_N = std::integral_constant<int, NL>;
+    // A stages of this K step, the next one and the one after it, in turn
+    uint32_t a0 = 0, a1 = C::A_STAGE, a2 = 2 * C::A_STAGE;
     auto kstep = [&](int kt, auto par) {
         constexpr int cur = decltype(par)::value, nxt = cur ^ 1;
-        // second half of tile kt+1 (the first K step of a tile fetches it a second time: harmless)
-        phase(fra[0], frb[0], fra[1], frb[1], 1, cur, kt + 1, nxt, U_H{}, U_N{});
-        phase(fra[1], frb[1], fra[0], frb[0], 2, cur, 0, 0, U_N{}, U_N{});
-        phase(fra[0], frb[0], fra[1], frb[1], 3, cur, 0, 0, U_N{}, U_N{});
-        // tile kt+1 has landed in this wave's share of stage nxt; after the barrier in everyone's,
-        // and nobody reads stage cur any more (this wave's last fragment reads of it have
-        // returned: lgkmcnt, which the MFMAs behind the barrier would wait for anyway): it
-        // receives tile kt+2
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();
-        phase(fra[1], frb[1], fra[0], frb[0], 0, nxt, kt + 2, cur, U_0{}, U_H{});
+        phase(fra[0], frb[0], fra[1], frb[1], 1, a0, cur, kt + 2, a2, 0, U_0{}, U_A{});
+        phase(fra[1], frb[1], fra[0], frb[0], 2, a0, cur, 0, 0, 0, U_N{}, U_N{});
+        phase(fra[0], frb[0], fra[1], frb[1], 3, a0, cur, 0, 0, 0, U_N{}, U_N{});
+        // tile kt+1 has landed in this wave's share of its stages (the A loads of tile kt+2 may still be on their
+        // way), after the barrier in everyone's, and nobody reads the stages of tile kt any more (this wave's last
+        // fragment reads of them have returned: lgkmcnt, which the MFMAs behind the barrier would wait for
+        // anyway): B's receives tile kt+2 now, A's tile kt+3 in the next K step
+        wait_loads<GA>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        phase(fra[1], frb[1], fra[0], frb[0], 0, a1, nxt, kt + 2, 0, cur, U_A{}, U_N{});
+        const uint32_t t = a0;
+        a0 = a1, a1 = a2, a2 = t;
     };
     int kt = 0;
     for (; kt + 1 < KT; kt += 2) {
@@ -1025,7 +1057,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
         kstep(kt + 1, std::integral_constant<int, 1>{});
     }
     if (kt < KT) kstep(kt, std::integral_constant<int, 0>{});
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the clamped loads past the end still target LDS
+    wait_loads<0>();  // the clamped loads past the end still target LDS
 
     epilogue<C, OUT_BF16>(g, acc, 1.0f, m0, n0, wm0, wn0, frow, fhalf);
 }
@@ -1033,13 +1065,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
 // ---- BF16, tiles of 16x16 MFMAs: decode batches and everything up to a few thousand tokens --------
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
-template <int N>
-__device__ __forceinline__ void wait_loads()
-{
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N < 63 ? N : 63) : "memory");
-}
 
 // Lane offset (bytes from the first row of the tile) of load group `rr / 8`: row rr of the tile, clamped to
 // the last of `total` rows, with the bank swizzle applied on the global side.
@@ -1050,6 +1075,21 @@ __device__ __forceinline__ uint32_t row_offset(int64_t first, int rr, int64_t to
     return (uint32_t)((row - first) * ld * 2 + (((lane & 7) ^ swz_key(rr)) * 16));
 }
 
+// A copy that the compiler cannot see through: it may store quads straight from accumulation registers,
+// and then kept the accumulators of the staged kernels half in one kind of register and half in the other
+// and moved all of them twice per K step.
+__device__ __forceinline__ f32x4 opaque_copy(f32x4 v)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = v[i];
+        float c;
+        asm("v_mov_b32 %0, %1" : "=v"(c) : "v"(a));
+        v[i] = c;
+    }
+    return v;
+}
+
 // Accumulator i of a 16x16 tile (W rows as the A operand, tokens as the B operand): W row 4 (lane / 16) + i,
 // token lane % 16, i.e. four consecutive columns of one row of Y.
 template <bool OUT_BF16>
@@ -1058,18 +1098,7 @@ __device__ __forceinline__ void store_quad(const GemmArgs &g, f32x4 v, int64_t m
     using T = std::conditional_t<OUT_BF16, __bf16, float>;
     if (m >= g.M || n >= g.N) return;
     T *dst = static_cast<T *>(g.y) + m * g.ldy + n;
-    if constexpr (!OUT_BF16) {
-        // (a copy that the compiler cannot see through: it may store quads straight from accumulation registers,
-        // and then kept the accumulators of the staged kernels half in one kind of register and half in the other
-        // and moved all of them twice per K step)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float a = v[i];
-            float c;
-            asm("v_mov_b32 %0, %1" : "=v"(c) : "v"(a));
-            v[i] = c;
-        }
-    }
+    if constexpr (!OUT_BF16) v = opaque_copy(v);
     if (n + 3 < g.N) {
         if constexpr (OUT_BF16) {
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -1268,8 +1297,11 @@ __global__ __launch_bounds__(64 * S) void bf16_short_kernel(GemmArgs g, int tile
 // waited for HBM (256x128 tile, 2048 tokens, K = 14336, N = 4096: 251 us with two stages, 186 with
 // three; 128x64 tile, 512 tokens: 93 against 211 for a register-staged 128x128 tile with one step of
 // look-ahead).  Beyond 96 to 144 KB of stages nothing is gained.  What bounds them then is the
-// LDS: a tile's bytes are written once at 64 and its fragments read at 128 bytes per clock.
-template <int TM, int TN, int WM, int WN, int NST, bool OUT_BF16>
+// LDS: a tile's bytes are written once at 64 and its fragments read at 128 bytes per clock, and, with few tiles to a
+// long K, what a compute unit loads: 48 to 55 bytes per ns whatever the depth (32 KB of lines in flight).  There K
+// slabs across workgroups (SLABS) allow larger tiles, whose operands are fewer bytes per product: 200 tokens on
+// K = 14336, N = 4096 3.7 MB per unit and 51 us in 64x64 tiles, 1.8 MB and 41 us in 128x128 with four slabs, second pass included.
+template <int TM, int TN, int WM, int WN, int NST, bool SLABS, bool OUT_BF16>
 __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int W = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STAGE = (BM + BN) * 128;
@@ -1280,24 +1312,30 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
     char *const L = reinterpret_cast<char *>(lds);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tiles = tiles_m * tiles_n, item = logical_id(blockIdx.x, SLABS ? tiles * g.ksplit : tiles);
+    const int slab = SLABS ? item / tiles : 0;
     int tm, tn;
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tile_of_logical(item - slab * tiles, tiles_m, tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int wm0 = (wave / WN) * (16 * TM), wn0 = (wave % WN) * (16 * TN);
-    const int KT = (int)(g.K / BK);
+    // this slab's K steps [s0, s0 + KT): the launcher leaves no slab empty
+    const int KA = (int)(g.K / BK), SL = SLABS ? (KA + g.ksplit - 1) / g.ksplit : KA;
+    const int s0 = slab * SL, KT = s0 + SL < KA ? SL : KA - s0;
+
+    const KOrder order(KT, SLABS ? 0 : 64, tm, tn);
 
     uint32_t vo[NL];
 #pragma unroll
     for (int u = 0; u < NL; ++u)
         vo[u] = u < NLX ? row_offset(m0, (u * W + wave) * 8 + (lane >> 3), g.M, g.lda, lane)
                         : row_offset(n0, ((u - NLX) * W + wave) * 8 + (lane >> 3), g.N, g.ldb, lane);
-    const char *const tx = static_cast<const char *>(g.a) + m0 * g.lda * 2;  // m0 < M, n0 < N
-    const char *const tw = static_cast<const char *>(g.b) + n0 * g.ldb * 2;
+    const char *const tx = static_cast<const char *>(g.a) + m0 * g.lda * 2 + (int64_t)s0 * (BK * 2);  // m0 < M, n0 < N
+    const char *const tw = static_cast<const char *>(g.b) + n0 * g.ldb * 2 + (int64_t)s0 * (BK * 2);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)L;
-    auto load_group = [&](int k, uint32_t stage, int u) {
-        k = k < KT ? k : KT - 1;  // past the end: the last step again, never used
+    // load u of the K step that starts `ko` bytes into the rows
+    auto load_group = [&](int64_t ko, uint32_t stage, int u) {
         load_rows_to_lds<false>(lds0 + stage + (u < NLX ? (u * W + wave) * 1024 : BM * 128 + ((u - NLX) * W + wave) * 1024),
-                                vo[u], (u < NLX ? tx : tw) + (int64_t)k * (BK * 2));
+                                vo[u], (u < NLX ? tx : tw) + ko);
     };
     const int row = lane & 15, grp = lane >> 4;
     int fx[2], fw[2];
@@ -1320,13 +1358,14 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
     // loads of K step kl into `lstage`, both spread evenly.
     auto phase = [&](const uint4(&f)[NF], uint4(&nf)[NF], int k, uint32_t stage, int kl, uint32_t lstage, auto loadc) {
         constexpr bool LOAD = decltype(loadc)::value;
+        const int64_t ko = LOAD ? (int64_t)order.at(kl) * (BK * 2) : 0;
 #pragma unroll
         for (int n = 0; n < NM; ++n) {
 #pragma unroll
             for (int q = n * NF / NM; q < (n + 1) * NF / NM; ++q) nf[q] = read_frag(stage, k, q);
             if constexpr (LOAD)
 #pragma unroll
-                for (int u = n * NL / NM; u < (n + 1) * NL / NM; ++u) load_group(kl, lstage, u);
+                for (int u = n * NL / NM; u < (n + 1) * NL / NM; ++u) load_group(ko, lstage, u);
             acc[n / TM][n % TM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[TM + n / TM]),
                                                                           __builtin_bit_cast(bf16x8, f[n % TM]),
                                                                           acc[n / TM][n % TM], 0, 0, 0);
@@ -1336,7 +1375,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
 #pragma unroll
     for (int d = 0; d < NST; ++d)
 #pragma unroll
-        for (int u = 0; u < NL; ++u) load_group(d, d * STAGE, u);
+        for (int u = 0; u < NL; ++u) load_group((int64_t)order.at(d) * (BK * 2), d * STAGE, u);
     wait_loads<(NST - 1) * NL>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -1359,8 +1398,15 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
 #pragma unroll
     for (int a = 0; a < TN; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
-            store_quad<OUT_BF16>(g, acc[a][b], m0 + wm0 + b * 16 + row, n0 + wn0 + a * 16 + 4 * grp);
+        for (int b = 0; b < TM; ++b) {
+            const int64_t m = m0 + wm0 + b * 16 + row, n = n0 + wn0 + a * 16 + 4 * grp;
+            if constexpr (SLABS) {  // partial sums (N % 4 == 0 here)
+                if (m < g.M && n < g.N)
+                    *reinterpret_cast<f32x4 *>(g.ws + ((int64_t)slab * g.M + m) * g.N + n) = opaque_copy(acc[a][b]);
+            } else {
+                store_quad<OUT_BF16>(g, acc[a][b], m, n);
+            }
+        }
 }
 
 // ---- fallback for K not a multiple of 64: one thread per output, exact products ---------------
@@ -1608,19 +1654,21 @@ static constexpr Bf16Tile kBf16Tiles[] = {
 #define MQ_X(TM, TN, WM, WN, NST) {MQ_KERNEL_BF16_STAGE, 16 * TM * WM, 16 * TN * WN, WM * WN},
     MQ_STAGE(MQ_X)
 #undef MQ_X
-    {MQ_KERNEL_BF16_D2L, 256, 128, 4}, {MQ_KERNEL_BF16_D2L, 256, 256, 4}, {MQ_KERNEL_BF16_SHORT, 16, 16, 8}};
+    {MQ_KERNEL_BF16_D2L, 256, 128, 4}, {MQ_KERNEL_BF16_D2L, 256, 192, 4}, {MQ_KERNEL_BF16_D2L, 256, 256, 4}, {MQ_KERNEL_BF16_SHORT, 16, 16, 8}};
 static constexpr TileCost kBf16Costs[] = {
     {3990.7, 490.23, 33.944, 0, 215.64}, {4232.3, 285.89, 67.673, 0, 121.71}, {4290.4, 1760.9, 116.09, 0, 101.7},
     {2500, 1917.2, 67.252, 0, 400}, {4165.3, 476.99, 85.889, 0, 152.39}, {3802.9, 1712.7, 145.39, 0, 63.315},
-    {4418.7, 542.73, 126.77, 0, 42.119}, {3161.5, 2935.1, 160.67, 0, 139.48},
-    {3178.4, 1632.6, 142.34, 3.1851, 395.14}, {3862.2, 2348.2, 178.4, 0, 108.89},
-    {3306.3, 2445.4, 255.17, 0, 27.392}, {3621.8, 2048.8, 209.56, 109.8, 48.971},
-    {3525.3, 2209.3, 219.72, 172.63, 116.05}, {3155.8, 3656.7, 320.78, 117.18, 96.95},
-    {3107.7, 5612.9, 439.75, 59.295, 35.466}, {2500, 5177.6, 384.7, 203.85, 95.535},
-    {2500, 6277.5, 638.11, 0, 134.09}, {2795.2, 9151.5, 684.2, 285.04, 37.859},
-    {6000, 2435.8, 866.71, 91.375, 59.163}, {6000, 6331.1, 699.25, 535.96, 41.413},
+    {4418.7, 542.73, 126.77, 0, 42.119}, {3161.5, 2935.1, 160.67, 0, 139.48}, {3178.4, 1632.6, 142.34, 3.1851, 395.14},
+    {3862.2, 2348.2, 178.4, 0, 108.89}, {3306.3, 2445.4, 255.17, 0, 25.607}, {3621.8, 2048.8, 209.56, 109.8, 53.171},
+    {3817.3, 2209.3, 219.72, 163.53, 116.05}, {3155.8, 3662.8, 313.3, 93.312, 95.188},
+    {2998.9, 6086, 430.49, 59.295, 34.702}, {2467.5, 6351.1, 397.88, 240.48, 97.026}, {2354.8, 6066.9, 636.14, 0, 134.09},
+    {2523.8, 8830.3, 678.75, 188.09, 35.62}, {1771, 7053.4, 593.91, 212.65, 75.361},
+    {3188.5, 4334.3, 740.91, 276.68, 87.327}, {2283, 7691.4, 903.92, 286.82, 58.652},
     {2665.9, 650.8, 106.65, 17.193, 247.09}};
 static_assert(sizeof(kBf16Costs) / sizeof(TileCost) == sizeof(kBf16Tiles) / sizeof(Bf16Tile), "one cost per tile");
+
+// us: the second pass of K slabs in the staged tiles, and each MB of partial sums
+static constexpr double kBf16SecondPass = 3.08, kBf16PartialSums = 0.212;
 
 struct Bf16Plan {
     int tile;   // index into kBf16Tiles
@@ -1631,11 +1679,14 @@ struct Bf16Plan {
 // two thirds come from caches), of which 55 % of the shorter one of trip and K steps hides.  A tile shape that leaves
 // a nearly empty last round loses to one that does not.  The costs are fitted to every tile's time on 4100 shapes
 // (1 to 8192 tokens; the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter, narrower and wider ones;
-// weights from HBM; both output types): the choice is on average 0.6 % slower than the fastest tile, 95 % of the shapes
-// within 3.3 %.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096, N = 28672: the weights alone take 44 us, the 224x128 tile 73: K steps and
-// trip overlap only in part there.
-// Slabs, when the caller's workspace allows some, shorten the K loop for a second pass of 3 us (64 tokens, K = 14336,
-// N = 4096: 30.8 us against 36.4 without; 33 to 57 tokens 27 to 30 us).
+// weights from HBM; both output types), those of gemm_bf16_d2l and of the second pass on 2000 later ones (32 to 8192 tokens): the
+// choice is on average 1.0 % slower than the fastest tile and slab count, 95 % of the shapes within 6.6 % (690 shapes outside
+// the fit: 1.2 and 7.5 %).  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096,
+// N = 28672: the weights alone take 44 us, the 224x128 tile 66: what a compute unit can load bounds it.
+// Slabs, when the caller's workspace allows some, shorten the K loop for a second pass: 33 to 64 tokens in narrow tiles
+// (64 on K = 14336, N = 4096: 30.8 us against 36.4 without; 33 to 57 tokens 27 to 30 us); more tokens in staged tiles (100 on the
+// same layer 42 -> 32 us, 200 52 -> 41, 400 71 -> 62, 200 on K = 25600, N = 5120 134 -> 87), where a margin of 5 % keeps
+// the rule's error from costing more than slabs bring.
 static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, int cus)
 {
     const double kt = (double)(K / BK), mem = 2.0 * ((double)N + 0.3 * (double)M) * (double)K / 5.3e6;
@@ -1647,14 +1698,26 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (tiles > (t.kernel == MQ_KERNEL_BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
         if (t.kernel == MQ_KERNEL_BF16_SHORT && (M > 16 || K > 1024)) continue;
-        int64_t slabs = 1;
-        for (;;) {
-            const double us = launch_us(kBf16Costs[i], tiles * slabs, kt / (double)slabs, mem, 0.45, out_bytes, cus) +
-                              (slabs > 1 ? 3.0 : 0.0);
-            if (us < best_us) best_us = us, best = Bf16Plan{i, (int)slabs};
-            if (slabs > 1 || t.kernel != MQ_KERNEL_BF16_RING || slab_limit < 2 || 2 * tiles > cus) break;
-            slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
+        // 256x192 exists twice: staged for a few K steps (1424 tokens on K = 192, N = 5384 14.3 us against 14.7), else with X one
+        // stage further ahead and 32x32 products (a tenth faster from K = 512 on)
+        if (t.bn == 192 && (t.kernel == MQ_KERNEL_BF16_STAGE) != (K < 512)) continue;
+        auto us = [&](int64_t slabs) {
+            return launch_us(kBf16Costs[i], tiles * slabs, kt / (double)slabs, mem, 0.45, out_bytes, cus);
+        };
+        auto take = [&](double t, int64_t slabs) {
+            if (t < best_us) best_us = t, best = Bf16Plan{i, (int)slabs};
+        };
+        take(us(1), 1);
+        if (t.kernel == MQ_KERNEL_BF16_RING && M <= 64 && 2 * tiles <= cus) {
+            const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
+            if (slabs >= 2) take(us(slabs) + 3.0, slabs);
         }
+        if (t.kernel == MQ_KERNEL_BF16_STAGE && M > 64)
+            for (int64_t slabs = 2; slabs <= slab_limit && slabs * tiles <= cus; ++slabs) {
+                const int64_t part = (K / BK + slabs - 1) / slabs;
+                if ((slabs - 1) * part >= K / BK) continue;  // (the last one would be empty)
+                take(1.05 * (us(slabs) + kBf16SecondPass + kBf16PartialSums * 4e-6 * (double)M * (double)N * (double)slabs), slabs);
+            }
     }
     return best;
 }
@@ -1686,6 +1749,22 @@ int launch_ring(const GemmArgs &g0, hipStream_t s, int slabs)
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
 
+template <int TM, int TN, int WM, int WN, int NST, bool OUT_BF16>
+int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
+{
+    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
+    GemmArgs g = g0;
+    g.ksplit = slabs;
+    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    if (tiles_m * tiles_n * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    // (the partial sums are FP32 for either output type)
+    auto *const kern = slabs > 1 ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>
+                                 : bf16_stage_kernel<TM, TN, WM, WN, NST, false, OUT_BF16>;
+    const int rc = enqueue(kern, dim3((unsigned)(tiles_m * tiles_n * slabs)), dim3(64 * WM * WN),
+                           stage_lds<TM, TN, WM, WN, NST>(), s, g, (int)tiles_m, (int)tiles_n);
+    return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
+}
+
 template <bool OUT_BF16>
 int launch_bf16(const GemmArgs &g, hipStream_t s)
 {
@@ -1701,14 +1780,14 @@ int launch_bf16(const GemmArgs &g, hipStream_t s)
     MQ_RING(MQ_X)
 #undef MQ_X
 #define MQ_X(TM, TN, WM, WN, NST) \
-    if (plan.tile == i++)                                                                                            \
-        return launch_tiles(bf16_stage_kernel<TM, TN, WM, WN, NST, OUT_BF16>, stage_lds<TM, TN, WM, WN, NST>(),      \
-                            16 * TM * WM, 16 * TN * WN, 64 * WM * WN, g, s);
+    if (plan.tile == i++) return launch_stage<TM, TN, WM, WN, NST, OUT_BF16>(g, s, plan.slabs);
     MQ_STAGE(MQ_X)
 #undef MQ_X
     using Mid = PCfg<256, 128, 2, 2>;
+    using Wide = PCfg<256, 192, 2, 2>;
     using Big = PCfg<256, 256, 2, 2>;
     if (plan.tile == i++) return launch_tiles(gemm_bf16_d2l<Mid, OUT_BF16>, Mid::LDS_BYTES, 256, 128, Mid::THREADS, g, s);
+    if (plan.tile == i++) return launch_tiles(gemm_bf16_d2l<Wide, OUT_BF16>, Wide::LDS_BYTES, 256, 192, Wide::THREADS, g, s);
     if (plan.tile == i++) return launch_tiles(gemm_bf16_d2l<Big, OUT_BF16>, Big::LDS_BYTES, 256, 256, Big::THREADS, g, s);
     return launch_tiles(bf16_short_kernel<8, OUT_BF16>, 0, 16, 16, 512, g, s);
 }
@@ -1915,6 +1994,7 @@ int configure_gemm_kernels()
                                    (int)bytes);
     };
     using Mid = PCfg<256, 128, 2, 2>;
+    using Wide = PCfg<256, 192, 2, 2>;
     using Big = PCfg<256, 256, 2, 2>;
     constexpr size_t X = 128 * 1024;  // accumulator exchange of the K-split variants
     hipError_t e = hipSuccess;
@@ -1931,6 +2011,7 @@ int configure_gemm_kernels()
     MQ_SMALL(MQ_X)
 #undef MQ_X
     both(gemm_bf16_d2l<Mid, true>, gemm_bf16_d2l<Mid, false>, Mid::LDS_BYTES);
+    both(gemm_bf16_d2l<Wide, true>, gemm_bf16_d2l<Wide, false>, Wide::LDS_BYTES);
     both(gemm_bf16_d2l<Big, true>, gemm_bf16_d2l<Big, false>, Big::LDS_BYTES);
 #define MQ_X(MT, NT, S) \
     both(bf16_ring_kernel<MT, NT, S, true, true>, bf16_ring_kernel<MT, NT, S, true, false>, ring_lds<MT, NT, S>()); \
@@ -1938,8 +2019,9 @@ int configure_gemm_kernels()
     MQ_RING(MQ_X)
 #undef MQ_X
 #define MQ_X(TM, TN, WM, WN, NST) \
-    both(bf16_stage_kernel<TM, TN, WM, WN, NST, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false>, \
-         stage_lds<TM, TN, WM, WN, NST>());
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false>, \
+         stage_lds<TM, TN, WM, WN, NST>()); \
+    if (e == hipSuccess) e = set(bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>, stage_lds<TM, TN, WM, WN, NST>());
     MQ_STAGE(MQ_X)
 #undef MQ_X
     return note_launch(e);
@@ -1963,13 +2045,24 @@ int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int c
 
 // Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none); the cost
 // rule decides how many it does use, at most one work item per compute unit, which is less than this
-// bound.  Only decode batches of 33 to 64 tokens with a long K and a narrow N can gain from a second pass; every slab keeps
-// 512 of K, and the partial sums' traffic (8 bytes per output and slab) stays below half of the weights'.
+// bound.  33 to 64 tokens (narrow tiles): a long K and a narrow N; every slab keeps 512 of K, and the partial
+// sums' traffic (8 bytes per output and slab) stays below half of the weights'.  More tokens (staged tiles): every slab
+// keeps 768 of K and the partial sums 16 MiB; from K = 5120 to 8192 slabs gain 1 % on average over the shapes where the rule
+// would take them and lose as much where its error is against them, beyond that 20 to 30 %, so the line lies there.
 int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
-    if (M <= 32 || M > 64 || N <= 0 || K < 8192 || K % 128 != 0) return 0;
+    if (M <= 32 || N <= 0 || ws_bytes <= 0 || N % 4 != 0) return 0;
+    if (M > 64) {
+        if (K <= 8192 || K % BK != 0) return 0;
+        if (ws_bytes > (16 << 20)) ws_bytes = 16 << 20;
+        if (M > ws_bytes / 8 || N > ws_bytes / 8) return 0;  // (M * N * 4 does not overflow below)
+        const int64_t most = ws_bytes / (M * N * 4), ks = K / BK / 12;
+        const int64_t got = ks < most ? ks : most;
+        return got >= 2 ? (int)got : 0;
+    }
+    if (K < 8192 || K % 128 != 0) return 0;
     const int64_t groups = (N + 127) / 128, steps = K / 128;
-    if (2 * groups >= cus || ws_bytes <= 0 || N % 4 != 0) return 0;
+    if (2 * groups >= cus) return 0;
     int64_t ks = 2 * cus / groups;
     if (ks > steps / 4) ks = steps / 4;
     if (ks > K / (8 * M)) ks = K / (8 * M);
