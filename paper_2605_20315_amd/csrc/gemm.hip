@@ -1301,7 +1301,7 @@ __global__ __launch_bounds__(64 * S) void bf16_short_kernel(GemmArgs g, int tile
 // long K, what a compute unit loads: 48 to 55 bytes per ns whatever the depth (32 KB of lines in flight).  There K
 // slabs across workgroups (SLABS) allow larger tiles, whose operands are fewer bytes per product: 200 tokens on
 // K = 14336, N = 4096 3.7 MB per unit and 51 us in 64x64 tiles, 1.8 MB and 41 us in 128x128 with four slabs, second pass included.
-template <int TM, int TN, int WM, int WN, int NST, bool SLABS, bool OUT_BF16>
+template <int TM, int TN, int WM, int WN, int NST, bool SLABS, bool STREAM, bool OUT_BF16>
 __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int W = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STAGE = (BM + BN) * 128;
@@ -1334,8 +1334,10 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)L;
     // load u of the K step that starts `ko` bytes into the rows
     auto load_group = [&](int64_t ko, uint32_t stage, int u) {
-        load_rows_to_lds<false>(lds0 + stage + (u < NLX ? (u * W + wave) * 1024 : BM * 128 + ((u - NLX) * W + wave) * 1024),
-                                vo[u], (u < NLX ? tx : tw) + ko);
+        if (u < NLX)
+            load_rows_to_lds<false>(lds0 + stage + (u * W + wave) * 1024, vo[u], tx + ko);
+        else
+            load_rows_to_lds<STREAM>(lds0 + stage + BM * 128 + ((u - NLX) * W + wave) * 1024, vo[u], tw + ko);
     };
     const int row = lane & 15, grp = lane >> 4;
     int fx[2], fw[2];
@@ -1644,7 +1646,7 @@ struct Bf16Tile {
     int bm, bn, waves;
 };
 #define MQ_RING(X) /* MT, NT, S */ \
-    X(1, 1, 8) X(1, 2, 4) X(1, 4, 4) X(2, 1, 8) X(2, 2, 4) X(2, 4, 4) X(3, 2, 4) X(3, 4, 4) X(4, 2, 4) X(4, 4, 4)
+    X(1, 1, 8) X(1, 2, 4) X(1, 4, 4) X(2, 1, 8) X(2, 2, 4) X(2, 4, 4) X(3, 2, 4) X(3, 4, 4) X(4, 2, 4) X(4, 4, 4) X(3, 7, 4)
 #define MQ_STAGE(X) /* TM, TN, WM, WN, NST */ \
     X(3, 2, 2, 2, 6) X(4, 2, 2, 2, 4) X(3, 4, 2, 2, 4) X(4, 2, 2, 4, 4) X(5, 4, 2, 2, 4) X(7, 4, 2, 2, 3) X(8, 4, 2, 2, 3) X(8, 6, 2, 2, 2)
 static constexpr Bf16Tile kBf16Tiles[] = {
@@ -1659,12 +1661,12 @@ static constexpr TileCost kBf16Costs[] = {
     {3990.7, 490.23, 33.944, 0, 215.64}, {4232.3, 285.89, 67.673, 0, 121.71}, {4290.4, 1760.9, 116.09, 0, 101.7},
     {2500, 1917.2, 67.252, 0, 400}, {4165.3, 476.99, 85.889, 0, 152.39}, {3802.9, 1712.7, 145.39, 0, 63.315},
     {4418.7, 542.73, 126.77, 0, 42.119}, {3161.5, 2935.1, 160.67, 0, 139.48}, {3178.4, 1632.6, 142.34, 3.1851, 395.14},
-    {3862.2, 2348.2, 178.4, 0, 108.89}, {3306.3, 2445.4, 255.17, 0, 25.607}, {3621.8, 2048.8, 209.56, 109.8, 53.171},
-    {3817.3, 2209.3, 219.72, 163.53, 116.05}, {3155.8, 3662.8, 313.3, 93.312, 95.188},
-    {2998.9, 6086, 430.49, 59.295, 34.702}, {2467.5, 6351.1, 397.88, 240.48, 97.026}, {2354.8, 6066.9, 636.14, 0, 134.09},
-    {2523.8, 8830.3, 678.75, 188.09, 35.62}, {1771, 7053.4, 593.91, 212.65, 75.361},
-    {3188.5, 4334.3, 740.91, 276.68, 87.327}, {2283, 7691.4, 903.92, 286.82, 58.652},
-    {2665.9, 650.8, 106.65, 17.193, 247.09}};
+    {3862.2, 2348.2, 178.4, 0, 108.89}, {2134.7, 8581.8, 196.48, 21.579, 10}, {3306.3, 2445.4, 255.17, 0, 25.607},
+    {3621.8, 2048.8, 209.56, 109.8, 53.171}, {3817.3, 2209.3, 219.72, 163.53, 116.05},
+    {3155.8, 3662.8, 313.3, 93.312, 95.188}, {2998.9, 6086, 430.49, 59.295, 34.702},
+    {2467.5, 6351.1, 397.88, 240.48, 97.026}, {2354.8, 6066.9, 636.14, 0, 134.09}, {2523.8, 8830.3, 678.75, 188.09, 35.62},
+    {1771, 7053.4, 593.91, 212.65, 75.361}, {3188.5, 4334.3, 740.91, 276.68, 87.327},
+    {2283, 7691.4, 903.92, 286.82, 58.652}, {2665.9, 650.8, 106.65, 17.193, 247.09}};
 static_assert(sizeof(kBf16Costs) / sizeof(TileCost) == sizeof(kBf16Tiles) / sizeof(Bf16Tile), "one cost per tile");
 
 // us: the second pass of K slabs in the staged tiles, and each MB of partial sums
@@ -1698,6 +1700,9 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (tiles > (t.kernel == MQ_KERNEL_BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
         if (t.kernel == MQ_KERNEL_BF16_SHORT && (M > 16 || K > 1024)) continue;
+        // 112 rows of W: fewer trips of 33 to 48 tokens to the compute units where N is wide (48 on K = 5120, N = 51200 115 us in 48x64
+        // tiles, 99 here; 40 on N = 25600 54 and 47; 33 to 48 on N = 28672 1 to 5 % faster); fewer tokens have little to save
+        if (t.bn == 112 && (M <= 32 || M > 48)) continue;
         // 256x192 exists twice: staged for a few K steps (1424 tokens on K = 192, N = 5384 14.3 us against 14.7), else with X one
         // stage further ahead and 32x32 products (a tenth faster from K = 512 on)
         if (t.bn == 192 && (t.kernel == MQ_KERNEL_BF16_STAGE) != (K < 512)) continue;
@@ -1749,6 +1754,12 @@ int launch_ring(const GemmArgs &g0, hipStream_t s, int slabs)
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
 
+// Staged tiles: a W that one row of tiles reads is read past the last-level cache (256 MB) where it is more than this many
+// bytes.  us from HBM, plain / streamed: 200 tokens on K = 4096, N = 28672 (235 MB) 65.6 / 63.6, 128 tokens 59.9 / 55.4; 200 on
+// K = 5120, N = 51200 156 / 150; 128 on K = 4096, N = 6144 (50 MB) 29.5 / 28.0, but the weights of a small model may all be
+// waiting in that cache, and are then 21.2 / 28.1.
+static constexpr int64_t kStreamW = 96 << 20;
+
 template <int TM, int TN, int WM, int WN, int NST, bool OUT_BF16>
 int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
 {
@@ -1757,9 +1768,12 @@ int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
     g.ksplit = slabs;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m * tiles_n * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
+    const bool stream = tiles_m == 1 && g.N > kStreamW / 2 / g.K;
     // (the partial sums are FP32 for either output type)
-    auto *const kern = slabs > 1 ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>
-                                 : bf16_stage_kernel<TM, TN, WM, WN, NST, false, OUT_BF16>;
+    auto *const kern = slabs > 1 ? (stream ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, true, false>
+                                           : bf16_stage_kernel<TM, TN, WM, WN, NST, true, false, false>)
+                                 : (stream ? bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, OUT_BF16>
+                                           : bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, OUT_BF16>);
     const int rc = enqueue(kern, dim3((unsigned)(tiles_m * tiles_n * slabs)), dim3(64 * WM * WN),
                            stage_lds<TM, TN, WM, WN, NST>(), s, g, (int)tiles_m, (int)tiles_n);
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
@@ -2019,9 +2033,12 @@ int configure_gemm_kernels()
     MQ_RING(MQ_X)
 #undef MQ_X
 #define MQ_X(TM, TN, WM, WN, NST) \
-    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false>, \
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, false>, \
          stage_lds<TM, TN, WM, WN, NST>()); \
-    if (e == hipSuccess) e = set(bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>, stage_lds<TM, TN, WM, WN, NST>());
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, false>, \
+         stage_lds<TM, TN, WM, WN, NST>()); \
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, true, true, false>, bf16_stage_kernel<TM, TN, WM, WN, NST, true, false, false>, \
+         stage_lds<TM, TN, WM, WN, NST>());
     MQ_STAGE(MQ_X)
 #undef MQ_X
     return note_launch(e);
