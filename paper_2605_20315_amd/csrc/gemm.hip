@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
     // The lane offsets are relative to the first row of the wave tile (whose 64-bit address is
     // scalar), so they fit 32 bits for any operand size.
     uint32_t vc[8], vs[8];
-    // Running pointers to the K step that the next load_tile reads, for the first A / B row of
+    // Running pointers to the K step that the next loads read, for the first A / B row of
     // this wave's tile (codes, scales); advance() moves them on by one K step and stops at the
     // last step of K, so the loads issued past the end of a tile re-read that step.  (Advancing
     // costs some twenty scalar instructions per K step, placed under the MFMAs of the phase in
@@ -286,17 +286,22 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         }
     };
     RawTile st[NSETS];
-    auto load_tile = [&](RawTile &r) {
+    // load u of a K step: codes (u even) or scales of operand tile u / 2
+    auto load_one = [&](RawTile &r, int u) {
         auto rsrc = [](const char *p) {
             return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), 0, -1, 0x00020000);
         };
-        const __amdgpu_buffer_rsrc_t rac = rsrc(pa_c), rbc = rsrc(pb_c), ras = rsrc(pa_s), rbs = rsrc(pb_s);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const u32x4 c = __builtin_amdgcn_raw_buffer_load_b128(q < 4 ? rac : rbc, (int)vc[q], 0, 0);
+        const int q = u / 2;
+        if (u % 2 == 0) {
+            const u32x4 c = __builtin_amdgcn_raw_buffer_load_b128(rsrc(q < 4 ? pa_c : pb_c), (int)vc[q], 0, 0);
             r.c[q] = make_uint4(c[0], c[1], c[2], c[3]);
-            r.s[q] = __builtin_amdgcn_raw_buffer_load_b32(q < 4 ? ras : rbs, (int)vs[q], 0, 0);
+        } else {
+            r.s[q] = __builtin_amdgcn_raw_buffer_load_b32(rsrc(q < 4 ? pa_s : pb_s), (int)vs[q], 0, 0);
         }
+    };
+    auto load_tile = [&](RawTile &r) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) load_one(r, u);
     };
     auto advance = [&]() {
         const int64_t adv = -(int64_t)(t_next + 1 < KT);  // all ones while a next K step exists (no branch)
@@ -311,14 +316,15 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
     // One byte permute picks the lane's two scale bytes, or zeros for a K step past the end.
     uint32_t sg[8];
     const uint32_t sel_valid = 0x0C000C00u | (uint32_t)(2 * fhalf) | ((uint32_t)(2 * fhalf + 1) << 16);
+    auto prep_scale = [&](const RawTile &r, uint32_t sel, int q) {
+        uint32_t sc = r.s[q];
+        asm("" : "+v"(sc));  // first use of the prefetched register stays here
+        sg[q] = __builtin_amdgcn_perm(0u, sc, sel) << 7;
+    };
     auto prep_scales = [&](const RawTile &r, bool valid) {
         const uint32_t sel = valid ? sel_valid : 0x0C0C0C0Cu;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            uint32_t sc = r.s[q];
-            asm("" : "+v"(sc));  // first use of the prefetched register stays here
-            sg[q] = __builtin_amdgcn_perm(0u, sc, sel) << 7;
-        }
+        for (int q = 0; q < 8; ++q) prep_scale(r, sel, q);
     };
     uint4 fr[2][8];
     // q0 .. q1-1: the operand tiles to expand (0..3 = A row tiles, 4..7 = B row tiles)
@@ -330,12 +336,9 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
             asm("" : "+v"(w));
             const _Float16 sig = __builtin_bit_cast(_Float16, (uint16_t)(p < 2 ? sg[q] : sg[q] >> 16));
             const f16x2 s = {sig, sig};
-            // four conversions, then four multiplies: a multiply issued right behind the
-            // conversion it consumes stalls the wave (measured 36 instead of 33 cycles per MFMA).
-            // The empty asm statements order through their operands only; they must not be
+            // (The empty asm statements order through their operands only; they must not be
             // volatile: a volatile asm counts as a side effect that no memory operation may
-            // cross, which pinned the loads of a K step behind all conversions of their phase
-            // and cost 4 to 6 % of the kernel.
+            // cross.)
             f16x2 c0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 0);
             f16x2 c1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 1);
             f16x2 c2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 2);
@@ -347,14 +350,39 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         }
     };
     f32x16 acc[4][4];
-    auto mfmas = [&](const uint4(&f)[8]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                    __builtin_bit_cast(f16x8, f[i]), __builtin_bit_cast(f16x8, f[4 + j]), acc[i][j], 0, 0, 0);
+    // The two halves of expanding one operand tile of a phase: four conversions, and, behind the next MFMA, their four multiplies
+    // (a multiply right behind the conversion that it consumes stalls the wave).
+    f16x2 half[4];
+    auto convert = [&](const RawTile &r, int p, int q) {
+        uint32_t w = p == 0 ? r.c[q].x : p == 1 ? r.c[q].y : p == 2 ? r.c[q].z : r.c[q].w;
+        asm("" : "+v"(w));
+        half[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 0);
+        half[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 1);
+        half[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 2);
+        half[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 3);
     };
+    auto multiply = [&](int p, int q, uint4(&f)[8]) {
+        const _Float16 sig = __builtin_bit_cast(_Float16, (uint16_t)(p < 2 ? sg[q] : sg[q] >> 16));
+        const f16x2 s = {sig, sig};
+        f[q] = make_uint4(__builtin_bit_cast(uint32_t, half[0] * s), __builtin_bit_cast(uint32_t, half[1] * s),
+                          __builtin_bit_cast(uint32_t, half[2] * s), __builtin_bit_cast(uint32_t, half[3] * s));
+    };
+    // The 16 MFMAs of a phase on fragments f, slot(n) behind MFMA n: four VALU instructions and a load or a few scalar ones fit
+    // under an MFMA's 32 cycles.  Nothing moves from one slot to another: left to the compiler within a phase, with only the number of
+    // instructions per MFMA asked for, the fours got out of step with the MFMAs, and conversions met their multiplies
+    // without one in between.  us, asked for / slot by slot: 8192 tokens on K = 4096, N = 28672 1290 / 1262, on K = 14336,
+    // N = 4096 610 / 603; 16384 on N = 4096 371 / 365; 1000 on N = 28672 183 / 181; 4096 on N = 6144 149.3 / 147.2.
+    auto phase = [&](const uint4(&f)[8], auto &&slot) {
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            acc[n / 4][n % 4] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                __builtin_bit_cast(f16x8, f[n / 4]), __builtin_bit_cast(f16x8, f[4 + n % 4]), acc[n / 4][n % 4], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            slot(n);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int64_t adv = 0;
     // one K step; R = kt % NSETS is the register set that holds tile kt
     auto kstep = [&](int kt, auto rr) {
         constexpr int R = decltype(rr)::value;
@@ -362,29 +390,63 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         // The last two A row tiles of this step's first phase are expanded here, right before
         // the MFMAs that use them (the ninth onwards), not in the load phase of the previous K
         // step, which is the one phase that fills the wave's issue slots (+0.5-1 %; three tiles
-        // deferred: no better).
-        expand_phase(cur, 0, fr[0], 2, 4);
-        expand_phase(cur, 1, fr[1]);
-        mfmas(fr[0]);
-        sched_phase<16, 5>();
-        expand_phase(cur, 2, fr[0]);
-        mfmas(fr[1]);
-        sched_phase<16, 4>();
-        // the scalar pointer arithmetic of the loads below, spread under this phase's MFMAs
-        advance();
-        expand_phase(cur, 3, fr[1]);
-        mfmas(fr[0]);
-        sched_phase<16, 4, 0, 16>();
+        // deferred: no better).  Ten tiles in sixteen slots: five in eight, two of them sharing a slot with the multiplies
+        // of the one before.
+        phase(fr[0], [&](int n) {
+            const int h = n / 8, e = n % 8;  // c m|c m c m|c m c m
+            auto tile = [&](int x, bool c) {  // the x-th of the ten
+                const int q = x < 2 ? 2 + x : x - 2;
+                if (c)
+                    convert(cur, x < 2 ? 0 : 1, q);
+                else
+                    multiply(x < 2 ? 0 : 1, q, x < 2 ? fr[0] : fr[1]);
+            };
+            const int t = 5 * h;
+            if (e == 0) tile(t, true);
+            if (e == 1) tile(t, false), tile(t + 1, true);
+            if (e == 2) tile(t + 1, false);
+            if (e == 3) tile(t + 2, true);
+            if (e == 4) tile(t + 2, false), tile(t + 3, true);
+            if (e == 5) tile(t + 3, false);
+            if (e == 6) tile(t + 4, true);
+            if (e == 7) tile(t + 4, false);
+        });
+        phase(fr[1], [&](int n) {
+            if (n % 2 == 0)
+                convert(cur, 2, n / 2);
+            else
+                multiply(2, n / 2, fr[0]);
+        });
+        phase(fr[0], [&](int n) {
+            if (n % 2 == 0)
+                convert(cur, 3, n / 2);
+            else
+                multiply(3, n / 2, fr[1]);
+            // the scalar pointer arithmetic of the loads below, spread under this phase's MFMAs
+            if (n == 1) adv = -(int64_t)(t_next + 1 < KT), t_next -= (int)adv;
+            if (n == 4) pa_c += g.a_c_step & adv;
+            if (n == 7) pb_c += g.b_c_step & adv;
+            if (n == 10) pa_s += g.a_s_step & adv;
+            if (n == 13) pb_s += g.b_s_step & adv;
+        });
         // The only loads in flight here are the 16 of the next K step, a whole step old: one wait
         // for all of them instead of one in front of each first use (this phase is the one that
         // fills the wave's issue slots, and a wait is an instruction like any other: +0.5-0.8 %).
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        prep_scales(nxt, kt + 1 < k1);
-        expand_phase(nxt, 0, fr[0], 0, 2);
-        expand_phase(nxt, 0, fr[0], 4, 8);
-        load_tile(cur);
-        mfmas(fr[1]);
-        sched_phase<16, 5, 16>();
+        const uint32_t sel = kt + 1 < k1 ? sel_valid : 0x0C0C0C0Cu;
+        phase(fr[1], [&](int n) {
+            if (n < 4) {
+                prep_scale(nxt, sel, 2 * n);
+                prep_scale(nxt, sel, 2 * n + 1);
+            } else {
+                const int x = (n - 4) / 2, q = x < 2 ? x : x + 2;
+                if (n % 2 == 0)
+                    convert(nxt, 0, q);
+                else
+                    multiply(0, q, fr[0]);
+            }
+            load_one(cur, n);
+        });
     };
 
     // Persistent workgroups: tile ids blockIdx.x, blockIdx.x + gridDim.x, ...  The first loads of
