@@ -299,9 +299,13 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
             r.s[q] = __builtin_amdgcn_raw_buffer_load_b32(rsrc(q < 4 ? pa_s : pb_s), (int)vs[q], 0, 0);
         }
     };
+    // The K steps in front of the loop, set by set: left to itself the compiler put loads of the second set before some of the first,
+    // and the first MFMAs then waited for both (row-major, 4096 tokens on K = 512, N = 4096 28.1 us, in order 27.6; 2500 tokens 28.7 and 28.1).
+    // Not where four waves share K: 488 tokens on K = 960, N = 5120 15.4 us, set by set 16.0.
     auto load_tile = [&](RawTile &r) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) load_one(r, u);
+        if constexpr (SPLIT < 4) __builtin_amdgcn_sched_barrier(0);
     };
     auto advance = [&]() {
         const int64_t adv = -(int64_t)(t_next + 1 < KT);  // all ones while a next K step exists (no branch)
@@ -433,6 +437,9 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         // for all of them instead of one in front of each first use (this phase is the one that
         // fills the wave's issue slots, and a wait is an instruction like any other: +0.5-0.8 %).
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        // The scales' loads first, then the codes': row-major operands, whose loads touch a line per row, take 1 to 3 % less than with
+        // codes and scales in turn, which had made them slower with the slots than without (8192 tokens on K = 14336, N = 4096 988 us
+        // before the slots, 997 in turn, 958 now; 3500 tokens 444, 450, 432); K-step-major the same within 0.3 %.
         const uint32_t sel = kt + 1 < k1 ? sel_valid : 0x0C0C0C0Cu;
         phase(fr[1], [&](int n) {
             if (n < 4) {
@@ -445,7 +452,7 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
                 else
                     multiply(0, q, fr[0]);
             }
-            load_one(cur, n);
+            load_one(cur, n < 8 ? 2 * n + 1 : 2 * (n - 8));
         });
     };
 

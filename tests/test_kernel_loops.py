@@ -1,6 +1,7 @@
-"""What the compiler made of the staged BF16 kernels: their K loops move no accumulator between the two kinds of register.  Quads stored
-straight from accumulation registers had the compiler keep half of the accumulators in each kind and move all of
-them twice per K step (three moves per MFMA), which the sums' bits do not show.  Read from the library that was built here."""
+"""What the compiler made of two kernels, read from the library that was built here; the results' bits do not show it.  The K loops of
+the staged BF16 kernels move no accumulator between the two kinds of register (quads stored straight from accumulation registers had the
+compiler keep half of them in each kind and move all of them twice per K step).  The direct NVFP4 kernels (K whole or in halves) start on
+their first K step without a wait for the second one's loads."""
 import os
 import re
 import shutil
@@ -28,17 +29,36 @@ def _innermost_mfma_loops(text):
     return [c for c in counts if c[0]]
 
 
-@pytest.mark.skipif(not os.path.exists(TOOLS + "llvm-objdump"), reason="no disassembler")
-def test_staged_bf16_loops_move_no_accumulators(tmp_path):
+def _kernels(tmp_path, part_of_name):
+    """{name: disassembly} of the library's kernels with this in their names."""
+    if not os.path.exists(TOOLS + "llvm-objdump"):
+        pytest.skip("no disassembler")
     lib = tmp_path / "lib.so"
     shutil.copy(_lib.LIB_PATH, lib)
     subprocess.run([TOOLS + "llvm-objdump", "--offloading", str(lib)], cwd=tmp_path, check=True, capture_output=True)
-    seen = {}
+    found = {}
     for part in sorted(tmp_path.glob("lib.so.*gfx950")):
         text = subprocess.run([TOOLS + "llvm-objdump", "-d", "--demangle", str(part)], check=True, capture_output=True, text=True).stdout
         for kernel in re.split(r"\n(?=[0-9a-f]{16} <)", text):
-            name = re.match(r"[0-9a-f]{16} <(?:void )?(?:mq::)?(?:\(anonymous namespace\)::)?(bf16_stage_kernel<.*?>)", kernel)
+            name = re.match(r"[0-9a-f]{16} <.*?(" + part_of_name + r"<.*?>)\(", kernel)
             if name:
-                seen[name.group(1)] = _innermost_mfma_loops(kernel)
+                found[name.group(1)] = kernel
+    return found
+
+
+def test_staged_bf16_loops_move_no_accumulators(tmp_path):
+    seen = {name: _innermost_mfma_loops(text) for name, text in _kernels(tmp_path, "bf16_stage_kernel").items()}
     assert len(seen) >= 32 and all(len(loops) == 1 for loops in seen.values()), seen
     assert not {n: c for n, c in seen.items() if c[0][1]}, "accumulator moves in a K loop (MFMAs, moves)"
+
+
+def test_direct_fp4_starts_with_the_second_k_step_in_flight(tmp_path):
+    kernels = _kernels(tmp_path, "gemm_fp4_direct")
+    assert len(kernels) == 6
+    for name, text in kernels.items():
+        if name.endswith(", 4>"):  # a wave has a quarter of K: faster with both steps' loads mixed
+            continue
+        before = text[:text.index("v_mfma")]
+        after_loads = before[before.rindex("buffer_load"):]
+        waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", after_loads)]
+        assert before.count("buffer_load") == 32 and min(waits, default=16) >= 16, (name, waits)
