@@ -220,6 +220,8 @@ int nvfp4_gemm_noalloc(const uint8_t *a_codes, const uint8_t *a_scales, const fl
  * speed-up is measured against): Y = X . W^T, X [M, K] and W [N, K] BF16 with row strides
  * ldx, ldw elements, FP32 accumulation, output as in nvfp4_gemm.
  * K % 8 == 0; x, w 16-byte aligned; ldx % 8 == 0, ldw % 8 == 0; y as in nvfp4_gemm.
+ * The same call on the same values gives the same bits.  The order of a row's FP32 sums may depend on its place in X
+ * (from K = 4096 on it does in the larger tiles), so two equal rows of one X may differ in the last bits of Y.
  */
 int bf16_gemm(const void *x_bf16, int64_t ldx, const void *w_bf16, int64_t ldw,
               int64_t M, int64_t N, int64_t K, void *y, int64_t ldy, int out, void *stream);

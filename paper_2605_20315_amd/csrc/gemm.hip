@@ -970,14 +970,19 @@ __device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off
 
 // The order in which a workgroup takes its K steps: groups of four in turn, each from a step of its own on.  Workgroups of
 // one XCD that read the same rows would otherwise all reach a K step together, and all of them wait for its trip from
-// memory; so one of them makes the trip and the others, a step or two later, find the lines in L2.  From `from` steps on: a
-// short K has the first trip of every line at its start, where four times as many different lines in flight cost more (staged
-// tiles, K = 512 to 1800: 3.5 % slower; 2000 to 4000: 1 % slower to 5 % faster; 4096: 3 % faster; 5120 and more: 7 %, up to 26 %).
-// Groups of two or eight: the same within 1 %.
+// memory; so one of them makes the trip and the others, a step or two later, find the lines in L2.  It is the tiles in one column
+// (tm), which share rows of W, that have to differ: with a start from tn alone the gain is gone (1.00 of the time without).  So
+// the order of a row's FP32 sums depends on its tile.
+// K slabs always; else from K = 4096 and 16 MB of W on.  Time with / without it, weights from HBM: 0.965 in staged tiles at K = 4096, 0.92
+// beyond (0.975 and 0.955 in gemm_bf16_d2l), 0.944 with slabs.  A shorter K has the first trip of every line at its start, where four times as
+// many different lines in flight cost more (staged tiles, K = 512 to 1800 1.035, 2000 to 4000 0.95 to 1.01); a smaller W is in L2 by
+// then (2227 tokens on K = 4096, N = 768 23.2 us with it, 21.3 without; 4500 tokens 32.4 and 31.3).  Where a larger W waits in the
+// last-level cache, there is less of a trip to share: 1.01 in staged tiles (1.02 at K = 4096, 1.04 at most), 1.006 in gemm_bf16_d2l;
+// the rule cannot see that.  Groups of two or eight: the same within 1 %.
 struct KOrder {
     int KT, whole, first;
-    __device__ __forceinline__ KOrder(int kt, int from, int tm, int tn)
-        : KT(kt), whole(kt >= from ? kt & ~3 : 0), first(__builtin_amdgcn_readfirstlane(tm + 2 * tn))
+    __device__ __forceinline__ KOrder(int kt, bool own, int tm, int tn)
+        : KT(kt), whole(own ? kt & ~3 : 0), first(__builtin_amdgcn_readfirstlane(tm + 2 * tn))
     {
     }
     __device__ __forceinline__ int at(int k) const
@@ -985,6 +990,7 @@ struct KOrder {
         k = k < KT ? k : KT - 1;  // past the end: a step that was read before, never used
         return k < whole ? (k & ~3) | ((k + first) & 3) : k;
     }
+    static __device__ __forceinline__ bool pays(const GemmArgs &g) { return g.K >= 4096 && g.N * g.K >= (8 << 20); }
 };
 
 // Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
@@ -1022,7 +1028,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
     const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
     const int frow = lane & 31, fhalf = lane >> 5;
     const int KT = (int)(g.K / BK);
-    const KOrder order(KT, 64, tm, tn);
+    const KOrder order(KT, KOrder::pays(g), tm, tn);
 
     // load u of this wave: rows 8 * (wave * GA + u) .. + 7 of the A tile (u < GA), else of the B tile
     // byte offsets from the tile's first row: 32 bits for any operand size
@@ -1387,7 +1393,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
     const int KA = (int)(g.K / BK), SL = SLABS ? (KA + g.ksplit - 1) / g.ksplit : KA;
     const int s0 = slab * SL, KT = s0 + SL < KA ? SL : KA - s0;
 
-    const KOrder order(KT, SLABS ? 0 : 64, tm, tn);
+    const KOrder order(KT, SLABS || KOrder::pays(g), tm, tn);
 
     uint32_t vo[NL];
 #pragma unroll

@@ -1,5 +1,5 @@
 """GPU parity of the BF16 product where K is cut into slabs across workgroups in the staged tiles, where workgroups take
-the K steps of a long K in orders of their own, in the decode tile of 112 rows of W, and where a W that one row of tiles reads is
+the K steps of a long K in orders of their own (and where they do not, for a W below 16 MB), in the decode tile of 112 rows of W, and where a W that one row of tiles reads is
 larger than 96 MB (read past the last-level cache): the last slab shorter than the others, groups of four steps with
 none to three left over, ragged M and N, strided operands and output, a workspace that holds fewer slabs than the rule would
 take.  Every output is compared with the oracle's FP64 product; nothing outside [M, N] and the slabs' sums may be written."""
@@ -11,7 +11,7 @@ import oracle
 import paper_2605_20315_amd as mq
 from paper_2605_20315_amd import workloads as wl
 
-from _gpu_util import check_gemm_bf16, check_gemm_fp32, check_workspace_use, dev_bf16, full_of_nan, host_bits
+from _gpu_util import ACC_REL, check_gemm_bf16, check_gemm_fp32, check_workspace_use, dev_bf16, full_of_nan, host_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 SLABS = [(70, 4100, 12480, "bf16_stage", (96, 128)), (82, 700, 8576, "bf16_stage", (96, 64)), (69, 80, 15168, "bf16_stage", (128, 64)), (131, 808, 11776, "bf16_stage", (96, 128)),
          (294, 524, 13376, "bf16_stage", (128, 128)), (129, 2360, 13760, "bf16_stage", (160, 128))]
 ORDERS = [(969, 6667, 512, "bf16_d2l", (256, 192)), (1027, 7244, 4160, "bf16_d2l", (256, 192)), (1539, 6957, 4224, "bf16_d2l", (256, 256)),
-          (257, 1030, 4096, None, None), (257, 1030, 4288, None, None)]
+          (257, 5133, 4096, "bf16_stage", (96, 64)), (257, 5133, 4288, "bf16_stage", (96, 64)), (1048, 7181, 4096, "bf16_d2l", (256, 192)),
+          (1048, 7181, 4288, "bf16_d2l", (256, 192)), (2227, 765, 4096, "bf16_stage", (128, 64)),
+          (257, 1030, 4096, "bf16_ring", (48, 32)), (257, 1030, 4288, "bf16_ring", (48, 32))]
 WIDE = [(44, 28077, 1088, "bf16_ring", (48, 112)), (33, 28077, 1152, "bf16_ring", (48, 112)), (100, 12305, 4160, "bf16_stage", None)]
 
 
@@ -70,3 +72,30 @@ def test_orders_of_the_k_steps_and_wide_w(M, N, K, kernel, tile):
     assert kernel in (None, plan["kernel"]) and tile in (None, plan["tile"])
     xd, wd, want = _operands(M, N, K)
     _check(xd, wd, None, want)
+
+
+@pytest.mark.parametrize("M,N,K,kernel,tile,own_orders", [
+    (1048, 7181, 4096, "bf16_d2l", (256, 192), True), (2048, 7168, 4160, "bf16_d2l", (256, 256), True), (257, 5133, 4288, "bf16_stage", (96, 64), True),
+    (2227, 768, 4096, "bf16_stage", (128, 64), False), (969, 6667, 512, "bf16_d2l", (256, 192), False), (530, 7457, 192, "bf16_stage", (160, 128), False)])
+def test_equal_rows_of_x(M, N, K, kernel, tile, own_orders):
+    """What the header says of two equal rows: the same sums in every tile, but for a long K on a large W, where a tile's order of K is its
+    own and they may differ by what the accumulation rounds; the same bits from run to run in any case."""
+    plan = mq.mq_bf16_gemm_launches(M, N, K, 0)[0]
+    assert (plan["kernel"], plan["tile"]) == (kernel, tile)
+    print(f"\n[case] equal rows M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rows = torch.randn((16, K), device="cuda", generator=g).to(torch.bfloat16)
+    x = rows.repeat((M + 15) // 16, 1)[:M].contiguous()
+    w = (torch.randn((N, K), device="cuda", generator=g) * K ** -0.5).to(torch.bfloat16)
+    ld = (N + 7) // 8 * 8
+    out = [torch.empty((M, ld), dtype=torch.float32, device="cuda")[:, :N] for _ in range(2)]
+    for y in out:
+        mq.bf16_gemm(x, w, mq.MQ_OUT_FP32, y)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    first = out[0][:16].repeat((M + 15) // 16, 1)[:M]
+    if own_orders:
+        bound = 2 * ACC_REL * x.float().norm(dim=1)[:, None] * w.float().norm(dim=1)[None, :]
+        assert bool(((out[0] - first).abs() <= bound).all())
+    else:
+        assert torch.equal(out[0], first)
