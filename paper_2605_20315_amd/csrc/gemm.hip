@@ -1372,7 +1372,7 @@ __global__ __launch_bounds__(64 * S) void bf16_short_kernel(GemmArgs g, int tile
 // long K, what a compute unit loads: 48 to 55 bytes per ns whatever the depth (32 KB of lines in flight).  There K
 // slabs across workgroups (SLABS) allow larger tiles, whose operands are fewer bytes per product: 200 tokens on
 // K = 14336, N = 4096 3.7 MB per unit and 51 us in 64x64 tiles, 1.8 MB and 41 us in 128x128 with four slabs, second pass included.
-template <int TM, int TN, int WM, int WN, int NST, bool SLABS, bool STREAM, bool OUT_BF16>
+template <int TM, int TN, int WM, int WN, int NST, bool SLABS, bool OUT_BF16>
 __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, int tiles_m, int tiles_n)
 {
     constexpr int W = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STAGE = (BM + BN) * 128;
@@ -1408,7 +1408,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
         if (u < NLX)
             load_rows_to_lds<false>(lds0 + stage + (u * W + wave) * 1024, vo[u], tx + ko);
         else
-            load_rows_to_lds<STREAM>(lds0 + stage + BM * 128 + ((u - NLX) * W + wave) * 1024, vo[u], tw + ko);
+            load_rows_to_lds<false>(lds0 + stage + BM * 128 + ((u - NLX) * W + wave) * 1024, vo[u], tw + ko);
     };
     const int row = lane & 15, grp = lane >> 4;
     int fx[2], fw[2];
@@ -1826,12 +1826,10 @@ int launch_ring(const GemmArgs &g0, hipStream_t s, int slabs)
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
 }
 
-// Staged tiles: a W that one row of tiles reads is read past the last-level cache (256 MB) where it is more than this many
-// bytes.  us from HBM, plain / streamed: 200 tokens on K = 4096, N = 28672 (235 MB) 65.6 / 63.6, 128 tokens 59.9 / 55.4; 200 on
-// K = 5120, N = 51200 156 / 150; 128 on K = 4096, N = 6144 (50 MB) 29.5 / 28.0, but the weights of a small model may all be
-// waiting in that cache, and are then 21.2 / 28.1.
-static constexpr int64_t kStreamW = 96 << 20;
-
+// W through the last-level cache (256 MB) also where one row of tiles reads it.  us of 128 tokens on K = 4096, N = 28672 (224 MB), through it /
+// past it: from HBM 56.3 / 54.2, a W that waits there 38.7 / 55.5; over 66 to 256 tokens and W of 96 to 256 MB 0.94 to 1.015 of the
+// time from HBM, 1.05 to 1.55 where it waits.  Larger ones: 266 MB 1.3 when read again and again, 288 to 448 MB 0.97 to 1.04
+// either way, 500 MB 0.975: no line that gains and costs nothing.
 template <int TM, int TN, int WM, int WN, int NST, bool OUT_BF16>
 int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
 {
@@ -1840,12 +1838,9 @@ int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
     g.ksplit = slabs;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m * tiles_n * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    const bool stream = tiles_m == 1 && g.N > kStreamW / 2 / g.K;
     // (the partial sums are FP32 for either output type)
-    auto *const kern = slabs > 1 ? (stream ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, true, false>
-                                           : bf16_stage_kernel<TM, TN, WM, WN, NST, true, false, false>)
-                                 : (stream ? bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, OUT_BF16>
-                                           : bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, OUT_BF16>);
+    auto *const kern = slabs > 1 ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>
+                                 : bf16_stage_kernel<TM, TN, WM, WN, NST, false, OUT_BF16>;
     const int rc = enqueue(kern, dim3((unsigned)(tiles_m * tiles_n * slabs)), dim3(64 * WM * WN),
                            stage_lds<TM, TN, WM, WN, NST>(), s, g, (int)tiles_m, (int)tiles_n);
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
@@ -2105,12 +2100,9 @@ int configure_gemm_kernels()
     MQ_RING(MQ_X)
 #undef MQ_X
 #define MQ_X(TM, TN, WM, WN, NST) \
-    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false, false>, \
+    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false>, \
          stage_lds<TM, TN, WM, WN, NST>()); \
-    both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, true, false>, \
-         stage_lds<TM, TN, WM, WN, NST>()); \
-    both(bf16_stage_kernel<TM, TN, WM, WN, NST, true, true, false>, bf16_stage_kernel<TM, TN, WM, WN, NST, true, false, false>, \
-         stage_lds<TM, TN, WM, WN, NST>());
+    if (e == hipSuccess) e = set(bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>, stage_lds<TM, TN, WM, WN, NST>());
     MQ_STAGE(MQ_X)
 #undef MQ_X
     return note_launch(e);
