@@ -401,14 +401,19 @@ __global__ __launch_bounds__(64 * ROWS) void rmsnorm_quantize_kernel(const uint1
 // and writes 0.5625 bytes per element.  A workgroup moves 32 rows x 16 K steps through LDS, so that both
 // sides see whole cache lines: 512 contiguous code bytes per row in the row-major order, 1 KB per K step
 // in the K-step-major one: [28672, 4096] 32 us (4.2 TB/s) in either direction, against 40 us to the K-step-major
-// order and 54 us from it with one thread per 32-byte unit, which touched a line per lane on one side.  Codes are read and written
-// past the last-level cache (7 MB of them and more come here; nothing reads them twice): inputs from HBM 29.5 -> 26.0 us,
-// behind the quantizer that wrote them [28672, 4096] scale, quantize and convert 119 -> 113 us, [4096, 14336] 66 -> 62.
+// order and 54 us from it with one thread per 32-byte unit, which touched a line per lane on one side.  STREAM: codes are read and written
+// past the last-level cache, whose room is better left to what is read again: from HBM 0.70 to 0.87 of the time ([28672, 4096] 29.0 -> 23.9 us to
+// the K-step-major order, 29.6 -> 21.9 from it), behind the quantizer that wrote them quantize and convert together 0.92 to 0.99
+// (74.8 -> 68.5 us; 13.6 of 14.2 at [4096, 4096]).  Only where the very same two buffers are converted again and again and all is
+// waiting in the cache does it cost: 11 to 18 MB 1.03 to 1.15 of the time.  From the K-step-major order smaller tensors are faster
+// through the cache (from HBM [2048, 4096] 4.6 us, 5.2 past it, [2432, 4096] 4.9 and 5.4; [4096, 2560] 6.2 and 5.6, [2816, 4096]
+// 6.5 and 5.5), hence the line at kStreamUnits; the other order's come here from 6.8 MB on, past that line.
 // LDS rows hold 32 chunks of 16 bytes plus two: the reads of 8 rows x 2 halves of a K step then fall on
 // different banks.
 constexpr int R_ROWS = 32, R_STEPS = 16, R_CHUNKS = 2 * R_STEPS, R_STRIDE = R_CHUNKS + 2;
+constexpr int64_t kStreamUnits = 5 << 15;  // of 36 bytes: 5.6 MB
 
-template <bool TO_KTILE>
+template <bool TO_KTILE, bool STREAM>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
@@ -427,13 +432,15 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
     auto inside = [&](int row, int t) { return r0 + row < rows && t0 + t < ksteps; };
     auto lin_at = [&](int row, int t) { return (r0 + row) * row_stride + t0 + t; };   // unit (row, K step)
     auto kt_at = [&](int row, int t) { return (int64_t)(t0 + t) * rows + r0 + row; };
+    auto get = [](const uint4 *p) { return STREAM ? load_stream(p) : *p; };
+    auto put = [](uint4 *p, uint4 v) { STREAM ? store_stream(p, v) : (void)(*p = v); };
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
         int row, chunk;
         TO_KTILE ? lin(j * kThreads + threadIdx.x, row, chunk) : kt(j * kThreads + threadIdx.x, row, chunk);
         if (inside(row, chunk / 2))
-            lc[row * R_STRIDE + chunk] = load_stream(reinterpret_cast<const uint4 *>(src_c) +
-                                                     (TO_KTILE ? lin_at(row, chunk / 2) : kt_at(row, chunk / 2)) * 2 + chunk % 2);
+            lc[row * R_STRIDE + chunk] = get(reinterpret_cast<const uint4 *>(src_c) +
+                                             (TO_KTILE ? lin_at(row, chunk / 2) : kt_at(row, chunk / 2)) * 2 + chunk % 2);
     }
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_STEPS / kThreads; ++j) {
@@ -449,8 +456,8 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
         int row, chunk;
         TO_KTILE ? kt(j * kThreads + threadIdx.x, row, chunk) : lin(j * kThreads + threadIdx.x, row, chunk);
         if (inside(row, chunk / 2))
-            store_stream(reinterpret_cast<uint4 *>(dst_c) + (TO_KTILE ? kt_at(row, chunk / 2) : lin_at(row, chunk / 2)) * 2 + chunk % 2,
-                         lc[row * R_STRIDE + chunk]);
+            put(reinterpret_cast<uint4 *>(dst_c) + (TO_KTILE ? kt_at(row, chunk / 2) : lin_at(row, chunk / 2)) * 2 + chunk % 2,
+                lc[row * R_STRIDE + chunk]);
     }
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_STEPS / kThreads; ++j) {
@@ -711,7 +718,9 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
             // (a launch sees its K steps as the first ones: the arrays from there on, with the whole row's stride)
             const int64_t t = g0 * R_STEPS, left = ksteps - t < ng * R_STEPS ? ksteps - t : ng * R_STEPS;
             const int64_t from = to_ktile ? t : t * rows, to = to_ktile ? t * rows : t;
-            auto kern = to_ktile ? relayout_kernel<true> : relayout_kernel<false>;
+            auto kern = to_ktile               ? relayout_kernel<true, true>
+                        : units < kStreamUnits ? relayout_kernel<false, false>
+                                               : relayout_kernel<false, true>;
             const int rc = enqueue(kern, dim3((unsigned)(n * ng)), dim3(kThreads), 0, s, src_c + from * 32, src_s + from * 4,
                                    dst_c + to * 32, dst_s + to * 4, rows, p0 * R_ROWS, ksteps, (int)left, (int)ng);
             if (rc != MQ_OK) return rc;

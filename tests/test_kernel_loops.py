@@ -1,7 +1,8 @@
-"""What the compiler made of two kernels, read from the library that was built here; the results' bits do not show it.  The K loops of
+"""What the compiler made of some kernels, read from the library that was built here; the results' bits do not show it.  The K loops of
 the staged BF16 kernels move no accumulator between the two kinds of register (quads stored straight from accumulation registers had the
 compiler keep half of them in each kind and move all of them twice per K step).  The direct NVFP4 kernels (K whole or in halves) start on
-their first K step without a wait for the second one's loads."""
+their first K step without a wait for the second one's loads.  The conversion from the K-step-major order exists for smaller tensors without
+non-temporal accesses."""
 import os
 import re
 import shutil
@@ -62,3 +63,10 @@ def test_direct_fp4_starts_with_the_second_k_step_in_flight(tmp_path):
         after_loads = before[before.rindex("buffer_load"):]
         waits = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", after_loads)]
         assert before.count("buffer_load") == 32 and min(waits, default=16) >= 16, (name, waits)
+
+
+def test_conversion_past_the_cache_only_where_it_pays(tmp_path):
+    kernels = _kernels(tmp_path, "relayout_kernel")
+    streamed = {name: (len(re.findall(r"global_load_dwordx4.* nt", text)), len(re.findall(r"global_store_dwordx4.* nt", text)))
+                for name, text in kernels.items()}
+    assert streamed == {"relayout_kernel<true, true>": (4, 4), "relayout_kernel<false, true>": (4, 4), "relayout_kernel<false, false>": (0, 0)}
