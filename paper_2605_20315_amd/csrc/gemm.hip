@@ -106,11 +106,10 @@ __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int &t
     tile_of_logical(logical_id(wg, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
 }
 
-// Scheduling hint for one phase: per MFMA a few VALU instructions, and now and then a global load
-// or a scalar instruction.  Nothing moves across a phase
+// Scheduling hint for one phase: per MFMA a few VALU instructions, and now and then a global load.  Nothing moves across a phase
 // boundary: in particular no consumer of a global load is hoisted towards the load, which would
 // turn the prefetch distance into a stall.
-template <int MFMAS, int VALU_PER, int VMEMS = 0, int SALUS = 0>
+template <int MFMAS, int VALU_PER, int VMEMS = 0>
 __device__ __forceinline__ void sched_phase()
 {
 #pragma unroll
@@ -118,7 +117,6 @@ __device__ __forceinline__ void sched_phase()
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // MFMA
         if (VALU_PER > 0) __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER, 0);
         if (VMEMS > 0 && i < VMEMS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-        if (SALUS > 0 && i < SALUS) __builtin_amdgcn_sched_group_barrier(0x004, 1, 0);  // SALU
     }
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -331,14 +329,14 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
         for (int q = 0; q < 8; ++q) prep_scale(r, sel, q);
     };
     uint4 fr[2][8];
-    // q0 .. q1-1: the operand tiles to expand (0..3 = A row tiles, 4..7 = B row tiles)
-    auto expand_phase = [&](const RawTile &r, int p, uint4(&f)[8], int q0 = 0, int q1 = 8) {
+    // In front of the loop: the first phase's tiles (0..3 = A row tiles, 4..7 = B row tiles) but for the two that kstep expands.
+    auto expand_first = [&](const RawTile &r) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            if (q < q0 || q >= q1) continue;
-            uint32_t w = p == 0 ? r.c[q].x : p == 1 ? r.c[q].y : p == 2 ? r.c[q].z : r.c[q].w;
+            if (q == 2 || q == 3) continue;
+            uint32_t w = r.c[q].x;
             asm("" : "+v"(w));
-            const _Float16 sig = __builtin_bit_cast(_Float16, (uint16_t)(p < 2 ? sg[q] : sg[q] >> 16));
+            const _Float16 sig = __builtin_bit_cast(_Float16, (uint16_t)sg[q]);
             const f16x2 s = {sig, sig};
             // (The empty asm statements order through their operands only; they must not be
             // volatile: a volatile asm counts as a side effect that no memory operation may
@@ -349,8 +347,8 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
             f16x2 c3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 3);
             asm("" : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3));
             c0 *= s, c1 *= s, c2 *= s, c3 *= s;
-            f[q] = make_uint4(__builtin_bit_cast(uint32_t, c0), __builtin_bit_cast(uint32_t, c1),
-                              __builtin_bit_cast(uint32_t, c2), __builtin_bit_cast(uint32_t, c3));
+            fr[0][q] = make_uint4(__builtin_bit_cast(uint32_t, c0), __builtin_bit_cast(uint32_t, c1),
+                                  __builtin_bit_cast(uint32_t, c2), __builtin_bit_cast(uint32_t, c3));
         }
     };
     f32x16 acc[4][4];
@@ -477,8 +475,7 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
         prep_scales(st[0], k0 < k1);
-        expand_phase(st[0], 0, fr[0], 0, 2);
-        expand_phase(st[0], 0, fr[0], 4, 8);
+        expand_first(st[0]);
         // No separate tail: the loop runs whole groups of NSETS K steps, and a step past the end
         // multiplies by zero scales.  (Peeled tail steps make the compiler shuffle all 256
         // accumulator registers at the control-flow joins.)
@@ -494,9 +491,9 @@ __global__ __launch_bounds__(256) void gemm_fp4_direct(GemmArgs g, int tiles_m, 
             set_tile((int64_t)tm * BM, (int64_t)tn * BN);
 #pragma unroll
             for (int u = 0; u < NSETS; ++u) {
-        if (u) advance();
-        load_tile(st[u]);
-    }
+                if (u) advance();
+                load_tile(st[u]);
+            }
         }
         if constexpr (SPLIT == 1) {
             epilogue<C, OUT_BF16>(g, acc, scale, m0, n0, wm0, wn0, frow, fhalf);
@@ -1744,6 +1741,9 @@ static_assert(sizeof(kBf16Costs) / sizeof(TileCost) == sizeof(kBf16Tiles) / size
 // us: the second pass of K slabs in the staged tiles, and each MB of partial sums
 static constexpr double kBf16SecondPass = 3.08, kBf16PartialSums = 0.212;
 
+// Whether a staged tile of `bn` rows of W exists with K slabs: 256x192 runs below K = 512 only, slabs are for a long K.
+constexpr bool stage_slabs(int bn) { return bn != 192; }
+
 struct Bf16Plan {
     int tile;   // index into kBf16Tiles
     int slabs;  // K slabs across workgroups (1: none)
@@ -1789,7 +1789,7 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
             const int64_t slabs = cus / tiles < slab_limit ? cus / tiles : slab_limit;
             if (slabs >= 2) take(us(slabs) + 3.0, slabs);
         }
-        if (t.kernel == MQ_KERNEL_BF16_STAGE && M > 64)
+        if (t.kernel == MQ_KERNEL_BF16_STAGE && M > 64 && stage_slabs(t.bn))
             for (int64_t slabs = 2; slabs <= slab_limit && slabs * tiles <= cus; ++slabs) {
                 const int64_t part = (K / BK + slabs - 1) / slabs;
                 if ((slabs - 1) * part >= K / BK) continue;  // (the last one would be empty)
@@ -1838,9 +1838,13 @@ int launch_stage(const GemmArgs &g0, hipStream_t s, int slabs)
     g.ksplit = slabs;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m * tiles_n * slabs > 0x7FFFFFFF) return MQ_ERR_SHAPE;
-    // (the partial sums are FP32 for either output type)
-    auto *const kern = slabs > 1 ? bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>
-                                 : bf16_stage_kernel<TM, TN, WM, WN, NST, false, OUT_BF16>;
+    auto *kern = bf16_stage_kernel<TM, TN, WM, WN, NST, false, OUT_BF16>;
+    if (slabs > 1) {
+        if constexpr (stage_slabs(BN))
+            kern = bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>;  // (the partial sums are FP32 for either output type)
+        else
+            return MQ_ERR_SHAPE;
+    }
     const int rc = enqueue(kern, dim3((unsigned)(tiles_m * tiles_n * slabs)), dim3(64 * WM * WN),
                            stage_lds<TM, TN, WM, WN, NST>(), s, g, (int)tiles_m, (int)tiles_n);
     return rc != MQ_OK || slabs == 1 ? rc : launch_slab_sum<OUT_BF16>(g, s);
@@ -2102,7 +2106,8 @@ int configure_gemm_kernels()
 #define MQ_X(TM, TN, WM, WN, NST) \
     both(bf16_stage_kernel<TM, TN, WM, WN, NST, false, true>, bf16_stage_kernel<TM, TN, WM, WN, NST, false, false>, \
          stage_lds<TM, TN, WM, WN, NST>()); \
-    if (e == hipSuccess) e = set(bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>, stage_lds<TM, TN, WM, WN, NST>());
+    if constexpr (stage_slabs(16 * TN * WN))  \
+        if (e == hipSuccess) e = set(bf16_stage_kernel<TM, TN, WM, WN, NST, true, false>, stage_lds<TM, TN, WM, WN, NST>());
     MQ_STAGE(MQ_X)
 #undef MQ_X
     return note_launch(e);
