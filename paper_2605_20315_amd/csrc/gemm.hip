@@ -1753,13 +1753,14 @@ struct Bf16Plan {
 // two thirds come from caches), of which 55 % of the shorter one of trip and K steps hides.  A tile shape that leaves
 // a nearly empty last round loses to one that does not.  The costs are fitted to every tile's time on 4100 shapes
 // (1 to 8192 tokens; the 8B and 32B layers, their 2-, 4- and 8-way shards and shorter, narrower and wider ones;
-// weights from HBM; both output types), those of gemm_bf16_d2l and of the second pass on 2000 later ones (32 to 8192 tokens): the
-// choice is on average 1.0 % slower than the fastest tile and slab count, 95 % of the shapes within 6.6 % (690 shapes outside
-// the fit: 1.2 and 7.5 %).  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096,
-// N = 28672: the weights alone take 44 us, the 224x128 tile 66: what a compute unit can load bounds it.
+// weights from HBM; both output types), those of gemm_bf16_d2l and of the second pass on 2000 later ones (32 to 8192 tokens), when the
+// slabs' loops were slower than they are.  On 1995 shapes outside the fit (65 to 900 tokens, K = 3000 to 25600) the choice is on average
+// 1.4 % slower than the fastest tile without slabs up to K = 5120 (95 % of the shapes within 10 %), and 4 % slower than the fastest tile and
+// slab count from K = 8256 on (within 20 %); of 428 choices with slabs three were slower than the best tile without, by 6 to 10 %.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096,
+// N = 28672: the weights alone take 44 us, the 224x128 tile 61 to 66: what a compute unit can load bounds it.
 // Slabs, when the caller's workspace allows some, shorten the K loop for a second pass: 33 to 64 tokens in narrow tiles
 // (64 on K = 14336, N = 4096: 30.8 us against 36.4 without; 33 to 57 tokens 27 to 30 us); more tokens in staged tiles (100 on the
-// same layer 42 -> 32 us, 200 52 -> 41, 400 71 -> 62, 200 on K = 25600, N = 5120 134 -> 87), where a margin of 5 % keeps
+// same layer 43 -> 34 us, 200 53 -> 42, 300 59 -> 56, 400 70 -> 63, 200 on K = 25600, N = 5120 99 -> 82), where a margin of 5 % keeps
 // the rule's error from costing more than slabs bring.
 static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, int cus)
 {
@@ -1772,8 +1773,11 @@ static Bf16Plan bf16_plan(int64_t M, int64_t N, int64_t K, int64_t slab_limit, i
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (tiles > (t.kernel == MQ_KERNEL_BF16_D2L ? 0x7FFFFFFF : kMaxSmallTiles)) continue;
         if (t.kernel == MQ_KERNEL_BF16_SHORT && (M > 16 || K > 1024)) continue;
-        // 112 rows of W: fewer trips of 33 to 48 tokens to the compute units where N is wide (48 on K = 5120, N = 51200 115 us in 48x64
-        // tiles, 99 here; 40 on N = 25600 54 and 47; 33 to 48 on N = 28672 1 to 5 % faster); fewer tokens have little to save
+        // 112 rows of W: fewer trips of 33 to 48 tokens to the compute units where N is wide (48 on K = 5120, N = 51200 114 us in 48x64
+        // tiles, 94 here; 40 on N = 25600 56 and 46; 33 to 48 on K = 4096, N = 28672 1 to 5 % faster) or, with K slabs, K long (48 on
+        // K = 25600, N = 5120 51.1 in three slabs of 48x64, 48.9 in five of these; on 38 shapes where the rule takes it 0.68 to
+        // 1.00 of the best other plan).  Fewer tokens are left to the narrow tiles, though not all are better off: 17 to 32 on K = 5120, N = 25600
+        // and 51200 would take 0.86 to 0.95 of the time in this tile, on N = 28672 and 20480 1.00 to 1.10, on N = 12800 and 14336 1.26 to 1.44.
         if (t.bn == 112 && (M <= 32 || M > 48)) continue;
         // 256x192 exists twice: staged for a few K steps (1424 tokens on K = 192, N = 5384 14.3 us against 14.7), else with X one
         // stage further ahead and 32x32 products (a tenth faster from K = 512 on)
@@ -2130,11 +2134,12 @@ int gemm_fp4_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int c
 }
 
 // Most K slabs across workgroups that the BF16 product may use, given this much workspace (0 or 1: none); the cost
-// rule decides how many it does use, at most one work item per compute unit, which is less than this
-// bound.  33 to 64 tokens (narrow tiles): a long K and a narrow N; every slab keeps 512 of K, and the partial
+// rule decides how many it does use, at most one work item per compute unit.  33 to 64 tokens (narrow tiles): a long K and a narrow N; every slab keeps 512 of K, and the partial
 // sums' traffic (8 bytes per output and slab) stays below half of the weights'.  More tokens (staged tiles): every slab
-// keeps 768 of K and the partial sums 16 MiB; from K = 5120 to 8192 slabs gain 1 % on average over the shapes where the rule
-// would take them and lose as much where its error is against them, beyond that 20 to 30 %, so the line lies there.
+// keeps 768 of K and the partial sums 16 MiB.  The line at K = 8192 is on the safe side of the rule's error, not where slabs cease to gain:
+// the best plan with slabs takes 0.96 of the time of the best one without over K = 5120 to 6144 (and is slower for half of the shapes), 0.93
+// to 7168, 0.91 to 8192, 0.73 beyond.  With these costs the rule would gain 5, 9 and 14 % there where it took slabs, but be more than
+// 1.5 % slower than without in 14 of 56, 6 of 80 and 2 of 79 such shapes (by 11 % at most), beyond in 3 of 375.
 int gemm_bf16_slab_limit(int64_t M, int64_t N, int64_t K, int64_t ws_bytes, int cus)
 {
     if (M <= 32 || N <= 0 || ws_bytes <= 0 || N % 4 != 0) return 0;

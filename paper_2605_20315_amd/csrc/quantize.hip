@@ -25,7 +25,8 @@ namespace {
 constexpr int kThreads = 256;
 
 // Non-temporal: the lines take no place in the last-level cache.  A pure stream from HBM then runs at 7.0 instead of 5.9 TB/s;
-// what is still in a cache is read from there all the same.
+// what waits in that cache is read more slowly this way (the quantizer on a [8192, 4096] tensor just written 15.3 us, through the
+// cache 13.5).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_stream(const uint4 *p)
 {
@@ -401,19 +402,20 @@ __global__ __launch_bounds__(64 * ROWS) void rmsnorm_quantize_kernel(const uint1
 // and writes 0.5625 bytes per element.  A workgroup moves 32 rows x 16 K steps through LDS, so that both
 // sides see whole cache lines: 512 contiguous code bytes per row in the row-major order, 1 KB per K step
 // in the K-step-major one: [28672, 4096] 32 us (4.2 TB/s) in either direction, against 40 us to the K-step-major
-// order and 54 us from it with one thread per 32-byte unit, which touched a line per lane on one side.  STREAM: codes are read and written
-// past the last-level cache, whose room is better left to what is read again: from HBM 0.70 to 0.87 of the time ([28672, 4096] 29.0 -> 23.9 us to
-// the K-step-major order, 29.6 -> 21.9 from it), behind the quantizer that wrote them quantize and convert together 0.92 to 0.99
-// (74.8 -> 68.5 us; 13.6 of 14.2 at [4096, 4096]).  Only where the very same two buffers are converted again and again and all is
-// waiting in the cache does it cost: 11 to 18 MB 1.03 to 1.15 of the time.  From the K-step-major order smaller tensors are faster
-// through the cache (from HBM [2048, 4096] 4.6 us, 5.2 past it, [2432, 4096] 4.9 and 5.4; [4096, 2560] 6.2 and 5.6, [2816, 4096]
-// 6.5 and 5.5), hence the line at kStreamUnits; the other order's come here from 6.8 MB on, past that line.
+// order and 54 us from it with one thread per 32-byte unit, which touched a line per lane on one side.
+// STREAM_OUT: codes are written past the last-level cache, which leaves its room to what is read again, wherever every line of the
+// destination is written whole, by one workgroup: 0.70 to 1.0 of the time, cached or not (of quantize and convert together 0.91 to 0.95;
+// [6144, 4096] in the same two buffers 5.4 -> 4.4 us).  Lines written in parts cost up to 1.08 ([5121, 12864] 15.3 -> 16.6 us).
+// STREAM_IN: they are read past it too where no line is shared by two workgroups, which would fetch it twice ([5120, 3200], rows of 12.5
+// lines, behind the quantizer 14.0 -> 14.7 us), and only from kStreamIn units on: smaller tensors may be waiting in the L2 caches,
+// the same two buffers of 11 to 18 MB then take 1.05 to 1.19 of the time; from 19.7 MB on 0.80 to 0.93, from HBM 0.69 to 0.76, quantize and
+// convert 0.88 ([28672, 4096] 80 -> 70 us).  (At 63 and 70 MB the same two buffers again and again, and nothing else, 0.97 to 1.06.)
 // LDS rows hold 32 chunks of 16 bytes plus two: the reads of 8 rows x 2 halves of a K step then fall on
 // different banks.
 constexpr int R_ROWS = 32, R_STEPS = 16, R_CHUNKS = 2 * R_STEPS, R_STRIDE = R_CHUNKS + 2;
-constexpr int64_t kStreamUnits = 5 << 15;  // of 36 bytes: 5.6 MB
+constexpr int64_t kStreamIn = 17 << 15;  // of 36 bytes: 19.1 MB
 
-template <bool TO_KTILE, bool STREAM>
+template <bool TO_KTILE, bool STREAM_IN, bool STREAM_OUT>
 __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__restrict__ src_c,
                                                             const uint8_t *__restrict__ src_s,
                                                             uint8_t *__restrict__ dst_c, uint8_t *__restrict__ dst_s,
@@ -432,8 +434,8 @@ __global__ __launch_bounds__(kThreads) void relayout_kernel(const uint8_t *__res
     auto inside = [&](int row, int t) { return r0 + row < rows && t0 + t < ksteps; };
     auto lin_at = [&](int row, int t) { return (r0 + row) * row_stride + t0 + t; };   // unit (row, K step)
     auto kt_at = [&](int row, int t) { return (int64_t)(t0 + t) * rows + r0 + row; };
-    auto get = [](const uint4 *p) { return STREAM ? load_stream(p) : *p; };
-    auto put = [](uint4 *p, uint4 v) { STREAM ? store_stream(p, v) : (void)(*p = v); };
+    auto get = [](const uint4 *p) { return STREAM_IN ? load_stream(p) : *p; };
+    auto put = [](uint4 *p, uint4 v) { STREAM_OUT ? store_stream(p, v) : (void)(*p = v); };
 #pragma unroll
     for (int j = 0; j < R_ROWS * R_CHUNKS / kThreads; ++j) {
         int row, chunk;
@@ -633,8 +635,10 @@ int launch_quantize_from(const Src &src, int64_t rows, int64_t K, const float *a
 }  // namespace
 
 // Row-major quantizer of more than the 256 MB that the last-level cache holds: no whole such tensor can be waiting there, and
-// what the pass reads would only displace the codes that the next one wants.  Scale, quantize and convert of a [51200, 5120] weight
-// 260 -> 244 us.  Below, the tensor may have just been written: [8192, 4096] then takes 13.5 us, streamed 15.3.
+// what the pass reads would only displace the codes that the next one wants.  Streamed / through the cache, 266 to 500 MB: alone 0.96 to
+// 0.99 of the time, behind the scale pass of the same tensor 0.96, with the conversion behind it 0.95 to 0.97, of a tensor just written 0.89 to
+// 0.93.  (Scale and quantizer again and again on one unchanged tensor and nothing else between: 1.02 to 1.12.)  Below, the tensor may
+// have just been written: [8192, 4096] then takes 13.5 us, streamed 15.3.
 static constexpr int64_t kStreamBytes = 256ll << 20;
 
 int launch_quantize(const uint16_t *x, int64_t rows, int64_t K, int64_t ldx, const float *alpha,
@@ -706,6 +710,9 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
         return enqueue(kern, dim3((unsigned)((units + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, src_c, src_s, dst_c, dst_s,
                        (uint32_t)rows, (uint32_t)ksteps, (uint32_t)units);
     }
+    const bool whole_lin = K % 256 == 0, whole_kt = rows % 4 == 0;  // every row's or K step's codes are whole lines
+    const bool out = (to_ktile ? whole_kt : whole_lin) && reinterpret_cast<uintptr_t>(dst_c) % 128 == 0;
+    const bool in = out && units >= kStreamIn && whole_lin && whole_kt && reinterpret_cast<uintptr_t>(src_c) % 128 == 0;
     const int64_t groups = (ksteps + R_STEPS - 1) / R_STEPS, panels = (rows + R_ROWS - 1) / R_ROWS;
     // a launch holds fewer than 2^32 threads: what is more goes into further launches, by rows and, where one panel
     // of rows has more workgroups than that (K beyond 1.7e10), by K steps
@@ -718,9 +725,8 @@ int launch_relayout(const uint8_t *src_c, const uint8_t *src_s, uint8_t *dst_c, 
             // (a launch sees its K steps as the first ones: the arrays from there on, with the whole row's stride)
             const int64_t t = g0 * R_STEPS, left = ksteps - t < ng * R_STEPS ? ksteps - t : ng * R_STEPS;
             const int64_t from = to_ktile ? t : t * rows, to = to_ktile ? t * rows : t;
-            auto kern = to_ktile               ? relayout_kernel<true, true>
-                        : units < kStreamUnits ? relayout_kernel<false, false>
-                                               : relayout_kernel<false, true>;
+            auto kern = to_ktile ? (in ? relayout_kernel<true, true, true> : out ? relayout_kernel<true, false, true> : relayout_kernel<true, false, false>)
+                                 : (in ? relayout_kernel<false, true, true> : out ? relayout_kernel<false, false, true> : relayout_kernel<false, false, false>);
             const int rc = enqueue(kern, dim3((unsigned)(n * ng)), dim3(kThreads), 0, s, src_c + from * 32, src_s + from * 4,
                                    dst_c + to * 32, dst_s + to * 4, rows, p0 * R_ROWS, ksteps, (int)left, (int)ng);
             if (rc != MQ_OK) return rc;

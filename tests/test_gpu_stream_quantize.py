@@ -1,10 +1,12 @@
 """The row-major quantizer of tensors larger than the last-level cache reads them non-temporally: the same bytes as the other
 quantizer and the conversion between the two orders give, on either side of the line (256 MiB of BF16) and with strided rows.  The
-conversion does so from 5.6 MB on: the documented permutation on either side of that line, in both directions."""
+conversion writes them so where rows or K steps are whole cache lines, and reads them so where both are, from 19.1 MB on: the documented
+permutation on either side of those lines, in both directions, and into buffers that start within a line."""
 import pytest
 import torch
 
 import paper_2605_20315_amd as mq
+from paper_2605_20315_amd import _lib
 
 pytestmark = pytest.mark.gpu
 
@@ -23,16 +25,32 @@ def test_row_major_quantizer_on_both_sides_of_the_line(rows, K, pad):
     assert torch.equal(codes.view(-1), back_codes.view(-1)) and torch.equal(scales.view(-1), back_scales.view(-1))
 
 
-@pytest.mark.parametrize("rows,K", [(2048, 4096), (2559, 4096), (2730, 3840), (4096, 2560), (2561, 4096), (3071, 4096), (3073, 4160)])
-def test_conversion_on_both_sides_of_its_line(rows, K):
-    print(f"\n[case] conversion {rows} x {K}", flush=True)
+@pytest.mark.parametrize("rows,K,offset", [
+    (2048, 4096, 0), (3073, 4096, 0), (3074, 4160, 0), (3076, 4160, 0), (3076, 4352, 0), (3076, 4352, 16), (3076, 4352, 64),
+    (8700, 4096, 0), (8704, 4096, 0), (8704, 4096, 16), (8705, 4096, 0), (8708, 4160, 0)])
+def test_conversion_on_both_sides_of_its_lines(rows, K, offset):
+    print(f"\n[case] conversion {rows} x {K} offset {offset}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(rows + K)
+
+    def buffer(shape, fill=None):
+        n = shape[0] * shape[1]
+        whole = torch.full((n + 256,), 0xA5, device="cuda", dtype=torch.uint8)
+        if fill is not None:
+            whole[offset:offset + n] = fill
+        return whole, whole[offset:offset + n].view(shape)
+
     codes = torch.randint(0, 256, (rows, K // 2), device="cuda", generator=g, dtype=torch.uint8)
     scales = torch.randint(0, 256, (rows, K // 16), device="cuda", generator=g, dtype=torch.uint8)
-    want_c = codes.view(rows, K // 64, 32).permute(1, 0, 2).reshape(-1)
-    want_s = scales.view(rows, K // 64, 4).permute(1, 0, 2).reshape(-1)
-    kcodes, kscales = mq.nvfp4_relayout(codes, scales, mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE)
-    back_c, back_s = mq.nvfp4_relayout(kcodes, kscales, mq.MQ_LAYOUT_KTILE, mq.MQ_LAYOUT_LINEAR)
+    want = (codes.view(rows, K // 64, 32).permute(1, 0, 2).reshape(-1), scales.view(rows, K // 64, 4).permute(1, 0, 2).reshape(-1))
+    src = [buffer(t.shape, t.reshape(-1)) for t in (codes, scales)]
+    there, back = [[buffer(t.shape) for t in (codes, scales)] for _ in range(2)]
+    lin, kt = mq.MQ_LAYOUT_LINEAR, mq.MQ_LAYOUT_KTILE
+    stream = torch.cuda.current_stream().cuda_stream
+    lib = _lib.load()
+    for a, b, frm, to in ((src, there, lin, kt), (there, back, kt, lin)):
+        assert lib.nvfp4_relayout(a[0][1].data_ptr(), a[1][1].data_ptr(), b[0][1].data_ptr(), b[1][1].data_ptr(), rows, K, frm, to, stream) == 0
     torch.cuda.synchronize()
-    assert torch.equal(kcodes.view(-1), want_c) and torch.equal(kscales.view(-1), want_s)
-    assert torch.equal(back_c, codes) and torch.equal(back_s, scales)
+    for i, t in enumerate((codes, scales)):
+        assert torch.equal(there[i][1].view(-1), want[i]) and torch.equal(back[i][1], t)
+        for whole, view in (there[i], back[i]):
+            assert bool((whole[:offset] == 0xA5).all()) and bool((whole[offset + view.numel():] == 0xA5).all())

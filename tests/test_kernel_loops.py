@@ -1,8 +1,8 @@
 """What the compiler made of some kernels, read from the library that was built here; the results' bits do not show it.  The K loops of
 the staged BF16 kernels move no accumulator between the two kinds of register (quads stored straight from accumulation registers had the
 compiler keep half of them in each kind and move all of them twice per K step).  The direct NVFP4 kernels (K whole or in halves) start on
-their first K step without a wait for the second one's loads.  The conversion from the K-step-major order exists for smaller tensors without
-non-temporal accesses."""
+their first K step without a wait for the second one's loads.  The conversion exists with non-temporal
+loads and stores, stores alone and neither."""
 import os
 import re
 import shutil
@@ -71,4 +71,5 @@ def test_conversion_past_the_cache_only_where_it_pays(tmp_path):
     kernels = _kernels(tmp_path, "relayout_kernel")
     streamed = {name: (len(re.findall(r"global_load_dwordx4.* nt", text)), len(re.findall(r"global_store_dwordx4.* nt", text)))
                 for name, text in kernels.items()}
-    assert streamed == {"relayout_kernel<true, true>": (4, 4), "relayout_kernel<false, true>": (4, 4), "relayout_kernel<false, false>": (0, 0)}
+    assert streamed == {f"relayout_kernel<{to}, {i}, {o}>": (4 * (i == "true"), 4 * (o == "true"))
+                        for to in ("true", "false") for i, o in (("true", "true"), ("false", "true"), ("false", "false"))}
