@@ -970,12 +970,13 @@ __device__ __forceinline__ void load_rows_to_lds(uint32_t dst, uint32_t lane_off
 // memory; so one of them makes the trip and the others, a step or two later, find the lines in L2.  It is the tiles in one column
 // (tm), which share rows of W, that have to differ: with a start from tn alone the gain is gone (1.00 of the time without).  So
 // the order of a row's FP32 sums depends on its tile.
-// K slabs always; else from K = 4096 and 16 MB of W on.  Time with / without it, weights from HBM: 0.965 in staged tiles at K = 4096, 0.92
-// beyond (0.975 and 0.955 in gemm_bf16_d2l), 0.944 with slabs.  A shorter K has the first trip of every line at its start, where four times as
-// many different lines in flight cost more (staged tiles, K = 512 to 1800 1.035, 2000 to 4000 0.95 to 1.01); a smaller W is in L2 by
-// then (2227 tokens on K = 4096, N = 768 23.2 us with it, 21.3 without; 4500 tokens 32.4 and 31.3).  Where a larger W waits in the
-// last-level cache, there is less of a trip to share: 1.01 in staged tiles (1.02 at K = 4096, 1.04 at most), 1.006 in gemm_bf16_d2l;
-// the rule cannot see that.  Groups of two or eight: the same within 1 %.
+// K slabs always; else from K = 4096 on.  Staged tiles, weights from HBM, with / without it over 2549 shapes: 0.96 of the time at K = 4096, 0.94
+// beyond, where W is less than 16 MB 0.94 and 0.91 (2496 tokens on K = 5120, N = 896 43 us without, 34 with; 671 on N = 1792 32 and 25),
+// 0.75 to 1.09; 10 % of the shapes are more than 1.5 % slower, those whose tiles had shared the XCDs' trips well already (2227
+// tokens on K = 4096, N = 768 21.3 and 23.2; 769 on N = 1536 19.7 and 20.8, but 762 24.4 and 20.0), which K and N do not tell.  With slabs 0.944.
+// A shorter K has the first trip of every line at its start, where four times as many different lines in flight cost more (staged
+// tiles, K = 512 to 1800 1.035, 2000 to 4000 0.95 to 1.01).  Where W waits in the last-level cache, there is less of a trip to share: 1.02 to
+// 1.03 at K = 4096, 1.01 to 1.02 beyond, 1.015 in gemm_bf16_d2l; the rule cannot see that.  Groups of two or eight: the same within 1 %.
 struct KOrder {
     int KT, whole, first;
     __device__ __forceinline__ KOrder(int kt, bool own, int tm, int tn)
@@ -987,7 +988,7 @@ struct KOrder {
         k = k < KT ? k : KT - 1;  // past the end: a step that was read before, never used
         return k < whole ? (k & ~3) | ((k + first) & 3) : k;
     }
-    static __device__ __forceinline__ bool pays(const GemmArgs &g) { return g.K >= 4096 && g.N * g.K >= (8 << 20); }
+    static constexpr int64_t kFrom = 4096;  // K
 };
 
 // Until at most `N` of this wave's loads are in flight (the counter holds 63) and its LDS reads are done.
@@ -1025,7 +1026,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_d2l(GemmArgs g, int tiles_m, in
     const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
     const int frow = lane & 31, fhalf = lane >> 5;
     const int KT = (int)(g.K / BK);
-    const KOrder order(KT, KOrder::pays(g), tm, tn);
+    const KOrder order(KT, g.K >= KOrder::kFrom, tm, tn);
 
     // load u of this wave: rows 8 * (wave * GA + u) .. + 7 of the A tile (u < GA), else of the B tile
     // byte offsets from the tile's first row: 32 bits for any operand size
@@ -1390,7 +1391,7 @@ __global__ __launch_bounds__(64 * WM * WN) void bf16_stage_kernel(GemmArgs g, in
     const int KA = (int)(g.K / BK), SL = SLABS ? (KA + g.ksplit - 1) / g.ksplit : KA;
     const int s0 = slab * SL, KT = s0 + SL < KA ? SL : KA - s0;
 
-    const KOrder order(KT, SLABS || KOrder::pays(g), tm, tn);
+    const KOrder order(KT, SLABS || g.K >= KOrder::kFrom, tm, tn);
 
     uint32_t vo[NL];
 #pragma unroll

@@ -1,6 +1,6 @@
 """GPU parity of the BF16 product where K is cut into slabs across workgroups in the staged tiles and in the
 decode tile of 112 rows of W, where workgroups take
-the K steps of a long K in orders of their own (and where they do not, for a W below 16 MB), in that decode tile without slabs, and for a
+the K steps of a long K in orders of their own, in that decode tile without slabs, and for a
 large W that one row of tiles reads: the last slab shorter than the others, groups of four steps with
 none to three left over, ragged M and N, strided operands and output, a workspace that holds fewer slabs than the rule would
 take.  Every output is compared with the oracle's FP64 product; nothing outside [M, N] and the slabs' sums may be written."""
@@ -79,9 +79,9 @@ def test_orders_of_the_k_steps_and_wide_w(M, N, K, kernel, tile):
 
 @pytest.mark.parametrize("M,N,K,kernel,tile,own_orders", [
     (1048, 7181, 4096, "bf16_d2l", (256, 192), True), (2048, 7168, 4160, "bf16_d2l", (256, 256), True), (257, 5133, 4288, "bf16_stage", (96, 64), True),
-    (2227, 768, 4096, "bf16_stage", (128, 64), False), (969, 6667, 512, "bf16_d2l", (256, 192), False), (530, 7457, 192, "bf16_stage", (160, 128), False)])
+    (2227, 768, 4096, "bf16_stage", (128, 64), True), (969, 6667, 512, "bf16_d2l", (256, 192), False), (530, 7457, 192, "bf16_stage", (160, 128), False)])
 def test_equal_rows_of_x(M, N, K, kernel, tile, own_orders):
-    """What the header says of two equal rows: the same sums in every tile, but for a long K on a large W, where a tile's order of K is its
+    """What the header says of two equal rows: the same sums in every tile, but for a long K, where a tile's order of K is its
     own and they may differ by what the accumulation rounds; the same bits from run to run in any case."""
     plan = mq.mq_bf16_gemm_launches(M, N, K, 0)[0]
     assert (plan["kernel"], plan["tile"]) == (kernel, tile)
