@@ -1757,8 +1757,9 @@ struct Bf16Plan {
 // weights from HBM; both output types), those of gemm_bf16_d2l and of the second pass on 2000 later ones (32 to 8192 tokens), when the
 // slabs' loops were slower than they are.  On 1995 shapes outside the fit (65 to 900 tokens, K = 3000 to 25600) the choice is on average
 // 1.4 % slower than the fastest tile without slabs up to K = 5120 (95 % of the shapes within 10 %), and 4 % slower than the fastest tile and
-// slab count from K = 8256 on (within 20 %); of 428 choices with slabs three were slower than the best tile without, by 6 to 10 %.  (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096,
-// N = 28672: the weights alone take 44 us, the 224x128 tile 61 to 66: what a compute unit can load bounds it.
+// slab count from K = 8256 on (within 20 %); of 428 choices with slabs three were slower than the best tile without, by 6 to 10 %.
+// (The output type does not enter: the BF16 output is the rounded FP32 output bit for bit.)  200 tokens on K = 4096, N = 28672: the weights
+// alone take 44 us, the 224x128 tile 61 to 66: what a compute unit can load bounds it.
 // Slabs, when the caller's workspace allows some, shorten the K loop for a second pass: 33 to 64 tokens in narrow tiles
 // (64 on K = 14336, N = 4096: 30.8 us against 36.4 without; 33 to 57 tokens 27 to 30 us); more tokens in staged tiles (100 on the
 // same layer 43 -> 34 us, 200 53 -> 42, 300 59 -> 56, 400 70 -> 63, 200 on K = 25600, N = 5120 99 -> 82), where a margin of 5 % keeps
